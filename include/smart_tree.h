@@ -84,8 +84,9 @@ enum { SMART_FP8_E4M3 = 2 };
  *                         K: ((d / 8) * block_size + slot) * 8 + d % 8
  *                         V: ((slot / 8) * head_dim + d) * 8 + slot % 8
  *                         (page contiguous; block_size and head_dim multiples of 8)
- * The bf16 matrix-core kernel requires SMART_KV_INTERLEAVED, block_size 16 and
- * head_dim 128; every other combination runs a slower general kernel. */
+ * The fastest bf16 kernel requires SMART_KV_INTERLEAVED, block_size 16 and head_dim
+ * 128; every other combination runs a tiled matrix-core kernel, or, where its rows
+ * are not aligned to 16 bytes (8 elements of an fp8 cache), a slow general kernel. */
 enum { SMART_KV_PLAIN = 0, SMART_KV_INTERLEAVED = 1 };
 
 /* smart_select_tree modes */
@@ -616,8 +617,9 @@ int32_t tree_verify_attention(smart_ctx* ctx, void* stream, const tva_params* pa
  * calls on one stream do not.  The array keeps the previous call's contents;
  * nothing in it needs to start at zero, every word that is read was written
  * by the same call before.
- * The general (non matrix-core) kernel needs no scratch memory and is used as
- * in tree_verify_attention.
+ * Calls that are not bf16 / interleaved / block_size 16 / head_dim 128 use no
+ * scratch memory here (the tiled kernel's workspace-free form, which is also what
+ * a captured tree_verify_attention of that kind runs).
  * Errors: as tree_verify_attention, plus SMART_ECAP as above, and SMART_EHIP
  * if the array's address could not be resolved when the context was created.
  * ------------------------------------------------------------------------- */

@@ -16,7 +16,7 @@ TIMELINE_SOURCE = "tva_mfma.hip"        # the one source with stamps (-DSMART_TV
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIP_SOURCES = ["smart_ctx.hip", "tree_pack_accept.hip", "kv_cache_write.hip", "tva_general.hip",
-               "tva_mfma.hip", "tva_api.hip", "tva_static.hip", "smart_select_device.hip", "tree_rope.hip",
+               "tva_mfma.hip", "tva_tiled.hip", "tva_api.hip", "tva_static.hip", "smart_select_device.hip", "tree_rope.hip",
                "tree_accept_sample.hip"]
 HOST_SOURCES = ["smart_select.cpp", "smart_cost_model.cpp"]
 

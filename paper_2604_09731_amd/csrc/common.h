@@ -67,11 +67,16 @@ struct TvaWorkspace {
 
 // Argument checks of tree_verify_attention (host only; nothing is enqueued).
 int32_t tva_check_params(const tva_params& p);
-// Entry points of the two attention implementations (validated params).  `fixed`: the buffers to use
+// Entry points of the attention implementations (validated params).  `fixed`: the buffers to use
 // instead of the context's own growable workspace (then nothing is allocated; SMART_ECAP if they are too small).
 int32_t tva_launch_general(smart_ctx* ctx, hipStream_t stream, const tva_params& p);
 int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed);
-// Dispatch between the two (validated params, the context's device current).
+// The tiled matrix-core path: every other type, layout, head dim and block size whose rows are aligned.
+int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed);
+bool tva_tiled_supported(const tva_params& p);
+void tva_tiled_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
+                         int32_t num_kv_heads, int32_t head_dim, size_t* ws_bytes, size_t* plan_bytes);
+// Dispatch between them (validated params, the context's device current).
 int32_t tva_dispatch(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed);
 // This device's copy of the library's static scratch array (the device must be current); resolved once per device.
 int32_t static_scratch(int device, void** ptr, size_t* bytes);

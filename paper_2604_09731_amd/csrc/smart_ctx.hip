@@ -216,6 +216,10 @@ extern "C" int32_t smart_reserve(smart_ctx* ctx, int32_t max_batch, int32_t max_
   SMART_HIP_CHECK(hipSetDevice(ctx->device));
   size_t ws = 0, plan = 0;
   smart::tva_mfma_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, &ws, &plan);
+  size_t tiled_ws = 0, tiled_plan = 0;  // (head dim 128: the larger one)
+  smart::tva_tiled_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, 128, &tiled_ws, &tiled_plan);
+  ws = tiled_ws > ws ? tiled_ws : ws;
+  plan = tiled_plan > plan ? tiled_plan : plan;
   int32_t rc = smart::ensure_workspace(ctx, nullptr, ws, plan);
   (void)hipSetDevice(prev);
   return rc;

@@ -1,5 +1,5 @@
 // tree_verify_attention: argument checks and dispatch between the matrix-core
-// path and the general kernel.
+// paths and the general kernel.
 #include "common.h"
 
 namespace smart {
@@ -44,6 +44,7 @@ int32_t tva_dispatch(smart_ctx* ctx, hipStream_t stream, const tva_params& p, co
   if (p.batch == 0 || p.total_nodes == 0) return SMART_OK;
   if (!ctx->opt_force_general && p.max_blocks_per_seq > 0 && tva_mfma_supported(p))
     return tva_launch_mfma(ctx, stream, p, fixed);
+  if (!ctx->opt_force_general && tva_tiled_supported(p)) return tva_launch_tiled(ctx, stream, p, fixed);
   return tva_launch_general(ctx, stream, p);  // needs no workspace
 }
 

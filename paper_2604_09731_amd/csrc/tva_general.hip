@@ -1,8 +1,8 @@
 // tree_verify_attention, general kernel: fp32 vector arithmetic, any supported
 // element type, cache layout, block size and head dim.  One wavefront per
-// (tree node, query head).  It serves fp32 inputs (where the tolerance is
-// 1e-5 and the sizes are small) and every shape the matrix-core kernel does
-// not cover; it is not tuned for bandwidth.
+// (tree node, query head).  It serves what the matrix-core kernels do not take:
+// rows that are not aligned to their 16-byte loads, calls without a cache, and
+// SMART_OPT_TVA_FORCE_GENERAL; it is not tuned for bandwidth.
 //
 // Per (node i, head h): keys are the sequence's cached prefix followed by the
 // tree nodes in anc_mask[i]; out = softmax(scale * q.k) . v over those keys

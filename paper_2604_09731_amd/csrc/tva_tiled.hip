@@ -1,0 +1,1045 @@
+// tree_verify_attention, tiled matrix-core path for what the interleaved-cache bf16 path does not cover: fp32 and
+// bf16, both cache layouts, head dims 64 and 128, any block size, fp8 caches.
+//
+// The prefix is a dense contraction of all rows of a kv head (tree nodes x query heads of the group) with the cached
+// keys, so a workgroup takes a row group of up to 128 rows and streams the keys past it: every K/V byte leaves HBM once
+// per row group, instead of once per (node, head) as in the general kernel, and the products run on the matrix cores.
+//
+//   * A step is 16 KB x D / 128 x 4 of K and V: four tiles of 32 keys (bf16) or 16 keys (fp32).  The 256 threads load a
+//     step with 16-byte loads into registers while the step before is being computed, and put it into LDS in between;
+//     two workgroups per compute unit cover each other's barriers.
+//   * Four wavefronts: with up to 32 rows each takes one tile of the step, with up to 64 rows two wavefronts share a
+//     row tile, with more every wavefront has 32 rows of its own and takes all four tiles.  The states that share a row
+//     tile are folded through LDS at the end of a piece, in a fixed order.
+//   * Scores are kept transposed (keys x rows): a row's softmax stays inside a lane (and its partner lanes), and the
+//     probabilities come out in the operand layout of the second product.
+//   * Plain pages are staged row by row with their 16-byte chunks permuted by row, so that the score product's reads
+//     (one row per lane) and the output product's reads (transposing LDS reads, ds_read_b64_tr_b16, for bf16) are both
+//     free of bank conflicts.  Interleaved pages are staged in operand order.
+//   * Nothing is rounded below what the general kernel holds: bf16 products are exact in binary32, a probability goes
+//     into the second product as the sum of three bf16 values, which is its binary32 value exactly (three MFMAs per
+//     tile instead of one; the loop is bound by its loads up to about 100 rows), and fp32 uses the fp32 MFMAs.
+//
+// Two forms.  Split: the units (steps of all segments = (sequence, kv head, row group)) are cut into equal shares, one
+// per workgroup, every piece leaves a partial (max, sum, O) in slot workgroup + segment, and a second kernel merges
+// them with the tree part.  Direct: one workgroup per segment, which also does the tree part; needs no workspace.
+//
+// The tree part (a node sees only itself and its ancestors, a handful of keys chosen by a 128-bit mask) is evaluated
+// on the vector ALUs in fp32 by walking the set bits, so what other nodes hold never enters a row.
+//
+// Measured against the general kernel (whole call): bf16 plain pages, batch 16, 32 / 8 heads of 128, prefixes of
+// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 0.20 ms; fp32 plain pages, batch 8, 8 / 2 heads of 64, prefixes of
+// 128 .. 1536, 15-node trees 778 -> 29 us, and its error against binary64 falls from 5.6e-7 to 3.1e-7 (shorter sums).
+//
+// The paper (Sec. 1) has the target model verify the tree in one forward pass; this is the attention sub-step.
+#include <math.h>
+
+#include "common.h"
+#include "wave.h"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) short shortx4;
+typedef __attribute__((ext_vector_type(4))) float floatx4;
+typedef __attribute__((ext_vector_type(8))) float floatx8;
+typedef __attribute__((ext_vector_type(16))) float floatx16;
+typedef __attribute__((ext_vector_type(4))) uint32_t uintx4;
+typedef __attribute__((ext_vector_type(2))) uint32_t uintx2;
+typedef __attribute__((ext_vector_type(2))) float floatx2;
+
+constexpr int kWave = 64;
+constexpr int kWaves = 4;
+constexpr int kThreads = kWave * kWaves;
+constexpr int kRowTile = 32;
+constexpr int kGroupRows = 128;      // rows of a row group: four row tiles
+constexpr int kTilesPerStep = 4;
+constexpr int kCombineLanes = 8;     // lanes per row in the finishing step
+constexpr float kLog2e = 1.4426950408889634f;
+// The value the exponentials are taken against follows the running maximum only when that has moved more than
+// 2^kRescaleStep above it (in the exponent's units): a partial's max, sum and O stay consistent with each other.
+constexpr float kRescaleStep = 8.f;
+
+template <typename T> struct TileKeys;
+template <> struct TileKeys<__bf16> { static constexpr int value = 32; };
+template <> struct TileKeys<float> { static constexpr int value = 16; };
+template <typename T> constexpr int step_keys() { return kTilesPerStep * TileKeys<T>::value; }
+
+__host__ __device__ constexpr int slot_floats(int D) { return kGroupRows * (D + 2); }
+
+struct TiledArgs {
+  const void* q;
+  const void* k_tree;
+  const void* v_tree;
+  const void* k_cache;
+  const void* v_cache;
+  const int32_t* block_table;
+  const int32_t* prefix_len;
+  const int32_t* cu_nodes;
+  const uint64_t* anc_mask;
+  void* out;
+  float* lse;
+  int32_t* status;
+  float* ws;       // split form: partial slots
+  int64_t* plan;   // split form: units, workers, then per sequence the units and the segments before it
+  int64_t block_stride, head_stride, token_stride;
+  int64_t seg_cap;  // segments the slots have room for
+  int32_t batch, total_nodes, Hq, Hkv, G, block_size, max_blocks, num_blocks;
+  int32_t direct;
+  uint32_t block8_magic;  // token / 8 / (block_size / 8) by multiplication; 0: block_size is 8
+  float scale;
+  float c;         // softmax scale in powers of two (log2 e folded in)
+  float c_stored;  // the same against stored key values: c k_scale
+  float m_scale;   // = k_scale: row maxima leave the prefix kernel in true units
+  float o_scale;   // = v_scale
+};
+
+// What a call uses of one sequence: lengths and sizes clamped to what the arrays hold.  A range that leaves the arrays
+// has no rows (nothing of it is read).
+struct Shape {
+  int len, base, n, rows, groups, steps;
+};
+
+template <int kStepKeys>
+__device__ inline Shape shape_of(const TiledArgs& a, int len, int base, int next) {
+  Shape s;
+  const int cap = a.max_blocks * a.block_size;
+  s.len = len < 0 ? 0 : (len > cap ? cap : len);
+  int64_t n = (int64_t)next - base;
+  n = n < 0 ? 0 : (n > SMART_MAX_NODES ? SMART_MAX_NODES : n);
+  if (base < 0 || base + n > a.total_nodes) n = 0;
+  s.base = base;
+  s.n = (int)n;
+  s.rows = s.n * a.G;
+  s.groups = (s.rows + kGroupRows - 1) / kGroupRows;
+  s.steps = s.groups > 0 ? (s.len + kStepKeys - 1) / kStepKeys : 0;
+  return s;
+}
+
+// Where a unit (or, in the direct form, a segment) lies: its sequence and what comes before that.
+struct Place {
+  int b;
+  int64_t units_before, segs_before;
+};
+
+// One wavefront goes through the batch, 64 sequences at a time.  `want` is a unit (kSegments = false) or a segment;
+// returns false if it is not there.  Totals come back as well when the whole batch was gone through (`all`).
+template <int kStepKeys, typename Visit>
+__device__ inline void scan_batch(const TiledArgs& a, int lane, int64_t* total_units, int64_t* total_segs, Visit visit) {
+  int64_t before_u = 0, before_s = 0;
+  for (int b0 = 0; b0 < a.batch; b0 += kWave) {
+    const int b = min(b0 + lane, a.batch - 1);
+    Shape s = shape_of<kStepKeys>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+    const bool there = b0 + lane < a.batch;
+    const int64_t segs = there ? (int64_t)s.groups * a.Hkv : 0;
+    const int64_t units = segs * s.steps;
+    int64_t tu, ts;
+    const int64_t eu = smart::wave_excl_scan(units, lane, &tu) + before_u;
+    const int64_t es = smart::wave_excl_scan(segs, lane, &ts) + before_s;
+    visit(b0, there, units, segs, eu, es);
+    before_u += tu;
+    before_s += ts;
+  }
+  *total_units = before_u;
+  *total_segs = before_s;
+}
+
+__device__ inline int clamp_block(int b, int num_blocks) { return b < 0 ? 0 : (b >= num_blocks ? num_blocks - 1 : b); }
+
+// Row m of a 16-row half of the score tile holds key sigma(m) when the values are staged as vectors of 8 consecutive
+// keys: swapping bits 2 and 3 makes the eight registers a lane ends up with eight consecutive keys.
+__device__ inline int sigma(int m) { return (m & 3) | ((m & 4) << 1) | ((m & 8) >> 1); }
+
+__device__ inline float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ inline float sum_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ inline float max_rows16(float x) {  // over the lanes with the same lane % 16
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max_halves(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ inline float sum_rows16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return sum_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+// exp2((x - m) c) with an empty reference (m = -inf: no key so far scored above -inf) giving 0 for x = -inf.
+__device__ inline float weight(float x, float m, float c) {
+  return __builtin_amdgcn_exp2f((x - (m == -INFINITY ? 0.f : m)) * c);
+}
+
+// ---- staging: global memory -> registers -> LDS --------------------------------------------------------------------
+// A chunk is 16 bytes of T in LDS: 8 bf16 or 4 fp32 elements, which come from as many bytes / 2 or / 4 of an fp8 cache.
+template <typename T, bool kFp8> struct RawChunk;
+template <> struct RawChunk<__bf16, false> { typedef uintx4 type; };
+template <> struct RawChunk<float, false> { typedef uintx4 type; };
+template <> struct RawChunk<__bf16, true> { typedef uintx2 type; };
+template <> struct RawChunk<float, true> { typedef uint32_t type; };
+
+__device__ inline uintx4 staged(uintx4 x, float) { return x; }
+__device__ inline uintx4 staged(uintx4 x, __bf16) { return x; }
+__device__ inline uintx4 staged(uintx2 x, __bf16) {  // eight E4M3 bytes -> bf16, exactly
+  const bf16x2 a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x[0], 1.0f, false);
+  const bf16x2 b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x[0], 1.0f, true);
+  const bf16x2 c = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x[1], 1.0f, false);
+  const bf16x2 d = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(x[1], 1.0f, true);
+  bf16x8 r;
+  r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
+  r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
+  return __builtin_bit_cast(uintx4, r);
+}
+__device__ inline uintx4 staged(uint32_t x, float) {  // four E4M3 bytes -> fp32, exactly
+  floatx4 r;
+  r[0] = __builtin_amdgcn_cvt_f32_fp8(x, 0);
+  r[1] = __builtin_amdgcn_cvt_f32_fp8(x, 1);
+  r[2] = __builtin_amdgcn_cvt_f32_fp8(x, 2);
+  r[3] = __builtin_amdgcn_cvt_f32_fp8(x, 3);
+  return __builtin_bit_cast(uintx4, r);
+}
+
+// The permutation of a plain row's chunks in LDS: chunk c of row `key` lies at position c ^ swizzle(key).  Sixteen
+// consecutive rows put the same chunk at sixteen positions of a 256-byte line (the score product reads one row per
+// lane), and four consecutive rows put a pair of chunks at four different pairs (the transposing reads).
+template <typename T, int D>
+__device__ inline int swizzle(int key) {
+  if (sizeof(T) == 4) return key & 15;
+  if (D == 128) return ((key & 7) << 1) | ((key >> 3) & 1);
+  return (((key >> 1) & 3) << 1) | ((key >> 3) & 1);
+}
+
+template <typename T, bool kFp8, bool kPlain, int D>
+struct Stager {
+  typedef typename RawChunk<T, kFp8>::type Raw;
+  static constexpr int kE = 16 / (int)sizeof(T);          // elements per chunk
+  static constexpr int kTileChunks = 4 * D;               // chunks of a tile's K (or V)
+  static constexpr int kStepChunks = kTilesPerStep * kTileChunks;
+  static constexpr int kPer = kStepChunks / kThreads;     // chunks a thread moves per step, of K and of V
+  static constexpr int kKeys = TileKeys<T>::value;
+  static constexpr int kStepKeys = step_keys<T>();
+
+  int32_t idk[kPer], idv[kPlain ? 1 : kPer];
+  Raw k[kPer], v[kPer];
+
+  // Key of the step that chunk p of K / of V starts at, and the chunk's element offset in its page given the slot.
+  __device__ static int key_of_k(int p) {
+    if (kPlain) return p / (D / kE);
+    const int x = p % kTileChunks, tile = p / kTileChunks;
+    return tile * kKeys + (sizeof(T) == 2 ? x & 31 : (x >> 1) & 15);
+  }
+  __device__ static int key_of_v(int p) {
+    if (kPlain) return key_of_k(p);
+    const int x = p % kTileChunks, tile = p / kTileChunks;
+    return tile * kKeys + 8 * (sizeof(T) == 2 ? x / D : (x >> 1) / D);
+  }
+  __device__ static int64_t offset_k(const TiledArgs& a, int p, int slot) {
+    if (kPlain) {
+      const int key = p / (D / kE);
+      return (int64_t)slot * a.token_stride + ((p % (D / kE)) ^ swizzle<T, D>(key)) * kE;
+    }
+    const int x = p % kTileChunks;
+    if (sizeof(T) == 2) return ((x >> 5) * a.block_size + slot) * 8;
+    return ((x >> 5) * a.block_size + slot) * 8 + 4 * (x & 1);
+  }
+  __device__ static int64_t offset_v(const TiledArgs& a, int p, int slot) {
+    if (kPlain) return offset_k(a, p, slot);
+    const int x = p % kTileChunks;
+    if (sizeof(T) == 2) return ((slot >> 3) * D + x % D) * 8;
+    return ((slot >> 3) * D + (x >> 1) % D) * 8 + 4 * (x & 1);
+  }
+  // Token of a key of the step, kept inside the prefix (what lies past it is masked later): a V vector of an
+  // interleaved page starts at a multiple of 8.
+  __device__ static int token_k(int step, int key, int len) { return min(step * kStepKeys + key, len - 1); }
+  __device__ static int token_v(int step, int key, int len) {
+    return kPlain ? token_k(step, key, len) : min(step * kStepKeys + key, (len - 1) & ~7);
+  }
+  __device__ static int block_of(const TiledArgs& a, int token) {
+    const uint32_t t8 = (uint32_t)token >> 3;
+    return a.block8_magic ? (int)__umulhi(t8, a.block8_magic) : (int)t8;
+  }
+
+  __device__ void load_ids(const TiledArgs& a, const int32_t* row, int step, int len, int tid) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      idk[i] = row[block_of(a, token_k(step, key_of_k(i * kThreads + tid), len))];
+      if (!kPlain) idv[i] = row[block_of(a, token_v(step, key_of_v(i * kThreads + tid), len))];
+    }
+  }
+  __device__ void load(const TiledArgs& a, int step, int len, int g, int tid) {
+    constexpr int kB = kFp8 ? 1 : (int)sizeof(T);  // bytes of a cache element
+    const char* kc = (const char*)a.k_cache + (int64_t)g * a.head_stride * kB;
+    const char* vc = (const char*)a.v_cache + (int64_t)g * a.head_stride * kB;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int p = i * kThreads + tid;
+      const int tk = token_k(step, key_of_k(p), len);
+      const int64_t at = clamp_block(idk[i], a.num_blocks) * a.block_stride +
+                         offset_k(a, p, tk - block_of(a, tk) * a.block_size);
+      k[i] = *(const Raw*)(kc + at * kB);
+      if (kPlain) v[i] = *(const Raw*)(vc + at * kB);
+    }
+    if (!kPlain) {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        const int p = i * kThreads + tid;
+        const int tv = token_v(step, key_of_v(p), len);
+        const int64_t at = clamp_block(idv[i], a.num_blocks) * a.block_stride +
+                           offset_v(a, p, tv - block_of(a, tv) * a.block_size);
+        v[i] = *(const Raw*)(vc + at * kB);
+      }
+    }
+  }
+  __device__ void store(uintx4* lds, int tid) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      lds[i * kThreads + tid] = staged(k[i], T());
+      lds[kStepChunks + i * kThreads + tid] = staged(v[i], T());
+    }
+  }
+};
+
+// ---- one wavefront's 32 rows against one staged tile ------------------------------------------------------------------
+template <typename T, bool kPlain, int D> struct Rows;
+
+typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
+
+template <bool kPlain, int D>
+struct Rows<__bf16, kPlain, D> {
+  static constexpr int kRowChunks = D / 8;
+  bf16x8 q[D / 16];
+  floatx16 o[D / 32];
+  float m, l;  // of row lane % 32; l: this half-wavefront's keys
+
+  __device__ void begin(const TiledArgs& a, int base, int g, int row0, int rows, int lane) {
+    const int h = lane >> 5, j = lane & 31;
+    const int rho = min(row0 + j, rows - 1);  // padding rows repeat the last real row; never read back
+    const int node = base + rho / a.G, head = g * a.G + rho % a.G;
+    const __bf16* qp = (const __bf16*)a.q + ((int64_t)node * a.Hq + head) * D + h * 8;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) q[ks] = *(const bf16x8*)(qp + ks * 16);
+    reset();
+  }
+  __device__ void reset() {
+#pragma unroll
+    for (int jt = 0; jt < D / 32; ++jt) o[jt] = (floatx16)(0.f);
+    m = -INFINITY;
+    l = 0.f;
+  }
+  __device__ static int key_of_row(int i) { return kPlain ? i : (i & 16) + sigma(i & 15); }
+
+  __device__ void tile(const uintx4* kt, const uintx4* vt, int n_valid, float c, int lane) {
+    const int h = lane >> 5, j = lane & 31;
+    floatx16 s = (floatx16)(0.f);
+    const int key = key_of_row(j);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) {
+      const int chunk = 2 * ks + h;
+      const int at = kPlain ? key * kRowChunks + (chunk ^ swizzle<__bf16, D>(key)) : chunk * 32 + key;
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kt[at]), q[ks], s, 0, 0, 0);
+    }
+    const bool ragged = n_valid < 32;
+    if (ragged) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (key_of_row(8 * (r >> 2) + 4 * h + (r & 3)) >= n_valid) s[r] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    mx = max_halves(mx);
+    const float m_new = fmaxf(m, mx);
+    if (__any((m_new - m) * c > kRescaleStep)) {
+      const float alpha = weight(m, m_new, c);
+      l *= alpha;
+#pragma unroll
+      for (int jt = 0; jt < D / 32; ++jt) o[jt] *= alpha;
+      m = m_new;
+    }
+    // p = hi + mid + lo exactly: three bf16 values hold the 24 bits of a binary32
+    bf16x8 hi[2], mid[2], lo[2];
+    float sum = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      floatx8 p;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        p[e] = weight(s[8 * kk + e], m, c);
+        sum += p[e];
+      }
+      hi[kk] = __builtin_convertvector(p, bf16x8);
+      const floatx8 r1 = p - __builtin_convertvector(hi[kk], floatx8);
+      mid[kk] = __builtin_convertvector(r1, bf16x8);
+      lo[kk] = __builtin_convertvector(r1 - __builtin_convertvector(mid[kk], floatx8), bf16x8);
+    }
+    l += sum;
+#pragma unroll
+    for (int jt = 0; jt < D / 32; ++jt)
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        bf16x8 v = value_operand(vt, jt, kk, lane);
+        if (ragged) {  // unowned slots may hold anything, NaN included
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int token = kPlain ? 16 * kk + 8 * (e >> 2) + 4 * h + (e & 3) : 16 * kk + 8 * h + e;
+            if (token >= n_valid) v[e] = (__bf16)0.f;
+          }
+        }
+        o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, hi[kk], o[jt], 0, 0, 0);
+        o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, mid[kk], o[jt], 0, 0, 0);
+        o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, lo[kk], o[jt], 0, 0, 0);
+      }
+  }
+  // Lane (h, j): head dim 32 jt + j of the eight keys whose probabilities the lane's half holds in registers 8 kk ...
+  __device__ static bf16x8 value_operand(const uintx4* vt, int jt, int kk, int lane) {
+    const int h = lane >> 5, j = lane & 31;
+    if (!kPlain) return __builtin_bit_cast(bf16x8, vt[(2 * kk + h) * D + 32 * jt + j]);
+    // transposing read: sixteen lanes fetch four rows of sixteen elements, lane i receives column i
+    const int li = lane & 15, jh = (lane >> 4) & 1;
+    shortx4 part[2];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int token = 16 * kk + 8 * half + 4 * h + (li >> 2);
+      const int chunk = 4 * jt + 2 * jh + ((li & 3) >> 1);
+      const char* at = (const char*)(vt + token * kRowChunks + (chunk ^ swizzle<__bf16, D>(token))) + 8 * (li & 1);
+      part[half] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)at);
+    }
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
+  }
+  // The state in LDS: O as [d / 4][32 rows][4], the row maxima, the row sums.
+  __device__ void put(float* region, int lane) {
+    const int h = lane >> 5, j = lane & 31;
+#pragma unroll
+    for (int jt = 0; jt < D / 32; ++jt)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        floatx4 x;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = o[jt][4 * r4 + i];
+        ((floatx4*)region)[(8 * jt + 2 * r4 + h) * kRowTile + j] = x;
+      }
+    const float sum = sum_halves(l);
+    if (h == 0) {
+      region[kRowTile * D + j] = m;
+      region[kRowTile * D + kRowTile + j] = sum;
+    }
+  }
+};
+
+template <bool kPlain, int D>
+struct Rows<float, kPlain, D> {
+  static constexpr int kRowChunks = D / 4;
+  floatx4 q[2][D / 16];
+  floatx4 o[2][D / 16];
+  float m[2], l[2];  // of rows lane % 16 and lane % 16 + 16; l: this quarter-wavefront's keys
+
+  __device__ void begin(const TiledArgs& a, int base, int g, int row0, int rows, int lane) {
+    const int quarter = lane >> 4, j = lane & 15;
+#pragma unroll
+    for (int nh = 0; nh < 2; ++nh) {
+      const int rho = min(row0 + 16 * nh + j, rows - 1);
+      const int node = base + rho / a.G, head = g * a.G + rho % a.G;
+      const float* qp = (const float*)a.q + ((int64_t)node * a.Hq + head) * D + 4 * quarter;
+#pragma unroll
+      for (int s = 0; s < D / 16; ++s) q[nh][s] = *(const floatx4*)(qp + 16 * s);
+    }
+    reset();
+  }
+  __device__ void reset() {
+#pragma unroll
+    for (int nh = 0; nh < 2; ++nh) {
+#pragma unroll
+      for (int t = 0; t < D / 16; ++t) o[nh][t] = (floatx4)(0.f);
+      m[nh] = -INFINITY;
+      l[nh] = 0.f;
+    }
+  }
+  __device__ void tile(const uintx4* kt, const uintx4* vt, int n_valid, float c, int lane) {
+    const int quarter = lane >> 4, i = lane & 15;
+    floatx4 s[2] = {(floatx4)(0.f), (floatx4)(0.f)};
+    // contraction step (t, e): the four quarters hold head dims 16 t + 4 quarter + e
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) {
+      const int chunk = 4 * t + quarter;
+      const int at = kPlain ? i * kRowChunks + (chunk ^ swizzle<float, D>(i)) : ((chunk >> 1) * 16 + i) * 2 + (chunk & 1);
+      const floatx4 k = __builtin_bit_cast(floatx4, kt[at]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int nh = 0; nh < 2; ++nh) s[nh] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[e], q[nh][t][e], s[nh], 0, 0, 0);
+    }
+    // register r of a lane: key 4 quarter + r
+    const bool ragged = n_valid < 16;
+    floatx4 p[2];
+    float m_new[2];
+    bool move = false;
+#pragma unroll
+    for (int nh = 0; nh < 2; ++nh) {
+      if (ragged) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (4 * quarter + r >= n_valid) s[nh][r] = -INFINITY;
+      }
+      const float mx = max_rows16(fmaxf(fmaxf(s[nh][0], s[nh][1]), fmaxf(s[nh][2], s[nh][3])));
+      m_new[nh] = fmaxf(m[nh], mx);
+      move = move || (m_new[nh] - m[nh]) * c > kRescaleStep;
+    }
+    if (__any(move)) {
+#pragma unroll
+      for (int nh = 0; nh < 2; ++nh) {
+        const float alpha = weight(m[nh], m_new[nh], c);
+        l[nh] *= alpha;
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t) o[nh][t] *= alpha;
+        m[nh] = m_new[nh];
+      }
+    }
+#pragma unroll
+    for (int nh = 0; nh < 2; ++nh) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[nh][r] = weight(s[nh][r], m[nh], c);
+      l[nh] += (p[nh][0] + p[nh][1]) + (p[nh][2] + p[nh][3]);
+    }
+    if (kPlain) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int token = 4 * quarter + r;
+#pragma unroll
+        for (int u = 0; u < D / 64; ++u) {  // lane i: head dims 64 u + 4 i + e
+          floatx4 v = __builtin_bit_cast(floatx4, vt[token * kRowChunks + ((16 * u + i) ^ swizzle<float, D>(token))]);
+          if (ragged && token >= n_valid) v = (floatx4)(0.f);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int nh = 0; nh < 2; ++nh)
+              o[nh][4 * u + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], p[nh][r], o[nh][4 * u + e], 0, 0, 0);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < D / 16; ++t) {  // lane i: head dim 16 t + i of the quarter's four keys
+        floatx4 v = __builtin_bit_cast(floatx4, vt[((quarter >> 1) * D + 16 * t + i) * 2 + (quarter & 1)]);
+        if (ragged) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (4 * quarter + r >= n_valid) v[r] = 0.f;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int nh = 0; nh < 2; ++nh)
+            o[nh][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r], p[nh][r], o[nh][t], 0, 0, 0);
+      }
+    }
+  }
+  __device__ void put(float* region, int lane) {
+    const int quarter = lane >> 4, j = lane & 15;
+    floatx4* dst = (floatx4*)region;
+#pragma unroll
+    for (int nh = 0; nh < 2; ++nh) {
+      const int row = 16 * nh + j;
+      if (kPlain) {  // register r of accumulator 4 u + e: head dim 64 u + 16 quarter + 4 r + e
+#pragma unroll
+        for (int u = 0; u < D / 64; ++u)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            floatx4 x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = o[nh][4 * u + e][r];
+            dst[(16 * u + 4 * quarter + r) * kRowTile + row] = x;
+          }
+      } else {  // register r of accumulator t: head dim 16 t + 4 quarter + r
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t) dst[(4 * t + quarter) * kRowTile + row] = o[nh][t];
+      }
+      const float sum = sum_rows16(l[nh]);
+      if (quarter == 0) {
+        region[kRowTile * D + row] = m[nh];
+        region[kRowTile * D + kRowTile + row] = sum;
+      }
+    }
+  }
+};
+
+constexpr int region_floats(int D) { return kRowTile * (D + 2); }
+
+// ---- finishing a row: the tree part, then the prefix partials ------------------------------------------------------
+__device__ inline floatx4 load4(const float* p) { return *(const floatx4*)p; }
+__device__ inline floatx4 load4(const __bf16* p) { return __builtin_convertvector(*(const bf16x4*)p, floatx4); }
+__device__ inline void store4(float* p, floatx4 x) { *(floatx4*)p = x; }
+__device__ inline void store4(__bf16* p, floatx4 x) { *(bf16x4*)p = __builtin_convertvector(x, bf16x4); }
+
+// Eight lanes per row; lane e of a row owns head dims 4 (e + 8 k) + 0 .. 3.  `merge(m, l, acc)` adds the row's prefix
+// partials.  All lanes of the wavefront come here together (rows that are not `active` have no keys and are not written).
+template <typename T, int D, typename Merge>
+__device__ inline void finish_row(const TiledArgs& a, int node, int head, int g, int base, int n, bool active, int e,
+                                  Merge merge) {
+  constexpr int K4 = D / 32;
+  uint64_t mlo = active ? a.anc_mask[2 * (size_t)node] : 0ull;
+  uint64_t mhi = active ? a.anc_mask[2 * (size_t)node + 1] : 0ull;
+  if (n < 64) mlo &= (1ull << n) - 1ull, mhi = 0ull;  // never index past the tree
+  else if (n < 128) mhi &= (1ull << (n - 64)) - 1ull;
+  const int64_t row = (int64_t)node * a.Hq + head;
+  floatx4 q[K4], acc[K4];
+#pragma unroll
+  for (int k = 0; k < K4; ++k) {
+    q[k] = active ? load4((const T*)a.q + row * D + 4 * (e + 8 * k)) : (floatx4)(0.f);
+    acc[k] = (floatx4)(0.f);
+  }
+  float m = -INFINITY, l = 0.f;
+  const T* kt = (const T*)a.k_tree + ((int64_t)base * a.Hkv + g) * D;
+  const T* vt = (const T*)a.v_tree + ((int64_t)base * a.Hkv + g) * D;
+  const int64_t node_stride = (int64_t)a.Hkv * D;
+  while (__any((mlo | mhi) != 0ull)) {
+    int jn[2];
+    bool have[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {  // two keys per step: their loads are in flight together
+      have[u] = (mlo | mhi) != 0ull;
+      jn[u] = 0;
+      if (mlo) { jn[u] = __ffsll((unsigned long long)mlo) - 1; mlo &= mlo - 1; }
+      else if (mhi) { jn[u] = 64 + __ffsll((unsigned long long)mhi) - 1; mhi &= mhi - 1; }
+    }
+    floatx4 kx[2][K4], vx[2][K4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int k = 0; k < K4; ++k) {
+        kx[u][k] = have[u] ? load4(kt + jn[u] * node_stride + 4 * (e + 8 * k)) : (floatx4)(0.f);
+        vx[u][k] = have[u] ? load4(vt + jn[u] * node_stride + 4 * (e + 8 * k)) : (floatx4)(0.f);
+      }
+    float dot[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      floatx4 d = q[0] * kx[u][0];
+#pragma unroll
+      for (int k = 1; k < K4; ++k) d += q[k] * kx[u][k];
+      float x = (d[0] + d[1]) + (d[2] + d[3]);
+      x += __shfl_xor(x, 1);
+      x += __shfl_xor(x, 2);
+      x += __shfl_xor(x, 4);
+      dot[u] = have[u] ? x : -INFINITY;
+    }
+    const float m_new = fmaxf(m, fmaxf(dot[0], dot[1]));
+    const float al = weight(m, m_new, a.c);
+    const float p0 = have[0] ? weight(dot[0], m_new, a.c) : 0.f, p1 = have[1] ? weight(dot[1], m_new, a.c) : 0.f;
+    l = l * al + (p0 + p1);
+    m = m_new;
+#pragma unroll
+    for (int k = 0; k < K4; ++k) acc[k] = acc[k] * al + (p0 * vx[0][k] + p1 * vx[1][k]);
+  }
+  if (!active) return;
+  merge(m, l, acc);
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+  for (int k = 0; k < K4; ++k) store4((T*)a.out + row * D + 4 * (e + 8 * k), acc[k] * inv);
+  if (a.lse && e == 0) a.lse[row] = l > 0.f ? m * a.scale + logf(l) : -INFINITY;
+}
+
+// One partial into a row's state; `o` points at the row's first four elements, `stride` floats to the next four.
+template <int K4>
+__device__ inline void merge_partial(float& m, float& l, floatx4 (&acc)[K4], float mc, float lc, const float* o,
+                                     int stride, int e, float c) {
+  floatx4 x[K4];
+#pragma unroll
+  for (int k = 0; k < K4; ++k) x[k] = *(const floatx4*)(o + (e + 8 * k) * stride);
+  const float m_new = fmaxf(m, mc);
+  const float al = weight(m, m_new, c), wt = weight(mc, m_new, c);
+  l = l * al + lc * wt;
+#pragma unroll
+  for (int k = 0; k < K4; ++k) acc[k] = acc[k] * al + wt * x[k];
+  m = m_new;
+}
+
+// Rows of no sequence (offsets that leave the arrays, rows past the trees): defined output.
+template <typename T, int D>
+__device__ inline void zero_row(const TiledArgs& a, int64_t row, int e) {
+#pragma unroll
+  for (int k = 0; k < D / 32; ++k) store4((T*)a.out + row * D + 4 * (e + 8 * k), (floatx4)(0.f));
+  if (a.lse && e == 0) a.lse[row] = -INFINITY;
+}
+
+// Last sequence b with cu_nodes[b] <= node (0 if there is none).
+__device__ inline int owner_of(const TiledArgs& a, int node) {
+  int lo = 0, hi = a.batch;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (a.cu_nodes[mid] <= node) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// ---- the prefix kernel ----------------------------------------------------------------------------------------------------
+template <typename T, bool kFp8, bool kPlain, int D>
+__global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
+  typedef Stager<T, kFp8, kPlain, D> Stage;
+  constexpr int kStepKeys = step_keys<T>();
+  constexpr int kRegion = region_floats(D);
+  constexpr int kStageBytes = 2 * Stage::kStepChunks * 16, kFoldBytes = kWaves * kRegion * 4;
+  __shared__ uintx4 lds[(kStageBytes > kFoldBytes ? kStageBytes : kFoldBytes) / 16];
+  __shared__ float s_ml[2][kGroupRows];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // consecutive workers (the row groups of a segment, the two ends of one) sit behind one L2
+  const int64_t wg = gridDim.x % 8 == 0 ? (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8 : (int64_t)blockIdx.x;
+
+  if (a.direct && a.status)
+    for (int b = (int)(wg * kWaves + wv); b < a.batch; b += gridDim.x * kWaves)
+      smart::tva_validate_block_table(b, a.block_table, a.prefix_len, a.max_blocks, a.block_size, a.num_blocks, a.status,
+                                      lane);
+
+  // Every wavefront plans for itself: what comes out is uniform over the workgroup.
+  Place at{-1, 0, 0};
+  int64_t u0 = 0, u1 = 1, U = 0, S = 0;
+  auto find = [&](int64_t want, bool by_segment) {
+    int64_t tu, ts;
+    scan_batch<kStepKeys>(a, lane, &tu, &ts, [&](int b0, bool, int64_t units, int64_t segs, int64_t eu, int64_t es) {
+      const int64_t first = by_segment ? es : eu, count = by_segment ? segs : units;
+      const uint64_t hit = __ballot(want >= first && want < first + count);
+      if (hit) {
+        const int i = __ffsll((unsigned long long)hit) - 1;
+        at.b = b0 + i;
+        at.units_before = smart::readlane64(eu, i);
+        at.segs_before = smart::readlane64(es, i);
+      }
+    });
+  };
+  if (a.direct) {
+    find(wg, true);
+  } else {
+    scan_batch<kStepKeys>(a, lane, &U, &S, [&](int b0, bool there, int64_t, int64_t, int64_t eu, int64_t es) {
+      if (wg == 0 && wv == 0 && there) {
+        a.plan[2 + b0 + lane] = eu;
+        a.plan[2 + a.batch + b0 + lane] = es;
+      }
+    });
+    if (S > a.seg_cap) U = 0;  // (offsets that are not a running sum: more segments than rows were counted for)
+    const int64_t W = U < (int64_t)gridDim.x ? U : (int64_t)gridDim.x;
+    if (wg == 0 && tid == 0) {
+      a.plan[0] = U;
+      a.plan[1] = W;
+    }
+    if (wg >= W) return;
+    u0 = (wg * U) / W;
+    u1 = ((wg + 1) * U) / W;
+    find(u0, false);
+  }
+
+  if (at.b >= 0) {
+    int b = at.b;
+    Shape sh = shape_of<kStepKeys>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+    while (u0 < u1) {
+      int g, group, t0, t1;
+      if (a.direct) {
+        const int local = (int)(wg - at.segs_before);
+        g = local / sh.groups;
+        group = local % sh.groups;
+        t0 = 0;
+        t1 = sh.steps;
+      } else {
+        const int64_t local = u0 - at.units_before;
+        const int seg = (int)(local / sh.steps);
+        g = seg / sh.groups;
+        group = seg % sh.groups;
+        t0 = (int)(local % sh.steps);
+        t1 = (int)min((int64_t)sh.steps, t0 + (u1 - u0));
+      }
+      b = __builtin_amdgcn_readfirstlane(b);
+      g = __builtin_amdgcn_readfirstlane(g);
+      group = __builtin_amdgcn_readfirstlane(group);
+      t0 = __builtin_amdgcn_readfirstlane(t0);
+      t1 = __builtin_amdgcn_readfirstlane(t1);
+      const int len = __builtin_amdgcn_readfirstlane(sh.len), rows = __builtin_amdgcn_readfirstlane(sh.rows);
+      const int row0 = group * kGroupRows;
+      const int group_rows = min(kGroupRows, rows - row0);
+      const int r = (group_rows + kRowTile - 1) / kRowTile;
+      // row tile, first tile of a step and stride between tiles of this wavefront
+      const int rt = r == 1 ? 0 : (r == 2 ? wv & 1 : wv);
+      const int first = r == 1 ? wv : (r == 2 ? wv >> 1 : 0);
+      const int stride = r == 1 ? 4 : (r == 2 ? 2 : 1);
+      const bool busy = rt < r;
+
+      Rows<T, kPlain, D> rowset;
+      rowset.begin(a, sh.base, g, row0 + (busy ? rt * kRowTile : 0), rows, lane);
+      const int32_t* table = a.block_table + (int64_t)b * a.max_blocks;
+      Stage st;
+      if (t0 < t1) {
+        st.load_ids(a, table, t0, len, tid);
+        st.load(a, t0, len, g, tid);
+        if (t0 + 1 < t1) st.load_ids(a, table, t0 + 1, len, tid);
+      }
+      for (int t = t0; t < t1; ++t) {
+        __syncthreads();  // everyone is done with the step before
+        st.store(lds, tid);
+        if (t + 1 < t1) {
+          st.load(a, t + 1, len, g, tid);
+          if (t + 2 < t1) st.load_ids(a, table, t + 2, len, tid);
+        }
+        __syncthreads();
+        if (busy)
+          for (int x = first; x < kTilesPerStep; x += stride) {
+            const int n_valid = len - t * kStepKeys - x * Stage::kKeys;
+            if (n_valid <= 0) break;
+            rowset.tile(lds + x * Stage::kTileChunks, lds + Stage::kStepChunks + x * Stage::kTileChunks, n_valid, a.c_stored, lane);
+          }
+      }
+      // fold: the states that share a row tile, in wavefront order
+      __syncthreads();
+      float* regions = (float*)lds;
+      rowset.put(regions + wv * kRegion, lane);
+      __syncthreads();
+      const int shared = r == 1 ? 4 : (r == 2 ? 2 : 1);  // states per row tile: regions rt, rt + r, ...
+      float* slot = a.direct ? nullptr : a.ws + (wg + at.segs_before + (int64_t)g * sh.groups + group) * slot_floats(D);
+      if (tid < r * kRowTile) {
+        const float* ml = regions + (tid >> 5) * kRegion + kRowTile * D + (tid & 31);
+        float m = ml[0], l = ml[kRowTile];
+        for (int k = 1; k < shared; ++k) {
+          const float mk = ml[k * r * kRegion], lk = ml[k * r * kRegion + kRowTile];
+          const float m_new = fmaxf(m, mk);
+          l = l * weight(m, m_new, a.c_stored) + lk * weight(mk, m_new, a.c_stored);
+          m = m_new;
+        }
+        s_ml[0][tid] = m;
+        s_ml[1][tid] = l;
+        if (slot) {
+          slot[kGroupRows * D + tid] = m * a.m_scale;  // (-inf stays -inf)
+          slot[kGroupRows * D + kGroupRows + tid] = l;
+        }
+      }
+      __syncthreads();
+      for (int i = tid; i < r * (D / 4) * kRowTile; i += kThreads) {
+        const int tile = i / (D / 4 * kRowTile), x = i % (D / 4 * kRowTile), row = x % kRowTile;
+        float* src = regions + tile * kRegion;
+        floatx4 o = ((const floatx4*)src)[x];
+        const float m = s_ml[0][tile * kRowTile + row];
+        if (shared > 1) {
+          o *= weight(src[kRowTile * D + row], m, a.c_stored);
+          for (int k = 1; k < shared; ++k)
+            o += ((const floatx4*)(src + k * r * kRegion))[x] * weight(src[k * r * kRegion + kRowTile * D + row], m, a.c_stored);
+        }
+        o *= a.o_scale;
+        if (slot) ((floatx4*)slot)[(x / kRowTile) * kGroupRows + tile * kRowTile + row] = o;
+        else ((floatx4*)src)[x] = o;  // (only this thread reads what it overwrites)
+      }
+      if (a.direct) {
+        __syncthreads();
+        const int e = tid & (kCombineLanes - 1);
+        for (int i0 = 0; i0 < group_rows; i0 += kThreads / kCombineLanes) {
+          const int i = i0 + tid / kCombineLanes;
+          const bool active = i < group_rows;
+          const int rho = row0 + (active ? i : 0);
+          const int node = sh.base + rho / a.G, head = g * a.G + rho % a.G;
+          finish_row<T, D>(a, node, head, g, sh.base, sh.n, active, e, [&](float& m, float& l, floatx4 (&acc)[D / 32]) {
+            if (t0 < t1)
+              merge_partial(m, l, acc, s_ml[0][i] * a.m_scale, s_ml[1][i],
+                            regions + (i >> 5) * kRegion + (i & 31) * 4, kRowTile * 4, e, a.c);
+          });
+        }
+        break;
+      }
+      u0 += t1 - t0;
+      // on to the next sequence with units
+      while (u0 < u1 && u0 >= at.units_before + (int64_t)a.Hkv * sh.groups * sh.steps) {
+        at.units_before += (int64_t)a.Hkv * sh.groups * sh.steps;
+        at.segs_before += (int64_t)a.Hkv * sh.groups;
+        ++b;
+        if (b >= a.batch) return;
+        sh = shape_of<kStepKeys>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+      }
+    }
+  }
+
+  if (a.direct) {  // rows nobody owns
+    for (int64_t node = wg; node < a.total_nodes; node += gridDim.x) {
+      const int b = owner_of(a, (int)node);
+      const Shape sh = shape_of<kStepKeys>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+      if (node >= sh.base && node - sh.base < sh.n) continue;
+      for (int h = tid / kCombineLanes; h < a.Hq; h += kThreads / kCombineLanes)
+        zero_row<T, D>(a, node * a.Hq + h, tid & (kCombineLanes - 1));
+    }
+  }
+}
+
+// ---- split form: merging the partials, with the tree part ----------------------------------------------------------
+// One wavefront per eight (node, head) rows.
+template <typename T, int D>
+__global__ __launch_bounds__(kThreads) void tva_tiled_finish_kernel(TiledArgs a, int step_keys_arg) {
+  const int lane = threadIdx.x & (kWave - 1), e = lane & (kCombineLanes - 1);
+  const int64_t wave = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
+  if (a.status)
+    for (int64_t b = wave; b < a.batch; b += (int64_t)gridDim.x * kWaves)
+      smart::tva_validate_block_table((int)b, a.block_table, a.prefix_len, a.max_blocks, a.block_size, a.num_blocks,
+                                      a.status, lane);
+  const int64_t n_rows = (int64_t)a.total_nodes * a.Hq;
+  const int64_t row_raw = wave * (kWave / kCombineLanes) + lane / kCombineLanes;
+  if (wave * (kWave / kCombineLanes) >= n_rows) return;
+  const bool there = row_raw < n_rows;
+  const int64_t row = there ? row_raw : n_rows - 1;
+  const int node = (int)(row / a.Hq), head = (int)(row % a.Hq), g = head / a.G;
+  int b;
+  if (a.batch <= kWave) {
+    // the offsets of the whole batch, one per lane; the wavefront's rows lie in a few consecutive nodes
+    const int cu = a.cu_nodes[min(lane, a.batch - 1)];
+    b = 0;
+    const int n0 = __builtin_amdgcn_readfirstlane(node), n1 = __builtin_amdgcn_readlane(node, kWave - 1);
+    for (int x = n0; x <= n1; ++x) {
+      const uint64_t below = __ballot(lane < a.batch && cu <= x);
+      if (node == x && below) b = 63 - __clzll((unsigned long long)below);
+    }
+  } else {
+    b = owner_of(a, node);
+  }
+  const Shape sh = step_keys_arg == 128 ? shape_of<128>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1])
+                                        : shape_of<64>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+  const int64_t U = a.plan[0], W = a.plan[1];
+  const int64_t units_before = a.plan[2 + b], segs_before = a.plan[2 + a.batch + b];
+  const bool owned = there && node >= sh.base && node - sh.base < sh.n && (sh.steps == 0 || U > 0);
+  finish_row<T, D>(a, node, head, g, sh.base, sh.n, owned, e, [&](float& m, float& l, floatx4 (&acc)[D / 32]) {
+    if (sh.steps == 0) return;
+    const int rho = (node - sh.base) * a.G + head % a.G;
+    const int local = g * sh.groups + rho / kGroupRows, r = rho % kGroupRows;
+    const int64_t ub = units_before + (int64_t)local * sh.steps, ue = ub + sh.steps - 1;
+    const int64_t w_first = ((ub + 1) * W - 1) / U, w_last = ((ue + 1) * W - 1) / U;
+    for (int64_t w = w_first; w <= w_last; ++w) {
+      const float* slot = a.ws + (w + segs_before + local) * slot_floats(D);
+      merge_partial(m, l, acc, slot[kGroupRows * D + r], slot[kGroupRows * D + kGroupRows + r], slot + r * 4,
+                    kGroupRows * 4, e, a.c);
+    }
+  });
+  if (there && !owned) zero_row<T, D>(a, row, e);
+}
+
+}  // namespace
+
+namespace smart {
+
+// Workers of the split form: two workgroups per compute unit.
+static int32_t tiled_workgroups(const smart_ctx* ctx) {
+  if (ctx->opt_workers > 0) return (int32_t)ctx->opt_workers;
+  return 2 * (ctx->num_cus > 0 ? ctx->num_cus : 256);
+}
+
+static int64_t tiled_segments(int32_t batch, int32_t total_nodes, int32_t num_q_heads, int32_t num_kv_heads) {
+  const int64_t G = num_q_heads / num_kv_heads;
+  return (int64_t)num_kv_heads * (((int64_t)total_nodes * G + kGroupRows - 1) / kGroupRows + batch);
+}
+
+void tva_tiled_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
+                         int32_t num_kv_heads, int32_t head_dim, size_t* ws_bytes, size_t* plan_bytes) {
+  const int64_t slots = tiled_workgroups(ctx) + tiled_segments(batch, total_nodes, num_q_heads, num_kv_heads) + 1;
+  *ws_bytes = (size_t)slots * slot_floats(head_dim) * sizeof(float);
+  *plan_bytes = sizeof(int64_t) * (2 + 2 * (size_t)batch);
+}
+
+// Every 16-byte chunk of a staged row, every query row and every tree row must be addressable with one load.
+bool tva_tiled_supported(const tva_params& p) {
+  const bool fp8 = p.kv_cache_dtype == SMART_FP8_E4M3;
+  const int chunk = p.dtype == SMART_F32 ? 4 : 8;                            // elements
+  const uintptr_t cache_align = fp8 ? (uintptr_t)chunk : 16;                 // bytes
+  auto aligned = [](const void* x, uintptr_t n) { return ((uintptr_t)x & (n - 1)) == 0; };
+  if (p.max_blocks_per_seq <= 0 || p.num_blocks <= 0) return false;
+  if (p.cache_block_stride % chunk || p.cache_head_stride % chunk) return false;
+  if (p.kv_layout == SMART_KV_PLAIN && p.cache_token_stride % chunk) return false;
+  return aligned(p.d_k_cache, cache_align) && aligned(p.d_v_cache, cache_align) && aligned(p.d_q, 16) &&
+         aligned(p.d_k_tree, 16) && aligned(p.d_v_tree, 16) && aligned(p.d_out, 16);
+}
+
+template <typename T, bool kFp8, bool kPlain, int D>
+static hipError_t launch_tiled(const TiledArgs& a, unsigned grid, hipStream_t stream) {
+  hipLaunchKernelGGL((tva_tiled_kernel<T, kFp8, kPlain, D>), dim3(grid), dim3(kThreads), 0, stream, a);
+  return hipGetLastError();
+}
+
+int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed) {
+  const int G = p.num_q_heads / p.num_kv_heads;
+  const bool fp8 = p.kv_cache_dtype == SMART_FP8_E4M3, f32 = p.dtype == SMART_F32;
+  const int64_t segs = tiled_segments(p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads);
+  const int64_t finish_waves = ((int64_t)p.total_nodes * p.num_q_heads + kWave / kCombineLanes - 1) / (kWave / kCombineLanes);
+  if (segs > 0x7FFFFFFF) return SMART_EINVAL;
+  // The workspace-free form: for callers that cannot allocate, for launches that are being captured (a graph must not
+  // hold a workspace that a later, larger call replaces), and when no memory is left.
+  bool direct = fixed != nullptr;
+  if (!direct) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (stream != nullptr && hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+    direct = capture != hipStreamCaptureStatusNone;
+  }
+  if (!direct) {
+    size_t ws_bytes, plan_bytes;
+    tva_tiled_workspace(ctx, p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads, p.head_dim, &ws_bytes, &plan_bytes);
+    const int32_t rc = ensure_workspace(ctx, stream, ws_bytes, plan_bytes);
+    if (rc == SMART_ENOMEM) direct = true;
+    else if (rc != SMART_OK) return rc;
+  }
+  TiledArgs a;
+  a.q = p.d_q;
+  a.k_tree = p.d_k_tree;
+  a.v_tree = p.d_v_tree;
+  a.k_cache = p.d_k_cache;
+  a.v_cache = p.d_v_cache;
+  a.block_table = p.d_block_table;
+  a.prefix_len = p.d_prefix_len;
+  a.cu_nodes = p.d_cu_nodes;
+  a.anc_mask = p.d_anc_mask;
+  a.out = p.d_out;
+  a.lse = p.d_lse;
+  a.status = p.d_status;
+  a.ws = direct ? nullptr : (float*)ctx->ws;
+  a.plan = direct ? nullptr : (int64_t*)ctx->plan;
+  a.block_stride = p.cache_block_stride;
+  a.head_stride = p.cache_head_stride;
+  a.token_stride = p.cache_token_stride;
+  a.seg_cap = segs;
+  a.batch = p.batch;
+  a.total_nodes = p.total_nodes;
+  a.Hq = p.num_q_heads;
+  a.Hkv = p.num_kv_heads;
+  a.G = G;
+  a.block_size = p.block_size;
+  a.max_blocks = p.max_blocks_per_seq;
+  a.num_blocks = p.num_blocks;
+  a.direct = direct ? 1 : 0;
+  // t8 / d by the high word of t8 * (floor(2^32 / d) + 1): exact for t8 < 2^28 and d <= 8
+  const uint32_t per8 = (uint32_t)p.block_size / 8;
+  a.block8_magic = per8 == 1 ? 0u : (uint32_t)((1ull << 32) / per8) + 1u;
+  a.scale = p.softmax_scale;
+  a.c = p.softmax_scale * kLog2e;
+  a.c_stored = a.c * (fp8 ? p.k_scale : 1.f);
+  a.m_scale = fp8 ? p.k_scale : 1.f;
+  a.o_scale = fp8 ? p.v_scale : 1.f;
+
+  int32_t rc = profile_begin(ctx, stream);
+  if (rc != SMART_OK) return rc;
+  const unsigned grid = direct ? (unsigned)segs : (unsigned)tiled_workgroups(ctx);
+  const bool plain = p.kv_layout == SMART_KV_PLAIN;
+  hipError_t err = hipErrorInvalidValue;
+#define SMART_TILED(T, FP8, PLAIN) \
+  err = p.head_dim == 128 ? launch_tiled<T, FP8, PLAIN, 128>(a, grid, stream) : launch_tiled<T, FP8, PLAIN, 64>(a, grid, stream)
+  if (f32) {
+    if (fp8) { if (plain) SMART_TILED(float, true, true); else SMART_TILED(float, true, false); }
+    else { if (plain) SMART_TILED(float, false, true); else SMART_TILED(float, false, false); }
+  } else {
+    if (fp8) { if (plain) SMART_TILED(__bf16, true, true); else SMART_TILED(__bf16, true, false); }
+    else { if (plain) SMART_TILED(__bf16, false, true); else SMART_TILED(__bf16, false, false); }
+  }
+#undef SMART_TILED
+  SMART_HIP_CHECK(err);
+  rc = profile_end(ctx, stream);
+  if (rc != SMART_OK || direct) return rc;
+  const dim3 fgrid((unsigned)((finish_waves + kWaves - 1) / kWaves));
+  if (f32) {
+    if (p.head_dim == 128) hipLaunchKernelGGL((tva_tiled_finish_kernel<float, 128>), fgrid, dim3(kThreads), 0, stream, a, step_keys<float>());
+    else hipLaunchKernelGGL((tva_tiled_finish_kernel<float, 64>), fgrid, dim3(kThreads), 0, stream, a, step_keys<float>());
+  } else {
+    if (p.head_dim == 128) hipLaunchKernelGGL((tva_tiled_finish_kernel<__bf16, 128>), fgrid, dim3(kThreads), 0, stream, a, step_keys<__bf16>());
+    else hipLaunchKernelGGL((tva_tiled_finish_kernel<__bf16, 64>), fgrid, dim3(kThreads), 0, stream, a, step_keys<__bf16>());
+  }
+  SMART_HIP_CHECK(hipGetLastError());
+  return SMART_OK;
+}
+
+}  // namespace smart

@@ -1,0 +1,197 @@
+"""The tiled matrix-core attention path (every type, layout, head dim and block size besides bf16 / interleaved /
+128 / 16) against the general kernel, which walks the keys of one row at a time in fp32, over the forms both accept.
+
+Tolerances.  fp32: both sides sum the same products in binary32 in different orders; a dot product of D <= 128
+terms and a weighted sum of at most 1300 keys move by a few 1e-7 of the output's scale, the repository's 1e-5 bounds
+them.  bf16: both sides hold scores, probabilities and sums in binary32 (the tiled path splits a probability into three
+bf16 values, exactly), so the outputs differ where a binary32 difference of that size crosses a rounding boundary:
+one bf16 unit, 2^-7 of the element at most.  lse: fp32 on both sides, |lse| < 16."""
+import numpy as np
+import pytest
+
+from paper_2604_09731_amd import binding as B
+from paper_2604_09731_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+ROW_SIZES = [1, 31, 32, 33, 64, 65, 127, 128]        # nodes; at G = 1 rows: edges of the 32-row tiles and 128-row groups
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return B.SmartTree(0)
+
+
+class Inputs:
+    def __init__(self, sizes, lens, Hq, Hkv, D, bs, dtype, layout, fp8=False, pad=0, seed=3, spare_columns=1):
+        import torch
+        g = np.random.default_rng(seed)
+        t = lambda a, dt=None: torch.from_numpy(np.ascontiguousarray(a, dt)).cuda()
+        self.layout, self.bs, self.D = layout, bs, D
+        sizes, lens = np.asarray(sizes), np.asarray(lens)
+        self.cu_host = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        N = int(self.cu_host[-1])
+        self.parent = t(np.concatenate([W.random_tree(int(n), g) for n in sizes]), np.int32)
+        self.cu, self.len = t(self.cu_host), t(lens, np.int32)
+        blocks = (lens + bs - 1) // bs
+        nb = int(blocks.sum()) + 2
+        perm = g.permutation(nb)
+        table = np.full((len(sizes), max(1, int(blocks.max())) + spare_columns), -1, np.int32)
+        at = 0
+        for b, m in enumerate(blocks):
+            table[b, :m] = perm[at:at + m]
+            at += int(m)
+        self.table = t(table)
+        tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+        rnd = lambda *s: t(g.standard_normal(s, dtype=np.float32)).to(tdt)
+        self.q, self.k_tree, self.v_tree = rnd(N, Hq, D), rnd(N, Hkv, D), rnd(N, Hkv, D)
+        self.kw = dict(k_scale=0.05, v_scale=0.25) if fp8 else {}
+        owned = np.zeros((nb, bs), bool)
+        for b, m in enumerate(lens):
+            for i in range(int(m)):
+                owned[table[b, i // bs], i % bs] = True
+        caches = []
+        for _ in range(2):
+            x = g.standard_normal((nb, Hkv, bs, D), dtype=np.float32) * (20 if fp8 else 1)
+            x[~owned[:, None, :].repeat(Hkv, 1)] = np.nan                      # nothing may read an unowned slot
+            x = t(x)
+            x = x.clamp(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8) if fp8 else x.to(tdt)
+            caches.append(x)
+        k, v = caches
+        if layout == B.SMART_KV_INTERLEAVED:
+            k = k.reshape(nb, Hkv, bs, D // 8, 8).permute(0, 1, 3, 2, 4).reshape(nb, Hkv, 1, bs * D)
+            v = v.reshape(nb, Hkv, bs // 8, 8, D).permute(0, 1, 2, 4, 3).reshape(nb, Hkv, 1, bs * D)
+        # pad: rows, pages and blocks further apart than they are long
+        def spread(c):
+            big = torch.zeros((c.shape[0], c.shape[1] + (1 if pad else 0), c.shape[2], c.shape[3] + pad), dtype=c.dtype, device="cuda")
+            view = big[:, :c.shape[1], :, :c.shape[3]]
+            view.copy_(c)
+            return view
+        self.k, self.v = spread(k), spread(v)
+
+    def run(self, lib, general=False, static=False, cu=None, table=None, status=None, out=None):
+        import torch
+        _, _, _, mask, _ = lib.tree_pack(self.cu, self.parent, self.len)
+        lib.set_option(B.SMART_OPT_TVA_FORCE_GENERAL, int(general))
+        try:
+            r = lib.tree_verify_attention(self.q, self.k_tree, self.v_tree, self.k, self.v,
+                                          self.table if table is None else table, self.len, self.cu if cu is None else cu,
+                                          mask, 1.0 / np.sqrt(self.D), self.layout, block_size=self.bs, want_lse=True,
+                                          static=static, status=status, out=out, **self.kw)
+        finally:
+            lib.set_option(B.SMART_OPT_TVA_FORCE_GENERAL, 0)
+        torch.cuda.synchronize()
+        return r
+
+
+def assert_close(got, ref):
+    import torch
+    for x, y in zip(got, ref):
+        x, y = x.double(), y.double()
+        assert torch.equal(torch.isinf(x), torch.isinf(y))
+        assert not torch.isnan(x).any()
+        fin = torch.isfinite(y)
+        if not fin.any():
+            continue
+        tol = 1e-5 * max(1.0, float(y[fin].abs().max()))
+        if got[0].dtype == torch.bfloat16 and x.ndim == 3:
+            assert bool(((x - y).abs() <= tol + 2.0 ** -7 * y.abs()).all())
+        else:
+            assert float((x - y)[fin].abs().max()) <= tol
+
+
+FORMS = [(dt, fp8, lay, D) for dt in ("f32", "bf16") for fp8 in (False, True)
+         for lay in (B.SMART_KV_PLAIN, B.SMART_KV_INTERLEAVED) for D in (64, 128)]
+
+
+@pytest.mark.parametrize("dtype,fp8,layout,D", FORMS)
+def test_every_form_equals_the_general_kernel(lib, dtype, fp8, layout, D):
+    """Tile, step and row-group edges: lengths around 16, 32, 64, 128 keys, tree sizes around 32 and 128 rows, block
+    sizes that do and do not divide a tile; the split and the workspace-free form."""
+    lens = [0, 1, 15, 17, 64, 65, 127, 300]
+    for bs, Hq, Hkv, pad in ((8, 3, 3, 0), (24, 8, 2, 8), (64, 7, 1, 16)):
+        x = Inputs(ROW_SIZES, lens, Hq, Hkv, D, bs, dtype, layout, fp8, pad=pad if layout == B.SMART_KV_PLAIN else 0)
+        ref = x.run(lib, general=True)
+        assert_close(x.run(lib), ref)
+        assert_close(x.run(lib, static=True), ref)
+
+
+@pytest.mark.parametrize("batch", [1, 64, 65, 130])
+@pytest.mark.parametrize("workers", [0, 1, 3])
+def test_batches_and_shares(lib, batch, workers):
+    """Batches around the 64 sequences one scan holds, empty trees and prefixes among them; shares of one worker that
+    run over many segments."""
+    g = np.random.default_rng(batch)
+    sizes, lens = g.integers(0, 9, batch), g.integers(0, 260, batch)
+    sizes[0] = 5
+    x = Inputs(sizes, lens, 8, 2, 64, 16, "f32", B.SMART_KV_PLAIN)
+    lib.set_option(B.SMART_OPT_TVA_WORKERS, workers)
+    try:
+        assert_close(x.run(lib), x.run(lib, general=True))
+    finally:
+        lib.set_option(B.SMART_OPT_TVA_WORKERS, 0)
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_what_the_general_kernel_does_with_odd_inputs(lib, static, dtype):
+    import torch
+    x = Inputs([5, 20, 70, 3, 9], [100, 333, 64, 0, 50], 8, 2, 128, 16, dtype, B.SMART_KV_PLAIN)
+    # rows past the trees (total_nodes as a capacity) and ranges that leave the arrays: zero, lse -inf
+    N = int(x.cu_host[-1])
+    for bad in (x.cu_host - [0, 0, 0, 0, 0, 9], [0, 5, 25, 95, 98, N + 4], [-1, 5, 25, 95, 98, N], [N + 1] * 6):
+        cu = torch.tensor(np.asarray(bad), dtype=torch.int32, device="cuda")
+        ref = x.run(lib, general=True, cu=cu, out=torch.full_like(x.q, 7.0))
+        assert_close(x.run(lib, cu=cu, static=static, out=torch.full_like(x.q, 7.0)), ref)
+    # block-table entries outside the cache: read as the nearest block, reported
+    table = x.table.clone()
+    table[1, 3], table[2, 3], table[0, 7] = -5, 10 ** 6, 10 ** 6
+    table[x.table < 0] = -9
+    status = [torch.full((5,), 77, dtype=torch.int32, device="cuda") for _ in range(2)]
+    x.k.nan_to_num_(0.0)
+    x.v.nan_to_num_(0.0)
+    ref = x.run(lib, general=True, table=table, status=status[0])
+    assert_close(x.run(lib, table=table, status=status[1], static=static), ref)
+    assert status[0].tolist() == status[1].tolist() == [0, 1, 1, 0, 0]
+    # what one node holds reaches only the nodes below it; infinite scores
+    x = Inputs([40], [90], 8, 2, 128, 16, dtype, B.SMART_KV_PLAIN)
+    x.v_tree[39] = float("nan")
+    x.k_tree[38] = float("inf")
+    x.q[37, 0] = float("-inf")
+    x.k[int(x.table[0, 2]), 1, 3] = float("inf")
+    got, ref = x.run(lib, static=static), x.run(lib, general=True)
+    for a, b in zip(got, ref):
+        assert torch.equal(torch.isnan(a), torch.isnan(b))
+        both = torch.isfinite(a) & torch.isfinite(b)
+        assert torch.equal(torch.isfinite(a), torch.isfinite(b)) and both.any()
+
+
+def test_unaligned_rows_run_the_general_kernel(lib):
+    """Strides that put rows off the 16-byte chunks the tiled path loads: the same call, the general kernel's bits."""
+    import torch
+    x = Inputs([9, 30], [100, 77], 8, 2, 64, 16, "bf16", B.SMART_KV_PLAIN, pad=2)
+    a, b = x.run(lib), x.run(lib, general=True)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+def test_a_captured_call_holds_no_workspace(lib):
+    """A graph of the call stays right after a larger call has replaced the context's workspace."""
+    import torch
+    own = B.SmartTree(0)
+    x = Inputs([9, 30, 4], [400, 77, 129], 8, 2, 64, 16, "f32", B.SMART_KV_PLAIN)
+    _, _, _, mask, _ = own.tree_pack(x.cu, x.parent, x.len)
+    out = torch.empty_like(x.q)
+    call = lambda: own.tree_verify_attention(x.q, x.k_tree, x.v_tree, x.k, x.v, x.table, x.len, x.cu, mask, 0.125, x.layout,
+                                             block_size=16, out=out)
+    call()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    big = Inputs([100] * 70, [40] * 70, 8, 2, 128, 16, "bf16", B.SMART_KV_PLAIN)
+    ref = x.run(own, general=True)[0]
+    for _ in range(3):
+        big.run(own)
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_close((out,), (ref,))
