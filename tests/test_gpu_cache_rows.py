@@ -1,0 +1,86 @@
+"""kv_cache_write over token runs: prompts that start anywhere in the token list, runs broken by skipped and
+out-of-range slots, permuted single tokens, tails shorter than a slot group; every type and layout, byte for byte."""
+import numpy as np
+import pytest
+
+from oracle import fp8 as F
+from oracle import kv_layout as KL
+from paper_2604_09731_amd import binding as B
+from paper_2604_09731_amd import workloads as W
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _slots(kind, n, bs, nb, rng):
+    if kind == "prompts":        # ragged prompts in permuted blocks
+        perm, out, at = rng.permutation(nb), [], 0
+        while len(out) < n:
+            m = int(rng.integers(1, 3 * bs))
+            out += [int(perm[(at + i // bs) % nb]) * bs + i % bs for i in range(m)]
+            at += (m + bs - 1) // bs
+        return np.array(out[:n], np.int64)
+    if kind == "offset":         # one run that starts inside a slot group
+        return np.arange(3, 3 + n, dtype=np.int64) % (nb * bs)
+    if kind == "reversed":
+        return np.arange(n, dtype=np.int64)[::-1].copy()
+    s = np.arange(n, dtype=np.int64)                       # "holes"
+    s[rng.integers(0, n, max(1, n // 9))] = -1
+    s[rng.integers(0, n, max(1, n // 20))] = nb * bs + 5
+    return s
+
+
+@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("f32", False), ("bf16", True), ("f32", True)])
+@pytest.mark.parametrize("layout", [B.SMART_KV_PLAIN, B.SMART_KV_INTERLEAVED])
+@pytest.mark.parametrize("kind", ["prompts", "offset", "reversed", "holes"])
+def test_token_runs(dtype, fp8, layout, kind):
+    import torch
+    lib = B.SmartTree(0)
+    rng = np.random.default_rng(5)
+    for n, Hkv, D, bs in ((1, 2, 64, 8), (7, 1, 8, 16), (8, 3, 64, 24), (9, 8, 128, 16), (61, 5, 128, 64), (200, 2, 72, 8)):
+        nb = 260 // bs + 30
+        k_src, v_src = (W._normal(1, i, (n, Hkv, D), 1.0, dtype) for i in (1, 2))
+        slots = _slots(kind, n, bs, nb, rng)
+        keep = {}
+        for t, s in enumerate(slots):                       # a slot named twice: no defined winner, so name it once
+            if 0 <= s < nb * bs and s in keep:
+                slots[t] = -1
+            keep[s] = t
+        f = lambda x: (W.bf16_bits_to_f32(x) if dtype == "bf16" else x).astype(np.float32)
+        val = [F.encode(f(x) / np.float32(sc)) for x, sc in ((k_src, 0.03), (v_src, 0.011))] if fp8 else [k_src, v_src]
+        plain = [np.zeros((nb, Hkv, bs, D), v.dtype) for v in val]
+        for t, s in enumerate(slots):
+            if 0 <= s < nb * bs:
+                for p, v in zip(plain, val):
+                    p[s // bs, :, s % bs] = v[t]
+        tk, tv = H.torch_elems(k_src, dtype, "cuda"), H.torch_elems(v_src, dtype, "cuda")
+        cdt = torch.uint8 if fp8 else tk.dtype
+        pad = 8 * D                                          # pages and blocks further apart than they are long
+        big = [torch.zeros((nb, Hkv + 1, bs * D + pad), dtype=cdt, device="cuda") for _ in range(2)]
+        kc, vc = big
+        args = (torch.from_numpy(slots).cuda(), kc, vc, layout, bs, nb, kc.stride(0), kc.stride(1))
+        if fp8:
+            lib.kv_cache_write_fp8(tk, tv, *args, 0.03, 0.011, token_stride=D)
+        else:
+            lib.kv_cache_write(tk, tv, *args, token_stride=D)
+        for c, p, which in zip(big, plain, "kv"):
+            got = c.cpu()
+            got = (got if fp8 else got.view(torch.int16 if dtype == "bf16" else torch.float32)).numpy().view(p.dtype)
+            want = p.reshape(nb, Hkv, bs * D) if layout == B.SMART_KV_PLAIN else KL.interleave_plain_cache(p, which)
+            assert np.array_equal(got[:, :Hkv, :bs * D], want.reshape(nb, Hkv, bs * D)), (n, Hkv, D, bs, which)
+            assert not got[:, Hkv:].any() and not got[:, :, bs * D:].any()
+
+
+def test_rows_off_the_chunks():
+    """A source that is not aligned to 16 bytes, and a token stride that is no multiple of 8: the same bytes."""
+    import torch
+    lib = B.SmartTree(0)
+    n, Hkv, D, bs, nb = 20, 2, 64, 16, 4
+    src = torch.randn(n * Hkv * D + 1, device="cuda").to(torch.bfloat16)
+    k, v = src[1:].view(n, Hkv, D), src[:-1].view(n, Hkv, D)
+    slots = torch.arange(n, device="cuda")
+    for stride in (D, D + 2):
+        kc, vc = (torch.zeros((nb, Hkv, bs, stride), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        lib.kv_cache_write(k, v, slots, kc, vc, B.SMART_KV_PLAIN, bs, nb, kc.stride(0), kc.stride(1), token_stride=stride)
+        for c, x in ((kc, k), (vc, v)):
+            assert torch.equal(c.permute(0, 2, 1, 3).reshape(nb * bs, Hkv, stride)[:n, :, :D], x)
