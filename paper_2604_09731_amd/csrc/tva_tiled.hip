@@ -5,12 +5,14 @@
 // keys, so a workgroup takes a row group of up to 128 rows and streams the keys past it: every K/V byte leaves HBM once
 // per row group, instead of once per (node, head) as in the general kernel, and the products run on the matrix cores.
 //
-//   * A step is 16 KB x D / 128 x 4 of K and V: four tiles of 32 keys (bf16) or 16 keys (fp32).  The 256 threads load a
-//     step with 16-byte loads into registers while the step before is being computed, and put it into LDS in between;
-//     two workgroups per compute unit cover each other's barriers.
-//   * Four wavefronts: with up to 32 rows each takes one tile of the step, with up to 64 rows two wavefronts share a
-//     row tile, with more every wavefront has 32 rows of its own and takes all four tiles.  The states that share a row
-//     tile are folded through LDS at the end of a piece, in a fixed order.
+//   * A step is four tiles of 32 keys (bf16) or 16 keys (fp32): 64 KB of K and V at head dim 128.  The 512 threads of a
+//     workgroup load a step with 16-byte loads into registers while the step before is being computed, and put it into
+//     the other of two LDS stages; one barrier per step.  (Eight wavefronts and not twice four: half the staging
+//     registers per thread.  With four the compiler spilled, and reloading a spill waits for every load in flight:
+//     the prefix kernel of the first workload below took 152 us instead of 98.)
+//   * Eight wavefronts, two per SIMD.  With up to 32 rows four of them take one tile of the step each, with up to 64 rows
+//     four wavefronts share a row tile, with more two do.  The states that share a row tile are folded through LDS
+//     at the end of a piece, in a fixed order.
 //   * Scores are kept transposed (keys x rows): a row's softmax stays inside a lane (and its partner lanes), and the
 //     probabilities come out in the operand layout of the second product.
 //   * Plain pages are staged row by row with their 16-byte chunks permuted by row, so that the score product's reads
@@ -28,8 +30,9 @@
 // on the vector ALUs in fp32 by walking the set bits, so what other nodes hold never enters a row.
 //
 // Measured against the general kernel (whole call): bf16 plain pages, batch 16, 32 / 8 heads of 128, prefixes of
-// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 0.20 ms; fp32 plain pages, batch 8, 8 / 2 heads of 64, prefixes of
-// 128 .. 1536, 15-node trees 778 -> 29 us, and its error against binary64 falls from 5.6e-7 to 3.1e-7 (shorter sums).
+// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 108 us (prefix kernel 91, of which 62 are the MFMAs of its fullest
+// workgroups; finishing kernel 18); fp32 plain pages, batch 8, 8 / 2 heads of 64, prefixes of 128 .. 1536, 15-node trees
+// 778 -> 24 us, and its error against binary64 falls from 5.6e-7 to 3.1e-7 (shorter sums).
 //
 // The paper (Sec. 1) has the target model verify the tree in one forward pass; this is the attention sub-step.
 #include <math.h>
@@ -51,8 +54,9 @@ typedef __attribute__((ext_vector_type(2))) uint32_t uintx2;
 typedef __attribute__((ext_vector_type(2))) float floatx2;
 
 constexpr int kWave = 64;
-constexpr int kWaves = 4;
+constexpr int kWaves = 8;
 constexpr int kThreads = kWave * kWaves;
+constexpr int kFinishWaves = 4;
 constexpr int kRowTile = 32;
 constexpr int kGroupRows = 128;      // rows of a row group: four row tiles
 constexpr int kTilesPerStep = 4;
@@ -87,8 +91,7 @@ struct TiledArgs {
   int64_t block_stride, head_stride, token_stride;
   int64_t seg_cap;  // segments the slots have room for
   int32_t batch, total_nodes, Hq, Hkv, G, block_size, max_blocks, num_blocks;
-  int32_t direct;
-  uint32_t block8_magic;  // token / 8 / (block_size / 8) by multiplication; 0: block_size is 8
+  uint32_t block8_magic;  // token / 8 / (block_size / 8) by multiplication
   float scale;
   float c;         // softmax scale in powers of two (log2 e folded in)
   float c_stored;  // the same against stored key values: c k_scale
@@ -96,13 +99,24 @@ struct TiledArgs {
   float o_scale;   // = v_scale
 };
 
+// The unit the split form cuts into shares is a cost: a step of a row group with r row tiles counts kStepCost[r].  The
+// two wavefronts of a SIMD have one tile of a step between them with one row tile, two with two, four with three or four
+// (the third's SIMD partner idles); up to two tiles of bf16 a step takes what its loads take (1.9 us measured), with
+// four what its products take (3.4 us); the fp32 products always set the pace.  Against shares of equal step counts the
+// prefix kernel of the first workload above takes 91 us instead of 98.
+template <typename T> struct StepCost;
+template <> struct StepCost<__bf16> { static constexpr int one = 4, two = 4, four = 7; };
+template <> struct StepCost<float> { static constexpr int one = 4, two = 7, four = 14; };
+
 // What a call uses of one sequence: lengths and sizes clamped to what the arrays hold.  A range that leaves the arrays
 // has no rows (nothing of it is read).
 struct Shape {
   int len, base, n, rows, groups, steps;
+  int cost_last;       // of a step of the last row group (the others: StepCost::four)
+  int64_t full, head;  // units of a full row group, of a kv head
 };
 
-template <int kStepKeys>
+template <typename T>
 __device__ inline Shape shape_of(const TiledArgs& a, int len, int base, int next) {
   Shape s;
   const int cap = a.max_blocks * a.block_size;
@@ -114,7 +128,11 @@ __device__ inline Shape shape_of(const TiledArgs& a, int len, int base, int next
   s.n = (int)n;
   s.rows = s.n * a.G;
   s.groups = (s.rows + kGroupRows - 1) / kGroupRows;
-  s.steps = s.groups > 0 ? (s.len + kStepKeys - 1) / kStepKeys : 0;
+  s.steps = s.groups > 0 ? (s.len + step_keys<T>() - 1) / step_keys<T>() : 0;
+  const int last = s.rows - (s.groups - 1) * kGroupRows;
+  s.cost_last = last <= kRowTile ? StepCost<T>::one : (last <= 2 * kRowTile ? StepCost<T>::two : StepCost<T>::four);
+  s.full = (int64_t)s.steps * StepCost<T>::four;
+  s.head = s.groups > 0 ? (s.groups - 1) * s.full + (int64_t)s.steps * s.cost_last : 0;
   return s;
 }
 
@@ -124,26 +142,30 @@ struct Place {
   int64_t units_before, segs_before;
 };
 
-// One wavefront goes through the batch, 64 sequences at a time.  `want` is a unit (kSegments = false) or a segment;
-// returns false if it is not there.  Totals come back as well when the whole batch was gone through (`all`).
-template <int kStepKeys, typename Visit>
-__device__ inline void scan_batch(const TiledArgs& a, int lane, int64_t* total_units, int64_t* total_segs, Visit visit) {
-  int64_t before_u = 0, before_s = 0;
+// One wavefront goes through the batch, 64 sequences at a time: visit(first sequence, lane has one, its units and
+// segments, units and segments before it).
+template <typename T, typename Visit>
+__device__ inline void scan_batch(const TiledArgs& a, int lane, int64_t* total_units, int64_t* total_segs,
+                                  int64_t* total_steps, Visit visit) {
+  int64_t before_u = 0, before_s = 0, before_t = 0;
   for (int b0 = 0; b0 < a.batch; b0 += kWave) {
     const int b = min(b0 + lane, a.batch - 1);
-    Shape s = shape_of<kStepKeys>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+    const Shape s = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
     const bool there = b0 + lane < a.batch;
     const int64_t segs = there ? (int64_t)s.groups * a.Hkv : 0;
-    const int64_t units = segs * s.steps;
-    int64_t tu, ts;
+    const int64_t units = there ? s.head * a.Hkv : 0;
+    int64_t tu, ts, tt;
+    smart::wave_excl_scan(segs * s.steps, lane, &tt);
     const int64_t eu = smart::wave_excl_scan(units, lane, &tu) + before_u;
     const int64_t es = smart::wave_excl_scan(segs, lane, &ts) + before_s;
     visit(b0, there, units, segs, eu, es);
     before_u += tu;
     before_s += ts;
+    before_t += tt;
   }
   *total_units = before_u;
   *total_segs = before_s;
+  *total_steps = before_t;
 }
 
 __device__ inline int clamp_block(int b, int num_blocks) { return b < 0 ? 0 : (b >= num_blocks ? num_blocks - 1 : b); }
@@ -259,8 +281,7 @@ struct Stager {
     return kPlain ? token_k(step, key, len) : min(step * kStepKeys + key, (len - 1) & ~7);
   }
   __device__ static int block_of(const TiledArgs& a, int token) {
-    const uint32_t t8 = (uint32_t)token >> 3;
-    return a.block8_magic ? (int)__umulhi(t8, a.block8_magic) : (int)t8;
+    return (int)__umulhi(((uint32_t)token >> 3) << 1, a.block8_magic);
   }
 
   __device__ void load_ids(const TiledArgs& a, const int32_t* row, int step, int len, int tid) {
@@ -294,11 +315,34 @@ struct Stager {
       }
     }
   }
-  __device__ void store(uintx4* lds, int tid) {
+  // `n_valid`: keys of this step inside the prefix.  Values past it become zero (their slots may hold anything, NaN
+  // included, and they are multiplied by probabilities of zero); their scores are masked.
+  __device__ void store(uintx4* lds, int tid, int n_valid) {
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       lds[i * kThreads + tid] = staged(k[i], T());
       lds[kStepChunks + i * kThreads + tid] = staged(v[i], T());
+    }
+    if (n_valid >= kStepKeys) return;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int p = i * kThreads + tid;
+      uintx4& x = lds[kStepChunks + p];
+      if (kPlain) {
+        if (key_of_v(p) >= n_valid) x = (uintx4)(0u);
+      } else if (sizeof(T) == 2) {  // eight keys of one head dim
+        const int keep = n_valid - key_of_v(p);
+        uintx4 y = x;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) y[w] = keep >= 2 * w + 2 ? y[w] : (keep == 2 * w + 1 ? y[w] & 0xFFFFu : 0u);
+        x = y;
+      } else {  // four keys of one head dim
+        const int keep = n_valid - key_of_v(p) - 4 * (p & 1);
+        uintx4 y = x;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) y[w] = w < keep ? y[w] : 0u;
+        x = y;
+      }
     }
   }
 };
@@ -334,16 +378,22 @@ struct Rows<__bf16, kPlain, D> {
 
   __device__ void tile(const uintx4* kt, const uintx4* vt, int n_valid, float c, int lane) {
     const int h = lane >> 5, j = lane & 31;
-    floatx16 s = (floatx16)(0.f);
     const int key = key_of_row(j);
+    bf16x8 kx[D / 16];  // all operands of a product are requested before its first MFMA
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks) {
       const int chunk = 2 * ks + h;
-      const int at = kPlain ? key * kRowChunks + (chunk ^ swizzle<__bf16, D>(key)) : chunk * 32 + key;
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kt[at]), q[ks], s, 0, 0, 0);
+      kx[ks] = __builtin_bit_cast(bf16x8, kt[kPlain ? key * kRowChunks + (chunk ^ swizzle<__bf16, D>(key)) : chunk * 32 + key]);
     }
-    const bool ragged = n_valid < 32;
-    if (ragged) {
+    floatx16 s = (floatx16)(0.f);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx[ks], q[ks], s, 0, 0, 0);
+    bf16x8 v[2][D / 32];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int jt = 0; jt < D / 32; ++jt) v[kk][jt] = value_operand(vt, jt, kk, lane);
+    if (n_valid < 32) {
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         if (key_of_row(8 * (r >> 2) + 4 * h + (r & 3)) >= n_valid) s[r] = -INFINITY;
@@ -360,39 +410,24 @@ struct Rows<__bf16, kPlain, D> {
       for (int jt = 0; jt < D / 32; ++jt) o[jt] *= alpha;
       m = m_new;
     }
-    // p = hi + mid + lo exactly: three bf16 values hold the 24 bits of a binary32
-    bf16x8 hi[2], mid[2], lo[2];
-    float sum = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
       floatx8 p;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        p[e] = weight(s[8 * kk + e], m, c);
-        sum += p[e];
-      }
-      hi[kk] = __builtin_convertvector(p, bf16x8);
-      const floatx8 r1 = p - __builtin_convertvector(hi[kk], floatx8);
-      mid[kk] = __builtin_convertvector(r1, bf16x8);
-      lo[kk] = __builtin_convertvector(r1 - __builtin_convertvector(mid[kk], floatx8), bf16x8);
+      for (int e = 0; e < 8; ++e) p[e] = weight(s[8 * kk + e], m, c);
+      l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      // p = hi + mid + lo exactly: three bf16 values hold the 24 bits of a binary32
+      const bf16x8 hi = __builtin_convertvector(p, bf16x8);
+      const floatx8 r1 = p - __builtin_convertvector(hi, floatx8);
+      const bf16x8 mid = __builtin_convertvector(r1, bf16x8);
+      const bf16x8 lo = __builtin_convertvector(r1 - __builtin_convertvector(mid, floatx8), bf16x8);
+#pragma unroll
+      for (int jt = 0; jt < D / 32; ++jt) o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[kk][jt], hi, o[jt], 0, 0, 0);
+#pragma unroll
+      for (int jt = 0; jt < D / 32; ++jt) o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[kk][jt], mid, o[jt], 0, 0, 0);
+#pragma unroll
+      for (int jt = 0; jt < D / 32; ++jt) o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[kk][jt], lo, o[jt], 0, 0, 0);
     }
-    l += sum;
-#pragma unroll
-    for (int jt = 0; jt < D / 32; ++jt)
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        bf16x8 v = value_operand(vt, jt, kk, lane);
-        if (ragged) {  // unowned slots may hold anything, NaN included
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int token = kPlain ? 16 * kk + 8 * (e >> 2) + 4 * h + (e & 3) : 16 * kk + 8 * h + e;
-            if (token >= n_valid) v[e] = (__bf16)0.f;
-          }
-        }
-        o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, hi[kk], o[jt], 0, 0, 0);
-        o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, mid[kk], o[jt], 0, 0, 0);
-        o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, lo[kk], o[jt], 0, 0, 0);
-      }
   }
   // Lane (h, j): head dim 32 jt + j of the eight keys whose probabilities the lane's half holds in registers 8 kk ...
   __device__ static bf16x8 value_operand(const uintx4* vt, int jt, int kk, int lane) {
@@ -510,8 +545,7 @@ struct Rows<float, kPlain, D> {
         const int token = 4 * quarter + r;
 #pragma unroll
         for (int u = 0; u < D / 64; ++u) {  // lane i: head dims 64 u + 4 i + e
-          floatx4 v = __builtin_bit_cast(floatx4, vt[token * kRowChunks + ((16 * u + i) ^ swizzle<float, D>(token))]);
-          if (ragged && token >= n_valid) v = (floatx4)(0.f);
+          const floatx4 v = __builtin_bit_cast(floatx4, vt[token * kRowChunks + ((16 * u + i) ^ swizzle<float, D>(token))]);
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -522,12 +556,7 @@ struct Rows<float, kPlain, D> {
     } else {
 #pragma unroll
       for (int t = 0; t < D / 16; ++t) {  // lane i: head dim 16 t + i of the quarter's four keys
-        floatx4 v = __builtin_bit_cast(floatx4, vt[((quarter >> 1) * D + 16 * t + i) * 2 + (quarter & 1)]);
-        if (ragged) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (4 * quarter + r >= n_valid) v[r] = 0.f;
-        }
+        const floatx4 v = __builtin_bit_cast(floatx4, vt[((quarter >> 1) * D + 16 * t + i) * 2 + (quarter & 1)]);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -568,92 +597,118 @@ struct Rows<float, kPlain, D> {
 constexpr int region_floats(int D) { return kRowTile * (D + 2); }
 
 // ---- finishing a row: the tree part, then the prefix partials ------------------------------------------------------
-__device__ inline floatx4 load4(const float* p) { return *(const floatx4*)p; }
-__device__ inline floatx4 load4(const __bf16* p) { return __builtin_convertvector(*(const bf16x4*)p, floatx4); }
+// Four elements as they lie in memory (converted where they are used: half the registers for bf16).
+template <typename T> struct Four { typedef floatx4 type; };
+template <> struct Four<__bf16> { typedef bf16x4 type; };
+__device__ inline floatx4 widen(floatx4 x) { return x; }
+__device__ inline floatx4 widen(bf16x4 x) { return __builtin_convertvector(x, floatx4); }
 __device__ inline void store4(float* p, floatx4 x) { *(floatx4*)p = x; }
 __device__ inline void store4(__bf16* p, floatx4 x) { *(bf16x4*)p = __builtin_convertvector(x, bf16x4); }
 
-// Eight lanes per row; lane e of a row owns head dims 4 (e + 8 k) + 0 .. 3.  `merge(m, l, acc)` adds the row's prefix
-// partials.  All lanes of the wavefront come here together (rows that are not `active` have no keys and are not written).
-template <typename T, int D, typename Merge>
-__device__ inline void finish_row(const TiledArgs& a, int node, int head, int g, int base, int n, bool active, int e,
-                                  Merge merge) {
-  constexpr int K4 = D / 32;
-  uint64_t mlo = active ? a.anc_mask[2 * (size_t)node] : 0ull;
-  uint64_t mhi = active ? a.anc_mask[2 * (size_t)node + 1] : 0ull;
-  if (n < 64) mlo &= (1ull << n) - 1ull, mhi = 0ull;  // never index past the tree
-  else if (n < 128) mhi &= (1ull << (n - 64)) - 1ull;
-  const int64_t row = (int64_t)node * a.Hq + head;
-  floatx4 q[K4], acc[K4];
-#pragma unroll
-  for (int k = 0; k < K4; ++k) {
-    q[k] = active ? load4((const T*)a.q + row * D + 4 * (e + 8 * k)) : (floatx4)(0.f);
-    acc[k] = (floatx4)(0.f);
-  }
+// Eight lanes per row; lane e of a row owns head dims 4 (e + 8 k) + 0 .. 3.  A row is a chain of memory round trips, so
+// what does not depend on each other is requested together: the mask and the query while the plan is looked up, the
+// next two tree keys while the last two are used, two partials at a time.  All lanes of a wavefront go through this
+// together (rows that are not `active` have no keys and are not written).
+template <typename T, int D>
+struct Finish {
+  static constexpr int K4 = D / 32;
+  typedef typename Four<T>::type Raw;
+  uint64_t mlo, mhi;
+  Raw q[K4];
+  floatx4 acc[K4];
   float m = -INFINITY, l = 0.f;
-  const T* kt = (const T*)a.k_tree + ((int64_t)base * a.Hkv + g) * D;
-  const T* vt = (const T*)a.v_tree + ((int64_t)base * a.Hkv + g) * D;
-  const int64_t node_stride = (int64_t)a.Hkv * D;
-  while (__any((mlo | mhi) != 0ull)) {
-    int jn[2];
+
+  __device__ void request(const TiledArgs& a, int node, int head, bool active, int e) {
+    mlo = active ? a.anc_mask[2 * (size_t)node] : 0ull;
+    mhi = active ? a.anc_mask[2 * (size_t)node + 1] : 0ull;
+    const T* qp = (const T*)a.q + ((int64_t)node * a.Hq + head) * D;
+#pragma unroll
+    for (int k = 0; k < K4; ++k) q[k] = active ? *(const Raw*)(qp + 4 * (e + 8 * k)) : Raw();
+#pragma unroll
+    for (int k = 0; k < K4; ++k) acc[k] = (floatx4)(0.f);
+  }
+
+  struct Keys {
+    Raw k[2][K4], v[2][K4];
     bool have[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {  // two keys per step: their loads are in flight together
-      have[u] = (mlo | mhi) != 0ull;
-      jn[u] = 0;
-      if (mlo) { jn[u] = __ffsll((unsigned long long)mlo) - 1; mlo &= mlo - 1; }
-      else if (mhi) { jn[u] = 64 + __ffsll((unsigned long long)mhi) - 1; mhi &= mhi - 1; }
-    }
-    floatx4 kx[2][K4], vx[2][K4];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int k = 0; k < K4; ++k) {
-        kx[u][k] = have[u] ? load4(kt + jn[u] * node_stride + 4 * (e + 8 * k)) : (floatx4)(0.f);
-        vx[u][k] = have[u] ? load4(vt + jn[u] * node_stride + 4 * (e + 8 * k)) : (floatx4)(0.f);
-      }
-    float dot[2];
+  };
+  __device__ Keys next_keys(const T* kt, const T* vt, int64_t node_stride, int e) {
+    Keys x;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      floatx4 d = q[0] * kx[u][0];
+      x.have[u] = (mlo | mhi) != 0ull;
+      int j = 0;
+      if (mlo) { j = __ffsll((unsigned long long)mlo) - 1; mlo &= mlo - 1; }
+      else if (mhi) { j = 64 + __ffsll((unsigned long long)mhi) - 1; mhi &= mhi - 1; }
 #pragma unroll
-      for (int k = 1; k < K4; ++k) d += q[k] * kx[u][k];
-      float x = (d[0] + d[1]) + (d[2] + d[3]);
-      x += __shfl_xor(x, 1);
-      x += __shfl_xor(x, 2);
-      x += __shfl_xor(x, 4);
-      dot[u] = have[u] ? x : -INFINITY;
+      for (int k = 0; k < K4; ++k) {
+        x.k[u][k] = x.have[u] ? *(const Raw*)(kt + j * node_stride + 4 * (e + 8 * k)) : Raw();
+        x.v[u][k] = x.have[u] ? *(const Raw*)(vt + j * node_stride + 4 * (e + 8 * k)) : Raw();
+      }
     }
-    const float m_new = fmaxf(m, fmaxf(dot[0], dot[1]));
-    const float al = weight(m, m_new, a.c);
-    const float p0 = have[0] ? weight(dot[0], m_new, a.c) : 0.f, p1 = have[1] ? weight(dot[1], m_new, a.c) : 0.f;
-    l = l * al + (p0 + p1);
-    m = m_new;
-#pragma unroll
-    for (int k = 0; k < K4; ++k) acc[k] = acc[k] * al + (p0 * vx[0][k] + p1 * vx[1][k]);
+    return x;
   }
-  if (!active) return;
-  merge(m, l, acc);
-  const float inv = l > 0.f ? 1.f / l : 0.f;
+  // The tree part: the set bits of the row's ancestor mask, lowest first, of a tree of n nodes.
+  __device__ void tree(const TiledArgs& a, int g, int base, int n, int e) {
+    if (n < 64) mlo &= (1ull << n) - 1ull, mhi = 0ull;  // never index past the tree
+    else if (n < 128) mhi &= (1ull << (n - 64)) - 1ull;
+    const T* kt = (const T*)a.k_tree + ((int64_t)base * a.Hkv + g) * D;
+    const T* vt = (const T*)a.v_tree + ((int64_t)base * a.Hkv + g) * D;
+    const int64_t node_stride = (int64_t)a.Hkv * D;
+    Keys cur = next_keys(kt, vt, node_stride, e);
+    while (__any(cur.have[0])) {
+      const Keys nxt = next_keys(kt, vt, node_stride, e);
+      float dot[2];
 #pragma unroll
-  for (int k = 0; k < K4; ++k) store4((T*)a.out + row * D + 4 * (e + 8 * k), acc[k] * inv);
-  if (a.lse && e == 0) a.lse[row] = l > 0.f ? m * a.scale + logf(l) : -INFINITY;
-}
-
-// One partial into a row's state; `o` points at the row's first four elements, `stride` floats to the next four.
-template <int K4>
-__device__ inline void merge_partial(float& m, float& l, floatx4 (&acc)[K4], float mc, float lc, const float* o,
-                                     int stride, int e, float c) {
-  floatx4 x[K4];
+      for (int u = 0; u < 2; ++u) {
+        floatx4 d = widen(q[0]) * widen(cur.k[u][0]);
 #pragma unroll
-  for (int k = 0; k < K4; ++k) x[k] = *(const floatx4*)(o + (e + 8 * k) * stride);
-  const float m_new = fmaxf(m, mc);
-  const float al = weight(m, m_new, c), wt = weight(mc, m_new, c);
-  l = l * al + lc * wt;
+        for (int k = 1; k < K4; ++k) d += widen(q[k]) * widen(cur.k[u][k]);
+        float x = (d[0] + d[1]) + (d[2] + d[3]);
+        x += __shfl_xor(x, 1);
+        x += __shfl_xor(x, 2);
+        x += __shfl_xor(x, 4);
+        dot[u] = cur.have[u] ? x : -INFINITY;
+      }
+      const float m_new = fmaxf(m, fmaxf(dot[0], dot[1]));
+      const float al = weight(m, m_new, a.c);
+      const float p0 = cur.have[0] ? weight(dot[0], m_new, a.c) : 0.f, p1 = cur.have[1] ? weight(dot[1], m_new, a.c) : 0.f;
+      l = l * al + (p0 + p1);
+      m = m_new;
 #pragma unroll
-  for (int k = 0; k < K4; ++k) acc[k] = acc[k] * al + wt * x[k];
-  m = m_new;
-}
+      for (int k = 0; k < K4; ++k) acc[k] = acc[k] * al + (p0 * widen(cur.v[0][k]) + p1 * widen(cur.v[1][k]));
+      cur = nxt;
+    }
+  }
+  // One partial: its max, sum and the row's O, which lies in groups of four elements `stride` floats apart.
+  struct Partial {
+    float m, l;
+    floatx4 o[K4];
+  };
+  __device__ static Partial fetch(float mc, float lc, const float* o, int stride, int e) {
+    Partial p;
+    p.m = mc;
+    p.l = lc;
+#pragma unroll
+    for (int k = 0; k < K4; ++k) p.o[k] = *(const floatx4*)(o + (e + 8 * k) * stride);
+    return p;
+  }
+  __device__ void merge(const Partial& p, float c) {
+    const float m_new = fmaxf(m, p.m);
+    const float al = weight(m, m_new, c), wt = weight(p.m, m_new, c);
+    l = l * al + p.l * wt;
+#pragma unroll
+    for (int k = 0; k < K4; ++k) acc[k] = acc[k] * al + wt * p.o[k];
+    m = m_new;
+  }
+  __device__ void write(const TiledArgs& a, int node, int head, int e) const {
+    const int64_t row = (int64_t)node * a.Hq + head;
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+    for (int k = 0; k < K4; ++k) store4((T*)a.out + row * D + 4 * (e + 8 * k), acc[k] * inv);
+    if (a.lse && e == 0) a.lse[row] = l > 0.f ? m * a.scale + logf(l) : -INFINITY;
+  }
+};
 
 // Rows of no sequence (offsets that leave the arrays, rows past the trees): defined output.
 template <typename T, int D>
@@ -674,12 +729,12 @@ __device__ inline int owner_of(const TiledArgs& a, int node) {
 }
 
 // ---- the prefix kernel ----------------------------------------------------------------------------------------------------
-template <typename T, bool kFp8, bool kPlain, int D>
+template <typename T, bool kFp8, bool kPlain, int D, bool kDirect>
 __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
   typedef Stager<T, kFp8, kPlain, D> Stage;
   constexpr int kStepKeys = step_keys<T>();
   constexpr int kRegion = region_floats(D);
-  constexpr int kStageBytes = 2 * Stage::kStepChunks * 16, kFoldBytes = kWaves * kRegion * 4;
+  constexpr int kStageBytes = 2 * 2 * Stage::kStepChunks * 16, kFoldBytes = kWaves * kRegion * 4;
   __shared__ uintx4 lds[(kStageBytes > kFoldBytes ? kStageBytes : kFoldBytes) / 16];
   __shared__ float s_ml[2][kGroupRows];
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -687,17 +742,17 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
   // consecutive workers (the row groups of a segment, the two ends of one) sit behind one L2
   const int64_t wg = gridDim.x % 8 == 0 ? (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8 : (int64_t)blockIdx.x;
 
-  if (a.direct && a.status)
+  if (kDirect && a.status)
     for (int b = (int)(wg * kWaves + wv); b < a.batch; b += gridDim.x * kWaves)
       smart::tva_validate_block_table(b, a.block_table, a.prefix_len, a.max_blocks, a.block_size, a.num_blocks, a.status,
                                       lane);
 
   // Every wavefront plans for itself: what comes out is uniform over the workgroup.
   Place at{-1, 0, 0};
-  int64_t u0 = 0, u1 = 1, U = 0, S = 0;
+  int64_t u0 = 0, u1 = 1, U = 0, S = 0, steps = 0;
   auto find = [&](int64_t want, bool by_segment) {
-    int64_t tu, ts;
-    scan_batch<kStepKeys>(a, lane, &tu, &ts, [&](int b0, bool, int64_t units, int64_t segs, int64_t eu, int64_t es) {
+    int64_t tu, ts, tt;
+    scan_batch<T>(a, lane, &tu, &ts, &tt, [&](int b0, bool, int64_t units, int64_t segs, int64_t eu, int64_t es) {
       const int64_t first = by_segment ? es : eu, count = by_segment ? segs : units;
       const uint64_t hit = __ballot(want >= first && want < first + count);
       if (hit) {
@@ -708,17 +763,17 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
       }
     });
   };
-  if (a.direct) {
+  if (kDirect) {
     find(wg, true);
   } else {
-    scan_batch<kStepKeys>(a, lane, &U, &S, [&](int b0, bool there, int64_t, int64_t, int64_t eu, int64_t es) {
+    scan_batch<T>(a, lane, &U, &S, &steps, [&](int b0, bool there, int64_t, int64_t, int64_t eu, int64_t es) {
       if (wg == 0 && wv == 0 && there) {
         a.plan[2 + b0 + lane] = eu;
         a.plan[2 + a.batch + b0 + lane] = es;
       }
     });
     if (S > a.seg_cap) U = 0;  // (offsets that are not a running sum: more segments than rows were counted for)
-    const int64_t W = U < (int64_t)gridDim.x ? U : (int64_t)gridDim.x;
+    const int64_t W = U == 0 ? 0 : (steps < (int64_t)gridDim.x ? steps : (int64_t)gridDim.x);
     if (wg == 0 && tid == 0) {
       a.plan[0] = U;
       a.plan[1] = W;
@@ -731,22 +786,27 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
 
   if (at.b >= 0) {
     int b = at.b;
-    Shape sh = shape_of<kStepKeys>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+    Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
     while (u0 < u1) {
       int g, group, t0, t1;
-      if (a.direct) {
+      if (kDirect) {
         const int local = (int)(wg - at.segs_before);
         g = local / sh.groups;
         group = local % sh.groups;
         t0 = 0;
         t1 = sh.steps;
       } else {
+        // (a share boundary inside a step goes down to the step's beginning)
         const int64_t local = u0 - at.units_before;
-        const int seg = (int)(local / sh.steps);
-        g = seg / sh.groups;
-        group = seg % sh.groups;
-        t0 = (int)(local % sh.steps);
-        t1 = (int)min((int64_t)sh.steps, t0 + (u1 - u0));
+        g = (int)(local / sh.head);
+        const int64_t in_head = local - g * sh.head;
+        group = (int)min(in_head / sh.full, (int64_t)sh.groups - 1);
+        const int64_t off = in_head - group * sh.full;
+        const int cost = group < sh.groups - 1 ? StepCost<T>::four : sh.cost_last;
+        const int64_t left = (int64_t)sh.steps * cost - off;  // units to the segment's end
+        t0 = (int)(off / cost);
+        t1 = u1 - u0 >= left ? sh.steps : (int)((off + u1 - u0) / cost);
+        u0 = min(u1, u0 + left);
       }
       b = __builtin_amdgcn_readfirstlane(b);
       g = __builtin_amdgcn_readfirstlane(g);
@@ -757,11 +817,11 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
       const int row0 = group * kGroupRows;
       const int group_rows = min(kGroupRows, rows - row0);
       const int r = (group_rows + kRowTile - 1) / kRowTile;
-      // row tile, first tile of a step and stride between tiles of this wavefront
-      const int rt = r == 1 ? 0 : (r == 2 ? wv & 1 : wv);
-      const int first = r == 1 ? wv : (r == 2 ? wv >> 1 : 0);
-      const int stride = r == 1 ? 4 : (r == 2 ? 2 : 1);
-      const bool busy = rt < r;
+      // row tile, first tile of a step and stride between tiles of this wavefront; wavefronts rt, rt + apart, ... share one
+      const int apart = r >= 3 ? 4 : r;
+      const int shared = r >= 3 ? 2 : 4;  // wavefronts per row tile
+      const int rt = wv & (apart - 1), first = r == 1 ? wv : (r == 2 ? wv >> 1 : wv >> 2);
+      const bool busy = rt < r && first < kTilesPerStep;
 
       Rows<T, kPlain, D> rowset;
       rowset.begin(a, sh.base, g, row0 + (busy ? rt * kRowTile : 0), rows, lane);
@@ -772,19 +832,20 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
         st.load(a, t0, len, g, tid);
         if (t0 + 1 < t1) st.load_ids(a, table, t0 + 1, len, tid);
       }
+      __syncthreads();  // the piece before is done with the LDS
       for (int t = t0; t < t1; ++t) {
-        __syncthreads();  // everyone is done with the step before
-        st.store(lds, tid);
+        uintx4* stage = lds + (t & 1) * (2 * Stage::kStepChunks);
+        st.store(stage, tid, len - t * kStepKeys);
         if (t + 1 < t1) {
           st.load(a, t + 1, len, g, tid);
           if (t + 2 < t1) st.load_ids(a, table, t + 2, len, tid);
         }
-        __syncthreads();
+        __syncthreads();  // the stage is full, and everyone is done with the other one
         if (busy)
-          for (int x = first; x < kTilesPerStep; x += stride) {
+          for (int x = first; x < kTilesPerStep; x += shared) {
             const int n_valid = len - t * kStepKeys - x * Stage::kKeys;
             if (n_valid <= 0) break;
-            rowset.tile(lds + x * Stage::kTileChunks, lds + Stage::kStepChunks + x * Stage::kTileChunks, n_valid, a.c_stored, lane);
+            rowset.tile(stage + x * Stage::kTileChunks, stage + Stage::kStepChunks + x * Stage::kTileChunks, n_valid, a.c_stored, lane);
           }
       }
       // fold: the states that share a row tile, in wavefront order
@@ -792,13 +853,12 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
       float* regions = (float*)lds;
       rowset.put(regions + wv * kRegion, lane);
       __syncthreads();
-      const int shared = r == 1 ? 4 : (r == 2 ? 2 : 1);  // states per row tile: regions rt, rt + r, ...
-      float* slot = a.direct ? nullptr : a.ws + (wg + at.segs_before + (int64_t)g * sh.groups + group) * slot_floats(D);
+      float* slot = kDirect ? nullptr : a.ws + (wg + at.segs_before + (int64_t)g * sh.groups + group) * slot_floats(D);
       if (tid < r * kRowTile) {
         const float* ml = regions + (tid >> 5) * kRegion + kRowTile * D + (tid & 31);
         float m = ml[0], l = ml[kRowTile];
         for (int k = 1; k < shared; ++k) {
-          const float mk = ml[k * r * kRegion], lk = ml[k * r * kRegion + kRowTile];
+          const float mk = ml[k * apart * kRegion], lk = ml[k * apart * kRegion + kRowTile];
           const float m_new = fmaxf(m, mk);
           l = l * weight(m, m_new, a.c_stored) + lk * weight(mk, m_new, a.c_stored);
           m = m_new;
@@ -816,16 +876,14 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
         float* src = regions + tile * kRegion;
         floatx4 o = ((const floatx4*)src)[x];
         const float m = s_ml[0][tile * kRowTile + row];
-        if (shared > 1) {
-          o *= weight(src[kRowTile * D + row], m, a.c_stored);
-          for (int k = 1; k < shared; ++k)
-            o += ((const floatx4*)(src + k * r * kRegion))[x] * weight(src[k * r * kRegion + kRowTile * D + row], m, a.c_stored);
-        }
+        o *= weight(src[kRowTile * D + row], m, a.c_stored);
+        for (int k = 1; k < shared; ++k)
+          o += ((const floatx4*)(src + k * apart * kRegion))[x] * weight(src[k * apart * kRegion + kRowTile * D + row], m, a.c_stored);
         o *= a.o_scale;
         if (slot) ((floatx4*)slot)[(x / kRowTile) * kGroupRows + tile * kRowTile + row] = o;
         else ((floatx4*)src)[x] = o;  // (only this thread reads what it overwrites)
       }
-      if (a.direct) {
+      if (kDirect) {
         __syncthreads();
         const int e = tid & (kCombineLanes - 1);
         for (int i0 = 0; i0 < group_rows; i0 += kThreads / kCombineLanes) {
@@ -833,30 +891,31 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
           const bool active = i < group_rows;
           const int rho = row0 + (active ? i : 0);
           const int node = sh.base + rho / a.G, head = g * a.G + rho % a.G;
-          finish_row<T, D>(a, node, head, g, sh.base, sh.n, active, e, [&](float& m, float& l, floatx4 (&acc)[D / 32]) {
-            if (t0 < t1)
-              merge_partial(m, l, acc, s_ml[0][i] * a.m_scale, s_ml[1][i],
-                            regions + (i >> 5) * kRegion + (i & 31) * 4, kRowTile * 4, e, a.c);
-          });
+          Finish<T, D> f;
+          f.request(a, node, head, active, e);
+          f.tree(a, g, sh.base, sh.n, e);
+          if (active && t0 < t1)
+            f.merge(f.fetch(s_ml[0][i] * a.m_scale, s_ml[1][i], regions + (i >> 5) * kRegion + (i & 31) * 4, kRowTile * 4, e),
+                    a.c);
+          if (active) f.write(a, node, head, e);
         }
         break;
       }
-      u0 += t1 - t0;
       // on to the next sequence with units
-      while (u0 < u1 && u0 >= at.units_before + (int64_t)a.Hkv * sh.groups * sh.steps) {
-        at.units_before += (int64_t)a.Hkv * sh.groups * sh.steps;
+      while (u0 < u1 && u0 >= at.units_before + a.Hkv * sh.head) {
+        at.units_before += a.Hkv * sh.head;
         at.segs_before += (int64_t)a.Hkv * sh.groups;
         ++b;
         if (b >= a.batch) return;
-        sh = shape_of<kStepKeys>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+        sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
       }
     }
   }
 
-  if (a.direct) {  // rows nobody owns
+  if (kDirect) {  // rows nobody owns
     for (int64_t node = wg; node < a.total_nodes; node += gridDim.x) {
       const int b = owner_of(a, (int)node);
-      const Shape sh = shape_of<kStepKeys>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+      const Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
       if (node >= sh.base && node - sh.base < sh.n) continue;
       for (int h = tid / kCombineLanes; h < a.Hq; h += kThreads / kCombineLanes)
         zero_row<T, D>(a, node * a.Hq + h, tid & (kCombineLanes - 1));
@@ -867,11 +926,11 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
 // ---- split form: merging the partials, with the tree part ----------------------------------------------------------
 // One wavefront per eight (node, head) rows.
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void tva_tiled_finish_kernel(TiledArgs a, int step_keys_arg) {
+__global__ __launch_bounds__(kFinishWaves * kWave, 2) void tva_tiled_finish_kernel(TiledArgs a) {
   const int lane = threadIdx.x & (kWave - 1), e = lane & (kCombineLanes - 1);
-  const int64_t wave = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
+  const int64_t wave = (int64_t)blockIdx.x * kFinishWaves + (threadIdx.x >> 6);
   if (a.status)
-    for (int64_t b = wave; b < a.batch; b += (int64_t)gridDim.x * kWaves)
+    for (int64_t b = wave; b < a.batch; b += (int64_t)gridDim.x * kFinishWaves)
       smart::tva_validate_block_table((int)b, a.block_table, a.prefix_len, a.max_blocks, a.block_size, a.num_blocks,
                                       a.status, lane);
   const int64_t n_rows = (int64_t)a.total_nodes * a.Hq;
@@ -880,6 +939,8 @@ __global__ __launch_bounds__(kThreads) void tva_tiled_finish_kernel(TiledArgs a,
   const bool there = row_raw < n_rows;
   const int64_t row = there ? row_raw : n_rows - 1;
   const int node = (int)(row / a.Hq), head = (int)(row % a.Hq), g = head / a.G;
+  Finish<T, D> f;
+  f.request(a, node, head, there, e);
   int b;
   if (a.batch <= kWave) {
     // the offsets of the whole batch, one per lane; the wavefront's rows lie in a few consecutive nodes
@@ -893,23 +954,33 @@ __global__ __launch_bounds__(kThreads) void tva_tiled_finish_kernel(TiledArgs a,
   } else {
     b = owner_of(a, node);
   }
-  const Shape sh = step_keys_arg == 128 ? shape_of<128>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1])
-                                        : shape_of<64>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+  const Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
   const int64_t U = a.plan[0], W = a.plan[1];
   const int64_t units_before = a.plan[2 + b], segs_before = a.plan[2 + a.batch + b];
   const bool owned = there && node >= sh.base && node - sh.base < sh.n && (sh.steps == 0 || U > 0);
-  finish_row<T, D>(a, node, head, g, sh.base, sh.n, owned, e, [&](float& m, float& l, floatx4 (&acc)[D / 32]) {
-    if (sh.steps == 0) return;
+  f.tree(a, g, sh.base, owned ? sh.n : 0, e);
+  if (owned && sh.steps > 0) {
     const int rho = (node - sh.base) * a.G + head % a.G;
-    const int local = g * sh.groups + rho / kGroupRows, r = rho % kGroupRows;
-    const int64_t ub = units_before + (int64_t)local * sh.steps, ue = ub + sh.steps - 1;
+    const int group = rho / kGroupRows, r = rho % kGroupRows, local = g * sh.groups + group;
+    const int64_t ub = units_before + g * sh.head + group * sh.full;
+    const int64_t ue = ub + (group < sh.groups - 1 ? sh.full : (int64_t)sh.steps * sh.cost_last) - 1;
     const int64_t w_first = ((ub + 1) * W - 1) / U, w_last = ((ue + 1) * W - 1) / U;
-    for (int64_t w = w_first; w <= w_last; ++w) {
+    auto partial = [&](int64_t w) {
       const float* slot = a.ws + (w + segs_before + local) * slot_floats(D);
-      merge_partial(m, l, acc, slot[kGroupRows * D + r], slot[kGroupRows * D + kGroupRows + r], slot + r * 4,
-                    kGroupRows * 4, e, a.c);
+      return f.fetch(slot[kGroupRows * D + r], slot[kGroupRows * D + kGroupRows + r], slot + r * 4, kGroupRows * 4, e);
+    };
+    for (int64_t w = w_first; w <= w_last; w += 2) {
+      const auto p0 = partial(w);
+      if (w < w_last) {
+        const auto p1 = partial(w + 1);
+        f.merge(p0, a.c);
+        f.merge(p1, a.c);
+      } else {
+        f.merge(p0, a.c);
+      }
     }
-  });
+  }
+  if (owned) f.write(a, node, head, e);
   if (there && !owned) zero_row<T, D>(a, row, e);
 }
 
@@ -917,10 +988,10 @@ __global__ __launch_bounds__(kThreads) void tva_tiled_finish_kernel(TiledArgs a,
 
 namespace smart {
 
-// Workers of the split form: two workgroups per compute unit.
+// Workers of the split form: one workgroup per compute unit.
 static int32_t tiled_workgroups(const smart_ctx* ctx) {
   if (ctx->opt_workers > 0) return (int32_t)ctx->opt_workers;
-  return 2 * (ctx->num_cus > 0 ? ctx->num_cus : 256);
+  return ctx->num_cus > 0 ? ctx->num_cus : 256;
 }
 
 static int64_t tiled_segments(int32_t batch, int32_t total_nodes, int32_t num_q_heads, int32_t num_kv_heads) {
@@ -949,8 +1020,11 @@ bool tva_tiled_supported(const tva_params& p) {
 }
 
 template <typename T, bool kFp8, bool kPlain, int D>
-static hipError_t launch_tiled(const TiledArgs& a, unsigned grid, hipStream_t stream) {
-  hipLaunchKernelGGL((tva_tiled_kernel<T, kFp8, kPlain, D>), dim3(grid), dim3(kThreads), 0, stream, a);
+static hipError_t launch_tiled(const TiledArgs& a, bool direct, unsigned grid, hipStream_t stream) {
+  if (direct)
+    hipLaunchKernelGGL((tva_tiled_kernel<T, kFp8, kPlain, D, true>), dim3(grid), dim3(kThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((tva_tiled_kernel<T, kFp8, kPlain, D, false>), dim3(grid), dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -1002,10 +1076,8 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   a.block_size = p.block_size;
   a.max_blocks = p.max_blocks_per_seq;
   a.num_blocks = p.num_blocks;
-  a.direct = direct ? 1 : 0;
-  // t8 / d by the high word of t8 * (floor(2^32 / d) + 1): exact for t8 < 2^28 and d <= 8
-  const uint32_t per8 = (uint32_t)p.block_size / 8;
-  a.block8_magic = per8 == 1 ? 0u : (uint32_t)((1ull << 32) / per8) + 1u;
+  // t8 / d as the high word of 2 t8 * (floor(2^31 / d) + 1): exact for t8 < 2^28 and d <= 8
+  a.block8_magic = (uint32_t)((1ull << 31) / ((uint32_t)p.block_size / 8)) + 1u;
   a.scale = p.softmax_scale;
   a.c = p.softmax_scale * kLog2e;
   a.c_stored = a.c * (fp8 ? p.k_scale : 1.f);
@@ -1018,7 +1090,7 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   const bool plain = p.kv_layout == SMART_KV_PLAIN;
   hipError_t err = hipErrorInvalidValue;
 #define SMART_TILED(T, FP8, PLAIN) \
-  err = p.head_dim == 128 ? launch_tiled<T, FP8, PLAIN, 128>(a, grid, stream) : launch_tiled<T, FP8, PLAIN, 64>(a, grid, stream)
+  err = p.head_dim == 128 ? launch_tiled<T, FP8, PLAIN, 128>(a, direct, grid, stream) : launch_tiled<T, FP8, PLAIN, 64>(a, direct, grid, stream)
   if (f32) {
     if (fp8) { if (plain) SMART_TILED(float, true, true); else SMART_TILED(float, true, false); }
     else { if (plain) SMART_TILED(float, false, true); else SMART_TILED(float, false, false); }
@@ -1030,13 +1102,13 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   SMART_HIP_CHECK(err);
   rc = profile_end(ctx, stream);
   if (rc != SMART_OK || direct) return rc;
-  const dim3 fgrid((unsigned)((finish_waves + kWaves - 1) / kWaves));
+  const dim3 fgrid((unsigned)((finish_waves + kFinishWaves - 1) / kFinishWaves));
   if (f32) {
-    if (p.head_dim == 128) hipLaunchKernelGGL((tva_tiled_finish_kernel<float, 128>), fgrid, dim3(kThreads), 0, stream, a, step_keys<float>());
-    else hipLaunchKernelGGL((tva_tiled_finish_kernel<float, 64>), fgrid, dim3(kThreads), 0, stream, a, step_keys<float>());
+    if (p.head_dim == 128) hipLaunchKernelGGL((tva_tiled_finish_kernel<float, 128>), fgrid, dim3(kFinishWaves * kWave), 0, stream, a);
+    else hipLaunchKernelGGL((tva_tiled_finish_kernel<float, 64>), fgrid, dim3(kFinishWaves * kWave), 0, stream, a);
   } else {
-    if (p.head_dim == 128) hipLaunchKernelGGL((tva_tiled_finish_kernel<__bf16, 128>), fgrid, dim3(kThreads), 0, stream, a, step_keys<__bf16>());
-    else hipLaunchKernelGGL((tva_tiled_finish_kernel<__bf16, 64>), fgrid, dim3(kThreads), 0, stream, a, step_keys<__bf16>());
+    if (p.head_dim == 128) hipLaunchKernelGGL((tva_tiled_finish_kernel<__bf16, 128>), fgrid, dim3(kFinishWaves * kWave), 0, stream, a);
+    else hipLaunchKernelGGL((tva_tiled_finish_kernel<__bf16, 64>), fgrid, dim3(kFinishWaves * kWave), 0, stream, a);
   }
   SMART_HIP_CHECK(hipGetLastError());
   return SMART_OK;
