@@ -482,8 +482,8 @@ __device__ inline TilePages tile_pages(const MainArgs& a, const int32_t* bt_row,
   return tp;
 }
 
-// A load of cache contents that this call reads once (kStream: marked nontemporal) or that another wavefront or a
-// later row group reads again (left to the caches).
+// A load of cache contents that this call reads once (kStream: marked nontemporal) or that another wavefront reads
+// again (left to the caches).
 template <bool kStream, typename T>
 __device__ inline T stream_load(const T* p) {
   if (kStream) return __builtin_nontemporal_load(p);
@@ -523,21 +523,28 @@ __device__ inline void load_v(bf16x8 (&v)[2][4], const MainArgs& a, const TilePa
 typedef __attribute__((ext_vector_type(2))) uint32_t fp8x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
-template <bool kStream>
-__device__ inline void load_k(fp8x8 (&k)[8], const MainArgs& a, const TilePages& tp, int lane) {
+// Where this lane's vectors of a tile begin (K: 256 bytes from one k step to the next; V: from one d tile to the next).
+__device__ inline const uint8_t* k_vectors(const MainArgs& a, const TilePages& tp, int lane) {
   const int h = lane >> 5, j = lane & 31;
   const int64_t mask = -(int64_t)(j >> 4);
   const int64_t page = tp.page0 ^ ((tp.page0 ^ tp.page1) & mask);
-  const uint8_t* kp = (const uint8_t*)a.k_cache + page + (h * 16 + sigma(j & 15)) * 8;
+  return (const uint8_t*)a.k_cache + page + (h * 16 + sigma(j & 15)) * 8;
+}
+__device__ inline const uint8_t* v_vectors(const MainArgs& a, int64_t page, int lane) {
+  return (const uint8_t*)a.v_cache + page + ((lane >> 5) * kD + (lane & 31)) * 8;
+}
+
+template <bool kStream>
+__device__ inline void load_k(fp8x8 (&k)[8], const MainArgs& a, const TilePages& tp, int lane) {
+  const uint8_t* kp = k_vectors(a, tp, lane);
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) k[ks] = stream_load<kStream>((const fp8x8*)(kp + ks * 256));
 }
 
 template <bool kStream>
 __device__ inline void load_v(fp8x8 (&v)[2][4], const MainArgs& a, const TilePages& tp, int lane) {
-  const int h = lane >> 5, j = lane & 31;
-  const uint8_t* vp0 = (const uint8_t*)a.v_cache + tp.page0 + (h * kD + j) * 8;
-  const uint8_t* vp1 = (const uint8_t*)a.v_cache + tp.page1 + (h * kD + j) * 8;
+  const uint8_t* vp0 = v_vectors(a, tp.page0, lane);
+  const uint8_t* vp1 = v_vectors(a, tp.page1, lane);
 #pragma unroll
   for (int jt = 0; jt < 4; ++jt) {
     v[0][jt] = stream_load<kStream>((const fp8x8*)(vp0 + jt * 256));
@@ -738,7 +745,7 @@ __device__ inline void small_last_tile(SmallState& S, Raw (&k)[8], Raw (&v)[2][4
   }
 }
 
-// kStream: no other wavefront and no later row group reads these tiles (see stream_load).
+// kStream: no other wavefront reads these tiles (see stream_load).
 template <typename Raw = bf16x8, bool kStream = true>
 __device__ inline void small_segment(SmallState& S, const MainArgs& a, int b, int g, int base, int t0,
                                      int t1, const SeqInfo si, int lane, int row0 = 0) {
@@ -1062,21 +1069,117 @@ __device__ inline void small_worker(const MainArgs& a, int64_t w, ClassPlan& cp,
   }
 }
 
-// ---- fp8 cache: every sequence in row groups of up to 64 rows, streamed into registers ---------
+// ---- fp8 cache: trees of up to 64 rows per kv head, streamed into registers ---------------------
 //
-// The same register-direct stream as class 0.  A row group with more than 32 rows has two row
-// tiles, one per half of the workgroup.
+// The same register-direct stream as class 0, with one or two row tiles per wavefront.
 
-// A row group of two row tiles: wavefronts 0..3 carry row tile 0, wavefronts 4..7 row tile 1, each
-// half cuts the piece's tiles four ways and both halves stream the SAME tiles (the second request
-// for a tile is served by the caches, HBM sees it once).  Their states meet in LDS like the eight
-// of a one-tile piece; wavefront w then merges accumulator registers 16 (w % 4) .. + 15 of the four
-// states of row tile w / 4 (always in wavefront order) and stores that slice of the 64-row slot.
-__device__ inline void fold_halves_and_store(const SmallState& S, float* lds, float* slot, int wv, int lane, float c,
-                                             float m_scale, float o_scale) {
+// A row group of two row tiles: every wavefront carries both, so a tile's bytes are loaded and converted once for the
+// workgroup (they were streamed by two halves of the workgroup, each of which converted them: 64 sequences of 16384
+// tokens, 40 .. 64 rows per kv head, took 626 us, as long as from a bf16 cache of twice the bytes; now 412).  Two states
+// leave no registers for the queries: they lie in LDS in operand order (16 KB, read once per tile).
+
+// Puts the 64 query rows of a row group into LDS ([row tile][k step][lane], 16 bytes each); ends with a barrier.
+__device__ inline void pair_queries(bf16x8* lds_q, const MainArgs& a, int g, int base, int M, int wv, int lane) {
   const int h = lane >> 5, j = lane & 31;
-  state_to_lds(S, lds + wv * kStateFloats, lane);
+  const int rho_raw = (wv >> 2) * kSmallRows + j;
+  const int rho = rho_raw < M ? rho_raw : M - 1;  // padding rows repeat the last real row; never read back
+  const int node = base + rho / a.G, head = g * a.G + rho % a.G;
+  const __bf16* qp = a.q + ((int64_t)node * a.Hq + head) * kD + h * 8;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int ks = 2 * (wv & 3) + i;
+    lds_q[((wv >> 2) * 8 + ks) * kWave + lane] = *(const bf16x8*)(qp + ks * 16);
+  }
   __syncthreads();
+}
+
+template <bool kMore>
+__device__ inline void pair_tile(SmallState (&S)[2], fp8x8 (&k)[8], fp8x8 (&v)[2][4], const bf16x8* lds_q, int lane,
+                                 float c, const MainArgs& a, const TilePages& next, int n_valid) {
+  floatx16 s[2] = {(floatx16)(0.f), (floatx16)(0.f)};
+  // (the scheduling barriers keep the query reads two steps ahead and no further: their registers are not there)
+  const uint8_t* kp = kMore ? k_vectors(a, next, lane) : nullptr;
+  bf16x8 qx[2][2];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) qx[0][rt] = lds_q[rt * 8 * kWave + lane];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) {
+    if (ks < 7) {
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) qx[(ks + 1) & 1][rt] = lds_q[(rt * 8 + ks + 1) * kWave + lane];
+    }
+    const bf16x8 kx = operand(k[ks]);
+    if (kMore) k[ks] = stream_load<true>((const fp8x8*)(kp + ks * 256));
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) s[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx, qx[ks & 1][rt], s[rt], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (!kMore && n_valid < kTile) {  // only a share's last tile can be ragged
+    mask_tail(s[0], v, n_valid, lane >> 5);
+    mask_tail(s[1], v, n_valid, lane >> 5);
+  }
+  bf16x8 pb[2][2];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    softmax_tile(s[rt], S[rt].m, S[rt].l, S[rt].o, pb[rt][0], pb[rt][1], c);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const uint8_t* vp[2] = {kMore ? v_vectors(a, next.page0, lane) : nullptr, kMore ? v_vectors(a, next.page1, lane) : nullptr};
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const bf16x8 vx = operand(v[kk][jt]);
+      if (kMore) v[kk][jt] = stream_load<true>((const fp8x8*)(vp[kk] + jt * 256));
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+        S[rt].o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vx, pb[rt][kk], S[rt].o[jt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// This wavefront's share [t0, t1) of a piece; the registers and requests are those of small_segment.
+__device__ inline void pair_segment(SmallState (&S)[2], const bf16x8* lds_q, const MainArgs& a, int b, int g, int t0, int t1,
+                                    const SeqInfo si, int lane) {
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) S[rt].o[jt] = (floatx16)(0.f);
+    S[rt].m = -INFINITY;
+    S[rt].l = 0.f;
+  }
+  if (t0 >= t1) return;
+  const int32_t* bt_row = a.block_table + (int64_t)b * a.max_blocks;
+  const int n_blocks = (si.len + kBlock - 1) / kBlock;
+  const float c = a.scale_log2e;
+  for (int tc = t0; tc < t1; tc += kChunkTiles) {
+    const int te = min(t1, tc + kChunkTiles);
+    BlockIds ids;
+    ids.lo = bt_row[min(2 * tc + lane, n_blocks - 1)];
+    ids.hi = bt_row[min(2 * tc + kWave + lane, n_blocks - 1)];
+    asm volatile("" ::"v"(ids.lo), "v"(ids.hi));  // landed before the stream starts: see small_segment
+    fp8x8 k[8], v[2][4];
+    {
+      const TilePages first = pages_from_ids(a, ids, 0, g);
+      load_k<true>(k, a, first, lane);
+      load_v<true>(v, a, first, lane);
+    }
+    const bool ends_here = te == t1;
+    const int loop_end = ends_here ? te - 1 : te;
+    int t = tc;
+    for (; t < loop_end; ++t) {
+      const TilePages next = pages_from_ids(a, ids, min(t + 1, te - 1) - tc, g);
+      pair_tile<true>(S, k, v, lds_q, lane, c, a, next, kTile);
+    }
+    if (ends_here) pair_tile<false>(S, k, v, lds_q, lane, c, a, TilePages{0, 0}, si.len - t * kTile);
+  }
+}
+
+// The eight states of a row group of two row tiles in LDS, row tile rt's in regions 4 rt .. 4 rt + 3, become one partial:
+// wavefront w merges accumulator registers 16 (w % 4) .. + 15 of the four states of row tile w / 4 (always in region
+// order) and stores that slice of the 64-row slot.
+__device__ inline void fold_quads_and_store(float* lds, float* slot, int wv, int lane, float c, float m_scale, float o_scale) {
+  const int h = lane >> 5, j = lane & 31;
   const int rt = wv >> 2, part = wv & 3;
   float mk[4], lk[4];
 #pragma unroll
@@ -1084,7 +1187,7 @@ __device__ inline void fold_halves_and_store(const SmallState& S, float* lds, fl
     mk[k] = lds[(4 * rt + k) * kStateFloats + 64 * kWave + lane];
     lk[k] = lds[(4 * rt + k) * kStateFloats + 65 * kWave + lane];
   }
-  float m_new = fmaxf(fmaxf(mk[0], mk[1]), fmaxf(mk[2], mk[3]));
+  const float m_new = fmaxf(fmaxf(mk[0], mk[1]), fmaxf(mk[2], mk[3]));
   float l_new = 0.f;
   floatx4 x[4] = {(floatx4)(0.f), (floatx4)(0.f), (floatx4)(0.f), (floatx4)(0.f)};
 #pragma unroll
@@ -1093,9 +1196,7 @@ __device__ inline void fold_halves_and_store(const SmallState& S, float* lds, fl
     const float sc = mk[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mk[k] - m_new) * c);
     l_new += lk[k] * sc;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      x[u] += state_quad(lds + (4 * rt + k) * kStateFloats, 4 * part + u, lane) * sc;
-    }
+    for (int u = 0; u < 4; ++u) x[u] += state_quad(lds + (4 * rt + k) * kStateFloats, 4 * part + u, lane) * sc;
   }
   // accumulator register 16 jt + 4 r4 + i of lane (h, j) is row j, head dims 4 (8 jt + 2 r4 + h) + i; here jt = part, r4 = u
 #pragma unroll
@@ -1111,6 +1212,45 @@ __device__ inline void fold_halves_and_store(const SmallState& S, float* lds, fl
   __syncthreads();  // the next piece reuses the LDS regions
 }
 
+// LDS holds eight states, not sixteen: wavefronts 4 .. 7 put their pairs there, wavefronts 0 .. 3 merge theirs with them
+// and put the result back.
+__device__ inline void fold_pairs_and_store(SmallState (&S)[2], float* lds, float* slot, int wv, int lane, float c,
+                                            float m_scale, float o_scale) {
+  if (wv >= 4) {
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) state_to_lds(S[rt], lds + (4 * rt + wv - 4) * kStateFloats, lane);
+  }
+  __syncthreads();
+  if (wv < 4) {
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      float* region = lds + (4 * rt + wv) * kStateFloats;
+      const float mk = region[64 * kWave + lane], lk = region[65 * kWave + lane];
+      const float m_new = fmaxf(S[rt].m, mk);
+      // an empty state has max -inf and contributes nothing
+      const float a0 = S[rt].m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((S[rt].m - m_new) * c);
+      const float a1 = mk == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mk - m_new) * c);
+#pragma unroll
+      for (int quad = 0; quad < 16; ++quad) {
+        const floatx4 x = state_quad(region, quad, lane);
+        floatx4 y;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] = S[rt].o[quad >> 2][4 * (quad & 3) + i] * a0 + x[i] * a1;
+        ((floatx4*)region)[quad * kWave + lane] = y;  // (a lane's own words only)
+      }
+      region[64 * kWave + lane] = m_new;
+      region[65 * kWave + lane] = S[rt].l * a0 + lk * a1;
+    }
+  }
+  __syncthreads();
+  fold_quads_and_store(lds, slot, wv, lane, c, m_scale, o_scale);
+}
+
+// kPair: two row tiles go to every wavefront; else one to each half of the workgroup (wavefronts 0 .. 3 carry row tile
+// 0, 4 .. 7 row tile 1, both halves stream the same tiles).  The kernel that holds the pair code runs its other branch, one
+// row tile, 7 % slower (386 us instead of 360 on the workload above with 32 rows; the same instructions, waiting longer),
+// so a batch of such trees runs the kernel without it: see tva_launch_mfma.
+template <bool kPair>
 __device__ inline void fp8_worker(const MainArgs& a, int64_t w, ClassPlan& cp, float* merge_lds /* 132 KB */) {
   const PlanView pv = plan_view(a.plan, a.batch);
   const int64_t U = cp.U, W = cp.W;
@@ -1129,32 +1269,35 @@ __device__ inline void fp8_worker(const MainArgs& a, int64_t w, ClassPlan& cp, f
     if (u0 >= seq_end) { ++b; continue; }
     const SeqInfo si = window_info(win, b);
     const int64_t local = u0 - seq_begin;
-    const int seg_local = (int)(local / si.tiles);  // kv head x row group of 64 rows
-    const int g = seg_local / si.rg;
-    const int row0 = (seg_local % si.rg) * kMediumRows;
+    const int g = (int)(local / si.tiles);  // (one row group: class 1 has at most 64 rows)
     const int t0 = (int)(local % si.tiles);
     const int64_t left = u1 - u0;
     const int nt = (int)(left < (int64_t)(si.tiles - t0) ? left : (int64_t)(si.tiles - t0));
-    const int64_t seg = (int64_t)__builtin_amdgcn_readlane(win.cum_segs, b - win.first) + seg_local;
+    const int64_t seg = (int64_t)__builtin_amdgcn_readlane(win.cum_segs, b - win.first) + g;
     const int base = __builtin_amdgcn_readlane(win.cu_nodes, b - win.first);
     float* slot = a.ws[1] + (size_t)(w + seg) * kMediumSlot;
-    SmallState S;
-    if (si.n * a.G - row0 <= kSmallRows) {
-      const int s0 = t0 + (int)(((int64_t)nt * wv) / kWgWaves);
-      const int s1 = t0 + (int)(((int64_t)nt * (wv + 1)) / kWgWaves);
-      // a tree with one tile of rows reads every K/V tile once; otherwise the other half of the workgroup or the
-      // other row groups read the same tiles again, out of the caches
-      if (si.rg == 1)
-        small_segment<fp8x8, true>(S, a, b, g, base, s0, s1, si, lane, row0);
-      else
-        small_segment<fp8x8, false>(S, a, b, g, base, s0, s1, si, lane, row0);
-      fold_and_store<true, kMediumRows>(S, merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale, 0);
+    const int s0 = t0 + (int)(((int64_t)nt * wv) / kWgWaves);
+    const int s1 = t0 + (int)(((int64_t)nt * (wv + 1)) / kWgWaves);
+    if (si.n * a.G <= kSmallRows) {
+      SmallState S;
+      small_segment<fp8x8>(S, a, b, g, base, s0, s1, si, lane);
+      fold_and_store<true, kMediumRows>(S, merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
+    } else if (kPair) {
+      bf16x8* lds_q = (bf16x8*)merge_lds;  // (the fold's regions: one after the other)
+      pair_queries(lds_q, a, g, base, si.n * a.G, wv, lane);
+      SmallState P[2];
+      pair_segment(P, lds_q, a, b, g, s0, s1, si, lane);
+      __syncthreads();  // nobody reads the queries any more
+      fold_pairs_and_store(P, merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
     } else {
       const int rt = wv >> 2, sub = wv & 3;
-      const int s0 = t0 + (int)(((int64_t)nt * sub) / 4);
-      const int s1 = t0 + (int)(((int64_t)nt * (sub + 1)) / 4);
-      small_segment<fp8x8, false>(S, a, b, g, base, s0, s1, si, lane, row0 + rt * kSmallRows);
-      fold_halves_and_store(S, merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
+      const int h0 = t0 + (int)(((int64_t)nt * sub) / 4);
+      const int h1 = t0 + (int)(((int64_t)nt * (sub + 1)) / 4);
+      SmallState S;
+      small_segment<fp8x8, false>(S, a, b, g, base, h0, h1, si, lane, rt * kSmallRows);
+      state_to_lds(S, merge_lds + wv * kStateFloats, lane);
+      __syncthreads();
+      fold_quads_and_store(merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
     }
     u0 += nt;
   }
@@ -1793,7 +1936,7 @@ __device__ inline void staged_worker(const MainArgs& a, int64_t w, ClassPlan& cp
 // ---- the prefix kernel: one launch, workgroups apportioned to the classes by the plan ------
 // kFp8: the cache holds E4M3 bytes; trees of up to 64 rows are class 1 and streamed into registers by
 // fp8_worker, larger ones are class 2 and go through the staged loop after conversion to bf16 in LDS.
-template <bool kFp8>
+template <bool kFp8, bool kPair = false>
 __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tva_prefix_kernel(MainArgs a) {
   __shared__ float4 lds_raw[8448];  // 132 KB, carved up per class (class 0: eight states of 16.5 KB)
@@ -1895,7 +2038,7 @@ void tva_prefix_kernel(MainArgs a) {
     }
   };)
   if (kFp8) {
-    if (wg >= first1 && wg < first2) fp8_worker(a, wg - first1, cp, (float*)lds_raw);
+    if (wg >= first1 && wg < first2) fp8_worker<kPair>(a, wg - first1, cp, (float*)lds_raw);
     else if (wg >= first2) staged_worker<2, true>(a, wg - first2, cp, (bf16x8*)lds_raw);
     SMART_TIMELINE(tl_end();)
     return;
@@ -2287,21 +2430,21 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   // (every class with work needs a workgroup, however few were asked for)
   const dim3 grid(workgroups > kClasses ? workgroups : kClasses);
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
-  if (profile_events(ctx, &ev_start, &ev_stop)) {
-    // a recorded call: the events ride on the dispatch and hold the kernel's own start and end
-    if (fp8)
-      hipExtLaunchKernelGGL(tva_prefix_kernel<true>, grid, dim3(kWgWaves * kWave), 0, stream, ev_start, ev_stop, 0, ma);
-    else
-      hipExtLaunchKernelGGL(tva_prefix_kernel<false>, grid, dim3(kWgWaves * kWave), 0, stream, ev_start, ev_stop, 0, ma);
-    SMART_HIP_CHECK(hipGetLastError());
-    profile_launched(ctx);
-  } else {
-    if (fp8)
-      hipLaunchKernelGGL(tva_prefix_kernel<true>, grid, dim3(kWgWaves * kWave), 0, stream, ma);
-    else
-      hipLaunchKernelGGL(tva_prefix_kernel<false>, grid, dim3(kWgWaves * kWave), 0, stream, ma);
-    SMART_HIP_CHECK(hipGetLastError());
-  }
+  // (no events: an ordinary launch; else the events ride on the dispatch and hold the kernel's own start and end)
+  const bool recorded = profile_events(ctx, &ev_start, &ev_stop);
+  // fp8 cache: the host knows the trees' mean size only.  A batch of trees of one row tile has a mean of at most 32 rows
+  // and runs the kernel that is best for them (360 us instead of 386, see fp8_worker); with a larger mean trees of two
+  // row tiles are the usual ones, and they gain more (412 us instead of 626) than the smaller ones lose.
+  const bool pair = fp8 && (int64_t)p.total_nodes * G > (int64_t)kSmallRows * p.batch;
+  auto launch = [&](void (*kernel)(MainArgs)) {
+    if (recorded) hipExtLaunchKernelGGL(kernel, grid, dim3(kWgWaves * kWave), 0, stream, ev_start, ev_stop, 0, ma);
+    else hipLaunchKernelGGL(kernel, grid, dim3(kWgWaves * kWave), 0, stream, ma);
+  };
+  if (pair) launch(tva_prefix_kernel<true, true>);
+  else if (fp8) launch(tva_prefix_kernel<true>);
+  else launch(tva_prefix_kernel<false>);
+  SMART_HIP_CHECK(hipGetLastError());
+  if (recorded) profile_launched(ctx);
 
   CombineArgs ca;
   ca.q = (const uint16_t*)p.d_q;
