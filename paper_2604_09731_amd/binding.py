@@ -374,13 +374,22 @@ def _torch():
     return torch
 
 
+# Marshalling is most of a small call's host time (a step of a few users waits for the host, not for the GPU): addresses
+# go to ctypes as plain integers (its argument types convert them; an object per address costs 0.2 us more), and
+# outputs of one type and length are rows of one allocation.
 def _stream_ptr():
-    torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _torch().cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
+
+
+def _i32_rows(rows, n, device, zero=False):
+    """`rows` int32 tensors of length n from one allocation."""
+    torch = _torch()
+    make = torch.zeros if zero else torch.empty
+    return make((rows, n), dtype=torch.int32, device=device).unbind(0)
 
 
 def _dtype_code(t):
@@ -459,9 +468,10 @@ class SmartTree:
         B = pinned_cu_nodes.shape[0] - 1
         N = int(pinned_cu_nodes[B])
         dev = prefix_len.device
-        i32 = lambda n: torch.empty(n, dtype=torch.int32, device=dev)
-        cu, par, tok = i32(B + 1), i32(N), (i32(N) if pinned_token is not None else None)
-        depth, position, node_seq, status = i32(N), i32(N), i32(N), i32(B)
+        par, depth, position, node_seq, *tok = _i32_rows(4 if pinned_token is None else 5, N, dev)
+        tok = tok[0] if tok else None
+        cu = torch.empty(B + 1, dtype=torch.int32, device=dev)
+        status = torch.empty(B, dtype=torch.int32, device=dev)
         anc_mask = torch.empty((N, 2), dtype=torch.int64, device=dev)
         rc = _lib().tree_upload_pack(self._h, _stream_ptr(), B, N, _ptr(pinned_cu_nodes), _ptr(pinned_parent),
                                      _ptr(pinned_token), _ptr(cu), _ptr(par), _ptr(tok), _ptr(prefix_len),
@@ -489,7 +499,8 @@ class SmartTree:
                                               _ptr(cost), _ptr(dcost), float(alpha), int(dilution), _ptr(out_node),
                                               _ptr(status))
         _check(rc, "smart_select_layer_device")
-        return out_node[:cap], status[:state.batch]
+        return (out_node if out_node.shape[0] == cap else out_node[:cap],
+                status if status.shape[0] == state.batch else status[:state.batch])
 
     def tree_compact_pack(self, state: DeviceLayerState, prefix_len, total_cap=None):
         """Returns (cu_nodes, parent, token, depth, position, node_seq, anc_mask, status); the per-node
@@ -498,15 +509,18 @@ class SmartTree:
         B = state.batch
         N = int(total_cap if total_cap is not None else B * state.budget)
         dev = prefix_len.device
-        i32 = lambda n: torch.zeros(max(1, n), dtype=torch.int32, device=dev)
-        cu, par, tok = i32(B + 1), i32(N), i32(N)
-        depth, position, node_seq, status = i32(N), i32(N), i32(N), i32(B)
-        anc_mask = torch.zeros((max(1, N), 2), dtype=torch.int64, device=dev)
+        # one allocation and one fill for everything: the masks (16 bytes a node) first, so that they stay aligned
+        n1, b1 = max(1, N), max(1, B)
+        masks, par, tok, depth, position, node_seq, cu, status = torch.zeros(
+            9 * n1 + B + 1 + b1, dtype=torch.int32, device=dev).split([4 * n1, n1, n1, n1, n1, n1, B + 1, b1])
+        anc_mask = masks.view(torch.int64).view(n1, 2)
         rc = _lib().tree_compact_pack(self._h, _stream_ptr(), ctypes.byref(state.struct), N, _ptr(prefix_len),
                                       _ptr(cu), _ptr(par), _ptr(tok), _ptr(depth), _ptr(position), _ptr(node_seq),
                                       _ptr(anc_mask), _ptr(status))
         _check(rc, "tree_compact_pack")
-        return cu, par[:N], tok[:N], depth[:N], position[:N], node_seq[:N], anc_mask[:N], status[:B]
+        if N == 0 or B == 0:
+            return cu, par[:N], tok[:N], depth[:N], position[:N], node_seq[:N], anc_mask[:N], status[:B]
+        return cu, par, tok, depth, position, node_seq, anc_mask, status
 
     # -- tree_rope ---------------------------------------------------------
     def tree_rope(self, position, q, k_tree, base=10000.0, rotary_dim=None, pairing=SMART_ROPE_HALF_SPLIT):
@@ -524,9 +538,7 @@ class SmartTree:
         B = cu_nodes.shape[0] - 1
         N = parent.shape[0]
         dev = cu_nodes.device
-        depth = torch.empty(N, dtype=torch.int32, device=dev)
-        position = torch.empty(N, dtype=torch.int32, device=dev)
-        node_seq = torch.empty(N, dtype=torch.int32, device=dev)
+        depth, position, node_seq = _i32_rows(3, N, dev)
         anc_mask = torch.empty((N, 2), dtype=torch.int64, device=dev)
         status = torch.empty(B, dtype=torch.int32, device=dev)
         rc = _lib().tree_pack(self._h, _stream_ptr(), B, N, _ptr(cu_nodes), _ptr(parent),
@@ -613,9 +625,8 @@ class SmartTree:
         torch = _torch()
         B = cu_nodes.shape[0] - 1
         dev = cu_nodes.device
-        accept_len = torch.empty(B, dtype=torch.int32, device=dev)
+        accept_len, bonus = _i32_rows(2, B, dev)
         accept_path = torch.empty((B, max_depth + 1), dtype=torch.int32, device=dev)
-        bonus = torch.empty(B, dtype=torch.int32, device=dev)
         rc = _lib().tree_accept(self._h, _stream_ptr(), B, max_depth, _ptr(cu_nodes), _ptr(parent),
                                 _ptr(token), _ptr(target_next), _ptr(accept_len), _ptr(accept_path),
                                 _ptr(bonus))
@@ -630,9 +641,8 @@ class SmartTree:
         dev = cu_nodes.device
         N, V = target_prob.shape
         assert target_prob.dtype == torch.float32 and target_prob.stride(1) == 1
-        accept_len = torch.empty(B, dtype=torch.int32, device=dev)
+        accept_len, bonus = _i32_rows(2, B, dev)
         accept_path = torch.empty((B, max_depth + 1), dtype=torch.int32, device=dev)
-        bonus = torch.empty(B, dtype=torch.int32, device=dev)
         rc = _lib().tree_accept_sample(self._h, _stream_ptr(), B, N, max_depth, V, _ptr(cu_nodes), _ptr(parent),
                                        _ptr(token), _ptr(target_prob), target_prob.stride(0), int(seed), int(step),
                                        _ptr(accept_len), _ptr(accept_path), _ptr(bonus))
@@ -648,8 +658,7 @@ class SmartTree:
         torch = _torch()
         B = cu_nodes.shape[0] - 1
         _, Hkv, D = k_tree.shape
-        new_len = torch.empty(B, dtype=torch.int32, device=cu_nodes.device)
-        status = torch.empty(B, dtype=torch.int32, device=cu_nodes.device)
+        new_len, status = _i32_rows(2, B, cu_nodes.device)
         args = (self._h, _stream_ptr(), _dtype_code(k_tree), layout, B, accept_path.shape[1] - 1,
                 Hkv, D, block_size, block_table.shape[1], num_blocks, _ptr(cu_nodes),
                 _ptr(accept_len), _ptr(accept_path), _ptr(k_tree), _ptr(v_tree), _ptr(block_table),
