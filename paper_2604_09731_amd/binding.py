@@ -378,7 +378,10 @@ def _torch():
 # go to ctypes as plain integers (its argument types convert them; an object per address costs 0.2 us more), and
 # outputs of one type and length are rows of one allocation.
 def _stream_ptr():
-    return _torch().cuda.current_stream().cuda_stream
+    cuda = _torch().cuda
+    # (the handle itself: building the Stream object around it takes 3 us, as long as a small call's kernel)
+    raw = getattr(_torch()._C, "_cuda_getCurrentRawStream", None)
+    return raw(cuda.current_device()) if raw is not None else cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
