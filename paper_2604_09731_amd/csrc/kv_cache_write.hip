@@ -78,6 +78,7 @@ constexpr int kThreads = 256;
 
 template <typename T> struct Elems8 { T v[8]; };
 template <typename T> struct alignas(2 * sizeof(T)) Elems2 { T v[2]; };
+template <typename T> struct alignas(4 * sizeof(T)) Elems4 { T v[4]; };
 
 template <typename T>
 __device__ inline Elems8<T> load8(const T* p) {
@@ -229,9 +230,11 @@ static void launch_rows(hipStream_t s, int kv_layout, int n_tokens, int Hkv, int
                        head_stride, token_stride, k_scale, v_scale);
 }
 
-// One workgroup per (path index i, sequence b).  Every workgroup of a sequence takes the same
-// accept / refuse decision from the same inputs; workgroup i = 0 reports it.
-template <typename T, typename C>
+// One workgroup per (path index i, sequence b).  Every wavefront takes the same accept / refuse decision from the same
+// inputs (a lane per path entry: two memory round trips, whatever the path's length); workgroup i = 0 reports it.
+// kChunks: rows move in 8-element chunks (V of interleaved pages: four elements read at once, stored one by one).
+// Four sequences, 8 kv heads of 128, max_depth 8: 5.5 us with a serial check of the path, 4.5 with this one.
+template <typename T, typename C, bool kChunks>
 __global__ __launch_bounds__(256) void tree_commit_kernel(
     int layout, int batch, int max_depth, int Hkv, int D, int block_size, int max_blocks, int num_blocks,
     const int32_t* __restrict__ cu_nodes, const int32_t* __restrict__ accept_len,
@@ -241,21 +244,27 @@ __global__ __launch_bounds__(256) void tree_commit_kernel(
     int64_t token_stride, int32_t* __restrict__ new_prefix_len, int32_t* __restrict__ status,
     float k_scale, float v_scale) {
   const int i = blockIdx.x, b = blockIdx.y;
+  const int lane = threadIdx.x & 63;
   const int base = cu_nodes[b];
   const int n = cu_nodes[b + 1] - base;
   const int a = accept_len[b];
   const int start = prefix_len[b];
   const int32_t* path = accept_path + (size_t)b * (max_depth + 1);
-  int verdict = SMART_OK;
+  int verdict = SMART_OK, node = 0, block = 0;  // node, block: of path entry i
   if (base < 0 || a < 0 || a > max_depth) {
     verdict = SMART_ETREE;
   } else if (start < 0 || (int64_t)start + a + 1 > (int64_t)max_blocks * block_size) {
     verdict = SMART_ECAP;
   } else {
-    for (int k = 0; k <= a; ++k) {  // at most max_depth + 1 <= 129 entries
+    for (int k0 = 0; k0 <= a; k0 += 64) {  // at most max_depth + 1 <= 129 entries
+      const int k = min(k0 + lane, a);
       const int v = path[k];
       const int blk = block_table[(size_t)b * max_blocks + (start + k) / block_size];
-      if (v < 0 || v >= n || blk < 0 || blk >= num_blocks) verdict = SMART_ETREE;
+      if (__any(v < 0 || v >= n || blk < 0 || blk >= num_blocks)) verdict = SMART_ETREE;
+      if (i >= k0 && i < k0 + 64) {
+        node = __builtin_amdgcn_readlane(v, i - k0);
+        block = __builtin_amdgcn_readlane(blk, i - k0);
+      }
     }
   }
   if (i == 0 && threadIdx.x == 0) {
@@ -263,13 +272,39 @@ __global__ __launch_bounds__(256) void tree_commit_kernel(
     new_prefix_len[b] = verdict == SMART_OK ? start + a + 1 : start;
   }
   if (verdict != SMART_OK || i > a) return;
-  const int pos = start + i;
-  const int64_t blk = block_table[(size_t)b * max_blocks + pos / block_size];
-  const int slot = pos % block_size;
-  const size_t src = (size_t)(base + path[i]) * Hkv * D;
+  const int slot = (start + i) % block_size;
+  const int64_t block_at = (int64_t)block * block_stride;
+  const size_t src = (size_t)(base + node) * Hkv * D;
+  if (kChunks) {
+    const int chunks = Hkv * D / 8;
+    const bool plain = layout == SMART_KV_PLAIN;
+    // the first `chunks` units move K (and V of plain pages), the rest four elements of an interleaved V each
+    for (int u = threadIdx.x; u < (plain ? chunks : 3 * chunks); u += 256) {
+      if (u < chunks) {
+        const int g = u / (D / 8), d8 = u - g * (D / 8);
+        const int64_t page = block_at + (int64_t)g * head_stride;
+        const Elems8<T> kx = load8(k_tree + src + 8 * u);
+        if (plain) {
+          const int64_t at = page + (int64_t)slot * token_stride + 8 * d8;
+          const Elems8<T> vx = load8(v_tree + src + 8 * u);
+          store8(k_cache + at, cache_elems<C>(kx, k_scale));
+          store8(v_cache + at, cache_elems<C>(vx, v_scale));
+        } else {
+          store8(k_cache + page + ((int64_t)d8 * block_size + slot) * 8, cache_elems<C>(kx, k_scale));
+        }
+      } else {
+        const int e = 4 * (u - chunks), g = e / D, d = e - g * D;
+        const Elems4<T> vx = *reinterpret_cast<const Elems4<T>*>(v_tree + src + e);
+        C* dst = v_cache + block_at + (int64_t)g * head_stride + ((int64_t)(slot / 8) * D + d) * 8 + slot % 8;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) dst[8 * x] = cache_elem<C>(vx.v[x], v_scale);
+      }
+    }
+    return;
+  }
   for (int e = threadIdx.x; e < Hkv * D; e += blockDim.x) {
     const int g = e / D, d = e % D;
-    const int64_t page = blk * block_stride + (int64_t)g * head_stride;
+    const int64_t page = block_at + (int64_t)g * head_stride;
     int64_t ko, vo;
     if (layout == SMART_KV_PLAIN) {
       ko = vo = page + (int64_t)slot * token_stride + d;
@@ -314,17 +349,25 @@ static int32_t commit_impl(smart_ctx* ctx, void* stream, int32_t dtype, bool fp8
     return SMART_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const dim3 grid(max_depth + 1, batch);
-#define SMART_LAUNCH_COMMIT(T, C)                                                                               \
-  hipLaunchKernelGGL((tree_commit_kernel<T, C>), grid, dim3(256), 0, s, kv_layout, batch, max_depth,           \
+  const bool chunks = rows_in_chunks(fp8, kv_layout, head_dim, d_k_tree, d_v_tree, d_k_cache, d_v_cache, cache_block_stride,
+                                     cache_head_stride, cache_token_stride);
+#define SMART_LAUNCH_COMMIT_AS(T, C, CHUNKS)                                                                    \
+  hipLaunchKernelGGL((tree_commit_kernel<T, C, CHUNKS>), grid, dim3(256), 0, s, kv_layout, batch, max_depth,   \
                      num_kv_heads, head_dim, block_size, max_blocks_per_seq, num_blocks, d_cu_nodes,           \
                      d_accept_len, d_accept_path, (const T*)d_k_tree, (const T*)d_v_tree, d_block_table,       \
                      d_prefix_len, (C*)d_k_cache, (C*)d_v_cache, cache_block_stride, cache_head_stride,        \
                      cache_token_stride, d_new_prefix_len, d_status, k_scale, v_scale)
+#define SMART_LAUNCH_COMMIT(T, C)                                                                               \
+  do {                                                                                                          \
+    if (chunks) SMART_LAUNCH_COMMIT_AS(T, C, true);                                                             \
+    else SMART_LAUNCH_COMMIT_AS(T, C, false);                                                                   \
+  } while (0)
   if (dtype == SMART_F32) {
     if (fp8) SMART_LAUNCH_COMMIT(float, uint8_t); else SMART_LAUNCH_COMMIT(float, float);
   } else {
     if (fp8) SMART_LAUNCH_COMMIT(uint16_t, uint8_t); else SMART_LAUNCH_COMMIT(uint16_t, uint16_t);
   }
+#undef SMART_LAUNCH_COMMIT_AS
 #undef SMART_LAUNCH_COMMIT
   SMART_HIP_CHECK(hipGetLastError());
   return SMART_OK;

@@ -84,3 +84,51 @@ def test_rows_off_the_chunks():
         lib.kv_cache_write(k, v, slots, kc, vc, B.SMART_KV_PLAIN, bs, nb, kc.stride(0), kc.stride(1), token_stride=stride)
         for c, x in ((kc, k), (vc, v)):
             assert torch.equal(c.permute(0, 2, 1, 3).reshape(nb * bs, Hkv, stride)[:n, :, :D], x)
+
+
+@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("f32", False), ("bf16", True)])
+@pytest.mark.parametrize("layout,pad", [(B.SMART_KV_PLAIN, 0), (B.SMART_KV_PLAIN, 2), (B.SMART_KV_INTERLEAVED, 0)])
+def test_commit_of_long_paths(dtype, fp8, layout, pad):
+    """Paths of up to 128 entries (a lane per entry, three turns), refused ones among them: an entry or a block past the
+    first 64 that is not there, no room in the table."""
+    import torch
+    lib = B.SmartTree(0)
+    rng = np.random.default_rng(9)
+    n, Hkv, D, bs, max_depth = 128, 3, 72, 8, 127
+    lens = np.array([5, 0, 9, 1, 2, 3, 200], np.int32)
+    alen = np.array([127, 63, 64, 0, 100, 100, 60], np.int32)
+    nseq, max_blocks = len(lens), 32
+    path = np.full((nseq, max_depth + 1), -1, np.int32)
+    for b in range(nseq):
+        path[b, :alen[b] + 1] = np.arange(alen[b] + 1)
+    path[4, 90] = n                                          # not a node
+    nb = nseq * max_blocks
+    table = rng.permutation(nb).reshape(nseq, max_blocks).astype(np.int32)
+    table[5, (3 + 80) // bs] = nb                            # not a block
+    cu = (np.arange(nseq + 1) * n).astype(np.int32)
+    expect = [0, 0, 0, 0, B.SMART_ETREE, B.SMART_ETREE, B.SMART_ECAP]
+    k, v = (W._normal(2, i, (nseq * n, Hkv, D), 1.0, dtype) for i in (1, 2))
+    f = lambda x: (W.bf16_bits_to_f32(x) if dtype == "bf16" else x).astype(np.float32)
+    val = [F.encode(f(x) / np.float32(sc)) for x, sc in ((k, 0.03), (v, 0.011))] if fp8 else [k, v]
+    plain = [np.zeros((nb, Hkv, bs, D), x.dtype) for x in val]
+    for b in range(nseq):
+        for i in range(alen[b] + 1 if expect[b] == 0 else 0):
+            pos = int(lens[b]) + i
+            for p, x in zip(plain, val):
+                p[table[b, pos // bs], :, pos % bs] = x[b * n + i]
+    tk, tv = H.torch_elems(k, dtype, "cuda"), H.torch_elems(v, dtype, "cuda")
+    shape = (nb, Hkv, bs, D + pad) if layout == B.SMART_KV_PLAIN else (nb, Hkv, bs * D)
+    kc, vc = (torch.zeros(shape, dtype=torch.uint8 if fp8 else tk.dtype, device="cuda") for _ in range(2))
+    t = lambda a: torch.from_numpy(a).cuda()
+    scales = dict(k_scale=0.03, v_scale=0.011) if fp8 else {}
+    new, status = lib.tree_commit(t(cu), t(alen), t(path), tk, tv, kc, vc, t(table), t(lens), layout, bs, nb, kc.stride(0),
+                                  kc.stride(1), token_stride=D + pad, **scales)
+    assert status.tolist() == expect
+    assert new.tolist() == [int(x + y + 1) if e == 0 else int(x) for x, y, e in zip(lens, alen, expect)]
+    for c, p, which in zip((kc, vc), plain, "kv"):
+        got = c.cpu()
+        got = (got if fp8 else got.view(torch.int16 if dtype == "bf16" else torch.float32)).numpy().view(p.dtype)
+        if layout == B.SMART_KV_PLAIN:
+            assert np.array_equal(got[..., :D], p) and not got[..., D:].any()
+        else:
+            assert np.array_equal(got, KL.interleave_plain_cache(p, which))
