@@ -1035,8 +1035,15 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   const int64_t finish_waves = ((int64_t)p.total_nodes * p.num_q_heads + kWave / kCombineLanes - 1) / (kWave / kCombineLanes);
   if (segs > 0x7FFFFFFF) return SMART_EINVAL;
   // The workspace-free form: for callers that cannot allocate, for launches that are being captured (a graph must not
-  // hold a workspace that a later, larger call replaces), and when no memory is left.
-  bool direct = fixed != nullptr;
+  // hold a workspace that a later, larger call replaces), and when no memory is left.  It is also the faster one, by the
+  // second launch, where a segment is a few steps, its rows fit one pass of the finishing step (64) and every segment has
+  // a compute unit: 15-node trees of 60 rows, batch 8, bf16 20.9 us against 15.8 at 33 tokens, 27.7 against 24.8 at 513,
+  // 29.9 against 33.8 at 1025; fp32 (a step is half as long and takes twice as long) 18.1 against 15.2 at 33 tokens,
+  // 19.0 against 19.4 at 129; batch 32, 376 segments, 27.2 against 30.7.
+  const int64_t longest = (int64_t)p.max_blocks_per_seq * p.block_size;
+  bool direct = fixed != nullptr ||
+                (longest <= (f32 ? step_keys<float>() : 4 * step_keys<__bf16>()) &&
+                 (int64_t)p.total_nodes * G <= 64 * (int64_t)p.batch && segs <= (ctx->num_cus > 0 ? ctx->num_cus : 256));
   if (!direct) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (stream != nullptr && hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();

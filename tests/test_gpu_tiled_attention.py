@@ -195,3 +195,13 @@ def test_a_captured_call_holds_no_workspace(lib):
         graph.replay()
         torch.cuda.synchronize()
         assert_close((out,), (ref,))
+
+
+@pytest.mark.parametrize("dtype,longest", [("bf16", 512), ("f32", 64)])
+def test_around_the_one_launch_rule(lib, dtype, longest):
+    """Small trees on tables that hold at most, and just more than, what one workgroup per segment takes; a mean of 64
+    rows and one above it."""
+    for sizes in ([16, 16], [16, 17], [1, 31]):
+        for extra in (0, 1):
+            x = Inputs(sizes, [longest, 5], 8, 2, 64, 16, dtype, B.SMART_KV_PLAIN, spare_columns=extra)
+            assert_close(x.run(lib), x.run(lib, general=True))
