@@ -16,6 +16,8 @@ struct smart_ctx {
   size_t ws_bytes = 0;
   int32_t* plan = nullptr;    // launch plan written by the planning kernel
   size_t plan_bytes = 0;
+  void* tiled_ws = nullptr;   // the tiled path's partial results and plan; no graph ever holds it
+  size_t tiled_ws_bytes = 0;
   // options
   int64_t opt_workers = 0;
   int64_t opt_force_general = 0;
@@ -50,6 +52,10 @@ void set_last_hip_error(hipError_t e);
 // Makes sure the context's workspace holds at least the given sizes.  May
 // synchronise `stream` (only when it has to grow).
 int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, size_t plan_bytes);
+// The same for the tiled path's buffer, which is apart from the one above: its calls served without a workspace before
+// they had a faster form, so they must not replace a buffer that a captured launch of another path still reads.  False
+// (nothing changed, no error left behind) if it cannot grow: the caller then takes its workspace-free form.
+bool ensure_tiled_workspace(smart_ctx* ctx, hipStream_t stream, size_t bytes);
 
 // Profiling hooks: bracket the dominant kernel of the current call.
 int32_t profile_begin(smart_ctx* ctx, hipStream_t stream);
@@ -74,8 +80,8 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
 // The tiled matrix-core path: every other type, layout, head dim and block size whose rows are aligned.
 int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed);
 bool tva_tiled_supported(const tva_params& p);
-void tva_tiled_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
-                         int32_t num_kv_heads, int32_t head_dim, size_t* ws_bytes, size_t* plan_bytes);
+size_t tva_tiled_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
+                           int32_t num_kv_heads, int32_t head_dim);
 // Dispatch between them (validated params, the context's device current).
 int32_t tva_dispatch(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed);
 // This device's copy of the library's static scratch array (the device must be current); resolved once per device.

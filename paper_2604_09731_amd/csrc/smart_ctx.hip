@@ -31,6 +31,28 @@ int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, si
   return SMART_OK;
 }
 
+bool ensure_tiled_workspace(smart_ctx* ctx, hipStream_t stream, size_t bytes) {
+  if (bytes <= ctx->tiled_ws_bytes) return true;
+  // another stream of this process may be under capture, which an allocation in the default mode would end
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  void* fresh = nullptr;
+  bool ok = hipMalloc(&fresh, bytes) == hipSuccess;
+  if (ok && ctx->tiled_ws) {
+    // work already enqueued may still use the old buffer
+    ok = hipStreamSynchronize(stream) == hipSuccess;
+    (void)hipFree(ok ? ctx->tiled_ws : fresh);
+  }
+  if (ok) {
+    ctx->tiled_ws = fresh;
+    ctx->tiled_ws_bytes = bytes;
+  } else {
+    (void)hipGetLastError();
+  }
+  if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return ok;
+}
+
 static void profile_free(smart_ctx* ctx) {
   for (int i = 0; i < ctx->prof_cap; ++i) {
     (void)hipEventDestroy(ctx->prof_start[i]);
@@ -120,12 +142,13 @@ extern "C" int32_t smart_create(smart_ctx** out_ctx, int32_t device_id) {
 extern "C" int32_t smart_destroy(smart_ctx* ctx) {
   if (!ctx) return SMART_EINVAL;
   int32_t rc = SMART_OK;
-  if (ctx->ws || ctx->plan || ctx->prof_cap) {
+  if (ctx->ws || ctx->plan || ctx->tiled_ws || ctx->prof_cap) {
     int prev = 0;
     if (hipGetDevice(&prev) == hipSuccess && hipSetDevice(ctx->device) == hipSuccess) {
       (void)hipDeviceSynchronize();
       if (ctx->ws && hipFree(ctx->ws) != hipSuccess) rc = SMART_EHIP;
       if (ctx->plan && hipFree(ctx->plan) != hipSuccess) rc = SMART_EHIP;
+      if (ctx->tiled_ws && hipFree(ctx->tiled_ws) != hipSuccess) rc = SMART_EHIP;
       smart::profile_free(ctx);
       (void)hipSetDevice(prev);
     } else {
@@ -216,11 +239,11 @@ extern "C" int32_t smart_reserve(smart_ctx* ctx, int32_t max_batch, int32_t max_
   SMART_HIP_CHECK(hipSetDevice(ctx->device));
   size_t ws = 0, plan = 0;
   smart::tva_mfma_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, &ws, &plan);
-  size_t tiled_ws = 0, tiled_plan = 0;  // (head dim 128: the larger one)
-  smart::tva_tiled_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, 128, &tiled_ws, &tiled_plan);
-  ws = tiled_ws > ws ? tiled_ws : ws;
-  plan = tiled_plan > plan ? tiled_plan : plan;
   int32_t rc = smart::ensure_workspace(ctx, nullptr, ws, plan);
+  // (head dim 128: the larger one; without it the tiled path runs its workspace-free form, which is no error)
+  if (rc == SMART_OK)
+    (void)smart::ensure_tiled_workspace(
+        ctx, nullptr, smart::tva_tiled_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, 128));
   (void)hipSetDevice(prev);
   return rc;
 }

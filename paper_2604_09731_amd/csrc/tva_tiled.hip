@@ -999,11 +999,17 @@ static int64_t tiled_segments(int32_t batch, int32_t total_nodes, int32_t num_q_
   return (int64_t)num_kv_heads * (((int64_t)total_nodes * G + kGroupRows - 1) / kGroupRows + batch);
 }
 
-void tva_tiled_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
-                         int32_t num_kv_heads, int32_t head_dim, size_t* ws_bytes, size_t* plan_bytes) {
+static size_t partials_bytes(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
+                             int32_t num_kv_heads, int32_t head_dim) {
   const int64_t slots = tiled_workgroups(ctx) + tiled_segments(batch, total_nodes, num_q_heads, num_kv_heads) + 1;
-  *ws_bytes = (size_t)slots * slot_floats(head_dim) * sizeof(float);
-  *plan_bytes = sizeof(int64_t) * (2 + 2 * (size_t)batch);
+  return ((size_t)slots * slot_floats(head_dim) * sizeof(float) + 255) & ~(size_t)255;
+}
+
+// the partial results, then the plan
+size_t tva_tiled_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
+                           int32_t num_kv_heads, int32_t head_dim) {
+  return partials_bytes(ctx, batch, total_nodes, num_q_heads, num_kv_heads, head_dim) +
+         sizeof(int64_t) * (2 + 2 * (size_t)batch);
 }
 
 // Every 16-byte chunk of a staged row, every query row and every tree row must be addressable with one load.
@@ -1049,13 +1055,9 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
     if (stream != nullptr && hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
     direct = capture != hipStreamCaptureStatusNone;
   }
-  if (!direct) {
-    size_t ws_bytes, plan_bytes;
-    tva_tiled_workspace(ctx, p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads, p.head_dim, &ws_bytes, &plan_bytes);
-    const int32_t rc = ensure_workspace(ctx, stream, ws_bytes, plan_bytes);
-    if (rc == SMART_ENOMEM) direct = true;
-    else if (rc != SMART_OK) return rc;
-  }
+  if (!direct)
+    direct = !ensure_tiled_workspace(
+        ctx, stream, tva_tiled_workspace(ctx, p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads, p.head_dim));
   TiledArgs a;
   a.q = p.d_q;
   a.k_tree = p.d_k_tree;
@@ -1069,8 +1071,10 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   a.out = p.d_out;
   a.lse = p.d_lse;
   a.status = p.d_status;
-  a.ws = direct ? nullptr : (float*)ctx->ws;
-  a.plan = direct ? nullptr : (int64_t*)ctx->plan;
+  a.ws = direct ? nullptr : (float*)ctx->tiled_ws;
+  a.plan = direct ? nullptr
+                  : (int64_t*)((char*)ctx->tiled_ws + partials_bytes(ctx, p.batch, p.total_nodes, p.num_q_heads,
+                                                                    p.num_kv_heads, p.head_dim));
   a.block_stride = p.cache_block_stride;
   a.head_stride = p.cache_head_stride;
   a.token_stride = p.cache_token_stride;

@@ -197,6 +197,41 @@ def test_a_captured_call_holds_no_workspace(lib):
         assert_close((out,), (ref,))
 
 
+def test_a_graph_of_the_interleaved_kernel_keeps_its_workspace(lib):
+    """Eager calls of this path grow a buffer of their own: a captured call of the interleaved bf16 kernel, which holds the
+    context's workspace, replays to the same bits between them.  One of them grows while the capture is under way."""
+    import torch
+    own = B.SmartTree(0)
+    x = Inputs([9, 30, 4], [400, 77, 129], 8, 2, 128, 16, "bf16", B.SMART_KV_INTERLEAVED)
+    big = [Inputs([100] * n, [600] * n, 8, 2, 128, 16, "bf16", B.SMART_KV_PLAIN) for n in (3, 20, 70)]
+    refs = [b.run(lib, general=True) for b in big]
+    _, _, _, mask, _ = own.tree_pack(x.cu, x.parent, x.len)
+    big_mask = own.tree_pack(big[0].cu, big[0].parent, big[0].len)[3]
+    out, big_out = torch.empty_like(x.q), torch.empty_like(big[0].q)
+    def call(i, m, o):
+        own.tree_verify_attention(i.q, i.k_tree, i.v_tree, i.k, i.v, i.table, i.len, i.cu, m, 1 / np.sqrt(128), i.layout,
+                                  block_size=16, out=o)
+    call(x, mask, out)
+    torch.cuda.synchronize()
+    ref = out.clone()
+    other = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(x, mask, out)
+        with torch.cuda.stream(other):
+            call(big[0], big_mask, big_out)
+    torch.cuda.synchronize()
+    assert_close((big_out,), (refs[0][0],))
+    for b, r in zip(big, refs):
+        assert_close(b.run(own), r)
+        junk = torch.full((1 << 24,), float("nan"), device="cuda")      # what a freed workspace would be handed out as
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+        del junk
+
+
 @pytest.mark.parametrize("dtype,longest", [("bf16", 512), ("f32", 64)])
 def test_around_the_one_launch_rule(lib, dtype, longest):
     """Small trees on tables that hold at most, and just more than, what one workgroup per segment takes; a mean of 64
