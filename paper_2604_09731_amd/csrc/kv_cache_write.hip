@@ -68,8 +68,9 @@ __global__ __launch_bounds__(256) void kv_cache_write_fp8_kernel(
 
 // ---- rows moved in 8-element chunks ------------------------------------------------------------------------------
 // Bound by memory: every row is read once and written once.  What the element-wise kernels above spend their time on is
-// V's 2-byte stores at a stride of 16 bytes and an integer division per element; here a thread moves 8 elements of K
-// at a time (16 bytes of bf16, contiguous in both layouts), and where eight consecutive tokens fill a whole slot group
+// V's 2-byte stores at a stride of 16 bytes and an integer division per element.  With enough tokens (rows_pay, below) a
+// thread moves 8 elements of K at a time (16 bytes of bf16, contiguous in both layouts), and where eight consecutive tokens
+// fill a whole slot group
 // (slots 8 s .. 8 s + 7 of a block, what every prompt longer than a few tokens consists of) V is transposed in registers:
 // a thread reads two head dims of the eight tokens and stores two whole 8-slot vectors.  A workgroup takes eight tokens.
 // 8190 tokens of 8 x 128 bf16 (67 MB moved), interleaved: 42.7 -> 17.8 us.
@@ -190,50 +191,65 @@ __global__ __launch_bounds__(kThreads) void kv_cache_write_rows_kernel(
     }
   }
   // V of tokens outside whole groups: a prompt's ragged end, single tokens
-  uint32_t single = (uint32_t)((__ballot(slot >= 0) & ~member) >> 7) & 0xFFu;
-  while (single) {
-    const int i = __ffs(single) - 1;
-    single &= single - 1;
-    const int s = __builtin_amdgcn_readlane(in_block, 7 + i);
-    const int64_t page = (int64_t)(uint32_t)__builtin_amdgcn_readlane(block, 7 + i) * block_stride;
-    for (int e = threadIdx.x; e < E; e += kThreads) {
-      const int g = e / D, d = e - g * D;
-      v_cache[page + (int64_t)g * head_stride + ((int64_t)(s >> 3) * D + d) * 8 + (s & 7)] =
-          cache_elem<C>(v_src[(int64_t)(t0 + i) * E + e], v_scale);
+  const uint32_t single = (uint32_t)((__ballot(slot >= 0) & ~member) >> 7) & 0xFFu;
+  if (single == 0) return;
+  for (int e = threadIdx.x; e < E; e += kThreads) {
+    const int g = e / D, d = e - g * D;
+    T x[kRowsPerWg];  // (all eight requested at once; a token past the end is read again, never stored)
+#pragma unroll
+    for (int i = 0; i < kRowsPerWg; ++i) x[i] = v_src[(int64_t)min(t0 + i, n_tokens - 1) * E + e];
+#pragma unroll
+    for (int i = 0; i < kRowsPerWg; ++i) {
+      if (((single >> i) & 1u) == 0) continue;
+      const int s = __builtin_amdgcn_readlane(in_block, 7 + i);
+      const int64_t page = (int64_t)(uint32_t)__builtin_amdgcn_readlane(block, 7 + i) * block_stride;
+      v_cache[page + (int64_t)g * head_stride + ((int64_t)(s >> 3) * D + d) * 8 + (s & 7)] = cache_elem<C>(x[i], v_scale);
     }
   }
 }
 
-// Whether every chunk of the call can be moved with one aligned access per side.
-static bool rows_in_chunks(bool fp8, int kv_layout, int head_dim, const void* k_src, const void* v_src,
+// Whether every chunk of the call can be moved with one aligned access per side (offsets inside a page are 32-bit there).
+static bool rows_in_chunks(bool fp8, int kv_layout, int head_dim, int block_size, const void* k_src, const void* v_src,
                            const void* k_cache, const void* v_cache, int64_t block_stride, int64_t head_stride,
                            int64_t token_stride) {
   const uintptr_t cache_align = fp8 ? 8 : 16;
   auto aligned = [](const void* p, uintptr_t n) { return ((uintptr_t)p & (n - 1)) == 0; };
-  return head_dim % 8 == 0 && block_stride % 8 == 0 && head_stride % 8 == 0 &&
+  return head_dim % 8 == 0 && (int64_t)head_dim * block_size < (1 << 30) && block_stride % 8 == 0 && head_stride % 8 == 0 &&
          (kv_layout == SMART_KV_INTERLEAVED || token_stride % 8 == 0) && aligned(k_src, 16) && aligned(v_src, 16) &&
          aligned(k_cache, cache_align) && aligned(v_cache, cache_align);
 }
 
-template <typename T, typename C>
-static void launch_rows(hipStream_t s, int kv_layout, int n_tokens, int Hkv, int D, int block_size, int num_blocks,
-                        const void* k_src, const void* v_src, const int64_t* slots, void* k_cache, void* v_cache,
-                        int64_t block_stride, int64_t head_stride, int64_t token_stride, float k_scale, float v_scale) {
+// Whether the chunk kernel is the faster one (start to end on the device, 6 prompts, chunk kernel against element-wise kernel).
+// Its threads do more one after the other, so it needs enough tokens to fill the chip:
+//   interleaved, 8 x 128 bf16: 400 tokens 6.7 us against 5.1, 800 6.3 / 6.9, 3200 9.9 / 19.1, 12800 25 / 66 (fp32 9.1 / 6.2,
+//   8.5 / 9.4, 17 / 29, 44 / 107); 2 x 64 bf16: 1200 3.6 / 3.5, 1600 3.7 / 3.9, 12800 5.4 / 12.2.
+//   Into fp8 the conversions bound both: 8 x 128 3200 17.2-19.2 / 17.4-17.7, 6400 25-27 / 28-31, 12800 32-39 / 50-55; 2 x 64
+//   6400 9.5 / 8.3, 12800 10.9 / 12.9.
+//   Plain pages need no transposing; 16-byte stores gain only for bf16: 8 x 128 at any size (4 tokens 2.6 / 2.9, 12800 16.8 /
+//   23.5), narrower rows from 2^18 elements on (2 x 64: 1600 tokens 2.8 / 2.9, 800 2.7 / 2.6); fp32 34 / 33, fp8 no gain.
+static bool rows_pay(bool f32, bool fp8, int kv_layout, int64_t n_tokens, int64_t row) {
+  if (kv_layout == SMART_KV_PLAIN) return !f32 && !fp8 && (row >= 1024 || n_tokens * row >= (1 << 18));
+  if (fp8) return n_tokens >= (row >= 512 ? 6400 : 12800);
+  return n_tokens >= (row >= 512 ? 800 : 1600);
+}
+
+template <typename T, typename C, bool kInterleaved>
+static void launch_rows(hipStream_t s, int n_tokens, int Hkv, int D, int block_size, int num_blocks, const void* k_src,
+                        const void* v_src, const int64_t* slots, void* k_cache, void* v_cache, int64_t block_stride,
+                        int64_t head_stride, int64_t token_stride, float k_scale, float v_scale) {
   const dim3 grid((unsigned)(((int64_t)n_tokens + kRowsPerWg - 1) / kRowsPerWg));
-  if (kv_layout == SMART_KV_INTERLEAVED)
-    hipLaunchKernelGGL((kv_cache_write_rows_kernel<T, C, true>), grid, dim3(kThreads), 0, s, n_tokens, Hkv, D, block_size,
-                       num_blocks, (const T*)k_src, (const T*)v_src, slots, (C*)k_cache, (C*)v_cache, block_stride,
-                       head_stride, token_stride, k_scale, v_scale);
-  else
-    hipLaunchKernelGGL((kv_cache_write_rows_kernel<T, C, false>), grid, dim3(kThreads), 0, s, n_tokens, Hkv, D, block_size,
-                       num_blocks, (const T*)k_src, (const T*)v_src, slots, (C*)k_cache, (C*)v_cache, block_stride,
-                       head_stride, token_stride, k_scale, v_scale);
+  hipLaunchKernelGGL((kv_cache_write_rows_kernel<T, C, kInterleaved>), grid, dim3(kThreads), 0, s, n_tokens, Hkv, D,
+                     block_size, num_blocks, (const T*)k_src, (const T*)v_src, slots, (C*)k_cache, (C*)v_cache,
+                     block_stride, head_stride, token_stride, k_scale, v_scale);
 }
 
 // One workgroup per (path index i, sequence b).  Every wavefront takes the same accept / refuse decision from the same
 // inputs (a lane per path entry: two memory round trips, whatever the path's length); workgroup i = 0 reports it.
 // kChunks: rows move in 8-element chunks (V of interleaved pages: four elements read at once, stored one by one).
 // Four sequences, 8 kv heads of 128, max_depth 8: 5.5 us with a serial check of the path, 4.5 with this one.
+// Element-wise all the same (the launch's rule; start to end on the device, chunks against elements): into fp8, rows that
+// leave most threads idle while the others convert eight elements each (2 x 64, four sequences 4.5 us against 3.0; 8 x 128
+// 4.4 against 5.1 of the serial check by element); many wide rows of interleaved bf16 (8 x 128, 128 sequences 11.0 / 8.9).
 template <typename T, typename C, bool kChunks>
 __global__ __launch_bounds__(256) void tree_commit_kernel(
     int layout, int batch, int max_depth, int Hkv, int D, int block_size, int max_blocks, int num_blocks,
@@ -349,8 +365,10 @@ static int32_t commit_impl(smart_ctx* ctx, void* stream, int32_t dtype, bool fp8
     return SMART_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const dim3 grid(max_depth + 1, batch);
-  const bool chunks = rows_in_chunks(fp8, kv_layout, head_dim, d_k_tree, d_v_tree, d_k_cache, d_v_cache, cache_block_stride,
-                                     cache_head_stride, cache_token_stride);
+  const int64_t row = (int64_t)num_kv_heads * head_dim;
+  const bool pays = fp8 ? row >= 1024 : kv_layout == SMART_KV_PLAIN || dtype == SMART_F32 || batch * row <= 64 * 1024;
+  const bool chunks = pays && rows_in_chunks(fp8, kv_layout, head_dim, block_size, d_k_tree, d_v_tree, d_k_cache,
+                                             d_v_cache, cache_block_stride, cache_head_stride, cache_token_stride);
 #define SMART_LAUNCH_COMMIT_AS(T, C, CHUNKS)                                                                    \
   hipLaunchKernelGGL((tree_commit_kernel<T, C, CHUNKS>), grid, dim3(256), 0, s, kv_layout, batch, max_depth,   \
                      num_kv_heads, head_dim, block_size, max_blocks_per_seq, num_blocks, d_cu_nodes,           \
@@ -424,10 +442,13 @@ extern "C" int32_t kv_cache_write(smart_ctx* ctx, void* stream, int32_t dtype, i
   if (n_tokens == 0) return SMART_OK;
   if (!d_k_src || !d_v_src || !d_slot_mapping || !d_k_cache || !d_v_cache) return SMART_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  if (rows_in_chunks(false, kv_layout, head_dim, d_k_src, d_v_src, d_k_cache, d_v_cache, cache_block_stride,
+  if (rows_pay(dtype == SMART_F32, false, kv_layout, n_tokens, (int64_t)num_kv_heads * head_dim) &&
+      rows_in_chunks(false, kv_layout, head_dim, block_size, d_k_src, d_v_src, d_k_cache, d_v_cache, cache_block_stride,
                      cache_head_stride, cache_token_stride)) {
-    auto launch = dtype == SMART_F32 ? launch_rows<float, float> : launch_rows<uint16_t, uint16_t>;
-    launch(s, kv_layout, n_tokens, num_kv_heads, head_dim, block_size, num_blocks, d_k_src, d_v_src, d_slot_mapping,
+    auto launch = kv_layout == SMART_KV_PLAIN ? launch_rows<uint16_t, uint16_t, false>
+                  : dtype == SMART_F32        ? launch_rows<float, float, true>
+                                              : launch_rows<uint16_t, uint16_t, true>;
+    launch(s, n_tokens, num_kv_heads, head_dim, block_size, num_blocks, d_k_src, d_v_src, d_slot_mapping,
            d_k_cache, d_v_cache, cache_block_stride, cache_head_stride, cache_token_stride, 1.f, 1.f);
     SMART_HIP_CHECK(hipGetLastError());
     return SMART_OK;
@@ -468,10 +489,11 @@ extern "C" int32_t kv_cache_write_fp8(smart_ctx* ctx, void* stream, int32_t src_
   if (n_tokens == 0) return SMART_OK;
   if (!d_k_src || !d_v_src || !d_slot_mapping || !d_k_cache || !d_v_cache) return SMART_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  if (rows_in_chunks(true, kv_layout, head_dim, d_k_src, d_v_src, d_k_cache, d_v_cache, cache_block_stride,
+  if (rows_pay(src_dtype == SMART_F32, true, kv_layout, n_tokens, (int64_t)num_kv_heads * head_dim) &&
+      rows_in_chunks(true, kv_layout, head_dim, block_size, d_k_src, d_v_src, d_k_cache, d_v_cache, cache_block_stride,
                      cache_head_stride, cache_token_stride)) {
-    auto launch = src_dtype == SMART_F32 ? launch_rows<float, uint8_t> : launch_rows<uint16_t, uint8_t>;
-    launch(s, kv_layout, n_tokens, num_kv_heads, head_dim, block_size, num_blocks, d_k_src, d_v_src, d_slot_mapping,
+    auto launch = src_dtype == SMART_F32 ? launch_rows<float, uint8_t, true> : launch_rows<uint16_t, uint8_t, true>;
+    launch(s, n_tokens, num_kv_heads, head_dim, block_size, num_blocks, d_k_src, d_v_src, d_slot_mapping,
            d_k_cache, d_v_cache, cache_block_stride, cache_head_stride, cache_token_stride, k_scale, v_scale);
     SMART_HIP_CHECK(hipGetLastError());
     return SMART_OK;

@@ -30,15 +30,12 @@ def _slots(kind, n, bs, nb, rng):
     return s
 
 
-@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("f32", False), ("bf16", True), ("f32", True)])
-@pytest.mark.parametrize("layout", [B.SMART_KV_PLAIN, B.SMART_KV_INTERLEAVED])
-@pytest.mark.parametrize("kind", ["prompts", "offset", "reversed", "holes"])
-def test_token_runs(dtype, fp8, layout, kind):
+def _check(dtype, fp8, layout, kind, sizes):
     import torch
     lib = B.SmartTree(0)
     rng = np.random.default_rng(5)
-    for n, Hkv, D, bs in ((1, 2, 64, 8), (7, 1, 8, 16), (8, 3, 64, 24), (9, 8, 128, 16), (61, 5, 128, 64), (200, 2, 72, 8)):
-        nb = 260 // bs + 30
+    for n, Hkv, D, bs in sizes:
+        nb = 2 * n // bs + 60
         k_src, v_src = (W._normal(1, i, (n, Hkv, D), 1.0, dtype) for i in (1, 2))
         slots = _slots(kind, n, bs, nb, rng)
         keep = {}
@@ -71,6 +68,27 @@ def test_token_runs(dtype, fp8, layout, kind):
             assert not got[:, Hkv:].any() and not got[:, :, bs * D:].any()
 
 
+@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("f32", False), ("bf16", True), ("f32", True)])
+@pytest.mark.parametrize("layout", [B.SMART_KV_PLAIN, B.SMART_KV_INTERLEAVED])
+@pytest.mark.parametrize("kind", ["prompts", "offset", "reversed", "holes"])
+def test_token_runs(dtype, fp8, layout, kind):
+    _check(dtype, fp8, layout, kind, ((1, 2, 64, 8), (7, 1, 8, 16), (8, 3, 64, 24), (9, 8, 128, 16), (61, 5, 128, 64), (200, 2, 72, 8)))
+
+
+@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("f32", False), ("bf16", True), ("f32", True)])
+@pytest.mark.parametrize("layout", [B.SMART_KV_PLAIN, B.SMART_KV_INTERLEAVED])
+@pytest.mark.parametrize("kind", ["prompts", "offset", "reversed", "holes"])
+def test_runs_that_move_in_chunks(dtype, fp8, layout, kind):
+    """Token counts on both sides of where the chunk kernel takes over, for narrow and for wide rows."""
+    if layout == B.SMART_KV_PLAIN:
+        sizes = ((3, 8, 128, 16), (17, 9, 128, 24), (1927, 1, 136, 24), (1928, 1, 136, 24))
+    elif fp8:
+        sizes = ((12799, 1, 8, 16), (12803, 1, 8, 64))
+    else:
+        sizes = ((799, 4, 128, 16), (805, 4, 128, 64), (1599, 3, 24, 24), (1600, 1, 72, 8), (1606, 3, 24, 24))
+    _check(dtype, fp8, layout, kind, sizes)
+
+
 def test_rows_off_the_chunks():
     """A source that is not aligned to 16 bytes, and a token stride that is no multiple of 8: the same bytes."""
     import torch
@@ -88,13 +106,14 @@ def test_rows_off_the_chunks():
 
 @pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("f32", False), ("bf16", True)])
 @pytest.mark.parametrize("layout,pad", [(B.SMART_KV_PLAIN, 0), (B.SMART_KV_PLAIN, 2), (B.SMART_KV_INTERLEAVED, 0)])
-def test_commit_of_long_paths(dtype, fp8, layout, pad):
+@pytest.mark.parametrize("Hkv", [3, 15])
+def test_commit_of_long_paths(dtype, fp8, layout, pad, Hkv):
     """Paths of up to 128 entries (a lane per entry, three turns), refused ones among them: an entry or a block past the
     first 64 that is not there, no room in the table."""
     import torch
     lib = B.SmartTree(0)
     rng = np.random.default_rng(9)
-    n, Hkv, D, bs, max_depth = 128, 3, 72, 8, 127
+    n, D, bs, max_depth = 128, 72, 8, 127                    # (rows of 216 and of 1080 elements: by element and in chunks)
     lens = np.array([5, 0, 9, 1, 2, 3, 200], np.int32)
     alen = np.array([127, 63, 64, 0, 100, 100, 60], np.int32)
     nseq, max_blocks = len(lens), 32
