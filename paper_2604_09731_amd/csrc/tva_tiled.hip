@@ -21,6 +21,12 @@
 //   * Nothing is rounded below what the general kernel holds: bf16 products are exact in binary32, a probability goes
 //     into the second product as the sum of three bf16 values, which is its binary32 value exactly (three MFMAs per
 //     tile instead of one; the loop is bound by its loads up to about 100 rows), and fp32 uses the fp32 MFMAs.
+//   * The same range, too.  A probability's smaller parts are often zero or negative and make NaN of an infinite value,
+//     and probabilities above 1 (kRescaleStep) can take the product with a very large one past binary32.  So a row that
+//     comes out infinite or NaN is evaluated once more, key by key (Finish::walk).  Looking at the finished rows takes the
+//     first workload below from 99.2 us to 99.7 and the workspace-free form from 10.6 .. 47.0 us to 10.9 .. 47.7; a look at
+//     every staged value took it to 102, smaller parts kept off the infinities inside the loop to 105, a loop that
+//     can go over a piece again to 104 (its offsets spill).
 //
 // Two forms.  Split: the units (steps of all segments = (sequence, kv head, row group)) are cut into equal shares, one
 // per workgroup, every piece leaves a partial (max, sum, O) in slot workgroup + segment, and a second kernel merges
@@ -91,6 +97,7 @@ struct TiledArgs {
   int64_t block_stride, head_stride, token_stride;
   int64_t seg_cap;  // segments the slots have room for
   int32_t batch, total_nodes, Hq, Hkv, G, block_size, max_blocks, num_blocks;
+  bool fp8, plain;        // the cache's element type and layout, where they are no template arguments
   uint32_t block8_magic;  // token / 8 / (block_size / 8) by multiplication
   float scale;
   float c;         // softmax scale in powers of two (log2 e folded in)
@@ -605,6 +612,16 @@ __device__ inline floatx4 widen(bf16x4 x) { return __builtin_convertvector(x, fl
 __device__ inline void store4(float* p, floatx4 x) { *(floatx4*)p = x; }
 __device__ inline void store4(__bf16* p, floatx4 x) { *(bf16x4*)p = __builtin_convertvector(x, bf16x4); }
 
+// Last sequence b with cu_nodes[b] <= node (0 if there is none).
+__device__ inline int owner_of(const TiledArgs& a, int node) {
+  int lo = 0, hi = a.batch;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (a.cu_nodes[mid] <= node) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
 // Eight lanes per row; lane e of a row owns head dims 4 (e + 8 k) + 0 .. 3.  A row is a chain of memory round trips, so
 // what does not depend on each other is requested together: the mask and the query while the plan is looked up, the
 // next two tree keys while the last two are used, two partials at a time.  All lanes of a wavefront go through this
@@ -708,6 +725,100 @@ struct Finish {
     for (int k = 0; k < K4; ++k) store4((T*)a.out + row * D + 4 * (e + 8 * k), acc[k] * inv);
     if (a.lse && e == 0) a.lse[row] = l > 0.f ? m * a.scale + logf(l) : -INFINITY;
   }
+  // Whether one of the eight lanes of this row holds an infinity or NaN that does not come from NaN scores (those stay NaN
+  // whichever way they are summed).  All lanes of the wavefront take part.
+  __device__ bool row_overflowed(int lane) const {
+    float x = 0.f;
+#pragma unroll
+    for (int k = 0; k < K4; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x = fmaf(acc[k][i], 0.f, x);
+    return ((__ballot(x != 0.f) >> (lane & ~(kCombineLanes - 1))) & ((1u << kCombineLanes) - 1u)) != 0 && l < INFINITY;
+  }
+  // The whole row again, key by key: the prefix, then the tree part, in binary32 products with probabilities of at most 1.
+  // For rows that are hardly ever seen, so it is small and not fast: 2 us a key (one sequence of 16384 tokens whose values
+  // hold an infinity 33 ms, the general kernel 13.4).
+  __device__ static void walk(const TiledArgs& a, int64_t row, bool active, int e) {
+    asm volatile("" : "+v"(row));  // everything is derived anew, so that nothing lives in registers until here
+    const int node = (int)(row / a.Hq), head = (int)(row % a.Hq), g = head / a.G;
+    const int b = owner_of(a, node);
+    const Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+    Finish f;
+    f.request(a, node, head, active, e);
+    const int len = active ? sh.len : 0;
+    constexpr int kAtOnce = 2;  // keys whose loads are in flight together (the last one again past the end)
+    for (int t0 = 0; __any(t0 < len); t0 += kAtOnce) {
+      floatx4 k4[kAtOnce][K4], v4[kAtOnce][K4];
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u) {
+        const int t = max(0, min(t0 + u, len - 1)), block = t / a.block_size, slot = t - block * a.block_size;
+        const int64_t page = clamp_block(a.block_table[(int64_t)b * a.max_blocks + block], a.num_blocks) * a.block_stride +
+                             g * a.head_stride;
+#pragma unroll
+        for (int k = 0; k < K4; ++k) {
+          const int d = 4 * (e + 8 * k);  // four head dims of K, and of V in plain pages, lie together
+          const int64_t row_at = page + slot * a.token_stride + d;
+          k4[u][k] = cached4(a, a.k_cache, a.plain ? row_at : page + ((d >> 3) * a.block_size + slot) * 8 + (d & 7), false);
+          v4[u][k] = cached4(a, a.v_cache, a.plain ? row_at : page + ((slot >> 3) * D + d) * 8 + (slot & 7), !a.plain);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u) f.add_key(k4[u], v4[u], t0 + u < len, a.m_scale, a.o_scale, a.c);
+    }
+    const T* kt = (const T*)a.k_tree + ((int64_t)sh.base * a.Hkv + g) * D;
+    const T* vt = (const T*)a.v_tree + ((int64_t)sh.base * a.Hkv + g) * D;
+    for (int j = 0; __any(active && j < sh.n); ++j) {
+      const bool have = active && j < sh.n && (((j < 64 ? f.mlo >> j : f.mhi >> (j - 64)) & 1ull) != 0);
+      floatx4 k4[K4], v4[K4];
+#pragma unroll
+      for (int k = 0; k < K4; ++k)
+        if (have) {
+          const int64_t at = j * (int64_t)a.Hkv * D + 4 * (e + 8 * k);
+          k4[k] = widen(*(const Raw*)(kt + at));
+          v4[k] = widen(*(const Raw*)(vt + at));
+        }
+      f.add_key(k4, v4, have, 1.f, 1.f, a.c);
+    }
+    if (active) f.write(a, node, head, e);
+  }
+  // Four elements of the cache: together (and aligned as such, like all chunks of this path), or eight elements apart.
+  __device__ static floatx4 cached4(const TiledArgs& a, const void* p, int64_t at, bool apart) {
+    floatx4 r;
+    if (a.fp8) {
+      const uint8_t* x = (const uint8_t*)p + at;
+      const uint32_t w = apart ? x[0] | x[8] << 8 | x[16] << 16 | (uint32_t)x[24] << 24 : *(const uint32_t*)x;
+      r[0] = __builtin_amdgcn_cvt_f32_fp8(w, 0);
+      r[1] = __builtin_amdgcn_cvt_f32_fp8(w, 1);
+      r[2] = __builtin_amdgcn_cvt_f32_fp8(w, 2);
+      r[3] = __builtin_amdgcn_cvt_f32_fp8(w, 3);
+      return r;
+    }
+    const T* x = (const T*)p + at;
+    if (!apart) return widen(*(const Raw*)x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = (float)x[8 * i];
+    return r;
+  }
+  __device__ void add_key(const floatx4 (&k4)[K4], const floatx4 (&v4)[K4], bool have, float k_scale, float v_scale, float c) {
+    float x = 0.f;
+    if (have) {
+#pragma unroll
+      for (int k = 0; k < K4; ++k) {
+        const floatx4 d = widen(q[k]) * k4[k];
+        x += (d[0] + d[1]) + (d[2] + d[3]);
+      }
+    }
+    x += __shfl_xor(x, 1);
+    x += __shfl_xor(x, 2);
+    x += __shfl_xor(x, 4);
+    x *= k_scale;
+    if (!have || x == -INFINITY) return;
+    const float m_new = fmaxf(m, x), p = exp2f((x - m_new) * c), al = m_new == m ? 1.f : exp2f((m - m_new) * c);
+    l = l * al + p;
+    m = m_new;
+#pragma unroll
+    for (int k = 0; k < K4; ++k) acc[k] = acc[k] * al + p * (v_scale * v4[k]);
+  }
 };
 
 // Rows of no sequence (offsets that leave the arrays, rows past the trees): defined output.
@@ -716,16 +827,6 @@ __device__ inline void zero_row(const TiledArgs& a, int64_t row, int e) {
 #pragma unroll
   for (int k = 0; k < D / 32; ++k) store4((T*)a.out + row * D + 4 * (e + 8 * k), (floatx4)(0.f));
   if (a.lse && e == 0) a.lse[row] = -INFINITY;
-}
-
-// Last sequence b with cu_nodes[b] <= node (0 if there is none).
-__device__ inline int owner_of(const TiledArgs& a, int node) {
-  int lo = 0, hi = a.batch;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (a.cu_nodes[mid] <= node) lo = mid; else hi = mid;
-  }
-  return lo;
 }
 
 // ---- the prefix kernel ----------------------------------------------------------------------------------------------------
@@ -898,6 +999,8 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
             f.merge(f.fetch(s_ml[0][i] * a.m_scale, s_ml[1][i], regions + (i >> 5) * kRegion + (i & 31) * 4, kRowTile * 4, e),
                     a.c);
           if (active) f.write(a, node, head, e);
+          const bool again = f.row_overflowed(lane) && active;
+          if (__any(again)) f.walk(a, (int64_t)node * a.Hq + head, again, e);
         }
         break;
       }
@@ -971,16 +1074,15 @@ __global__ __launch_bounds__(kFinishWaves * kWave, 2) void tva_tiled_finish_kern
     };
     for (int64_t w = w_first; w <= w_last; w += 2) {
       const auto p0 = partial(w);
-      if (w < w_last) {
-        const auto p1 = partial(w + 1);
-        f.merge(p0, a.c);
-        f.merge(p1, a.c);
-      } else {
-        f.merge(p0, a.c);
-      }
+      auto p1 = partial(min(w + 1, w_last));  // (no branch around it, so that both are requested before the first is used)
+      if (w == w_last) p1.m = -INFINITY;
+      f.merge(p0, a.c);
+      f.merge(p1, a.c);
     }
   }
   if (owned) f.write(a, node, head, e);
+  const bool again = f.row_overflowed(lane) && owned;
+  if (__any(again)) f.walk(a, (int64_t)node * a.Hq + head, again, e);
   if (there && !owned) zero_row<T, D>(a, row, e);
 }
 
@@ -1087,6 +1189,8 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   a.block_size = p.block_size;
   a.max_blocks = p.max_blocks_per_seq;
   a.num_blocks = p.num_blocks;
+  a.fp8 = fp8;
+  a.plain = p.kv_layout == SMART_KV_PLAIN;
   // t8 / d as the high word of 2 t8 * (floor(2^31 / d) + 1): exact for t8 < 2^28 and d <= 8
   a.block8_magic = (uint32_t)((1ull << 31) / ((uint32_t)p.block_size / 8)) + 1u;
   a.scale = p.softmax_scale;
@@ -1098,7 +1202,7 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   int32_t rc = profile_begin(ctx, stream);
   if (rc != SMART_OK) return rc;
   const unsigned grid = direct ? (unsigned)segs : (unsigned)tiled_workgroups(ctx);
-  const bool plain = p.kv_layout == SMART_KV_PLAIN;
+  const bool plain = a.plain;
   hipError_t err = hipErrorInvalidValue;
 #define SMART_TILED(T, FP8, PLAIN) \
   err = p.head_dim == 128 ? launch_tiled<T, FP8, PLAIN, 128>(a, direct, grid, stream) : launch_tiled<T, FP8, PLAIN, 64>(a, direct, grid, stream)

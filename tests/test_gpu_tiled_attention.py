@@ -240,3 +240,60 @@ def test_around_the_one_launch_rule(lib, dtype, longest):
         for extra in (0, 1):
             x = Inputs(sizes, [longest, 5], 8, 2, 64, 16, dtype, B.SMART_KV_PLAIN, spare_columns=extra)
             assert_close(x.run(lib), x.run(lib, general=True))
+
+
+def _value_column(x, b, token, g, d):
+    """The view of one cached value (whatever the layout): x.v[page, g, ...] of sequence b's token, head dim d."""
+    page, slot = int(x.table[b, token // x.bs]), token % x.bs
+    if x.layout == B.SMART_KV_PLAIN:
+        return x.v[page, g, slot, d:d + 1]
+    at = ((slot // 8) * x.D + d) * 8 + slot % 8
+    return x.v[page, g, 0, at:at + 1]
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("layout", [B.SMART_KV_PLAIN, B.SMART_KV_INTERLEAVED])
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("f32", 64)])
+def test_infinite_cached_values(lib, static, layout, dtype, D):
+    """p times an infinite value is that infinity for every p > 0; opposite infinities in one head dim and NaN give NaN.
+    In the first, an inner and the last (ragged) step, for one and for several row tiles."""
+    import torch
+    inf = float("inf")
+    bs = 16 if D == 64 else 8
+    x = Inputs([40, 9, 3], [700, 333, 40], 8, 2, D, bs, dtype, layout)
+    for b, token, g, d, value in ((0, 3, 0, 5, inf), (0, 300, 1, 6, -inf), (0, 699, 0, 63, inf), (1, 0, 1, 0, -inf),
+                                  (1, 332, 0, 33, inf), (1, 10, 0, 17, inf), (1, 200, 0, 17, -inf), (2, 39, 0, 1, -inf),
+                                  (2, 7, 1, 40, float("nan")), (2, 8, 1, 41, inf)):
+        _value_column(x, b, token, g, d).fill_(value)
+    (out, lse), (ref, ref_lse) = x.run(lib, static=static), x.run(lib, general=True)
+    assert bool(torch.isposinf(ref).any()) and bool(torch.isneginf(ref).any()) and bool(torch.isnan(ref).any())
+    for test in (torch.isposinf, torch.isneginf, torch.isnan):
+        assert torch.equal(test(out), test(ref))
+    fin = torch.isfinite(ref)
+    assert_close((torch.where(fin, out, 0), lse), (torch.where(fin, ref, 0), ref_lse))
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("layout", [B.SMART_KV_PLAIN, B.SMART_KV_INTERLEAVED])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("nodes", [3, 30, 64])
+def test_values_near_the_end_of_the_range(lib, static, layout, dtype, nodes):
+    """Values of 2^118 whose weighted sum stays below 2^128 as long as no weight exceeds 1, under scores that rise by less
+    than the step in which the reference follows the maximum.  (One worker: all steps of a segment in one piece.)"""
+    import torch
+    x = Inputs([nodes], [512], 2, 1, 64, 16, dtype, layout)
+    x.q.fill_(1.0)
+    x.k_tree.zero_()
+    x.v_tree.fill_(2.0 ** 118)
+    x.v.fill_(2.0 ** 118)
+    for token in range(512):                     # score 0, then 5 (D k / sqrt(D))
+        page, slot = int(x.table[0, token // 16]), token % 16
+        k = x.k[page, 0] if layout == B.SMART_KV_PLAIN else x.k[page, 0, 0].view(8, 16, 8).transpose(0, 1)
+        k[slot] = 0.0 if token < 128 else 0.625
+    lib.set_option(B.SMART_OPT_TVA_WORKERS, 1)
+    try:
+        got, ref = x.run(lib, static=static), x.run(lib, general=True)
+    finally:
+        lib.set_option(B.SMART_OPT_TVA_WORKERS, 0)
+    assert bool(torch.isfinite(ref[0]).all())
+    assert_close(got, ref)
