@@ -546,8 +546,10 @@ int32_t kv_cache_write_fp8(smart_ctx* ctx, void* stream, int32_t src_dtype, int3
  * on are then either left untouched or zero-filled, never read.
  * d_cu_nodes must be a running sum, 0 <= cu[b] <= cu[b+1] <= total_nodes; a
  * batch whose offsets are not (checked on the device) is treated as a batch of
- * empty trees by the matrix-core path (no output row is written); the general
- * kernel zero-fills the rows of a sequence whose range leaves [0, total_nodes].
+ * empty trees by the interleaved bf16 / block_size 16 / head_dim 128 path (no
+ * output row is written); the other kernels give a row to one sequence (the one
+ * a binary search finds) and zero-fill rows that no range inside
+ * [0, total_nodes] holds.
  * Any group size G = Hq / Hkv is accepted (a tree's rows per kv head, n x G,
  * are served in groups of up to 256).
  * Host errors: SMART_EINVAL for null pointers, Hq % Hkv != 0,

@@ -95,7 +95,6 @@ struct TiledArgs {
   float* ws;       // split form: partial slots
   int64_t* plan;   // split form: units, workers, then per sequence the units and the segments before it
   int64_t block_stride, head_stride, token_stride;
-  int64_t seg_cap;  // segments the slots have room for
   int32_t batch, total_nodes, Hq, Hkv, G, block_size, max_blocks, num_blocks;
   bool fp8, plain;        // the cache's element type and layout, where they are no template arguments
   uint32_t block8_magic;  // token / 8 / (block_size / 8) by multiplication
@@ -150,15 +149,21 @@ struct Place {
 };
 
 // One wavefront goes through the batch, 64 sequences at a time: visit(first sequence, lane has one, its units and
-// segments, units and segments before it).
+// segments, units and segments before it).  False: an offset is smaller than the one before it.  Ascending offsets make
+// the sequences' ranges disjoint, which is what the segments and slots of a call were counted by; a call whose
+// offsets are not ascending has no segments at all and its rows are evaluated one by one (Finish::walk), each for the
+// sequence that owner_of finds, like the general kernel's.
 template <typename T, typename Visit>
-__device__ inline void scan_batch(const TiledArgs& a, int lane, int64_t* total_units, int64_t* total_segs,
+__device__ inline bool scan_batch(const TiledArgs& a, int lane, int64_t* total_units, int64_t* total_segs,
                                   int64_t* total_steps, Visit visit) {
   int64_t before_u = 0, before_s = 0, before_t = 0;
+  bool ascending = true;
   for (int b0 = 0; b0 < a.batch; b0 += kWave) {
     const int b = min(b0 + lane, a.batch - 1);
-    const Shape s = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+    const int base = a.cu_nodes[b], next = a.cu_nodes[b + 1];
+    const Shape s = shape_of<T>(a, a.prefix_len[b], base, next);
     const bool there = b0 + lane < a.batch;
+    ascending = ascending && !__any(next < base);
     const int64_t segs = there ? (int64_t)s.groups * a.Hkv : 0;
     const int64_t units = there ? s.head * a.Hkv : 0;
     int64_t tu, ts, tt;
@@ -173,6 +178,7 @@ __device__ inline void scan_batch(const TiledArgs& a, int lane, int64_t* total_u
   *total_units = before_u;
   *total_segs = before_s;
   *total_steps = before_t;
+  return ascending;
 }
 
 __device__ inline int clamp_block(int b, int num_blocks) { return b < 0 ? 0 : (b >= num_blocks ? num_blocks - 1 : b); }
@@ -853,7 +859,7 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
   int64_t u0 = 0, u1 = 1, U = 0, S = 0, steps = 0;
   auto find = [&](int64_t want, bool by_segment) {
     int64_t tu, ts, tt;
-    scan_batch<T>(a, lane, &tu, &ts, &tt, [&](int b0, bool, int64_t units, int64_t segs, int64_t eu, int64_t es) {
+    return scan_batch<T>(a, lane, &tu, &ts, &tt, [&](int b0, bool, int64_t units, int64_t segs, int64_t eu, int64_t es) {
       const int64_t first = by_segment ? es : eu, count = by_segment ? segs : units;
       const uint64_t hit = __ballot(want >= first && want < first + count);
       if (hit) {
@@ -864,17 +870,19 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
       }
     });
   };
+  bool ascending;
   if (kDirect) {
-    find(wg, true);
+    ascending = find(wg, true);
+    if (!ascending) at.b = -1;
   } else {
-    scan_batch<T>(a, lane, &U, &S, &steps, [&](int b0, bool there, int64_t, int64_t, int64_t eu, int64_t es) {
+    ascending = scan_batch<T>(a, lane, &U, &S, &steps, [&](int b0, bool there, int64_t, int64_t, int64_t eu, int64_t es) {
       if (wg == 0 && wv == 0 && there) {
         a.plan[2 + b0 + lane] = eu;
         a.plan[2 + a.batch + b0 + lane] = es;
       }
     });
-    if (S > a.seg_cap) U = 0;  // (offsets that are not a running sum: more segments than rows were counted for)
-    const int64_t W = U == 0 ? 0 : (steps < (int64_t)gridDim.x ? steps : (int64_t)gridDim.x);
+    if (!ascending) U = -1;
+    const int64_t W = U <= 0 ? 0 : (steps < (int64_t)gridDim.x ? steps : (int64_t)gridDim.x);
     if (wg == 0 && tid == 0) {
       a.plan[0] = U;
       a.plan[1] = W;
@@ -1015,13 +1023,18 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
     }
   }
 
-  if (kDirect) {  // rows nobody owns
+  if (kDirect) {  // rows nobody owns; all rows of a call without segments
     for (int64_t node = wg; node < a.total_nodes; node += gridDim.x) {
       const int b = owner_of(a, (int)node);
       const Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
-      if (node >= sh.base && node - sh.base < sh.n) continue;
-      for (int h = tid / kCombineLanes; h < a.Hq; h += kThreads / kCombineLanes)
-        zero_row<T, D>(a, node * a.Hq + h, tid & (kCombineLanes - 1));
+      const bool owned = node >= sh.base && node - sh.base < sh.n;
+      if (owned && ascending) continue;
+      const int e = tid & (kCombineLanes - 1);
+      for (int h0 = 0; h0 < a.Hq; h0 += kThreads / kCombineLanes) {
+        const int h = h0 + tid / kCombineLanes;
+        if (owned) Finish<T, D>::walk(a, node * a.Hq + min(h, a.Hq - 1), h < a.Hq, e);
+        else if (h < a.Hq) zero_row<T, D>(a, node * a.Hq + h, e);
+      }
     }
   }
 }
@@ -1044,6 +1057,7 @@ __global__ __launch_bounds__(kFinishWaves * kWave, 2) void tva_tiled_finish_kern
   const int node = (int)(row / a.Hq), head = (int)(row % a.Hq), g = head / a.G;
   Finish<T, D> f;
   f.request(a, node, head, there, e);
+  const int64_t U = a.plan[0], W = a.plan[1];
   int b;
   if (a.batch <= kWave) {
     // the offsets of the whole batch, one per lane; the wavefront's rows lie in a few consecutive nodes
@@ -1057,12 +1071,12 @@ __global__ __launch_bounds__(kFinishWaves * kWave, 2) void tva_tiled_finish_kern
   } else {
     b = owner_of(a, node);
   }
+  if (U < 0) b = owner_of(a, node);  // offsets that are not ascending
   const Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
-  const int64_t U = a.plan[0], W = a.plan[1];
   const int64_t units_before = a.plan[2 + b], segs_before = a.plan[2 + a.batch + b];
-  const bool owned = there && node >= sh.base && node - sh.base < sh.n && (sh.steps == 0 || U > 0);
+  const bool owned = there && node >= sh.base && (int64_t)node - sh.base < sh.n;
   f.tree(a, g, sh.base, owned ? sh.n : 0, e);
-  if (owned && sh.steps > 0) {
+  if (owned && sh.steps > 0 && U > 0) {
     const int rho = (node - sh.base) * a.G + head % a.G;
     const int group = rho / kGroupRows, r = rho % kGroupRows, local = g * sh.groups + group;
     const int64_t ub = units_before + g * sh.head + group * sh.full;
@@ -1081,7 +1095,7 @@ __global__ __launch_bounds__(kFinishWaves * kWave, 2) void tva_tiled_finish_kern
     }
   }
   if (owned) f.write(a, node, head, e);
-  const bool again = f.row_overflowed(lane) && owned;
+  const bool again = (f.row_overflowed(lane) || U < 0) && owned;
   if (__any(again)) f.walk(a, (int64_t)node * a.Hq + head, again, e);
   if (there && !owned) zero_row<T, D>(a, row, e);
 }
@@ -1180,7 +1194,6 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   a.block_stride = p.cache_block_stride;
   a.head_stride = p.cache_head_stride;
   a.token_stride = p.cache_token_stride;
-  a.seg_cap = segs;
   a.batch = p.batch;
   a.total_nodes = p.total_nodes;
   a.Hq = p.num_q_heads;

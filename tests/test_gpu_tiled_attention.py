@@ -297,3 +297,21 @@ def test_values_near_the_end_of_the_range(lib, static, layout, dtype, nodes):
         lib.set_option(B.SMART_OPT_TVA_WORKERS, 0)
     assert bool(torch.isfinite(ref[0]).all())
     assert_close(got, ref)
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("dtype,fp8,layout", [("bf16", False, B.SMART_KV_PLAIN), ("f32", True, B.SMART_KV_INTERLEAVED),
+                                              ("f32", False, B.SMART_KV_PLAIN), ("bf16", True, B.SMART_KV_INTERLEAVED)])
+def test_offsets_that_are_not_ascending(lib, static, dtype, fp8, layout):
+    """Overlapping ranges, more segments than the rows were counted for, descending offsets, batches on both sides of 64:
+    every row has the one owner that the general kernel finds, and its value."""
+    import torch
+    g = np.random.default_rng(4)
+    for sizes, lens, offsets in (([5, 20, 70, 3, 9], [100, 333, 64, 0, 50], [0, 25, 5, 95, 98, 107]),
+                                 ([2] * 64, list(g.integers(0, 90, 64)), [0, 128] * 32 + [0]),
+                                 ([2] * 65, list(g.integers(0, 90, 65)), list(range(130, -1, -2))),
+                                 ([30, 40], [70, 90], [40, 0, 70]), ([30, 40], [70, 90], [50, -3, 70])):
+        x = Inputs(sizes, lens, 8, 2, 64, 8, dtype, layout, fp8)
+        cu = torch.tensor(offsets, dtype=torch.int64).to(torch.int32).cuda()
+        ref = x.run(lib, general=True, cu=cu, out=torch.full_like(x.q, 7.0))
+        assert_close(x.run(lib, cu=cu, static=static, out=torch.full_like(x.q, 7.0)), ref)
