@@ -122,7 +122,9 @@ int32_t smart_create(smart_ctx** out_ctx, int32_t device_id);
 int32_t smart_destroy(smart_ctx* ctx);
 /* Pre-sizes the attention workspace for calls with at most this many sequences,
  * total tree nodes, query heads and kv heads (head_dim <= 128), so that later
- * tree_verify_attention calls do not allocate. */
+ * tree_verify_attention calls do not allocate.  (One buffer serves every kernel.  A
+ * tiled call that it is too small for grows a second one, kept until smart_destroy;
+ * where there is no memory for that it runs its workspace-free form.) */
 int32_t smart_reserve(smart_ctx* ctx, int32_t max_batch, int32_t max_total_nodes,
                       int32_t max_q_heads, int32_t max_kv_heads);
 int32_t smart_set_option(smart_ctx* ctx, int32_t key, int64_t value);

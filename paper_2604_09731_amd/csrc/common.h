@@ -16,8 +16,9 @@ struct smart_ctx {
   size_t ws_bytes = 0;
   int32_t* plan = nullptr;    // launch plan written by the planning kernel
   size_t plan_bytes = 0;
-  void* tiled_ws = nullptr;   // the tiled path's partial results and plan; no graph ever holds it
+  void* tiled_ws = nullptr;   // the tiled path's partial results and plan where ws is too small; no graph ever holds it
   size_t tiled_ws_bytes = 0;
+  size_t tiled_refused = SIZE_MAX;  // the smallest size of it that there was no memory for
   // options
   int64_t opt_workers = 0;
   int64_t opt_force_general = 0;
@@ -52,10 +53,11 @@ void set_last_hip_error(hipError_t e);
 // Makes sure the context's workspace holds at least the given sizes.  May
 // synchronise `stream` (only when it has to grow).
 int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, size_t plan_bytes);
-// The same for the tiled path's buffer, which is apart from the one above: its calls served without a workspace before
-// they had a faster form, so they must not replace a buffer that a captured launch of another path still reads.  False
-// (nothing changed, no error left behind) if it cannot grow: the caller then takes its workspace-free form.
-bool ensure_tiled_workspace(smart_ctx* ctx, hipStream_t stream, size_t bytes);
+// The tiled path's buffer: the one above if it is large enough (calls of a context are serialised), else one of its own,
+// which grows.  Its calls are served without a workspace too, so they never replace a buffer that a captured launch of
+// another path still reads.  SMART_ENOMEM (no error left behind): no memory, the caller takes its workspace-free form;
+// the size is not asked for again until smart_reserve is called.
+int32_t tiled_workspace(smart_ctx* ctx, hipStream_t stream, size_t bytes, void** ws);
 
 // Profiling hooks: bracket the dominant kernel of the current call.
 int32_t profile_begin(smart_ctx* ctx, hipStream_t stream);
@@ -80,8 +82,9 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
 // The tiled matrix-core path: every other type, layout, head dim and block size whose rows are aligned.
 int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed);
 bool tva_tiled_supported(const tva_params& p);
-size_t tva_tiled_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
-                           int32_t num_kv_heads, int32_t head_dim);
+// Its buffer for any call of at most these sizes (head counts that divide in any way, any head dim).
+size_t tva_tiled_reserve(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
+                         int32_t num_kv_heads);
 // Dispatch between them (validated params, the context's device current).
 int32_t tva_dispatch(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed);
 // This device's copy of the library's static scratch array (the device must be current); resolved once per device.

@@ -31,26 +31,32 @@ int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, si
   return SMART_OK;
 }
 
-bool ensure_tiled_workspace(smart_ctx* ctx, hipStream_t stream, size_t bytes) {
-  if (bytes <= ctx->tiled_ws_bytes) return true;
+int32_t tiled_workspace(smart_ctx* ctx, hipStream_t stream, size_t bytes, void** ws) {
+  *ws = bytes <= ctx->ws_bytes ? ctx->ws : ctx->tiled_ws;
+  if (bytes <= ctx->ws_bytes || bytes <= ctx->tiled_ws_bytes) return SMART_OK;
+  if (bytes >= ctx->tiled_refused) return SMART_ENOMEM;
   // another stream of this process may be under capture, which an allocation in the default mode would end
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
   void* fresh = nullptr;
-  bool ok = hipMalloc(&fresh, bytes) == hipSuccess;
-  if (ok && ctx->tiled_ws) {
+  hipError_t e = hipMalloc(&fresh, bytes);
+  int32_t rc = e == hipSuccess ? SMART_OK : (e == hipErrorOutOfMemory ? SMART_ENOMEM : SMART_EHIP);
+  if (rc == SMART_OK && ctx->tiled_ws) {
     // work already enqueued may still use the old buffer
-    ok = hipStreamSynchronize(stream) == hipSuccess;
-    (void)hipFree(ok ? ctx->tiled_ws : fresh);
+    e = hipStreamSynchronize(stream);
+    if (e != hipSuccess) rc = SMART_EHIP;
+    (void)hipFree(rc == SMART_OK ? ctx->tiled_ws : fresh);
   }
-  if (ok) {
-    ctx->tiled_ws = fresh;
+  if (rc == SMART_OK) {
+    *ws = ctx->tiled_ws = fresh;
     ctx->tiled_ws_bytes = bytes;
   } else {
+    set_last_hip_error(e);
     (void)hipGetLastError();
+    if (rc == SMART_ENOMEM) ctx->tiled_refused = bytes;
   }
   if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
-  return ok;
+  return rc;
 }
 
 static void profile_free(smart_ctx* ctx) {
@@ -239,11 +245,10 @@ extern "C" int32_t smart_reserve(smart_ctx* ctx, int32_t max_batch, int32_t max_
   SMART_HIP_CHECK(hipSetDevice(ctx->device));
   size_t ws = 0, plan = 0;
   smart::tva_mfma_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, &ws, &plan);
-  int32_t rc = smart::ensure_workspace(ctx, nullptr, ws, plan);
-  // (head dim 128: the larger one; without it the tiled path runs its workspace-free form, which is no error)
-  if (rc == SMART_OK)
-    (void)smart::ensure_tiled_workspace(
-        ctx, nullptr, smart::tva_tiled_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, 128));
+  // (one buffer for both: the tiled path's needs are the smaller ones but for rounding in its favour)
+  const size_t tiled = smart::tva_tiled_reserve(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads);
+  const int32_t rc = smart::ensure_workspace(ctx, nullptr, ws > tiled ? ws : tiled, plan);
+  ctx->tiled_refused = SIZE_MAX;
   (void)hipSetDevice(prev);
   return rc;
 }

@@ -1115,17 +1115,16 @@ static int64_t tiled_segments(int32_t batch, int32_t total_nodes, int32_t num_q_
   return (int64_t)num_kv_heads * (((int64_t)total_nodes * G + kGroupRows - 1) / kGroupRows + batch);
 }
 
-static size_t partials_bytes(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
-                             int32_t num_kv_heads, int32_t head_dim) {
-  const int64_t slots = tiled_workgroups(ctx) + tiled_segments(batch, total_nodes, num_q_heads, num_kv_heads) + 1;
-  return ((size_t)slots * slot_floats(head_dim) * sizeof(float) + 255) & ~(size_t)255;
+static size_t partials_bytes(const smart_ctx* ctx, int64_t segs, int32_t head_dim) {
+  return ((size_t)(tiled_workgroups(ctx) + segs + 1) * slot_floats(head_dim) * sizeof(float) + 255) & ~(size_t)255;
 }
+static size_t plan_bytes(int32_t batch) { return sizeof(int64_t) * (2 + 2 * (size_t)batch); }
 
-// the partial results, then the plan
-size_t tva_tiled_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
-                           int32_t num_kv_heads, int32_t head_dim) {
-  return partials_bytes(ctx, batch, total_nodes, num_q_heads, num_kv_heads, head_dim) +
-         sizeof(int64_t) * (2 + 2 * (size_t)batch);
+// (no smaller head counts have more segments: Hkv ceil(N G / 128) < N Hq / 128 + Hkv)
+size_t tva_tiled_reserve(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
+                         int32_t num_kv_heads) {
+  const int64_t segs = ((int64_t)total_nodes * num_q_heads + kGroupRows - 1) / kGroupRows + (int64_t)num_kv_heads * (batch + 1);
+  return partials_bytes(ctx, segs, 128) + plan_bytes(batch);
 }
 
 // Every 16-byte chunk of a staged row, every query row and every tree row must be addressable with one load.
@@ -1171,9 +1170,13 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
     if (stream != nullptr && hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
     direct = capture != hipStreamCaptureStatusNone;
   }
-  if (!direct)
-    direct = !ensure_tiled_workspace(
-        ctx, stream, tva_tiled_workspace(ctx, p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads, p.head_dim));
+  void* ws = nullptr;
+  const size_t partials = partials_bytes(ctx, segs, p.head_dim);  // then the plan
+  if (!direct) {
+    const int32_t rc = tiled_workspace(ctx, stream, partials + plan_bytes(p.batch), &ws);
+    if (rc == SMART_EHIP) return rc;
+    direct = rc != SMART_OK;
+  }
   TiledArgs a;
   a.q = p.d_q;
   a.k_tree = p.d_k_tree;
@@ -1187,10 +1190,8 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   a.out = p.d_out;
   a.lse = p.d_lse;
   a.status = p.d_status;
-  a.ws = direct ? nullptr : (float*)ctx->tiled_ws;
-  a.plan = direct ? nullptr
-                  : (int64_t*)((char*)ctx->tiled_ws + partials_bytes(ctx, p.batch, p.total_nodes, p.num_q_heads,
-                                                                    p.num_kv_heads, p.head_dim));
+  a.ws = direct ? nullptr : (float*)ws;
+  a.plan = direct ? nullptr : (int64_t*)((char*)ws + partials);
   a.block_stride = p.cache_block_stride;
   a.head_stride = p.cache_head_stride;
   a.token_stride = p.cache_token_stride;
