@@ -136,10 +136,17 @@ __global__ __launch_bounds__(kThreads) void kv_cache_write_rows_kernel(
   member |= member << 4;  // a group's eight tokens
   const uint32_t block = slot >= 0 ? (uint32_t)((uint64_t)slot / (uint32_t)block_size) : 0u;
   const int in_block = slot >= 0 ? (int)(slot - (int64_t)block * block_size) : -1;
+  // Token i of the eight: its slot and block, from the lane that holds them.  Every lane of the wavefront has to take part
+  // (a lane that has left a loop need not keep its registers), so the loops below end for whole wavefronts.
+  auto slot_of = [&](int i) { return __builtin_amdgcn_readlane(in_block, 7 + i); };
+  auto block_of = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane(block, 7 + i); };
+  const int first = threadIdx.x & ~63;
   const int E = Hkv * D, chunks = E / 8;
 
   // K (and V of plain pages, or of tokens outside whole groups): four tokens of one chunk per thread and turn
-  for (int u = threadIdx.x; u < 2 * chunks; u += kThreads) {
+  for (int u0 = first; u0 < 2 * chunks; u0 += kThreads) {
+    const bool mine = u0 + lane < 2 * chunks;
+    const int u = min(u0 + lane, 2 * chunks - 1);  // (loaded again, never stored)
     const int half = u >= chunks ? 1 : 0, c = u - half * chunks;
     const int g = c / (D / 8), d8 = c - g * (D / 8);
     const int64_t head = (int64_t)g * head_stride;
@@ -150,13 +157,20 @@ __global__ __launch_bounds__(kThreads) void kv_cache_write_rows_kernel(
       kx[i] = load8(k_src + (int64_t)tok * E + 8 * c);
       if (!kInterleaved) vx[i] = load8(v_src + (int64_t)tok * E + 8 * c);
     }
+    int s_of[4];
+    uint32_t b_of[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int s0 = __builtin_amdgcn_readlane(in_block, 7 + i), s1 = __builtin_amdgcn_readlane(in_block, 11 + i);
-      const uint32_t b0 = __builtin_amdgcn_readlane(block, 7 + i), b1 = __builtin_amdgcn_readlane(block, 11 + i);
-      const int s = half ? s1 : s0;
-      if (s < 0) continue;
-      const int64_t page = (int64_t)(half ? b1 : b0) * block_stride + head;
+      const int s0 = slot_of(i), s1 = slot_of(4 + i);
+      const uint32_t b0 = block_of(i), b1 = block_of(4 + i);
+      s_of[i] = half ? s1 : s0;
+      b_of[i] = half ? b1 : b0;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int s = s_of[i];
+      if (s < 0 || !mine) continue;
+      const int64_t page = (int64_t)b_of[i] * block_stride + head;
       if (kInterleaved) {
         store8(k_cache + page + (d8 * block_size + s) * 8, cache_elems<C>(kx[i], k_scale));
       } else {
@@ -193,17 +207,18 @@ __global__ __launch_bounds__(kThreads) void kv_cache_write_rows_kernel(
   // V of tokens outside whole groups: a prompt's ragged end, single tokens
   const uint32_t single = (uint32_t)((__ballot(slot >= 0) & ~member) >> 7) & 0xFFu;
   if (single == 0) return;
-  for (int e = threadIdx.x; e < E; e += kThreads) {
-    const int g = e / D, d = e - g * D;
+  for (int e0 = first; e0 < E; e0 += kThreads) {
+    const int e = min(e0 + lane, E - 1), g = e / D, d = e - g * D;
     T x[kRowsPerWg];  // (all eight requested at once; a token past the end is read again, never stored)
 #pragma unroll
     for (int i = 0; i < kRowsPerWg; ++i) x[i] = v_src[(int64_t)min(t0 + i, n_tokens - 1) * E + e];
 #pragma unroll
     for (int i = 0; i < kRowsPerWg; ++i) {
-      if (((single >> i) & 1u) == 0) continue;
-      const int s = __builtin_amdgcn_readlane(in_block, 7 + i);
-      const int64_t page = (int64_t)(uint32_t)__builtin_amdgcn_readlane(block, 7 + i) * block_stride;
-      v_cache[page + (int64_t)g * head_stride + ((int64_t)(s >> 3) * D + d) * 8 + (s & 7)] = cache_elem<C>(x[i], v_scale);
+      if (((single >> i) & 1u) == 0) continue;  // (the same for all lanes)
+      const int s = slot_of(i);
+      const int64_t page = (int64_t)block_of(i) * block_stride;
+      if (e0 + lane < E)
+        v_cache[page + (int64_t)g * head_stride + ((int64_t)(s >> 3) * D + d) * 8 + (s & 7)] = cache_elem<C>(x[i], v_scale);
     }
   }
 }

@@ -79,13 +79,14 @@ def test_token_runs(dtype, fp8, layout, kind):
 @pytest.mark.parametrize("layout", [B.SMART_KV_PLAIN, B.SMART_KV_INTERLEAVED])
 @pytest.mark.parametrize("kind", ["prompts", "offset", "reversed", "holes"])
 def test_runs_that_move_in_chunks(dtype, fp8, layout, kind):
-    """Token counts on both sides of where the chunk kernel takes over, for narrow and for wide rows."""
+    """Token counts on both sides of where the chunk kernel takes over, for narrow rows (down to one chunk: most lanes have
+    nothing to move) and for wide ones."""
     if layout == B.SMART_KV_PLAIN:
-        sizes = ((3, 8, 128, 16), (17, 9, 128, 24), (1927, 1, 136, 24), (1928, 1, 136, 24))
+        sizes = ((3, 8, 128, 16), (17, 9, 128, 24), (1927, 1, 136, 24), (1928, 1, 136, 24), (32768, 1, 8, 16))
     elif fp8:
         sizes = ((12799, 1, 8, 16), (12803, 1, 8, 64))
     else:
-        sizes = ((799, 4, 128, 16), (805, 4, 128, 64), (1599, 3, 24, 24), (1600, 1, 72, 8), (1606, 3, 24, 24))
+        sizes = ((799, 4, 128, 16), (805, 4, 128, 64), (1599, 3, 24, 24), (1600, 1, 72, 8), (1606, 3, 24, 24), (1605, 1, 8, 16))
     _check(dtype, fp8, layout, kind, sizes)
 
 
