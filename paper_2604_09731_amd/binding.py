@@ -376,7 +376,11 @@ def _torch():
 
 # Marshalling is most of a small call's host time (a step of a few users waits for the host, not for the GPU): addresses
 # go to ctypes as plain integers (its argument types convert them; an object per address costs 0.2 us more), and
-# outputs of one type and length are rows of one allocation.
+# int32 outputs of one length are rows of one allocation, each where an allocation of its own would begin (the device
+# allocator hands out multiples of 512 bytes).  Whoever keeps one of them keeps the memory of all: clone() it instead.
+_ROW = 128      # int32 elements
+
+
 def _stream_ptr():
     cuda = _torch().cuda
     # (the handle itself: building the Stream object around it takes 3 us, as long as a small call's kernel)
@@ -388,11 +392,14 @@ def _ptr(t):
     return t.data_ptr() if t is not None else None
 
 
-def _i32_rows(rows, n, device, zero=False):
+def _whole_rows(n):
+    return (n + _ROW - 1) // _ROW * _ROW
+
+
+def _i32_rows(rows, n, device):
     """`rows` int32 tensors of length n from one allocation."""
     torch = _torch()
-    make = torch.zeros if zero else torch.empty
-    return make((rows, n), dtype=torch.int32, device=device).unbind(0)
+    return torch.empty_strided((rows, n), (_whole_rows(n), 1), dtype=torch.int32, device=device).unbind(0)
 
 
 def _dtype_code(t):
@@ -512,11 +519,15 @@ class SmartTree:
         B = state.batch
         N = int(total_cap if total_cap is not None else B * state.budget)
         dev = prefix_len.device
-        # one allocation and one fill for everything: the masks (16 bytes a node) first, so that they stay aligned
+        # one allocation and one fill for everything: the masks (16 bytes a node), the rows of node values, the offsets, the
+        # statuses, each in whole rows
         n1, b1 = max(1, N), max(1, B)
-        masks, par, tok, depth, position, node_seq, cu, status = torch.zeros(
-            9 * n1 + B + 1 + b1, dtype=torch.int32, device=dev).split([4 * n1, n1, n1, n1, n1, n1, B + 1, b1])
-        anc_mask = masks.view(torch.int64).view(n1, 2)
+        p, at = _whole_rows(n1), _whole_rows(4 * n1)
+        buf = torch.zeros(at + 5 * p + _whole_rows(B + 1) + b1, dtype=torch.int32, device=dev)
+        anc_mask = buf[:4 * n1].view(torch.int64).view(n1, 2)
+        par, tok, depth, position, node_seq = buf.as_strided((5, n1), (p, 1), at).unbind(0)
+        cu = buf.as_strided((B + 1,), (1,), at + 5 * p)
+        status = buf.as_strided((b1,), (1,), at + 5 * p + _whole_rows(B + 1))
         rc = _lib().tree_compact_pack(self._h, _stream_ptr(), ctypes.byref(state.struct), N, _ptr(prefix_len),
                                       _ptr(cu), _ptr(par), _ptr(tok), _ptr(depth), _ptr(position), _ptr(node_seq),
                                       _ptr(anc_mask), _ptr(status))
