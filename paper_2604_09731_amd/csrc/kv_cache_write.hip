@@ -259,12 +259,10 @@ static void launch_rows(hipStream_t s, int n_tokens, int Hkv, int D, int block_s
 }
 
 // One workgroup per (path index i, sequence b).  Every wavefront takes the same accept / refuse decision from the same
-// inputs (a lane per path entry: two memory round trips, whatever the path's length); workgroup i = 0 reports it.
-// kChunks: rows move in 8-element chunks (V of interleaved pages: four elements read at once, stored one by one).
-// Four sequences, 8 kv heads of 128, max_depth 8: 5.5 us with a serial check of the path, 4.5 with this one.
-// Element-wise all the same (the launch's rule; start to end on the device, chunks against elements): into fp8, rows that
-// leave most threads idle while the others convert eight elements each (2 x 64, four sequences 4.5 us against 3.0; 8 x 128
-// 4.4 against 5.1 of the serial check by element); many wide rows of interleaved bf16 (8 x 128, 128 sequences 11.0 / 8.9).
+// inputs (a lane per path entry: two memory round trips per 64 entries); workgroup i = 0 reports it.
+// kChunks: rows move in 8-element chunks (V of interleaved pages: four elements read at once, stored one by one); see
+// commit_in_chunks.  Four sequences, 8 kv heads of 128, max_depth 8, interleaved bf16: 4.0 us with a serial check of the
+// path, 3.6 with this one by element, 3.4 in chunks (start to end on the device).
 template <typename T, typename C, bool kChunks>
 __global__ __launch_bounds__(256) void tree_commit_kernel(
     int layout, int batch, int max_depth, int Hkv, int D, int block_size, int max_blocks, int num_blocks,
@@ -350,6 +348,20 @@ __global__ __launch_bounds__(256) void tree_commit_kernel(
 
 }  // namespace
 
+// Whether chunks are the faster way (start to end on the device, paths of 5 entries, chunks against elements).
+//   Into fp8 a thread converts eight elements in a row, so rows have to occupy the workgroup: 8 x 128, 1 .. 128 sequences,
+//   4.2 .. 8.0 us against 4.5 .. 8.3; 4 x 128 plain 4.2 .. 5.4 against 3.5 .. 4.5, interleaved equal; 2 x 64 4.1 .. 5.5 against
+//   2.9 .. 3.9.
+//   Plain pages: 8 x 128 2.7 .. 4.2 against 3.2 .. 4.7, 4 x 128 2.7 .. 3.7 against 2.8 .. 3.9; 4 x 64 and 2 x 64 2.6 .. 3.7 against
+//   2.6 .. 3.6.
+//   Interleaved pages: 8 x 128 up to 8 sequences 3.3 .. 3.7 against 3.5 .. 3.8, 16 equal, 32 5.0 .. 5.2 against 4.8 .. 4.9, 128 bf16
+//   11.0 against 9.0; 4 x 128 2.9 .. 3.2 against 3.0 .. 3.2, 16 equal, 128 6.1 .. 7.7 against 5.2 .. 7.1; 4 x 64 and 2 x 64
+//   2.8 .. 4.9 against 2.7 .. 4.6.
+static bool commit_in_chunks(bool fp8, int kv_layout, int64_t batch, int64_t row) {
+  if (fp8) return row >= 1024;
+  return row >= 512 && (kv_layout == SMART_KV_PLAIN || batch <= 16);
+}
+
 static int32_t commit_impl(smart_ctx* ctx, void* stream, int32_t dtype, bool fp8, int32_t kv_layout,
                            int32_t batch, int32_t max_depth, int32_t num_kv_heads, int32_t head_dim,
                            int32_t block_size, int32_t max_blocks_per_seq, int32_t num_blocks,
@@ -380,10 +392,9 @@ static int32_t commit_impl(smart_ctx* ctx, void* stream, int32_t dtype, bool fp8
     return SMART_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const dim3 grid(max_depth + 1, batch);
-  const int64_t row = (int64_t)num_kv_heads * head_dim;
-  const bool pays = fp8 ? row >= 1024 : kv_layout == SMART_KV_PLAIN || dtype == SMART_F32 || batch * row <= 64 * 1024;
-  const bool chunks = pays && rows_in_chunks(fp8, kv_layout, head_dim, block_size, d_k_tree, d_v_tree, d_k_cache,
-                                             d_v_cache, cache_block_stride, cache_head_stride, cache_token_stride);
+  const bool chunks = commit_in_chunks(fp8, kv_layout, batch, (int64_t)num_kv_heads * head_dim) &&
+                      rows_in_chunks(fp8, kv_layout, head_dim, block_size, d_k_tree, d_v_tree, d_k_cache, d_v_cache,
+                                     cache_block_stride, cache_head_stride, cache_token_stride);
 #define SMART_LAUNCH_COMMIT_AS(T, C, CHUNKS)                                                                    \
   hipLaunchKernelGGL((tree_commit_kernel<T, C, CHUNKS>), grid, dim3(256), 0, s, kv_layout, batch, max_depth,   \
                      num_kv_heads, head_dim, block_size, max_blocks_per_seq, num_blocks, d_cu_nodes,           \

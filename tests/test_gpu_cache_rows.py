@@ -105,16 +105,16 @@ def test_rows_off_the_chunks():
             assert torch.equal(c.permute(0, 2, 1, 3).reshape(nb * bs, Hkv, stride)[:n, :, :D], x)
 
 
-@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("f32", False), ("bf16", True)])
+@pytest.mark.parametrize("dtype,fp8", [("bf16", False), ("f32", False), ("bf16", True), ("f32", True)])
 @pytest.mark.parametrize("layout,pad", [(B.SMART_KV_PLAIN, 0), (B.SMART_KV_PLAIN, 2), (B.SMART_KV_INTERLEAVED, 0)])
-@pytest.mark.parametrize("Hkv", [3, 15])
+@pytest.mark.parametrize("Hkv", [3, 8, 15])
 def test_commit_of_long_paths(dtype, fp8, layout, pad, Hkv):
     """Paths of up to 128 entries (a lane per entry, three turns), refused ones among them: an entry or a block past the
     first 64 that is not there, no room in the table."""
     import torch
     lib = B.SmartTree(0)
     rng = np.random.default_rng(9)
-    n, D, bs, max_depth = 128, 72, 8, 127                    # (rows of 216 and of 1080 elements: by element and in chunks)
+    n, D, bs, max_depth = 128, 72, 8, 127                    # (rows of 216, 576 and 1080 elements: by element, in chunks but for fp8, in chunks)
     lens = np.array([5, 0, 9, 1, 2, 3, 200], np.int32)
     alen = np.array([127, 63, 64, 0, 100, 100, 60], np.int32)
     nseq, max_blocks = len(lens), 32
