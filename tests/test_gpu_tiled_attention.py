@@ -1,8 +1,9 @@
 """The tiled matrix-core attention path (every type, layout, head dim and block size besides bf16 / interleaved /
-128 / 16) against the general kernel, which walks the keys of one row at a time in fp32, over the forms both accept.
+128 / 16) against the general kernel, which walks the keys of one row at a time in fp32, over the forms both accept,
+with prefixes of up to 700 keys; and against the oracle in 64 bits with prefixes of up to 2500.
 
 Tolerances.  fp32: both sides sum the same products in binary32 in different orders; a dot product of D <= 128
-terms and a weighted sum of at most 1300 keys move by a few 1e-7 of the output's scale, the repository's 1e-5 bounds
+terms and a weighted sum of the keys move by a few 1e-7 of the output's scale, the repository's 1e-5 bounds
 them.  bf16: both sides hold scores, probabilities and sums in binary32 (the tiled path splits a probability into three
 bf16 values, exactly), so the outputs differ where a binary32 difference of that size crosses a rounding boundary:
 one bf16 unit, 2^-7 of the element at most.  lse: fp32 on both sides, |lse| < 16."""
@@ -58,6 +59,8 @@ class Inputs:
             x = x.clamp(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8) if fp8 else x.to(tdt)
             caches.append(x)
         k, v = caches
+        self.plain = [c.view(torch.float8_e4m3fn).float() * self.kw[s] if fp8 else c.float()
+                      for c, s in zip(caches, ("k_scale", "v_scale"))]             # [block, kv head, slot, head dim]
         if layout == B.SMART_KV_INTERLEAVED:
             k = k.reshape(nb, Hkv, bs, D // 8, 8).permute(0, 1, 3, 2, 4).reshape(nb, Hkv, 1, bs * D)
             v = v.reshape(nb, Hkv, bs // 8, 8, D).permute(0, 1, 2, 4, 3).reshape(nb, Hkv, 1, bs * D)
@@ -315,3 +318,24 @@ def test_offsets_that_are_not_ascending(lib, static, dtype, fp8, layout):
         cu = torch.tensor(offsets, dtype=torch.int64).to(torch.int32).cuda()
         ref = x.run(lib, general=True, cu=cu, out=torch.full_like(x.q, 7.0))
         assert_close(x.run(lib, cu=cu, static=static, out=torch.full_like(x.q, 7.0)), ref)
+
+
+@pytest.mark.parametrize("dtype,fp8,layout,D", FORMS)
+def test_every_form_equals_the_oracle_on_long_prefixes(lib, oracle_attention, dtype, fp8, layout, D):
+    """Many steps per piece and many pieces per segment, in the split and the workspace-free form.  The weighted mean of |V|
+    (the oracle's result for |V|) is what rounding errors of scores and sums are relative to: 1e-5 of it; a bf16 output is
+    rounded once more, by at most 2^-8 of it (8 significant bits)."""
+    import torch
+    bs = 8 if layout == B.SMART_KV_INTERLEAVED else (24 if D == 64 else 16)     # (interleaved 128 / 16 is the other path's)
+    x = Inputs([9, 40, 3, 64], [2500, 1301, 700, 5], 8, 2, D, bs, dtype, layout, fp8)
+    n = lambda t: np.ascontiguousarray(t.float().cpu().numpy())
+    def oracle(f):
+        k, v = x.plain
+        return oracle_attention.tree_attention(n(x.q), n(x.k_tree), f(n(x.v_tree)), n(k), f(n(v)), x.table.cpu().numpy(),
+                                               x.len.cpu().numpy(), x.cu_host, x.parent.cpu().numpy(), 1.0 / np.sqrt(D))
+    ref, ref_lse = oracle(lambda a: a)
+    bound = 1e-5 * oracle(np.abs)[0] + (2.0 ** -8 * np.abs(ref) if dtype == "bf16" else 0.0)
+    for static in (False, True):
+        out, lse = x.run(lib, static=static)
+        assert (np.abs(out.double().cpu().numpy() - ref) <= bound).all()
+        assert np.abs(lse.double().cpu().numpy() - ref_lse).max() <= 2e-5
