@@ -531,12 +531,13 @@ int32_t kv_cache_write_fp8(smart_ctx* ctx, void* stream, int32_t src_dtype, int3
  *   out[i,h,:] = softmax_keys(softmax_scale * <q[i,h,:], k[g,:]>) . v[g,:]
  *   lse[i,h]   = log sum_keys exp(score)                      (optional)
  * Scores, softmax and accumulation are fp32 (bf16 inputs are multiplied on
- * the matrix cores with fp32 accumulation; softmax weights are rounded to
- * bf16 before the second product).  With an fp8 cache (kv_cache_dtype =
+ * the matrix cores with fp32 accumulation; the kernel for bf16 / interleaved /
+ * block_size 16 / head_dim 128 rounds softmax weights to bf16 before the second
+ * product, the others hold them in fp32).  With an fp8 cache (kv_cache_dtype =
  * SMART_FP8_E4M3) the cached keys and values are k_scale / v_scale times the
- * stored E4M3 values (exact in bf16); everything else is as above.  (The
- * matrix-core kernel then streams every sequence in row groups of 64 rows, so
- * trees with more than 64 rows per kv head re-read their prefix per group.)
+ * stored E4M3 values (exact in bf16); everything else is as above.  A tree's
+ * rows per kv head, n x G, are served in groups of up to 256 (of 128 by the
+ * tiled kernel), each of which reads the prefix once.
  *
  * Shapes: q, out [total_nodes][Hq][D]; k_tree, v_tree [total_nodes][Hkv][D]
  * (tree K/V are not in the cache yet); block_table [batch][max_blocks_per_seq]
@@ -552,8 +553,7 @@ int32_t kv_cache_write_fp8(smart_ctx* ctx, void* stream, int32_t src_dtype, int3
  * output row is written); the other kernels give a row to one sequence (the one
  * a binary search finds) and zero-fill rows that no range inside
  * [0, total_nodes] holds.
- * Any group size G = Hq / Hkv is accepted (a tree's rows per kv head, n x G,
- * are served in groups of up to 256).
+ * Any group size G = Hq / Hkv is accepted.
  * Host errors: SMART_EINVAL for null pointers, Hq % Hkv != 0,
  * total_nodes x Hq >= 2^31, head_dim not in {64, 128}, block_size not a
  * multiple of 8 or > 64, unknown dtype / layout, strides smaller than a page;
@@ -622,8 +622,11 @@ int32_t tree_verify_attention(smart_ctx* ctx, void* stream, const tva_params* pa
  * nothing in it needs to start at zero, every word that is read was written
  * by the same call before.
  * Calls that are not bf16 / interleaved / block_size 16 / head_dim 128 use no
- * scratch memory here (the tiled kernel's workspace-free form, which is also what
- * a captured tree_verify_attention of that kind runs).
+ * scratch memory here: they run the tiled kernel's workspace-free form, which is
+ * also what a captured tree_verify_attention of that kind runs.  It merges in
+ * another order than the other form (the same results but for rounding) and gives
+ * one workgroup to a sequence's kv head and 128 rows, so a call with few of them
+ * and a long prefix takes longer than outside a capture.
  * Errors: as tree_verify_attention, plus SMART_ECAP as above, and SMART_EHIP
  * if the array's address could not be resolved when the context was created.
  * ------------------------------------------------------------------------- */

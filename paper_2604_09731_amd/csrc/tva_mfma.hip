@@ -2434,7 +2434,10 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   const bool recorded = profile_events(ctx, &ev_start, &ev_stop);
   // fp8 cache: the host knows the trees' mean size only.  A batch of trees of one row tile has a mean of at most 32 rows
   // and runs the kernel that is best for them (360 us instead of 386, see fp8_worker); with a larger mean trees of two
-  // row tiles are the usual ones, and they gain more (412 us instead of 626) than the smaller ones lose.
+  // row tiles are the usual ones, and they gain more (412 us instead of 626) than the smaller ones lose.  (The mean can
+  // also come from a few trees of class 2 among many of one row tile.  Those decide such a launch's time: 64 sequences of
+  // 6000 tokens, 60 trees of 32 rows and 4 of 1024, 257 us here and 262 with the other kernel; 62 and 2 equal; 48 of 32
+  // and 16 of 96 190 and 188.)
   const bool pair = fp8 && (int64_t)p.total_nodes * G > (int64_t)kSmallRows * p.batch;
   auto launch = [&](void (*kernel)(MainArgs)) {
     if (recorded) hipExtLaunchKernelGGL(kernel, grid, dim3(kWgWaves * kWave), 0, stream, ev_start, ev_stop, 0, ma);

@@ -36,7 +36,7 @@
 // on the vector ALUs in fp32 by walking the set bits, so what other nodes hold never enters a row.
 //
 // Measured against the general kernel (whole call): bf16 plain pages, batch 16, 32 / 8 heads of 128, prefixes of
-// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 108 us (prefix kernel 91, of which 62 are the MFMAs of its fullest
+// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 102 us (prefix kernel 91, of which 62 are the MFMAs of its fullest
 // workgroups; finishing kernel 18); fp32 plain pages, batch 8, 8 / 2 heads of 64, prefixes of 128 .. 1536, 15-node trees
 // 778 -> 24 us, and its error against binary64 falls from 5.6e-7 to 3.1e-7 (shorter sums).
 //
@@ -1161,6 +1161,11 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   // a compute unit: 15-node trees of 60 rows, batch 8, bf16 20.9 us against 15.8 at 33 tokens, 27.7 against 24.8 at 513,
   // 29.9 against 33.8 at 1025; fp32 (a step is half as long and takes twice as long) 18.1 against 15.2 at 33 tokens,
   // 19.0 against 19.4 at 129; batch 32, 376 segments, 27.2 against 30.7.
+  // Where it runs for its other reasons it can leave compute units idle: 8 kv heads, 4 heads each, one bf16 sequence of
+  // 16384 tokens, one node, 200 us (128 steps in a row on 8 of them; split 39, general kernel 13340), 64 nodes 454 (64,
+  // 18089); four such sequences 204 .. 465; fp32, 2 x 4 heads of 64, 397 .. 1218 (46 .. 54, 8165 .. 8500).
+  // Lengths are on the device, so a wide table with hardly anything in it runs split: 4096 tokens wide, prefixes of one
+  // token, 16-node trees, 14.7 .. 15.5 us in fp32 where the general kernel takes 12.8 .. 13.8; from 8 tokens on it is behind.
   const int64_t longest = (int64_t)p.max_blocks_per_seq * p.block_size;
   bool direct = fixed != nullptr ||
                 (longest <= (f32 ? step_keys<float>() : 4 * step_keys<__bf16>()) &&
