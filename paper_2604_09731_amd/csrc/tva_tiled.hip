@@ -148,37 +148,38 @@ struct Place {
   int64_t units_before, segs_before;
 };
 
-// One wavefront goes through the batch, 64 sequences at a time: visit(first sequence, lane has one, its units and
-// segments, units and segments before it).  False: an offset is smaller than the one before it.  Ascending offsets make
-// the sequences' ranges disjoint, which is what the segments and slots of a call were counted by; a call whose
-// offsets are not ascending has no segments at all and its rows are evaluated one by one (Finish::walk), each for the
-// sequence that owner_of finds, like the general kernel's.
+// What lies before a place in the batch, or in all of it.  Ascending offsets make the sequences' ranges disjoint, which is
+// what the segments and slots of a call were counted by; a call whose offsets are not ascending has no segments at all and
+// its rows are evaluated one by one (Finish::walk), each for the sequence that owner_of finds, like the general kernel's.
+struct Sums {
+  int64_t units, segs, steps;
+  int flags;
+};
+constexpr int kDescending = 1;  // an offset is smaller than the one before it
+constexpr int kIrregular = 2;   // a range leaves the arrays or holds more nodes than a tree can have
+
+// One wavefront goes through chunks c0 .. c1 - 1 of 64 sequences: visit(first sequence, lane has one, its units and segments,
+// units and segments before it); `sums` moves from before the chunks to behind them.
 template <typename T, typename Visit>
-__device__ inline bool scan_batch(const TiledArgs& a, int lane, int64_t* total_units, int64_t* total_segs,
-                                  int64_t* total_steps, Visit visit) {
-  int64_t before_u = 0, before_s = 0, before_t = 0;
-  bool ascending = true;
-  for (int b0 = 0; b0 < a.batch; b0 += kWave) {
+__device__ inline void scan_batch(const TiledArgs& a, int lane, int c0, int c1, Sums* sums, Visit visit) {
+  for (int b0 = c0 * kWave; b0 < min(c1 * kWave, a.batch); b0 += kWave) {
     const int b = min(b0 + lane, a.batch - 1);
     const int base = a.cu_nodes[b], next = a.cu_nodes[b + 1];
     const Shape s = shape_of<T>(a, a.prefix_len[b], base, next);
     const bool there = b0 + lane < a.batch;
-    ascending = ascending && !__any(next < base);
+    if (__any(next < base)) sums->flags |= kDescending;
+    if (__any(s.n != (int64_t)next - base)) sums->flags |= kIrregular;
     const int64_t segs = there ? (int64_t)s.groups * a.Hkv : 0;
     const int64_t units = there ? s.head * a.Hkv : 0;
     int64_t tu, ts, tt;
     smart::wave_excl_scan(segs * s.steps, lane, &tt);
-    const int64_t eu = smart::wave_excl_scan(units, lane, &tu) + before_u;
-    const int64_t es = smart::wave_excl_scan(segs, lane, &ts) + before_s;
+    const int64_t eu = smart::wave_excl_scan(units, lane, &tu) + sums->units;
+    const int64_t es = smart::wave_excl_scan(segs, lane, &ts) + sums->segs;
     visit(b0, there, units, segs, eu, es);
-    before_u += tu;
-    before_s += ts;
-    before_t += tt;
+    sums->units += tu;
+    sums->segs += ts;
+    sums->steps += tt;
   }
-  *total_units = before_u;
-  *total_segs = before_s;
-  *total_steps = before_t;
-  return ascending;
 }
 
 __device__ inline int clamp_block(int b, int num_blocks) { return b < 0 ? 0 : (b >= num_blocks ? num_blocks - 1 : b); }
@@ -844,6 +845,7 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
   constexpr int kStageBytes = 2 * 2 * Stage::kStepChunks * 16, kFoldBytes = kWaves * kRegion * 4;
   __shared__ uintx4 lds[(kStageBytes > kFoldBytes ? kStageBytes : kFoldBytes) / 16];
   __shared__ float s_ml[2][kGroupRows];
+  __shared__ Sums s_part[kWaves];
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   // consecutive workers (the row groups of a segment, the two ends of one) sit behind one L2
@@ -854,12 +856,28 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
       smart::tva_validate_block_table(b, a.block_table, a.prefix_len, a.max_blocks, a.block_size, a.num_blocks, a.status,
                                       lane);
 
-  // Every wavefront plans for itself: what comes out is uniform over the workgroup.
+  // Every wavefront plans for itself: what comes out is uniform over the workgroup.  Batches of more than 512 sequences are
+  // summed by the eight wavefronts together (an eighth each) and searched in the eighth that holds what is looked for: a
+  // chunk is a memory round trip, and this runs once per workgroup.  (Workspace-free form, 4096 sequences of 33 tokens, one
+  // node, 8 kv heads of 128, bf16: 4378 us with every wavefront going through all of it, 2389 now; 1024 sequences 508 and
+  // 354; split 904 and 841, 231 and 215.)
   Place at{-1, 0, 0};
-  int64_t u0 = 0, u1 = 1, U = 0, S = 0, steps = 0;
+  int64_t u0 = 0, u1 = 1;
+  Sums all{};
+  const int chunks = (a.batch + kWave - 1) / kWave;
+  const bool divided = chunks > kWaves;
+  auto first_chunk = [&](int w) { return (int)((int64_t)chunks * w / kWaves); };
   auto find = [&](int64_t want, bool by_segment) {
-    int64_t tu, ts, tt;
-    return scan_batch<T>(a, lane, &tu, &ts, &tt, [&](int b0, bool, int64_t units, int64_t segs, int64_t eu, int64_t es) {
+    Sums before{};
+    int c0 = 0, c1 = chunks;
+    for (int k = 0; divided && k < kWaves; ++k) {
+      c0 = first_chunk(k);
+      c1 = first_chunk(k + 1);
+      if (want < (by_segment ? before.segs + s_part[k].segs : before.units + s_part[k].units)) break;
+      before.units += s_part[k].units;
+      before.segs += s_part[k].segs;
+    }
+    scan_batch<T>(a, lane, c0, c1, &before, [&](int b0, bool, int64_t units, int64_t segs, int64_t eu, int64_t es) {
       const int64_t first = by_segment ? es : eu, count = by_segment ? segs : units;
       const uint64_t hit = __ballot(want >= first && want < first + count);
       if (hit) {
@@ -869,20 +887,38 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
         at.segs_before = smart::readlane64(es, i);
       }
     });
+    return before.flags;
   };
-  bool ascending;
+  auto keep_plan = [&](int b0, bool there, int64_t, int64_t, int64_t eu, int64_t es) {
+    if (wg == 0 && (divided || wv == 0) && there) {
+      a.plan[2 + b0 + lane] = eu;
+      a.plan[2 + a.batch + b0 + lane] = es;
+    }
+  };
+  if (divided) {
+    Sums mine{};
+    scan_batch<T>(a, lane, first_chunk(wv), first_chunk(wv + 1), &mine, [](int, bool, int64_t, int64_t, int64_t, int64_t) {});
+    if (lane == 0) s_part[wv] = mine;
+    __syncthreads();
+    Sums before{};
+    for (int k = 0; k < kWaves; ++k) {
+      if (k == wv) before = all;
+      all.units += s_part[k].units;
+      all.segs += s_part[k].segs;
+      all.steps += s_part[k].steps;
+      all.flags |= s_part[k].flags;
+    }
+    if (!kDirect && wg == 0) scan_batch<T>(a, lane, first_chunk(wv), first_chunk(wv + 1), &before, keep_plan);
+  } else if (!kDirect) {
+    scan_batch<T>(a, lane, 0, chunks, &all, keep_plan);
+  }
   if (kDirect) {
-    ascending = find(wg, true);
-    if (!ascending) at.b = -1;
+    const int flags = find(wg, true);
+    if (!divided) all.flags = flags;
+    if (all.flags & kDescending) at.b = -1;
   } else {
-    ascending = scan_batch<T>(a, lane, &U, &S, &steps, [&](int b0, bool there, int64_t, int64_t, int64_t eu, int64_t es) {
-      if (wg == 0 && wv == 0 && there) {
-        a.plan[2 + b0 + lane] = eu;
-        a.plan[2 + a.batch + b0 + lane] = es;
-      }
-    });
-    if (!ascending) U = -1;
-    const int64_t W = U <= 0 ? 0 : (steps < (int64_t)gridDim.x ? steps : (int64_t)gridDim.x);
+    const int64_t U = all.flags & kDescending ? -1 : all.units;
+    const int64_t W = U <= 0 ? 0 : (all.steps < (int64_t)gridDim.x ? all.steps : (int64_t)gridDim.x);
     if (wg == 0 && tid == 0) {
       a.plan[0] = U;
       a.plan[1] = W;
@@ -1023,8 +1059,11 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
     }
   }
 
-  if (kDirect) {  // rows nobody owns; all rows of a call without segments
+  if (kDirect) {  // rows nobody owns (regular offsets: only before the first and behind the last); all rows of a call without segments
+    const int first_node = a.cu_nodes[0], end_node = a.cu_nodes[a.batch];
+    const bool ascending = (all.flags & kDescending) == 0;
     for (int64_t node = wg; node < a.total_nodes; node += gridDim.x) {
+      if (all.flags == 0 && node >= first_node && node < end_node) continue;
       const int b = owner_of(a, (int)node);
       const Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
       const bool owned = node >= sh.base && node - sh.base < sh.n;

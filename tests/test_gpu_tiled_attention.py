@@ -119,20 +119,40 @@ def test_every_form_equals_the_general_kernel(lib, dtype, fp8, layout, D):
         assert_close(x.run(lib, static=True), ref)
 
 
-@pytest.mark.parametrize("batch", [1, 64, 65, 130])
+@pytest.mark.parametrize("batch", [1, 64, 65, 130, 512, 513, 1100])
 @pytest.mark.parametrize("workers", [0, 1, 3])
 def test_batches_and_shares(lib, batch, workers):
-    """Batches around the 64 sequences one scan holds, empty trees and prefixes among them; shares of one worker that
-    run over many segments."""
+    """Batches around the 64 sequences one scan holds and the 512 that every wavefront scans for itself, empty trees and
+    prefixes among them; shares of one worker that run over many segments; the workspace-free form."""
     g = np.random.default_rng(batch)
     sizes, lens = g.integers(0, 9, batch), g.integers(0, 260, batch)
     sizes[0] = 5
     x = Inputs(sizes, lens, 8, 2, 64, 16, "f32", B.SMART_KV_PLAIN)
     lib.set_option(B.SMART_OPT_TVA_WORKERS, workers)
     try:
-        assert_close(x.run(lib), x.run(lib, general=True))
+        ref = x.run(lib, general=True)
+        assert_close(x.run(lib), ref)
+        assert_close(x.run(lib, static=True), ref)
     finally:
         lib.set_option(B.SMART_OPT_TVA_WORKERS, 0)
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("batch", [3, 600])
+def test_rows_nobody_owns_around_the_trees(lib, static, batch):
+    """Rows before the first and behind the last range, of a range longer than a tree, of one that leaves the arrays."""
+    import torch
+    x = Inputs([2] * (batch - 2) + [100, 52], [17, 0, 70] * (batch // 3), 8, 2, 64, 16, "f32", B.SMART_KV_PLAIN)
+    N = int(x.cu_host[-1])
+    inside, shifted, beyond, longer = (x.cu_host.copy() for _ in range(4))
+    inside[0], inside[-2:] = 1, [N - 60, N - 9]
+    shifted[:2] = -1, 1
+    beyond[-1] = N + 1
+    longer[-2] = N - 2                          # 150 nodes: 128 of them are served
+    for cu in (x.cu_host, inside, shifted, beyond, longer):
+        cu = torch.tensor(cu, dtype=torch.int32, device="cuda")
+        ref = x.run(lib, general=True, cu=cu, out=torch.full_like(x.q, 7.0))
+        assert_close(x.run(lib, cu=cu, static=static, out=torch.full_like(x.q, 7.0)), ref)
 
 
 @pytest.mark.parametrize("static", [False, True])
@@ -313,6 +333,7 @@ def test_offsets_that_are_not_ascending(lib, static, dtype, fp8, layout):
     for sizes, lens, offsets in (([5, 20, 70, 3, 9], [100, 333, 64, 0, 50], [0, 25, 5, 95, 98, 107]),
                                  ([2] * 64, list(g.integers(0, 90, 64)), [0, 128] * 32 + [0]),
                                  ([2] * 65, list(g.integers(0, 90, 65)), list(range(130, -1, -2))),
+                                 ([2] * 600, list(g.integers(0, 90, 600)), list(range(0, 800, 2)) + list(range(700, 1101, 2))),
                                  ([30, 40], [70, 90], [40, 0, 70]), ([30, 40], [70, 90], [50, -3, 70])):
         x = Inputs(sizes, lens, 8, 2, 64, 8, dtype, layout, fp8)
         cu = torch.tensor(offsets, dtype=torch.int64).to(torch.int32).cuda()
