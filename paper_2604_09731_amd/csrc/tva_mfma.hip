@@ -1246,22 +1246,22 @@ __device__ inline void fold_pairs_and_store(SmallState (&S)[2], float* lds, floa
   fold_quads_and_store(lds, slot, wv, lane, c, m_scale, o_scale);
 }
 
-// kPair: two row tiles go to every wavefront; else one to each half of the workgroup (wavefronts 0 .. 3 carry row tile
-// 0, 4 .. 7 row tile 1, both halves stream the same tiles).  The kernel that holds the pair code runs its other branch, one
-// row tile, 7 % slower (386 us instead of 360 on the workload above with 32 rows; the same instructions, waiting longer),
-// so a batch of such trees runs the kernel without it: see tva_launch_mfma.
+// (The loop of small_segment is 237 instructions long where the states are handed to the fold by reference as here, 247 with
+// the same calls written out in the worker: 40 trees of 48 rows, 1500 tokens, prefix kernel 35.1 us instead of 36.3.)
+__device__ inline void fold_halves_and_store(const SmallState& S, float* lds, float* slot, int wv, int lane, float c,
+                                             float m_scale, float o_scale) {
+  state_to_lds(S, lds + wv * kStateFloats, lane);
+  __syncthreads();
+  fold_quads_and_store(lds, slot, wv, lane, c, m_scale, o_scale);
+}
+
+// A worker's pieces.  kPair: two row tiles go to every wavefront; else one to each half of the workgroup (wavefronts 0 .. 3
+// carry row tile 0, 4 .. 7 row tile 1, both halves stream the same tiles).
 template <bool kPair>
-__device__ inline void fp8_worker(const MainArgs& a, int64_t w, ClassPlan& cp, float* merge_lds /* 132 KB */) {
+__device__ inline void fp8_pieces(const MainArgs& a, int64_t w, ClassPlan& cp, float* merge_lds, int64_t u0, int64_t u1, int b,
+                                  int wv, int lane) {
   const PlanView pv = plan_view(a.plan, a.batch);
-  const int64_t U = cp.U, W = cp.W;
   PlanWindow& win = cp.win;
-  if (w >= W || U <= 0) return;
-  int64_t u0 = (w * U) / W;
-  const int64_t u1 = ((w + 1) * U) / W;
-  if (u0 >= u1) return;
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int b = locate(cp, pv, a.cu_nodes, 1, a.batch, u0, lane);
   while (u0 < u1 && b < a.batch) {
     follow(cp, pv, a.cu_nodes, 1, a.batch, b, lane);
     const int64_t seq_begin = window_cum_units(win, b - win.first);
@@ -1295,12 +1295,41 @@ __device__ inline void fp8_worker(const MainArgs& a, int64_t w, ClassPlan& cp, f
       const int h1 = t0 + (int)(((int64_t)nt * (sub + 1)) / 4);
       SmallState S;
       small_segment<fp8x8, false>(S, a, b, g, base, h0, h1, si, lane, rt * kSmallRows);
-      state_to_lds(S, merge_lds + wv * kStateFloats, lane);
-      __syncthreads();
-      fold_quads_and_store(merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
+      fold_halves_and_store(S, merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
     }
     u0 += nt;
   }
+}
+
+// A pair costs more to start (queries through LDS) and to fold (two states per wavefront), so it needs long pieces.  Whole
+// calls, 64 / 8 heads of 8 nodes, halves against pairs: 32 sequences of 500 tokens 26.9 / 32.9 us, 1500 (47 tiles) 40.0 /
+// 44.9, 2500 (79) 58.1 / 57.5, 4000 (125) 82.8 / 74.3, 8000 154 / 118; 2 sequences of 4000 (17 tiles a piece) 32.0 / 37.3.
+// A worker whose share or whose first sequence is shorter than this, or whose first tree has one row tile, goes through its
+// pieces without them (decided once per worker and in a loop of its own: decided per piece in one loop, spilled registers are
+// reloaded in every piece behind the loads in flight: 32 sequences of 1500 tokens 44.5 us, this way 40.9).
+constexpr int kPairTiles = 72;
+// kPair: of the kernel, which can do both; it runs the other loop a little slower than the kernel that has only that one (60
+// trees of one row tile and 4 of class 2, 9000 tokens, 238 us against 237; 20 trees of 48 and 20 of 80 rows, 1500 tokens, 70
+// against 67), so a batch that cannot have long pieces runs that: see tva_launch_mfma.
+template <bool kPair>
+__device__ inline void fp8_worker(const MainArgs& a, int64_t w, ClassPlan& cp, float* merge_lds /* 132 KB */) {
+  const PlanView pv = plan_view(a.plan, a.batch);
+  const int64_t U = cp.U, W = cp.W;
+  if (w >= W || U <= 0) return;
+  const int64_t u0 = (w * U) / W, u1 = ((w + 1) * U) / W;
+  if (u0 >= u1) return;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = locate(cp, pv, a.cu_nodes, 1, a.batch, u0, lane);
+  if (kPair && b < a.batch) {
+    follow(cp, pv, a.cu_nodes, 1, a.batch, b, lane);
+    const SeqInfo first = window_info(cp.win, b - cp.win.first);
+    if (u1 - u0 >= kPairTiles && first.tiles >= kPairTiles && first.n * a.G > kSmallRows) {
+      fp8_pieces<true>(a, w, cp, merge_lds, u0, u1, b, wv, lane);
+      return;
+    }
+  }
+  fp8_pieces<false>(a, w, cp, merge_lds, u0, u1, b, wv, lane);
 }
 
 // ---- classes 1 and 2: K/V tiles staged in LDS, shared by the eight wavefronts of a workgroup --
@@ -2432,13 +2461,14 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
   // (no events: an ordinary launch; else the events ride on the dispatch and hold the kernel's own start and end)
   const bool recorded = profile_events(ctx, &ev_start, &ev_stop);
-  // fp8 cache: the host knows the trees' mean size only.  A batch of trees of one row tile has a mean of at most 32 rows
-  // and runs the kernel that is best for them (360 us instead of 386, see fp8_worker); with a larger mean trees of two
-  // row tiles are the usual ones, and they gain more (412 us instead of 626) than the smaller ones lose.  (The mean can
-  // also come from a few trees of class 2 among many of one row tile.  Those decide such a launch's time: 64 sequences of
-  // 6000 tokens, 60 trees of 32 rows and 4 of 1024, 257 us here and 262 with the other kernel; 62 and 2 equal; 48 of 32
-  // and 16 of 96 190 and 188.)
-  const bool pair = fp8 && (int64_t)p.total_nodes * G > (int64_t)kSmallRows * p.batch;
+  // fp8 cache: the host knows the trees' mean size and what the block table can hold.  A batch of trees of one row tile has
+  // a mean of at most 32 rows, and a table that holds fewer than kPairTiles tiles a sequence, or too few in all for such
+  // shares, has no long pieces: those run the kernel that has no pairs.  With a larger mean and longer tables trees of two
+  // row tiles are the usual ones and gain most (64 sequences of 16384 tokens, 4 .. 10 nodes of 8 rows, 712 -> 503 us); the
+  // rest is decided by each worker (fp8_worker).
+  const int64_t longest = ((int64_t)p.max_blocks_per_seq * kBlock + kTile - 1) / kTile;  // tiles
+  const bool pair = fp8 && (int64_t)p.total_nodes * G > (int64_t)kSmallRows * p.batch && longest >= kPairTiles &&
+                    longest * p.batch * p.num_kv_heads >= (int64_t)kPairTiles * workgroups;
   auto launch = [&](void (*kernel)(MainArgs)) {
     if (recorded) hipExtLaunchKernelGGL(kernel, grid, dim3(kWgWaves * kWave), 0, stream, ev_start, ev_stop, 0, ma);
     else hipLaunchKernelGGL(kernel, grid, dim3(kWgWaves * kWave), 0, stream, ma);

@@ -1059,7 +1059,8 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
     }
   }
 
-  if (kDirect) {  // rows nobody owns (regular offsets: only before the first and behind the last); all rows of a call without segments
+  // rows nobody owns (regular offsets: only before the first and behind the last); all rows of a call without segments
+  if (kDirect) {
     const int first_node = a.cu_nodes[0], end_node = a.cu_nodes[a.batch];
     const bool ascending = (all.flags & kDescending) == 0;
     for (int64_t node = wg; node < a.total_nodes; node += gridDim.x) {

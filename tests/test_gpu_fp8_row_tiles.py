@@ -1,6 +1,6 @@
-"""fp8 cache, trees around one and two row tiles of 32 rows per kv head: batches whose mean size picks the kernel that
-gives both row tiles to every wavefront, and batches whose mean picks the one that gives one to each half of the
-workgroup; against the general kernel, which holds probabilities in binary32.
+"""fp8 cache, trees around one and two row tiles of 32 rows per kv head: batches whose mean size and table pick the kernel
+that gives both row tiles of a long piece to every wavefront (and those of a short one to a half of the workgroup each),
+and batches that run the kernel with halves only; against the general kernel, which holds probabilities in binary32.
 
 Tolerance, element by element.  bf16 has 8 significant bits, so rounding to it moves a number by at most u = 2^-8 of
 itself.  The matrix-core path rounds each probability (the row sums are of the unrounded ones), which moves an output by
@@ -17,13 +17,13 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("sizes", [[8, 9, 16, 17], [12, 16, 16, 9], [1, 1, 1, 12], [1, 2, 1, 16, 1, 1]])
-@pytest.mark.parametrize("workers", [0, 1, 5])
+@pytest.mark.parametrize("workers", [0, 1, 4, 5])
 def test_one_and_two_row_tiles(sizes, workers):
-    """G = 4: 32, 33 .. 64 and 65 rows; long shares of one worker (several chunks of 64 tiles per wavefront), shares
-    shorter than a wavefront's turn, ragged ends and an empty prefix."""
+    """G = 4: 32, 33 .. 64 and 65 rows; long shares of one worker (several chunks of 64 tiles per wavefront), pieces around
+    the 72 tiles from which on they go as pairs, shares shorter than a wavefront's turn, ragged ends and an empty prefix."""
     import torch
     lib = B.SmartTree(0)
-    lens = ([1, 2049, 700, 33, 95, 31] if workers != 1 else [20000, 33, 517, 0, 64, 1])[:len(sizes)]
+    lens = {1: [20000, 33, 517, 0, 64, 1], 4: [2303, 9001, 2272, 2273, 95, 2400]}.get(workers, [1, 2049, 700, 33, 95, 31])[:len(sizes)]
     x = Inputs(sizes, lens, 8, 2, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, fp8=True, seed=len(sizes) + workers)
     ref, ref_lse = x.run(lib, general=True)
     v, v_tree = x.v, x.v_tree
