@@ -1200,16 +1200,21 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   // second launch, where a segment is a few steps, its rows fit one pass of the finishing step (64) and every segment has
   // a compute unit: 15-node trees of 60 rows, batch 8, bf16 20.9 us against 15.8 at 33 tokens, 27.7 against 24.8 at 513,
   // 29.9 against 33.8 at 1025; fp32 (a step is half as long and takes twice as long) 18.1 against 15.2 at 33 tokens,
-  // 19.0 against 19.4 at 129; batch 32, 376 segments, 27.2 against 30.7.
+  // 19.0 against 19.4 at 129; batch 32, 376 segments, 27.2 against 30.7.  Larger trees too where a segment is a single step
+  // (the tree part of a deep tree takes most of the time then, and here all rows of a workgroup read the same tree): 33
+  // tokens, one sequence of 48 nodes, 32 / 8 heads of 128, bf16 28.7 us against 21.3 (general kernel 36.7), 8 / 2 of 64, fp32
+  // 24.8 against 17.7 (22.1), 66 nodes 22.8 against 18.2 (25.6), up to a mean of 384 rows (64 / 8 heads, 48 nodes, 19.1 against
+  // 17.9); 512 rows 18.7 against 19.9.
   // Where it runs for its other reasons it can leave compute units idle: 8 kv heads, 4 heads each, one bf16 sequence of
   // 16384 tokens, one node, 200 us (128 steps in a row on 8 of them; split 39, general kernel 13340), 64 nodes 454 (64,
   // 18089); four such sequences 204 .. 465; fp32, 2 x 4 heads of 64, 397 .. 1218 (46 .. 54, 8165 .. 8500).
   // Lengths are on the device, so a wide table with hardly anything in it runs split: 4096 tokens wide, prefixes of one
   // token, 16-node trees, 14.7 .. 15.5 us in fp32 where the general kernel takes 12.8 .. 13.8; from 8 tokens on it is behind.
   const int64_t longest = (int64_t)p.max_blocks_per_seq * p.block_size;
-  bool direct = fixed != nullptr ||
-                (longest <= (f32 ? step_keys<float>() : 4 * step_keys<__bf16>()) &&
-                 (int64_t)p.total_nodes * G <= 64 * (int64_t)p.batch && segs <= (ctx->num_cus > 0 ? ctx->num_cus : 256));
+  const int64_t step = f32 ? step_keys<float>() : step_keys<__bf16>(), rows = (int64_t)p.total_nodes * G;
+  const bool few_steps = (longest <= step && rows <= 384 * (int64_t)p.batch) ||
+                         (!f32 && longest <= 4 * step && rows <= 64 * (int64_t)p.batch);
+  bool direct = fixed != nullptr || (few_steps && segs <= (ctx->num_cus > 0 ? ctx->num_cus : 256));
   if (!direct) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (stream != nullptr && hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();

@@ -255,11 +255,12 @@ def test_a_graph_of_the_interleaved_kernel_keeps_its_workspace(lib):
         del junk
 
 
-@pytest.mark.parametrize("dtype,longest", [("bf16", 512), ("f32", 64)])
-def test_around_the_one_launch_rule(lib, dtype, longest):
-    """Small trees on tables that hold at most, and just more than, what one workgroup per segment takes; a mean of 64
-    rows and one above it."""
-    for sizes in ([16, 16], [16, 17], [1, 31]):
+@pytest.mark.parametrize("dtype,longest,rows", [("bf16", 512, 64), ("bf16", 128, 384), ("f32", 64, 384)])
+def test_around_the_one_launch_rule(lib, dtype, longest, rows):
+    """Small trees on tables that hold at most, and just more than, what one workgroup per segment takes; a mean of as many
+    rows as the rule takes and one above it."""
+    n = rows // 4
+    for sizes in ([n, n], [n, n + 1], [1, 2 * n - 1 if n < 64 else 128]):
         for extra in (0, 1):
             x = Inputs(sizes, [longest, 5], 8, 2, 64, 16, dtype, B.SMART_KV_PLAIN, spare_columns=extra)
             assert_close(x.run(lib), x.run(lib, general=True))
