@@ -16,6 +16,8 @@ struct smart_ctx {
   size_t ws_bytes = 0;
   int32_t* plan = nullptr;    // launch plan written by the planning kernel
   size_t plan_bytes = 0;
+  int32_t* arrive = nullptr;  // arrival counters of the matrix-core path, behind the plan; zero between calls
+  size_t counters = 0;
   void* tiled_ws = nullptr;   // the tiled path's partial results and plan where ws is too small; no graph ever holds it
   size_t tiled_ws_bytes = 0;
   size_t tiled_refused = SIZE_MAX;  // the smallest size of it that there was no memory for
@@ -51,13 +53,16 @@ void set_last_hip_error(hipError_t e);
   } while (0)
 
 // Makes sure the context's workspace holds at least the given sizes.  May
-// synchronise `stream` (only when it has to grow).
-int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, size_t plan_bytes);
+// synchronise `stream` (only when it has to grow).  Arrival counters that it allocates are zero.
+int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, size_t plan_bytes, size_t counters);
 // The tiled path's buffer: the one above if it is large enough (calls of a context are serialised), else one of its own,
 // which grows.  Its calls are served without a workspace too, so they never replace a buffer that a captured launch of
 // another path still reads.  SMART_ENOMEM (no error left behind): no memory, the caller takes its workspace-free form;
 // the size is not asked for again until smart_reserve is called.
 int32_t tiled_workspace(smart_ctx* ctx, hipStream_t stream, size_t bytes, void** ws);
+
+// Enqueues the clearing of arrival counters.
+int32_t zero_counters(hipStream_t stream, int32_t* counters, size_t n);
 
 // Profiling hooks: bracket the dominant kernel of the current call.
 int32_t profile_begin(smart_ctx* ctx, hipStream_t stream);
@@ -92,7 +97,7 @@ int32_t static_scratch(int device, void** ptr, size_t* bytes);
 bool tva_mfma_supported(const tva_params& p);
 // Workspace the matrix-core path needs for a problem of this size.
 void tva_mfma_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
-                        int32_t num_kv_heads, size_t* ws_bytes, size_t* plan_bytes);
+                        int32_t num_kv_heads, size_t* ws_bytes, size_t* plan_bytes, size_t* counters);
 int32_t tva_mfma_default_workers(const smart_ctx* ctx);
 
 #ifdef __HIPCC__

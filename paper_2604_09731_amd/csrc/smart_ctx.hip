@@ -8,8 +8,20 @@ namespace smart {
 static thread_local hipError_t g_last_hip_error = hipSuccess;
 void set_last_hip_error(hipError_t e) { g_last_hip_error = e; }
 
-int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, size_t plan_bytes) {
-  if (ws_bytes <= ctx->ws_bytes && plan_bytes <= ctx->plan_bytes) return SMART_OK;
+static __global__ void zero_counters_kernel(int32_t* counters, size_t n) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) counters[i] = 0;
+}
+
+int32_t zero_counters(hipStream_t stream, int32_t* counters, size_t n) {
+  if (n == 0) return SMART_OK;
+  hipLaunchKernelGGL(zero_counters_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, counters, n);
+  SMART_HIP_CHECK(hipGetLastError());
+  return SMART_OK;
+}
+
+int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, size_t plan_bytes, size_t counters) {
+  if (ws_bytes <= ctx->ws_bytes && plan_bytes <= ctx->plan_bytes && counters <= ctx->counters) return SMART_OK;
   // Work already enqueued may still use the old buffers.
   SMART_HIP_CHECK(hipStreamSynchronize(stream));
   if (ws_bytes > ctx->ws_bytes) {
@@ -20,13 +32,25 @@ int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, si
     if (e != hipSuccess) { set_last_hip_error(e); (void)hipGetLastError(); return SMART_ENOMEM; }
     ctx->ws_bytes = ws_bytes;
   }
-  if (plan_bytes > ctx->plan_bytes) {
+  if (plan_bytes > ctx->plan_bytes || counters > ctx->counters) {
+    if (plan_bytes < ctx->plan_bytes) plan_bytes = ctx->plan_bytes;
+    if (counters < ctx->counters) counters = ctx->counters;
+    plan_bytes = (plan_bytes + 255) & ~(size_t)255;
     if (ctx->plan) SMART_HIP_CHECK(hipFree(ctx->plan));
-    ctx->plan = nullptr;
-    ctx->plan_bytes = 0;
-    hipError_t e = hipMalloc((void**)&ctx->plan, plan_bytes);
+    ctx->plan = ctx->arrive = nullptr;
+    ctx->plan_bytes = ctx->counters = 0;
+    hipError_t e = hipMalloc((void**)&ctx->plan, plan_bytes + counters * sizeof(int32_t));
     if (e != hipSuccess) { set_last_hip_error(e); (void)hipGetLastError(); return SMART_ENOMEM; }
+    // the counters start from zero and every launch leaves them so
+    int32_t* const arrive = (int32_t*)((char*)ctx->plan + plan_bytes);
+    if (counters > 0) {
+      const int32_t rc = zero_counters(stream, arrive, counters);
+      if (rc != SMART_OK) return rc;
+      SMART_HIP_CHECK(hipStreamSynchronize(stream));  // (the next call may be on another stream)
+    }
     ctx->plan_bytes = plan_bytes;
+    ctx->arrive = arrive;
+    ctx->counters = counters;
   }
   return SMART_OK;
 }
@@ -243,11 +267,11 @@ extern "C" int32_t smart_reserve(smart_ctx* ctx, int32_t max_batch, int32_t max_
   int prev = 0;
   SMART_HIP_CHECK(hipGetDevice(&prev));
   SMART_HIP_CHECK(hipSetDevice(ctx->device));
-  size_t ws = 0, plan = 0;
-  smart::tva_mfma_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, &ws, &plan);
+  size_t ws = 0, plan = 0, counters = 0;
+  smart::tva_mfma_workspace(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads, &ws, &plan, &counters);
   // (one buffer for both: the tiled path's needs are the smaller ones but for rounding in its favour)
   const size_t tiled = smart::tva_tiled_reserve(ctx, max_batch, max_total_nodes, max_q_heads, max_kv_heads);
-  const int32_t rc = smart::ensure_workspace(ctx, nullptr, ws > tiled ? ws : tiled, plan);
+  const int32_t rc = smart::ensure_workspace(ctx, nullptr, ws > tiled ? ws : tiled, plan, counters);
   ctx->tiled_refused = SIZE_MAX;
   (void)hipSetDevice(prev);
   return rc;

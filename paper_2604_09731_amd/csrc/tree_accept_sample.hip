@@ -294,7 +294,7 @@ extern "C" int32_t tree_accept_sample(smart_ctx* ctx, void* stream, int32_t batc
   SMART_HIP_CHECK(hipGetDevice(&prev));
   if (prev != ctx->device) SMART_HIP_CHECK(hipSetDevice(ctx->device));
   const size_t need = (size_t)(total_nodes > 0 ? total_nodes : 1) * kRanges * sizeof(uint64_t);
-  int32_t rc = smart::ensure_workspace(ctx, (hipStream_t)stream, need, 0);
+  int32_t rc = smart::ensure_workspace(ctx, (hipStream_t)stream, need, 0, 0);
   if (rc == SMART_OK) {
     uint64_t* sums = (uint64_t*)ctx->ws;
     // Four ranges per wavefront (eight vectors in flight per lane) once that still leaves every compute unit two

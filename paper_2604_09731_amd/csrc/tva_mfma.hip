@@ -25,10 +25,13 @@
 //    tiles of 32 rows each in class 2.
 //
 //  * the tree part (a node sees only itself and its ancestors: a handful of
-//    keys selected by a 128-bit mask) is sparse and tiny.  It is evaluated in
-//    fp32 on the vector ALUs inside the combine kernel, by walking the set
-//    bits of the node's ancestor mask, and merged with the prefix partials by
-//    the usual log-sum-exp merge.
+//    keys selected by a 128-bit mask) is sparse and tiny.  In the usual form of
+//    the launch (kFinish) the prefix kernel evaluates it as one to four more
+//    tiles of masked keys, merges the pieces of a segment and writes the rows:
+//    one launch.  Where few segments are cut into many pieces, the prefix
+//    kernel leaves its partials and a combine kernel, spread over the whole
+//    chip, walks the set bits of each row's mask on the vector ALUs and merges:
+//    see finishes().
 //
 // The paper (Sec. 1) only says that the tree is verified in one forward pass
 // of the target model; this file is the attention sub-step of that pass.
@@ -76,6 +79,9 @@ constexpr int kMediumSlot = kMediumRows * kD + 2 * kMediumRows;
 constexpr int kLargeSlot = kLargeRows * kD + 2 * kLargeRows;
 __host__ __device__ inline int class_rows(int cls) { return cls == 0 ? kSmallRows : (cls == 1 ? kMediumRows : kLargeRows); }
 __host__ __device__ inline int class_slot(int cls) { return cls == 0 ? kSmallSlot : (cls == 1 ? kMediumSlot : kLargeSlot); }
+// kFinish: every wavefront leaves the row maxima and sums of its row tile beside its part of O.
+constexpr int kFinishTail = kWgWaves * 2 * 32;
+__host__ __device__ inline int finish_slot(int cls) { return class_rows(cls) * kD + kFinishTail; }
 constexpr int kCombineRows = 8;       // rows per combine wavefront (8 lanes per row)
 constexpr int kMinTilesPerWorker[kClasses] = {16, 16, 8};  // workers are 8-wave workgroups
 constexpr int kChunkTiles = 64;       // tiles whose block ids one pair of registers holds
@@ -117,6 +123,12 @@ constexpr int kLargeTileCost[kLargeRows / 32 + 1] = {11, 11, 11, 12, 12, 16, 16,
 // (the same currency for a tile of classes 0 and 1, for dealing the workgroups to the classes)
 constexpr int kClassTileCost[kClasses] = {10, 10, 1};
 constexpr int kFp8StreamTileCost = 5;
+// What a segment costs beside its prefix tiles where the prefix kernel finishes the rows itself (kFinish): its tree part,
+// and where workers hold several segments its start and end, in units of classes 0 and 1 (a tile) and of class 2: see
+// tree_cost.
+struct TreeCost {
+  int32_t small, large;
+};
 
 // What the unit space of class 2 holds of one sequence: per kv head its row groups in order, all but the last
 // with eight row tiles.
@@ -126,20 +138,28 @@ struct LargeSpans {
   int64_t span_last;   // units of the last row group
   int64_t span_head;   // units of one kv head: (rg - 1) span_full + span_last
 };
-__host__ __device__ inline LargeSpans large_spans(const SeqInfo& si, int G) {
+template <bool kFinish>
+__host__ __device__ inline LargeSpans large_spans(const SeqInfo& si, int G, TreeCost tc) {
   LargeSpans ls;
   const int rows_last = si.n * G - (si.rg - 1) * kLargeRows;
   ls.cost_last = kLargeTileCost[rows_last > 0 ? (rows_last + 31) / 32 : 0];
-  const bool any = si.tiles > 0 && si.rg > 0;
-  ls.span_full = any ? (int64_t)si.tiles * kLargeTileCost[kLargeRows / 32] : 0;
-  ls.span_last = any ? (int64_t)si.tiles * ls.cost_last : 0;
+  const bool any = (kFinish || si.tiles > 0) && si.rg > 0;
+  const int tree = kFinish ? tc.large : 0;
+  ls.span_full = any ? (int64_t)si.tiles * kLargeTileCost[kLargeRows / 32] + tree : 0;
+  ls.span_last = any ? (int64_t)si.tiles * ls.cost_last + tree : 0;
   ls.span_head = any ? (si.rg - 1) * ls.span_full + ls.span_last : 0;
   return ls;
 }
+// Units of a segment of class 0 or 1.
+template <bool kFinish>
+__host__ __device__ inline int segment_units(const SeqInfo& si, TreeCost tc) {
+  return si.tiles + (kFinish ? tc.small : 0);
+}
 // Units of the whole sequence (classes 0 and 1: its tiles per kv head; class 2: in the cost currency).
-__host__ __device__ inline int64_t sequence_units(const SeqInfo& si, int cls, int G, int Hkv) {
-  if (cls < 2) return (int64_t)si.tiles * Hkv * si.rg;
-  return large_spans(si, G).span_head * Hkv;
+template <bool kFinish>
+__host__ __device__ inline int64_t sequence_units(const SeqInfo& si, int cls, int G, int Hkv, TreeCost tc) {
+  if (cls < 2) return (int64_t)segment_units<kFinish>(si, tc) * Hkv * si.rg;
+  return large_spans<kFinish>(si, G, tc).span_head * Hkv;
 }
 // Tile of a class-2 segment at which a share that begins `off` units into the segment begins (a share boundary
 // inside a tile goes down to the tile's beginning).
@@ -237,8 +257,8 @@ __device__ inline bool offsets_malformed(int base, int next, int total_nodes) {
 // are loaded most, so the classes never need more workgroups than were launched.  Returns the workers
 // per class and the first workgroup of each class (entry kClasses: one past the last).
 // kOnlySmall: the plan of the fp8-cache kernel, which has no class 0 (plan_class).
-template <bool kOnlySmall = false>
-__device__ inline void apportion(const int64_t (&all_u)[kClasses], int workgroups, int64_t (&workers)[kClasses],
+template <bool kOnlySmall, bool kFinish>
+__device__ inline void apportion(const int64_t (&all_u)[kClasses], const int64_t (&all_s)[kClasses], TreeCost tc, int workgroups, int64_t (&workers)[kClasses],
                                  int64_t (&first_wg)[kClasses + 1]) {
   const int64_t tot_u[kClasses] = {kOnlySmall ? 0 : all_u[0], all_u[1], all_u[2]};
   // (fp8 cache: class 1 is the register stream of half as many bytes per tile; measured 4 .. 8 units per tile
@@ -283,7 +303,11 @@ __device__ inline void apportion(const int64_t (&all_u)[kClasses], int workgroup
 #pragma unroll
   for (int c = 0; c < kClasses; ++c) {
     int64_t w = wg[c];  // a worker is a workgroup in every class
-    const int64_t cap = tot_u[c] / (kMinTilesPerWorker[c] * (c == 2 ? kLargeTileCost[0] : 1));
+    // (by the prefix tiles alone, so that segments of 64 tiles go to four workers each, tree parts or not; and a worker for
+    // every segment: one sequence of 200 tokens, 8 kv heads, on three workers 26.7 us, on eight 10.4)
+    int64_t cap = (tot_u[c] - (kFinish ? all_s[c] * (c == 2 ? tc.large : tc.small) : 0)) /
+                  (kMinTilesPerWorker[c] * (c == 2 ? kLargeTileCost[0] : 1));
+    if (cap < all_s[c]) cap = all_s[c];
     if (w > cap) w = cap;
     if (tot_u[c] > 0 && w < 1) w = 1;
     workers[c] = w;
@@ -293,10 +317,10 @@ __device__ inline void apportion(const int64_t (&all_u)[kClasses], int workgroup
   first_wg[kClasses] = first;
 }
 
-template <bool kOnlySmall>
+template <bool kOnlySmall, bool kFinish>
 __global__ __launch_bounds__(kWave) void tva_plan_kernel(
     void* plan_base, int batch, int total_nodes, int G, int Hkv, int max_blocks, int workgroups,
-    SegCaps caps, const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ cu_nodes) {
+    SegCaps caps, TreeCost tc, const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ cu_nodes) {
   PlanView pv = plan_view(plan_base, batch);
   const int t = threadIdx.x;
   const int per = (batch + kWave - 1) / kWave;
@@ -311,7 +335,7 @@ __global__ __launch_bounds__(kWave) void tva_plan_kernel(
     pv.info[b] = si;
     const int rows = si.n * G;
     const int c = plan_class<kOnlySmall>(rows);
-    units[c] += sequence_units(si, c, G, Hkv);
+    units[c] += sequence_units<kFinish>(si, c, G, Hkv, tc);
     segs[c] += Hkv * si.rg;
     chunks += Hkv * ((rows + kCombineRows - 1) / kCombineRows);
   }
@@ -329,7 +353,7 @@ __global__ __launch_bounds__(kWave) void tva_plan_kernel(
   }
   if (t == 0) {
     int64_t workers[kClasses], first_wg[kClasses + 1];
-    apportion<kOnlySmall>(tot_u, workgroups, workers, first_wg);
+    apportion<kOnlySmall, kFinish>(tot_u, tot_s, tc, workgroups, workers, first_wg);
     for (int c = 0; c < kClasses; ++c) {
       pv.cum_units[c][batch] = tot_u[c];
       pv.cum_segs[c][batch] = (int32_t)tot_s[c];
@@ -353,7 +377,7 @@ __global__ __launch_bounds__(kWave) void tva_plan_kernel(
       pv.cum_segs[k][b] = (int32_t)s[k];
     }
     pv.cum_chunks[b] = (int32_t)ch;
-    u[c] += sequence_units(si, c, G, Hkv);
+    u[c] += sequence_units<kFinish>(si, c, G, Hkv, tc);
     s[c] += Hkv * si.rg;
     ch += Hkv * ((rows + kCombineRows - 1) / kCombineRows);
   }
@@ -375,10 +399,10 @@ struct LanePlan {
   int32_t chunks;
 };
 
-template <bool kOnlySmall = false>
+template <bool kOnlySmall, bool kFinish>
 __device__ inline void lane_plan(LanePlan& p, const int32_t* prefix_len, const int32_t* cu_nodes, int batch,
                                  int total_nodes, int G, int Hkv, int max_blocks, int workgroups,
-                                 const SegCaps& caps, int lane) {
+                                 const SegCaps& caps, TreeCost tc, int lane) {
   const int b = min(lane, batch - 1);
   const int32_t len = prefix_len[b], base = cu_nodes[min(lane, batch)], next = cu_nodes[b + 1];
   const bool malformed = __any(lane < batch && offsets_malformed(base, next, total_nodes));
@@ -391,7 +415,7 @@ __device__ inline void lane_plan(LanePlan& p, const int32_t* prefix_len, const i
   for (int pass = 0; pass < 2; ++pass) {
     const int rows = si.n * G;
     const int cls = plan_class<kOnlySmall>(rows);
-    const int64_t my_units = sequence_units(si, cls, G, Hkv);
+    const int64_t my_units = sequence_units<kFinish>(si, cls, G, Hkv, tc);
     const int64_t my_segs = Hkv * si.rg;
     int64_t tot_s, tot_c;
 #pragma unroll
@@ -406,12 +430,29 @@ __device__ inline void lane_plan(LanePlan& p, const int32_t* prefix_len, const i
     si.n = si.rg = 0;
   }
   p.si = si;
-  apportion<kOnlySmall>(p.units, workgroups, p.workers, p.first_wg);
+  const int64_t total_segs[kClasses] = {p.total_segs[0], p.total_segs[1], p.total_segs[2]};
+  apportion<kOnlySmall, kFinish>(p.units, total_segs, tc, workgroups, p.workers, p.first_wg);
 }
 
 // ---------------------------------------------------------------------------
 // prefix kernels
 // ---------------------------------------------------------------------------
+// What a kernel that finishes the rows itself needs behind its streaming loops (kFinish): the tree's own rows, the results
+// and the arrival counters (one per wavefront and segment; class c's begin at arrive_first[c] segments).
+struct FinishArgs {
+  const __bf16* q;
+  const __bf16* k_tree;
+  const __bf16* v_tree;
+  const uint32_t* anc_mask;  // four words per node
+  __bf16* out;
+  float* lse;
+  float* ws[3];
+  int32_t* arrive;
+  int32_t arrive_first[3];
+  int32_t Hq, Hkv, G;
+  float scale, scale_log2e;  // (without k_scale)
+};
+
 struct MainArgs {
   const __bf16* q;
   const __bf16* k_cache;
@@ -424,10 +465,13 @@ struct MainArgs {
   int64_t block_stride, head_stride;
   int32_t batch, total_nodes, Hq, Hkv, G, max_blocks, num_blocks, workgroups;
   SegCaps caps;  // segments per class the partial-result slots have room for
+  TreeCost tree_cost;  // kFinish
   float scale_log2e;
   // fp8 cache only: k_cache / v_cache then point at bytes (E4M3), scale_log2e already includes k_scale,
   // a partial's row maxima are multiplied by m_scale (= k_scale) and its O by o_scale (= v_scale)
   float m_scale, o_scale;
+  int32_t* status;  // kFinish: of the block-table check
+  FinishArgs fin;
 };
 
 // Wave-uniform data (block table, plan) is read through the constant address
@@ -666,6 +710,393 @@ __device__ inline void store_partial(float* slot, int rows_in_slot, int qt, cons
   }
 }
 
+// ---- kFinish: the prefix kernel evaluates the tree part and finishes the rows itself -------------------------------
+//
+// The tree part is one more tile (or up to four) of masked keys behind the last prefix tile, on the matrix cores, and
+// belongs to the piece that ends the segment.  A segment that one worker holds alone is finished from registers.  Where
+// several workers hold pieces of it, the one that comes last merges them: a wavefront writes its part of the piece through
+// to memory, waits for that, and counts itself in (one counter per segment and wavefront, so no wavefront waits for
+// another); who finds all others counted takes their parts and writes the rows.  Nobody ever waits for another workgroup.
+// Usually a worker's last piece begins a segment that its neighbour ended first thing, so it finds the neighbour counted
+// before it has written anything, and merges from registers.  The parts are merged in the order of the workers with the
+// same operations whoever does it, so the result does not depend on timing.  The counters return to zero.
+// What it costs and saves (stamps; 32 sequences of 4 .. 64 nodes, 8B shapes): the tree part 3.4 .. 5 us and a part's store
+// and count 2.2 us per segment, merge and rows at the end 3.2 us, where the combine kernel took 18 us and a launch; the call
+// 128.9 -> 116.4 us, one sequence of 7 nodes and 517 tokens 19.0 -> 14.9.
+struct Finish {
+  int pieces, mine;  // pieces of the segment, and which of them this is
+  int slot, seg;     // this piece's slot of the class (the pieces of a segment have consecutive ones); segment of the class
+  int base, g, rows, row0;  // first node, kv head, rows of the kv head, first row of the row group
+};
+
+// The arguments, read again from where the launch put them.  Held in registers across the streaming loops they displace
+// what the loops use, which then comes lane by lane from where the compiler put it (fifteen v_readlane per tile).
+__device__ inline MainArgs kernel_args() {
+  uintptr_t p = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const MainArgs*)(const __attribute__((address_space(4))) MainArgs*)p;
+}
+
+// What a stream uses of the arguments, each in registers of its own: as parts of the groups that one load fetched they would
+// be kept, or put aside and fetched back, together with the rest of the group.
+__device__ inline MainArgs stream_args(MainArgs a) {
+  asm volatile("" : "+s"(a.block_stride), "+s"(a.head_stride), "+s"(a.num_blocks), "+s"(a.scale_log2e));
+  return a;
+}
+
+// This wavefront's counter of segment f.seg.
+template <int kCls>
+__device__ inline int32_t* counter_of(const FinishArgs& a, const Finish& f, int wv) {
+  return a.arrive + ((int64_t)a.arrive_first[kCls] + f.seg) * kWgWaves + wv;
+}
+
+// (a lane number that the compiler does not know to be loop-invariant: what follows from it is then computed where it is
+// used and does not occupy registers during the stream)
+__device__ inline int fresh(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// Workers w_first .. w_last whose shares touch units [ub, ub + span).
+__device__ inline void segment_workers(int64_t ub, int64_t span, int64_t U, int64_t W, int64_t& w_first, int64_t& w_last) {
+  w_first = ((ub + 1) * W - 1) / U;
+  w_last = ((ub + span) * W - 1) / U;
+}
+
+__device__ inline Finish finish_of(int64_t ub, int64_t span, int64_t U, int64_t W, int64_t w, int64_t seg, int base, int g,
+                                   int rows, int row0) {
+  int64_t w_first, w_last;
+  segment_workers(ub, span, U, W, w_first, w_last);
+  Finish f;
+  f.pieces = __builtin_amdgcn_readfirstlane((int)(w_last - w_first) + 1);
+  f.mine = __builtin_amdgcn_readfirstlane((int)(w - w_first));
+  f.slot = __builtin_amdgcn_readfirstlane((int)(w + seg));
+  f.seg = __builtin_amdgcn_readfirstlane((int)seg);
+  f.base = base;
+  f.g = g;
+  f.rows = rows;
+  f.row0 = row0;
+  return f;
+}
+
+// (through a buffer resource: these builtins carry the cache policy that is coherent across the XCDs, sc1)
+constexpr int kDevicePolicy = 16;
+typedef __attribute__((ext_vector_type(4))) uint32_t uintx4;
+__device__ inline __amdgpu_buffer_rsrc_t slot_buffer(float* slot, int floats) {
+  return __builtin_amdgcn_make_buffer_rsrc(slot, 0, floats * 4, 0x00027000);
+}
+__device__ inline floatx4 load_part(__amdgpu_buffer_rsrc_t r, int offset) {
+  return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, offset, 0, kDevicePolicy));
+}
+__device__ inline float load_word(__amdgpu_buffer_rsrc_t r, int offset) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, offset, 0, kDevicePolicy));
+}
+
+__device__ inline int arrivals(const int32_t* counter) {
+  return __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// (x, m, l) and (y, mc, lc) -> (x, m, l); an empty state has maximum -inf and sums of zero.
+template <int kQuads>
+__device__ inline void merge_part(floatx4 (&x)[kQuads], float& m, float& l, const floatx4 (&y)[kQuads], float mc, float lc,
+                                  float c) {
+  const float m_new = fmaxf(m, mc);
+  const float al = m == m_new ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * c);
+  const float wt = mc == m_new ? 1.f : __builtin_amdgcn_exp2f((mc - m_new) * c);
+#pragma unroll
+  for (int u = 0; u < kQuads; ++u)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[u][i] = fmaf(x[u][i], al, wt * y[u][i]);
+  l = fmaf(l, al, wt * lc);
+  m = m_new;
+}
+
+// Rows of this wavefront's row tile, accumulator quads quad0 .. : normalised, rounded and stored.  Lanes (0, j) and (1, j)
+// hold halves of each eight head dims of row j; they trade so that each stores 16 bytes.
+template <int kQuads>
+__device__ inline void write_rows(const FinishArgs& a, const Finish& f, const floatx4 (&x)[kQuads], float m, float l, int quad0,
+                                  int rt, int lane) {
+  const int h = lane >> 5, j = lane & 31;
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+  const int rho = f.row0 + rt * 32 + j;
+  const bool real = rho < f.rows;
+  const int64_t row = (int64_t)(f.base + rho / a.G) * a.Hq + f.g * a.G + rho % a.G;
+  __bf16* op = a.out + row * kD + 8 * (quad0 + h);
+#pragma unroll
+  for (int u = 0; u < kQuads; u += 2) {
+    floatx8 y;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      y[i] = x[u][i] * inv;
+      y[4 + i] = x[u + 1][i] * inv;
+    }
+    const uintx4 w = __builtin_bit_cast(uintx4, __builtin_convertvector(y, bf16x8));
+    const auto lo = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+    uintx4 z;
+    z[0] = lo[0], z[1] = hi[0], z[2] = lo[1], z[3] = hi[1];
+    if (real) *(uintx4*)(op + 8 * u) = z;
+  }
+  if (a.lse && real && quad0 == 0 && h == 0) a.lse[row] = l > 0.f ? m * a.scale + logf(l) : -INFINITY;
+}
+
+// One wavefront's part of a piece, quads quad0 .. of row tile rt (l: of the whole row).
+// `early`: the counter as read some time before; it only grows until everyone is counted.
+template <int kCls, int kQuads>
+__device__ inline void finish_part(const FinishArgs& a, const Finish& f, floatx4 (&x)[kQuads], float m, float l, int quad0,
+                                   int rt, int early, int wv, int lane) {
+  lane = fresh(lane);
+  const int h = lane >> 5, j = lane & 31;
+  if (f.pieces > 1) {
+    constexpr int kO = (kCls == 0 ? kSmallRows : kCls == 1 ? kMediumRows : kLargeRows) * kD, kSlot = kO + kFinishTail;
+    const float c = a.scale_log2e;
+    int32_t* const counter = counter_of<kCls>(a, f, wv);
+    const int at = ((rt * 32 + 2 * quad0 + h) * 32 + j) * 16, ml = (kO + wv * 64 + j) * 4;
+    const bool in_place = early == f.pieces - 1 && (f.mine == 0 || f.pieces == 2);
+    if (!in_place) {
+      const __amdgpu_buffer_rsrc_t r = slot_buffer(a.ws[kCls] + (size_t)f.slot * kSlot, kSlot);
+#pragma unroll
+      for (int u = 0; u < kQuads; ++u)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, x[u]), r, at + u * 1024, 0, kDevicePolicy);
+      if (h == 0) {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m), r, ml, 0, kDevicePolicy);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(l), r, ml + 128, 0, kDevicePolicy);
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      int before = 0;
+      if (lane == 0) before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__builtin_amdgcn_readfirstlane(before) != f.pieces - 1) return;
+    }
+    asm volatile("" ::: "memory");  // (the parts are requested after the counter said that they are there)
+    if (lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    float* const first = a.ws[kCls] + (size_t)(f.slot - f.mine) * kSlot;
+    int k = 1;
+    if (!in_place || f.mine != 0) {
+      const __amdgpu_buffer_rsrc_t r = slot_buffer(first, kSlot);
+      floatx4 y[kQuads];
+#pragma unroll
+      for (int u = 0; u < kQuads; ++u) y[u] = load_part(r, at + u * 1024);
+      float mc = load_word(r, ml), lc = load_word(r, ml + 128);
+      if (in_place) {  // two pieces, this is the second
+        merge_part(y, mc, lc, x, m, l, c);
+        k = 2;
+      }
+#pragma unroll
+      for (int u = 0; u < kQuads; ++u) x[u] = y[u];
+      m = mc;
+      l = lc;
+    }
+    for (; k < f.pieces; ++k) {
+      const __amdgpu_buffer_rsrc_t r = slot_buffer(first + (size_t)k * kSlot, kSlot);
+      floatx4 y[kQuads];
+#pragma unroll
+      for (int u = 0; u < kQuads; ++u) y[u] = load_part(r, at + u * 1024);
+      const float mc = load_word(r, ml), lc = load_word(r, ml + 128);
+      merge_part(x, m, l, y, mc, lc, c);
+    }
+  }
+  write_rows(a, f, x, m, l, quad0, rt, lane);
+}
+
+// Ancestor mask of row rho: word tt holds tree keys 32 tt .. 32 tt + 31; bits past the tree are cleared.
+__device__ inline uint32_t mask_word(const FinishArgs& a, int base, int rows, int rho, int n, int tt) {
+  const int node = base + (rho < rows ? rho : rows - 1) / a.G;
+  const uint32_t w = a.anc_mask[4 * (int64_t)node + tt];
+  const int left = n - 32 * tt;
+  return left >= 32 ? w : (left > 0 ? w & ((1u << left) - 1u) : 0u);
+}
+
+// Scores of a tile of tree keys -> probabilities (softmax_tile, for masked keys; the reference follows the maximum at
+// once, so that a probability is at most 1 however large the tree's values are).
+__device__ inline void softmax_tree(floatx16& s, uint32_t word, float& m, float& l, floatx16 (&o)[4], bf16x8& pb0,
+                                    bf16x8& pb1, float c, int h) {
+  const uint32_t bits = word >> (8 * h);  // register r holds key 16 (r / 8) + 8 h + r % 8: see sigma
+  float mx = -INFINITY;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) mx = fmaxf(mx, (bits >> (16 * (r >> 3) + (r & 7))) & 1u ? s[r] : -INFINITY);
+  mx = max_across_halves(mx);
+  const float m_new = fmaxf(m, mx);
+  const float alpha = m_new == m ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * c);
+  l *= alpha;
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt) o[jt] *= alpha;
+  m = m_new;
+  const float mc = m * c;
+  floatx8 p0, p1;
+  float sum = 0.f;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    p0[r] = (bits >> r) & 1u ? __builtin_amdgcn_exp2f(fmaf(s[r], c, -mc)) : 0.f;
+    p1[r] = (bits >> (16 + r)) & 1u ? __builtin_amdgcn_exp2f(fmaf(s[r + 8], c, -mc)) : 0.f;
+    sum += p0[r] + p1[r];
+  }
+  l += sum;
+  pb0 = __builtin_convertvector(p0, bf16x8);
+  pb1 = __builtin_convertvector(p1, bf16x8);
+}
+
+// Largest magnitude, as bits, of the elements of eight bf16 values seen so far, per half of a dword.
+typedef __attribute__((ext_vector_type(2))) uint16_t ushortx2;
+typedef __attribute__((ext_vector_type(8))) uint16_t ushort8;
+__device__ inline void note_magnitude(ushortx2& top, const ushort8& v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    ushortx2 x;
+    x[0] = v[2 * i] & 0x7FFF;
+    x[1] = v[2 * i + 1] & 0x7FFF;
+    top = __builtin_elementwise_max(top, x);
+  }
+}
+__device__ inline bool not_finite(const ushortx2& top) { return top[0] >= 0x7F80 || top[1] >= 0x7F80; }
+
+// The rows of a tree's keys (its first node's row of kv head g on): a uniform base and 32-bit offsets behind it.
+struct TreeRows {
+  const char *k, *v;
+  int pitch, last;  // bytes from node to node; last node
+};
+__device__ inline TreeRows tree_rows(const FinishArgs& a, int base, int g, int n) {
+  const int64_t at = ((int64_t)base * a.Hkv + g) * kD;
+  return TreeRows{(const char*)(a.k_tree + at), (const char*)(a.v_tree + at), a.Hkv * kD * 2, n - 1};
+}
+// A lane's operand vectors of a tile of tree keys.  K: key row j, head dims 16 ks + 8 h ..; V: head dim 32 jt + j, tokens
+// 16 kk + 8 h ..: gathered, 64 contiguous bytes per half wavefront and token.  Keys past the tree repeat its last one.
+__device__ inline bf16x8 tree_k(const TreeRows& t, int tt, int ks, int lane) {
+  const int h = lane >> 5, j = lane & 31;
+  const uint32_t at = min(32 * tt + (j & 16) + sigma(j & 15), t.last) * t.pitch + h * 16;
+  return *(const bf16x8*)(t.k + at + ks * 32);
+}
+__device__ inline ushort8 tree_v(const TreeRows& t, int tt, int kk, int jt, int lane) {
+  const int h = lane >> 5, j = lane & 31;
+  ushort8 v;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t at = min(32 * tt + 16 * kk + 8 * h + e, t.last) * t.pitch + j * 2;
+    v[e] = *(const uint16_t*)(t.v + at + jt * 64);
+  }
+  return v;
+}
+// Infinite and NaN elements -> 0: on the matrix cores a zero probability times such a value would reach the rows that do
+// not see it.
+__device__ inline void clear_not_finite(ushort8& v) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = (v[e] & 0x7F80) == 0x7F80 ? 0 : v[e];
+}
+// What clear_not_finite took away, added to the rows that do see it: a positive probability times an infinity is that
+// infinity, and NaN stays NaN.
+__device__ inline void add_not_finite(floatx16 (&o)[4], const FinishArgs& a, const TreeRows& t, int base, int rows, int rho, int n,
+                                      int lane) {
+  for (int tt = 0; 32 * tt < n; ++tt) {
+    uint32_t bits = mask_word(a, base, rows, rho, n, tt);
+    while (__any(bits != 0u)) {
+      const uint32_t at = (bits != 0u ? 32 * tt + __ffs(bits) - 1 : 0) * t.pitch + (lane >> 5) * 8;
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const uint16_t v = *(const uint16_t*)(t.v + at + 64 * jt + 16 * (r >> 2) + 2 * (r & 3));
+          if (bits != 0u && (v & 0x7F80) == 0x7F80) o[jt][r] += __uint_as_float((uint32_t)v << 16);
+        }
+      bits &= bits - 1u;
+    }
+  }
+}
+
+// One tile of tree keys against the 32 rows from `row` on, operands straight from memory (for loops that have no barrier).
+__device__ inline void tree_tile(floatx16 (&o)[4], float& m, float& l, const FinishArgs& a, int base, int g, int rows, int row,
+                                 int n, int tt, int lane) {
+  const float c = a.scale_log2e;
+  lane = fresh(lane);
+  const int h = lane >> 5, j = lane & 31;
+  const TreeRows t = tree_rows(a, base, g, n);
+  ushort8 v[2][4];
+  bf16x8 k[8], q[8];
+  const int rho = row + j < rows ? row + j : rows - 1;
+  const __bf16* qp = a.q + ((int64_t)(base + rho / a.G) * a.Hq + g * a.G + rho % a.G) * kD + h * 8;
+  const uint32_t word = mask_word(a, base, rows, rho, n, tt);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) {
+    k[ks] = tree_k(t, tt, ks, lane);
+    q[ks] = *(const bf16x8*)(qp + ks * 16);
+  }
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) v[kk][jt] = tree_v(t, tt, kk, jt, lane);
+  floatx16 s = (floatx16)(0.f);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k[ks], q[ks], s, 0, 0, 0);
+  bf16x8 pb0, pb1;
+  softmax_tree(s, word, m, l, o, pb0, pb1, c, h);
+  ushortx2 top = {0, 0};
+#pragma unroll
+  for (int i = 0; i < 8; ++i) note_magnitude(top, v[i >> 2][i & 3]);
+  const bool mend = __any(not_finite(top));
+  if (mend) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) clear_not_finite(v[i >> 2][i & 3]);
+  }
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt) {
+    o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v[0][jt]), pb0, o[jt], 0, 0, 0);
+    o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v[1][jt]), pb1, o[jt], 0, 0, 0);
+  }
+  if (mend) add_not_finite(o, a, t, base, rows, rho, n, lane);
+}
+
+// The whole workgroup puts up to four tiles of tree keys into LDS stages 0 .. 3 in operand order: wavefront w K step w and
+// V vector w of each.  request_tree asks for two tiles; stage_tree, entered after a barrier behind which nobody reads a
+// stage and no request for one is in flight, stores them, sees to the rest, and returns after a barrier whether a value is
+// infinite or NaN (flags: a word per wavefront).
+struct TreePair {
+  bf16x8 k[2];
+  ushort8 v[2];
+};
+__device__ inline void request_tree(TreePair& p, const TreeRows& t, int tt, int wv, int lane) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    p.k[i] = tree_k(t, tt + i, wv, lane);
+    p.v[i] = tree_v(t, tt + i, wv >> 2, wv & 3, lane);
+  }
+}
+__device__ inline bool stage_tree(TreePair& p, const TreeRows& t, bf16x8* lds, uint32_t* flags, int wv, int lane) {
+  ushortx2 top = {0, 0};
+  for (int tt = 0;;) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      note_magnitude(top, p.v[i]);
+      if (__any(not_finite(top))) clear_not_finite(p.v[i]);
+      lds[((tt + i) * 16 + wv) * kWave + lane] = p.k[i];
+      lds[((tt + i) * 16 + 8 + wv) * kWave + lane] = __builtin_bit_cast(bf16x8, p.v[i]);
+    }
+    tt += 2;
+    if (32 * tt > t.last) break;
+    request_tree(p, t, tt, wv, lane);
+  }
+  const bool mend = __any(not_finite(top));
+  if (lane == 0) flags[wv] = mend ? 1u : 0u;
+  __syncthreads();
+  uint32_t any = 0u;
+#pragma unroll
+  for (int i = 0; i < kWgWaves; ++i) any |= flags[i];
+  return any != 0u;
+}
+
+// Staged tile tt against this wavefront's rows.
+__device__ inline void staged_tree_tile(floatx16 (&o)[4], float& m, float& l, const bf16x8 (&q)[8], uint32_t word,
+                                        const bf16x8* lds, int tt, float c, int lane) {
+  const bf16x8* st = lds + tt * 16 * kWave + lane;
+  floatx16 s = (floatx16)(0.f);
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st[ks * kWave], q[ks], s, 0, 0, 0);
+  bf16x8 pb0, pb1;
+  softmax_tree(s, word, m, l, o, pb0, pb1, c, lane >> 5);
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt) {
+    o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st[(8 + jt) * kWave], pb0, o[jt], 0, 0, 0);
+    o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st[(12 + jt) * kWave], pb1, o[jt], 0, 0, 0);
+  }
+}
+
 // Locates the sequence that holds unit u0 in one class's unit space.
 __device__ inline int find_sequence(const int64_t* cum_units, int batch, int64_t u0) {
   int lo = 0, hi = batch;
@@ -826,9 +1257,11 @@ __device__ inline floatx4 state_quad(const float* state, int quad, int lane) {
 // kSlotRows / qt: the slot holds kSlotRows rows and this is its row tile qt.
 // kLoadsInFlight: the caller has global loads outstanding that the barriers must not wait for (the next piece's
 // first tile); the barriers then only wait for this wavefront's LDS traffic.
-template <bool kScaled = false, int kSlotRows = kSmallRows, bool kLoadsInFlight = false>
+// kFinish: the wavefront's slice goes to finish_part instead.
+template <bool kScaled = false, int kSlotRows = kSmallRows, bool kLoadsInFlight = false, bool kFinish = false>
 __device__ inline void fold_and_store(const SmallState& S, float* lds, float* slot, int wv, int lane, float c,
-                                      float m_scale = 1.f, float o_scale = 1.f, int qt = 0) {
+                                      float m_scale = 1.f, float o_scale = 1.f, int qt = 0,
+                                      const FinishArgs* fa = nullptr, const Finish* f = nullptr, int early = 0) {
   const int h = lane >> 5, j = lane & 31;
   state_to_lds(S, lds + wv * kStateFloats, lane);
   if (kLoadsInFlight)
@@ -863,6 +1296,11 @@ __device__ inline void fold_and_store(const SmallState& S, float* lds, float* sl
     x[0] *= o_scale;
     x[1] *= o_scale;
     m_new *= m_scale;  // (-inf stays -inf)
+  }
+  if (kFinish) {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // the next piece reuses the LDS regions
+    finish_part<kSlotRows == kSmallRows ? 0 : 1, 2>(*fa, *f, x, m_new, sum_across_halves(l_new), 2 * wv, qt, early, wv, lane);
+    return;
   }
   // accumulator register 16 jt + 4 r4 + i of lane (h, j) is row j, head dims 4 (8 jt + 2 r4 + h) + i
   const int jt = wv >> 1, r4 = 2 * (wv & 1);
@@ -972,14 +1410,16 @@ constexpr int kSmallWaves = kWgWaves;
 
 // A piece: the part of a worker's unit range that lies in one (sequence, kv head) segment.
 struct SmallPiece {
-  int b, g, base, t0, nt;
-  int64_t seg;
+  int b, g, base, t0, nt;  // (kFinish: a segment's tree part counts as its tile si.tiles)
+  int units;               // of the worker's range that the piece takes up
+  int64_t seg, ub;         // segment of the class, its first unit
   SeqInfo si;
   bool valid;
 };
 
 // The piece that starts at unit u0 of the worker's range [.., u1) (sequences without units of this class are
 // skipped; b moves along).
+template <bool kFinish>
 __device__ inline SmallPiece small_piece(ClassPlan& cp, const PlanView& pv, const MainArgs& a, int64_t u0, int64_t u1,
                                          int& b, int lane) {
   SmallPiece p;
@@ -993,11 +1433,19 @@ __device__ inline SmallPiece small_piece(ClassPlan& cp, const PlanView& pv, cons
     p.si = window_info(win, b);
     // (the divisions run on the vector unit; everything is wavefront-uniform and goes back to scalar registers)
     const int64_t local = u0 - seq_begin;
+    const int units = segment_units<kFinish>(p.si, a.tree_cost);
     p.b = __builtin_amdgcn_readfirstlane(b);
-    p.g = __builtin_amdgcn_readfirstlane((int)(local / p.si.tiles));
-    p.t0 = __builtin_amdgcn_readfirstlane((int)(local % p.si.tiles));
+    p.g = __builtin_amdgcn_readfirstlane((int)(local / units));
+    p.t0 = __builtin_amdgcn_readfirstlane((int)(local % units));
     const int64_t left = u1 - u0;
-    p.nt = __builtin_amdgcn_readfirstlane((int)(left < (int64_t)(p.si.tiles - p.t0) ? left : (int64_t)(p.si.tiles - p.t0)));
+    p.nt = __builtin_amdgcn_readfirstlane((int)(left < (int64_t)(units - p.t0) ? left : (int64_t)(units - p.t0)));
+    p.units = p.nt;
+    if (kFinish) {
+      p.ub = uniform64(u0 - p.t0);
+      const int end = p.t0 + p.nt;
+      p.t0 = min(p.t0, p.si.tiles);
+      p.nt = min(end, p.si.tiles) - p.t0 + (end == units ? 1 : 0);
+    }
     p.seg = uniform64((int64_t)__builtin_amdgcn_readlane(win.cum_segs, b - win.first) + p.g);
     p.base = __builtin_amdgcn_readlane(win.cu_nodes, b - win.first);
     p.valid = true;
@@ -1025,8 +1473,8 @@ __device__ inline void small_touch(uint32_t (&touched)[4], const MainArgs& a, co
   touched[3] = *(const uint32_t*)(a.q + ((int64_t)node * a.Hq + head) * kD + h * 64);
 }
 
-__device__ inline void small_worker(const MainArgs& a, int64_t w, ClassPlan& cp, float* merge_lds /* 132 KB: eight states */) {
-  const PlanView pv = plan_view(a.plan, a.batch);
+template <bool kFinish>
+__device__ inline void small_worker(const MainArgs& a0, int64_t w, ClassPlan& cp, float* merge_lds /* 132 KB: eight states */) {
   const int64_t U = cp.U, W = cp.W;
   if (w >= W || U <= 0) return;
   int64_t u0 = (w * U) / W;
@@ -1034,12 +1482,14 @@ __device__ inline void small_worker(const MainArgs& a, int64_t w, ClassPlan& cp,
   if (u0 >= u1) return;
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int b = locate(cp, pv, a.cu_nodes, 0, a.batch, u0, lane);
-  SmallPiece cur = small_piece(cp, pv, a, u0, u1, b, lane);
+  int b = locate(cp, plan_view(a0.plan, a0.batch), a0.cu_nodes, 0, a0.batch, u0, lane);
+  SmallPiece cur = small_piece<kFinish>(cp, plan_view(a0.plan, a0.batch), a0, u0, u1, b, lane);
   while (cur.valid) {
+    const MainArgs a = kFinish ? kernel_args() : a0;
+    const PlanView pv = plan_view(a.plan, a.batch);
     // The piece after this one is located first: what this wavefront will read first of it is requested before
     // the fold of this piece, so that the stream does not start from memory latency at every piece boundary.
-    const SmallPiece nxt = small_piece(cp, pv, a, u0 + cur.nt, u1, b, lane);
+    const SmallPiece nxt = small_piece<kFinish>(cp, pv, a, u0 + cur.units, u1, b, lane);
     // this wavefront's share of the piece, and of the next
     const int s0 = cur.t0 + (int)(((int64_t)cur.nt * wv) / kSmallWaves);
     const int s1 = cur.t0 + (int)(((int64_t)cur.nt * (wv + 1)) / kSmallWaves);
@@ -1048,7 +1498,7 @@ __device__ inline void small_worker(const MainArgs& a, int64_t w, ClassPlan& cp,
       n0 = nxt.t0 + (int)(((int64_t)nxt.nt * wv) / kSmallWaves);
       n1 = nxt.t0 + (int)(((int64_t)nxt.nt * (wv + 1)) / kSmallWaves);
     }
-    const bool pre = n0 < n1;
+    const bool pre = n0 < (kFinish ? min(n1, nxt.si.tiles) : n1);
     // block ids of the next share's first tile: scalar loads, issued a whole share ahead
     int32_t nb0 = 0, nb1 = 0;
     if (pre) {
@@ -1057,14 +1507,25 @@ __device__ inline void small_worker(const MainArgs& a, int64_t w, ClassPlan& cp,
       nb0 = sload(row + min(2 * n0, nblk - 1));
       nb1 = sload(row + min(2 * n0 + 1, nblk - 1));
     }
+    Finish fin;
+    if (kFinish)
+      fin = finish_of(cur.ub, segment_units<true>(cur.si, a.tree_cost), U, W, w, cur.seg, cur.base, cur.g, cur.si.n * a.G, 0);
     SmallState S;
-    small_segment(S, a, cur.b, cur.g, cur.base, s0, s1, cur.si, lane);
+    small_segment(S, a, cur.b, cur.g, cur.base, s0, kFinish ? min(s1, cur.si.tiles) : s1, cur.si, lane);
     uint32_t touched[4] = {0u, 0u, 0u, 0u};
-    if (pre) small_touch(touched, a, nxt, n0, nb0, nb1, lane);
-    fold_and_store<false, kSmallRows, true>(S, merge_lds, a.ws[0] + (size_t)(w + cur.seg) * kSmallSlot, wv, lane,
-                                            a.scale_log2e);
+    if (kFinish) {
+      const FinishArgs fa = kernel_args().fin;
+      const int early = fin.pieces > 1 ? arrivals(counter_of<0>(fa, fin, wv)) : 0;
+      if (pre) small_touch(touched, a, nxt, n0, nb0, nb1, lane);
+      if (s1 > cur.si.tiles) tree_tile(S.o, S.m, S.l, fa, cur.base, cur.g, fin.rows, 0, cur.si.n, 0, lane);
+      fold_and_store<false, kSmallRows, true, true>(S, merge_lds, nullptr, wv, lane, a.scale_log2e, 1.f, 1.f, 0, &fa, &fin, early);
+    } else {
+      if (pre) small_touch(touched, a, nxt, n0, nb0, nb1, lane);
+      fold_and_store<false, kSmallRows, true>(S, merge_lds, a.ws[0] + (size_t)(w + cur.seg) * kSmallSlot, wv, lane,
+                                              a.scale_log2e);
+    }
     asm volatile("" ::"v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
-    u0 += cur.nt;
+    u0 += cur.units;
     cur = nxt;
   }
 }
@@ -1178,7 +1639,9 @@ __device__ inline void pair_segment(SmallState (&S)[2], const bf16x8* lds_q, con
 // The eight states of a row group of two row tiles in LDS, row tile rt's in regions 4 rt .. 4 rt + 3, become one partial:
 // wavefront w merges accumulator registers 16 (w % 4) .. + 15 of the four states of row tile w / 4 (always in region
 // order) and stores that slice of the 64-row slot.
-__device__ inline void fold_quads_and_store(float* lds, float* slot, int wv, int lane, float c, float m_scale, float o_scale) {
+template <bool kFinish>
+__device__ inline void fold_quads_and_store(float* lds, float* slot, int wv, int lane, float c, float m_scale, float o_scale,
+                                            const FinishArgs* fa, const Finish* f, int early) {
   const int h = lane >> 5, j = lane & 31;
   const int rt = wv >> 2, part = wv & 3;
   float mk[4], lk[4];
@@ -1197,6 +1660,11 @@ __device__ inline void fold_quads_and_store(float* lds, float* slot, int wv, int
     l_new += lk[k] * sc;
 #pragma unroll
     for (int u = 0; u < 4; ++u) x[u] += state_quad(lds + (4 * rt + k) * kStateFloats, 4 * part + u, lane) * sc;
+  }
+  if (kFinish) {
+    __syncthreads();  // the next piece reuses the LDS regions
+    finish_part<1, 4>(*fa, *f, x, m_new, sum_across_halves(l_new), 4 * part, rt, early, wv, lane);
+    return;
   }
   // accumulator register 16 jt + 4 r4 + i of lane (h, j) is row j, head dims 4 (8 jt + 2 r4 + h) + i; here jt = part, r4 = u
 #pragma unroll
@@ -1243,61 +1711,101 @@ __device__ inline void fold_pairs_and_store(SmallState (&S)[2], float* lds, floa
     }
   }
   __syncthreads();
-  fold_quads_and_store(lds, slot, wv, lane, c, m_scale, o_scale);
+  fold_quads_and_store<false>(lds, slot, wv, lane, c, m_scale, o_scale, nullptr, nullptr, 0);
 }
 
 // (The loop of small_segment is 237 instructions long where the states are handed to the fold by reference as here, 247 with
 // the same calls written out in the worker: 40 trees of 48 rows, 1500 tokens, prefix kernel 35.1 us instead of 36.3.)
+template <bool kFinish>
 __device__ inline void fold_halves_and_store(const SmallState& S, float* lds, float* slot, int wv, int lane, float c,
-                                             float m_scale, float o_scale) {
+                                             float m_scale, float o_scale, const FinishArgs* fa, const Finish* f, int early) {
   state_to_lds(S, lds + wv * kStateFloats, lane);
   __syncthreads();
-  fold_quads_and_store(lds, slot, wv, lane, c, m_scale, o_scale);
+  fold_quads_and_store<kFinish>(lds, slot, wv, lane, c, m_scale, o_scale, fa, f, early);
 }
 
 // A worker's pieces.  kPair: two row tiles go to every wavefront; else one to each half of the workgroup (wavefronts 0 .. 3
 // carry row tile 0, 4 .. 7 row tile 1, both halves stream the same tiles).
-template <bool kPair>
-__device__ inline void fp8_pieces(const MainArgs& a, int64_t w, ClassPlan& cp, float* merge_lds, int64_t u0, int64_t u1, int b,
+// kFinish: the states take on true units before the tree part (its keys and values have no scales) and the fold; the tree
+// part goes to a row tile's last wavefront, or its last two.
+__device__ inline void to_true_units(SmallState& S, float m_scale, float o_scale) {
+  S.m *= m_scale;  // (-inf stays -inf)
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt) S.o[jt] *= o_scale;
+}
+
+template <bool kPair, bool kFinish>
+__device__ inline void fp8_pieces(const MainArgs& a0, int64_t w, ClassPlan& cp, float* merge_lds, int64_t u0, int64_t u1, int b,
                                   int wv, int lane) {
-  const PlanView pv = plan_view(a.plan, a.batch);
   PlanWindow& win = cp.win;
-  while (u0 < u1 && b < a.batch) {
+  for (;;) {
+    const MainArgs a = kFinish ? kernel_args() : a0;
+    if (!(u0 < u1 && b < a.batch)) break;
+    const PlanView pv = plan_view(a.plan, a.batch);
     follow(cp, pv, a.cu_nodes, 1, a.batch, b, lane);
     const int64_t seq_begin = window_cum_units(win, b - win.first);
     const int64_t seq_end = window_cum_units(win, b + 1 - win.first);
     if (u0 >= seq_end) { ++b; continue; }
     const SeqInfo si = window_info(win, b);
     const int64_t local = u0 - seq_begin;
-    const int g = (int)(local / si.tiles);  // (one row group: class 1 has at most 64 rows)
-    const int t0 = (int)(local % si.tiles);
+    const int units = segment_units<kFinish>(si, a.tree_cost);
+    const int g = (int)(local / units);  // (one row group: class 1 has at most 64 rows)
+    const int begin = (int)(local % units);
     const int64_t left = u1 - u0;
-    const int nt = (int)(left < (int64_t)(si.tiles - t0) ? left : (int64_t)(si.tiles - t0));
+    const int end = begin + (int)(left < (int64_t)(units - begin) ? left : (int64_t)(units - begin));
+    // prefix tiles t0 .. t1 of the piece; its tree part counts as one more
+    const int t0 = min(begin, si.tiles), t1 = min(end, si.tiles);
+    const bool tree = kFinish && end == units;
+    const int nt = t1 - t0 + (tree ? 1 : 0);
     const int64_t seg = (int64_t)__builtin_amdgcn_readlane(win.cum_segs, b - win.first) + g;
     const int base = __builtin_amdgcn_readlane(win.cu_nodes, b - win.first);
-    float* slot = a.ws[1] + (size_t)(w + seg) * kMediumSlot;
-    const int s0 = t0 + (int)(((int64_t)nt * wv) / kWgWaves);
-    const int s1 = t0 + (int)(((int64_t)nt * (wv + 1)) / kWgWaves);
-    if (si.n * a.G <= kSmallRows) {
+    const int M = si.n * a.G;
+    float* slot = kFinish ? nullptr : a.ws[1] + (size_t)(w + seg) * kMediumSlot;
+    Finish fin;
+    if (kFinish) fin = finish_of(u0 - begin, units, cp.U, cp.W, w, seg, base, g, M, 0);
+    FinishArgs fa;
+    int early = 0;
+    float c = a.scale_log2e, m_scale = a.m_scale, o_scale = a.o_scale;
+    auto streamed = [&]() {
+      if (!kFinish) return;
+      const MainArgs z = kernel_args();
+      fa = z.fin;
+      c = fa.scale_log2e;
+      m_scale = z.m_scale;
+      o_scale = z.o_scale;
+      if (fin.pieces > 1) early = arrivals(counter_of<1>(fa, fin, wv));
+    };
+    const int s0 = min(t1, t0 + (int)(((int64_t)nt * wv) / kWgWaves));
+    const int s1 = min(t1, t0 + (int)(((int64_t)nt * (wv + 1)) / kWgWaves));
+    if (M <= kSmallRows) {
       SmallState S;
-      small_segment<fp8x8>(S, a, b, g, base, s0, s1, si, lane);
-      fold_and_store<true, kMediumRows>(S, merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
+      small_segment<fp8x8>(S, kFinish ? stream_args(a) : a, b, g, base, s0, s1, si, lane);
+      streamed();
+      if (kFinish) to_true_units(S, m_scale, o_scale);
+      if (tree && wv == kWgWaves - 1) tree_tile(S.o, S.m, S.l, fa, base, g, M, 0, si.n, 0, lane);
+      fold_and_store<!kFinish, kMediumRows, false, kFinish>(S, merge_lds, slot, wv, lane, c, m_scale, o_scale, 0, &fa, &fin,
+                                                            early);
     } else if (kPair) {
       bf16x8* lds_q = (bf16x8*)merge_lds;  // (the fold's regions: one after the other)
-      pair_queries(lds_q, a, g, base, si.n * a.G, wv, lane);
+      pair_queries(lds_q, a, g, base, M, wv, lane);
       SmallState P[2];
       pair_segment(P, lds_q, a, b, g, s0, s1, si, lane);
       __syncthreads();  // nobody reads the queries any more
-      fold_pairs_and_store(P, merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
+      fold_pairs_and_store(P, merge_lds, slot, wv, lane, c, m_scale, o_scale);
     } else {
       const int rt = wv >> 2, sub = wv & 3;
-      const int h0 = t0 + (int)(((int64_t)nt * sub) / 4);
-      const int h1 = t0 + (int)(((int64_t)nt * (sub + 1)) / 4);
+      const int h0 = min(t1, t0 + (int)(((int64_t)nt * sub) / 4));
+      const int h1 = min(t1, t0 + (int)(((int64_t)nt * (sub + 1)) / 4));
       SmallState S;
-      small_segment<fp8x8, false>(S, a, b, g, base, h0, h1, si, lane, rt * kSmallRows);
-      fold_halves_and_store(S, merge_lds, slot, wv, lane, a.scale_log2e, a.m_scale, a.o_scale);
+      small_segment<fp8x8, false>(S, kFinish ? stream_args(a) : a, b, g, base, h0, h1, si, lane, rt * kSmallRows);
+      streamed();
+      if (kFinish) to_true_units(S, m_scale, o_scale);
+      if (tree && sub >= 2 && 32 * (3 - sub) < si.n)
+        tree_tile(S.o, S.m, S.l, fa, base, g, M, rt * kSmallRows, si.n, 3 - sub, lane);
+      fold_halves_and_store<kFinish>(S, merge_lds, slot, wv, lane, c, kFinish ? 1.f : m_scale, kFinish ? 1.f : o_scale, &fa,
+                                     &fin, early);
     }
-    u0 += nt;
+    u0 += end - begin;
   }
 }
 
@@ -1311,7 +1819,7 @@ constexpr int kPairTiles = 72;
 // kPair: of the kernel, which can do both; it runs the other loop a little slower than the kernel that has only that one (60
 // trees of one row tile and 4 of class 2, 9000 tokens, 238 us against 237; 20 trees of 48 and 20 of 80 rows, 1500 tokens, 70
 // against 67), so a batch that cannot have long pieces runs that: see tva_launch_mfma.
-template <bool kPair>
+template <bool kPair, bool kFinish>
 __device__ inline void fp8_worker(const MainArgs& a, int64_t w, ClassPlan& cp, float* merge_lds /* 132 KB */) {
   const PlanView pv = plan_view(a.plan, a.batch);
   const int64_t U = cp.U, W = cp.W;
@@ -1325,11 +1833,11 @@ __device__ inline void fp8_worker(const MainArgs& a, int64_t w, ClassPlan& cp, f
     follow(cp, pv, a.cu_nodes, 1, a.batch, b, lane);
     const SeqInfo first = window_info(cp.win, b - cp.win.first);
     if (u1 - u0 >= kPairTiles && first.tiles >= kPairTiles && first.n * a.G > kSmallRows) {
-      fp8_pieces<true>(a, w, cp, merge_lds, u0, u1, b, wv, lane);
+      fp8_pieces<true, false>(a, w, cp, merge_lds, u0, u1, b, wv, lane);
       return;
     }
   }
-  fp8_pieces<false>(a, w, cp, merge_lds, u0, u1, b, wv, lane);
+  fp8_pieces<false, kFinish>(a, w, cp, merge_lds, u0, u1, b, wv, lane);
 }
 
 // ---- classes 1 and 2: K/V tiles staged in LDS, shared by the eight wavefronts of a workgroup --
@@ -1610,9 +2118,11 @@ __device__ inline void woven_tile(const floatx16& s, floatx16& s_next, floatx16 
 // kFp8: the cache holds E4M3 bytes.  LDS then holds four bf16 stages (a tile is used during two iterations) and,
 // behind them, kStages raw slots of 8 KB; a wavefront converts its own share of tile t + 1 as soon as it has
 // landed (nobody else touches those bytes), before the barrier that publishes the stage.
-template <bool kRows, bool kFp8 = false>
+// kFinish: tiles t0 .. t1 may be none, `tree`: the segment's tree part belongs to this piece; the rows go to finish_part.
+template <bool kRows, bool kFp8 = false, bool kFinish = false>
 __device__ inline void staged_segment(const MainArgs& a, int b, int g, int base, int row0, int t0, int t1,
-                                      const SeqInfo si, float* slot, int wv, int lane, bf16x8* lds) {
+                                      const SeqInfo si, float* slot, int wv, int lane, bf16x8* lds, bool tree = false,
+                                      const Finish* fin = nullptr) {
   constexpr int kRing = kFp8 ? 4 : kStages;  // bf16 stages
   constexpr int kLoads = kFp8 ? 4 : 2;       // vector-memory loads per tile and wavefront
   const int h = lane >> 5, j = lane & 31;
@@ -1657,62 +2167,104 @@ __device__ inline void staged_segment(const MainArgs& a, int b, int g, int base,
   };
 
   __builtin_amdgcn_s_barrier();  // the previous segment is done with every stage
+  if (!kFinish || t0 < t1) {
 #pragma unroll
-  for (int i = 0; i < kStages - 1; ++i)  // tiles t0 .. t0 + kStages - 2; past the end: the last tile again (L2 hits)
-    request(block_id(t0 + i, 0), block_id(t0 + i, 1), t0 + i, t0 + i > last || si.rg > 1);
-  int32_t nb0 = block_id(t0 + kStages - 1, 0), nb1 = block_id(t0 + kStages - 1, 1);
-  asm volatile("" ::"s"(nb0), "s"(nb1));
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads * (kStages - 2)) : "memory");  // tile t0 is in
-  convert(t0);
-  land(t0);
-  __builtin_amdgcn_s_barrier();
-  floatx16 s;
-  if (kRows) {
-    score_tile(s, rd + (t0 & (kRing - 1)) * (kStageVecs * 16), q);
-    if (si.len - t0 * kTile < kTile) mask_scores(s, si.len - t0 * kTile, h);
-  }
-  // iteration t: s_in holds the scores of tile t, s_out receives those of tile t + 1.  Only a sequence's last tile
-  // can be ragged, so the iterations that land and mask a full tile (kChecked = false) carry no test for it.
-  auto iter = [&](auto checked, int t, const floatx16& s_in, floatx16& s_out) {
-    constexpr bool kChecked = decltype(checked)::value;
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads * (kStages - 3)) : "memory");  // tile t + 1 is in
-    convert(t + 1);
-    if (kChecked) land(t + 1);
-    // every share of tile t + 1 is visible, and everyone is done with tile t - 1
-    __builtin_amdgcn_s_barrier();
-    auto fetch = [&]() {
-      request(nb0, nb1, t + kStages - 1, t + kStages - 1 > last || si.rg > 1);
-      nb0 = block_id(t + kStages, 0);
-      nb1 = block_id(t + kStages, 1);
-    };
-    if (kRows) {
-      const uint32_t k_addr = rd + ((t + 1) & (kRing - 1)) * (kStageVecs * 16);
-      const uint32_t v_addr = rd + (t & (kRing - 1)) * (kStageVecs * 16) + 8 * kWave * 16;
-      woven_tile(s_in, s_out, o, m, l, q, k_addr, v_addr, c, fetch);
-      if (kChecked) {
-        const int nv_next = si.len - (t + 1) * kTile;
-        if (nv_next < kTile) mask_scores(s_out, nv_next, h);
-      }
-    } else {
-      fetch();
-    }
-    // the block ids are in before the next iteration issues its LDS reads (no wait among them)
+    for (int i = 0; i < kStages - 1; ++i)  // tiles t0 .. t0 + kStages - 2; past the end: the last tile again (L2 hits)
+      request(block_id(t0 + i, 0), block_id(t0 + i, 1), t0 + i, t0 + i > last || si.rg > 1);
+    int32_t nb0 = block_id(t0 + kStages - 1, 0), nb1 = block_id(t0 + kStages - 1, 1);
     asm volatile("" ::"s"(nb0), "s"(nb1));
-  };
-  // tile t + 1 is full for every t < len / kTile - 1
-  const int t_plain = min(t1, si.len / kTile - 1);
-  floatx16 s2;
-  int t = t0;
-  for (; t + 2 <= t_plain; t += 2) {
-    iter(std::false_type{}, t, s, s2);
-    iter(std::false_type{}, t + 1, s2, s);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads * (kStages - 2)) : "memory");  // tile t0 is in
+    convert(t0);
+    land(t0);
+    __builtin_amdgcn_s_barrier();
+    floatx16 s;
+    if (kRows) {
+      score_tile(s, rd + (t0 & (kRing - 1)) * (kStageVecs * 16), q);
+      if (si.len - t0 * kTile < kTile) mask_scores(s, si.len - t0 * kTile, h);
+    }
+    // iteration t: s_in holds the scores of tile t, s_out receives those of tile t + 1.  Only a sequence's last tile
+    // can be ragged, so the iterations that land and mask a full tile (kChecked = false) carry no test for it.
+    auto iter = [&](auto checked, int t, const floatx16& s_in, floatx16& s_out) {
+      constexpr bool kChecked = decltype(checked)::value;
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoads * (kStages - 3)) : "memory");  // tile t + 1 is in
+      convert(t + 1);
+      if (kChecked) land(t + 1);
+      // every share of tile t + 1 is visible, and everyone is done with tile t - 1
+      __builtin_amdgcn_s_barrier();
+      auto fetch = [&]() {
+        request(nb0, nb1, t + kStages - 1, t + kStages - 1 > last || si.rg > 1);
+        nb0 = block_id(t + kStages, 0);
+        nb1 = block_id(t + kStages, 1);
+      };
+      if (kRows) {
+        const uint32_t k_addr = rd + ((t + 1) & (kRing - 1)) * (kStageVecs * 16);
+        const uint32_t v_addr = rd + (t & (kRing - 1)) * (kStageVecs * 16) + 8 * kWave * 16;
+        woven_tile(s_in, s_out, o, m, l, q, k_addr, v_addr, c, fetch);
+        if (kChecked) {
+          const int nv_next = si.len - (t + 1) * kTile;
+          if (nv_next < kTile) mask_scores(s_out, nv_next, h);
+        }
+      } else {
+        fetch();
+      }
+      // the block ids are in before the next iteration issues its LDS reads (no wait among them)
+      asm volatile("" ::"s"(nb0), "s"(nb1));
+    };
+    // tile t + 1 is full for every t < len / kTile - 1
+    const int t_plain = min(t1, si.len / kTile - 1);
+    floatx16 s2;
+    int t = t0;
+    for (; t + 2 <= t_plain; t += 2) {
+      iter(std::false_type{}, t, s, s2);
+      iter(std::false_type{}, t + 1, s2, s);
+    }
+    for (; t < t1; ++t) {
+      iter(std::true_type{}, t, s, s2);
+      s = s2;
+    }
   }
-  for (; t < t1; ++t) {
-    iter(std::true_type{}, t, s, s2);
-    s = s2;
+  if (!kFinish) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no fetch of this segment may land later
+    if (kRows) store_partial(slot, kLargeRows, wv, o, m, l, lane, a.m_scale, a.o_scale);
+    return;
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no fetch of this segment may land later
-  if (kRows) store_partial(slot, kLargeRows, wv, o, m, l, lane, a.m_scale, a.o_scale);
+  if (kFp8 && kRows) {  // (true units: see fp8_pieces)
+    m *= a.m_scale;
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) o[jt] *= a.o_scale;
+  }
+  const FinishArgs fa = kernel_args().fin;
+  int early = 0;
+  if (kRows && fin->pieces > 1) early = arrivals(counter_of<2>(fa, *fin, wv));
+  if (!tree) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    const int ln = fresh(lane);
+    const TreeRows t = tree_rows(fa, base, g, si.n);
+    TreePair pair;
+    request_tree(pair, t, 0, wv, ln);
+    uint32_t word[4];
+    if (kRows)
+#pragma unroll
+      for (int tt = 0; tt < 4; ++tt) word[tt] = mask_word(fa, base, M, row0 + (ln & 31), si.n, tt);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    const bool mend = stage_tree(pair, t, lds, (uint32_t*)(lds + kStages * kStageVecs), wv, ln);
+    if (kRows) {
+      for (int tt = 0; 32 * tt < si.n; ++tt)
+        staged_tree_tile(o, m, l, q, tt == 0 ? word[0] : tt == 1 ? word[1] : tt == 2 ? word[2] : word[3], lds, tt,
+                         fa.scale_log2e, ln);
+      if (mend) add_not_finite(o, fa, t, base, M, row0 + (ln & 31), si.n, ln);
+    }
+  }
+  if (kRows) {
+    floatx4 x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[u][i] = o[u >> 2][4 * (u & 3) + i];
+    finish_part<2, 16>(fa, *fin, x, m, sum_across_halves(l), 0, wv, early, wv, lane);
+  }
 }
 
 // One staged tile against this wavefront's 32 rows, nothing woven in: all 16 operand reads
@@ -1758,9 +2310,9 @@ __device__ inline void plain_tile(floatx16 (&o)[4], float& m, float& l, const bf
 // K + key group) become one partial: all eight states go to LDS, and after one barrier
 // wavefront w merges, for row tile w / K, accumulator registers [(w % K) 64 / K, ...) of
 // that row tile's K states (always in key-group order) and stores that slice.
-template <int R>
+template <int R, bool kFinish = false>
 __device__ inline void fold_groups(const SmallState& S, float* lds, float* slot, int rows_in_slot, int wv, int lane,
-                                   float c) {
+                                   float c, const FinishArgs* fa = nullptr, const Finish* f = nullptr, int early = 0) {
   constexpr int K = kWgWaves / R, kRegs = 64 / K;
   const int h = lane >> 5, j = lane & 31;
   state_to_lds(S, lds + wv * kStateFloats, lane);
@@ -1794,6 +2346,13 @@ __device__ inline void fold_groups(const SmallState& S, float* lds, float* slot,
 #pragma unroll
     for (int u = 0; u < kRegs / 4; ++u) x[u] += part[k][u] * sc;
   }
+  if (kFinish) {
+    __syncthreads();  // the next segment reuses the LDS
+    if (rt * 32 < f->rows)
+      finish_part<1, kRegs / 4>(*fa, *f, x, m_new, sum_across_halves(l_new), part_index * (kRegs / 4), rt, early,
+                                               wv, lane);
+    return;
+  }
   // accumulator register 16 jt + 4 r4 + i of lane (h, j) is row j, head dims 4 (8 jt + 2 r4 + h) + i
   const bool in_slot = rt * 32 < rows_in_slot;  // a 64-row slot has no room for row tiles 2 and 3 (they hold no rows)
 #pragma unroll
@@ -1816,9 +2375,10 @@ __device__ inline void fold_groups(const SmallState& S, float* lds, float* slot,
 // iteration), so that the stream, not the per-tile arithmetic of one wavefront, sets the pace.
 // Tiles are staged as in staged_segment (every wavefront fetches an eighth of every tile); the
 // iterations 8 / K - 1 ahead of the one being consumed are in flight.
-template <int R>
+template <int R, bool kFinish = false>
 __device__ inline void grouped_segment(const MainArgs& a, int b, int g, int base, int t0, int t1, const SeqInfo si,
-                                       float* slot, int rows_in_slot, int wv, int lane, bf16x8* lds) {
+                                       float* slot, int rows_in_slot, int wv, int lane, bf16x8* lds, bool tree = false,
+                                       const Finish* fin = nullptr) {
   constexpr int K = kWgWaves / R;
   constexpr int kAhead = kStages / K - 1;
   // (row tile = wv / K: when only the first row tiles hold rows, the busy wavefronts sit on different SIMDs)
@@ -1855,49 +2415,74 @@ __device__ inline void grouped_segment(const MainArgs& a, int b, int g, int base
   };
 
   __builtin_amdgcn_s_barrier();  // the previous segment is done with the LDS
+  if (!kFinish || t0 < t1) {
 #pragma unroll
-  for (int i = 0; i < kAhead * K; ++i)  // past the end: the last tile again (L2 hits), never consumed
-    request_tile(a, f, block_id(t0 + i, 0), block_id(t0 + i, 1), g, stage_of(t0 + i), wv, t0 + i > last || si.rg > 1);
-  int32_t nb[K][2];
-#pragma unroll
-  for (int x = 0; x < K; ++x) {
-    nb[x][0] = block_id(t0 + kAhead * K + x, 0);
-    nb[x][1] = block_id(t0 + kAhead * K + x, 1);
-  }
-  for (int tb = t0; tb < t1; tb += K) {
-#pragma unroll
-    for (int x = 0; x < K; ++x) asm volatile("" ::"s"(nb[x][0]), "s"(nb[x][1]));  // ids are in (no wait among LDS reads)
-    // this wavefront's share of the K tiles of this iteration has landed: what may still be
-    // outstanding are the kAhead - 1 iterations after it, 2 K fetches each
-    if (K == 4) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-#pragma unroll
-    for (int x = 0; x < K; ++x) land(tb + x);
-    // every share of this iteration's tiles is visible, and everyone is done with the previous iteration's
-    __builtin_amdgcn_s_barrier();
-#pragma unroll
-    for (int x = 0; x < K; ++x)
-      request_tile(a, f, nb[x][0], nb[x][1], g, stage_of(tb + kAhead * K + x), wv, tb + kAhead * K + x > last || si.rg > 1);
+    for (int i = 0; i < kAhead * K; ++i)  // past the end: the last tile again (L2 hits), never consumed
+      request_tile(a, f, block_id(t0 + i, 0), block_id(t0 + i, 1), g, stage_of(t0 + i), wv, t0 + i > last || si.rg > 1);
+    int32_t nb[K][2];
 #pragma unroll
     for (int x = 0; x < K; ++x) {
-      nb[x][0] = block_id(tb + (kAhead + 1) * K + x, 0);
-      nb[x][1] = block_id(tb + (kAhead + 1) * K + x, 1);
+      nb[x][0] = block_id(t0 + kAhead * K + x, 0);
+      nb[x][1] = block_id(t0 + kAhead * K + x, 1);
     }
-    const int t = tb + kg;
-    if (has_rows && t < t1) {
-      const uint32_t stage = rd + (t & (kStages - 1)) * (kStageVecs * 16);
-      plain_tile(S.o, S.m, S.l, q, stage, stage + 8 * kWave * 16, c, si.len - t * kTile, h);
+    for (int tb = t0; tb < t1; tb += K) {
+#pragma unroll
+      for (int x = 0; x < K; ++x) asm volatile("" ::"s"(nb[x][0]), "s"(nb[x][1]));  // ids are in (no wait among LDS reads)
+      // this wavefront's share of the K tiles of this iteration has landed: what may still be
+      // outstanding are the kAhead - 1 iterations after it, 2 K fetches each
+      if (K == 4) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+#pragma unroll
+      for (int x = 0; x < K; ++x) land(tb + x);
+      // every share of this iteration's tiles is visible, and everyone is done with the previous iteration's
+      __builtin_amdgcn_s_barrier();
+#pragma unroll
+      for (int x = 0; x < K; ++x)
+        request_tile(a, f, nb[x][0], nb[x][1], g, stage_of(tb + kAhead * K + x), wv, tb + kAhead * K + x > last || si.rg > 1);
+#pragma unroll
+      for (int x = 0; x < K; ++x) {
+        nb[x][0] = block_id(tb + (kAhead + 1) * K + x, 0);
+        nb[x][1] = block_id(tb + (kAhead + 1) * K + x, 1);
+      }
+      const int t = tb + kg;
+      if (has_rows && t < t1) {
+        const uint32_t stage = rd + (t & (kStages - 1)) * (kStageVecs * 16);
+        plain_tile(S.o, S.m, S.l, q, stage, stage + 8 * kWave * 16, c, si.len - t * kTile, h);
+      }
     }
+  }
+  FinishArgs fa;
+  int early = 0;
+  if (kFinish) {
+    fa = kernel_args().fin;
+    if (fin->pieces > 1) early = arrivals(counter_of<1>(fa, *fin, wv));
+  }
+  TreePair pair;
+  uint32_t word = 0u;
+  TreeRows t;
+  const int ln = fresh(lane);
+  if (kFinish && tree) {  // at most 64 nodes: two tiles of tree keys, one per key group
+    t = tree_rows(fa, base, g, si.n);
+    request_tree(pair, t, 0, wv, ln);
+    word = mask_word(fa, base, M, rt * 32 + (ln & 31), si.n, kg);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no fetch of this segment may land later
   __builtin_amdgcn_s_barrier();                      // and nobody still reads a stage: the fold reuses the LDS
-  fold_groups<R>(S, (float*)lds, slot, rows_in_slot, wv, lane, c);
+  if (kFinish && tree) {
+    const bool mend = stage_tree(pair, t, lds, (uint32_t*)(lds + kStages * kStageVecs), wv, ln);
+    if (has_rows) {
+      if (32 * kg < si.n) staged_tree_tile(S.o, S.m, S.l, q, word, lds, kg, c, ln);
+      if (mend && kg == 0) add_not_finite(S.o, fa, t, base, M, rt * 32 + (ln & 31), si.n, ln);
+    }
+    __syncthreads();
+  }
+  if (kFinish) fold_groups<R, true>(S, (float*)lds, nullptr, rows_in_slot, wv, lane, c, &fa, fin, early);
+  else fold_groups<R>(S, (float*)lds, slot, rows_in_slot, wv, lane, c);
 }
 
 // Worker of classes 1 and 2 (kCls): a workgroup walks the pieces of its share of the class's units.
-template <int kCls, bool kFp8 = false>
-__device__ inline void staged_worker(const MainArgs& a, int64_t w, ClassPlan& cp, bf16x8* lds /* 132 KB: kStages tiles, or eight states */) {
-  const PlanView pv = plan_view(a.plan, a.batch);
+template <int kCls, bool kFp8 = false, bool kFinish = false>
+__device__ inline void staged_worker(const MainArgs& a0, int64_t w, ClassPlan& cp, bf16x8* lds /* 132 KB: kStages tiles, or eight states */) {
   const int64_t U = cp.U, W = cp.W;
   PlanWindow& win = cp.win;
   if (w >= W || U <= 0) return;
@@ -1906,8 +2491,10 @@ __device__ inline void staged_worker(const MainArgs& a, int64_t w, ClassPlan& cp
   if (u0 >= u1) return;
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int b = locate(cp, pv, a.cu_nodes, kCls, a.batch, u0, lane);
-  while (u0 < u1 && b < a.batch) {
+  int b = locate(cp, plan_view(a0.plan, a0.batch), a0.cu_nodes, kCls, a0.batch, u0, lane);
+  while (u0 < u1 && b < a0.batch) {
+    const MainArgs a = kFinish ? kernel_args() : a0;
+    const PlanView pv = plan_view(a.plan, a.batch);
     follow(cp, pv, a.cu_nodes, kCls, a.batch, b, lane);
     const int64_t seq_begin = window_cum_units(win, b - win.first);
     const int64_t seq_end = window_cum_units(win, b + 1 - win.first);
@@ -1916,21 +2503,27 @@ __device__ inline void staged_worker(const MainArgs& a, int64_t w, ClassPlan& cp
     const int64_t local = u0 - seq_begin;
     const int base = __builtin_amdgcn_readlane(win.cu_nodes, b - win.first);
     if (kCls == 1) {
-      const int seg_local = (int)(local / si.tiles);
-      const int t0 = (int)(local % si.tiles);
+      const int units = segment_units<kFinish>(si, a.tree_cost);
+      const int seg_local = (int)(local / units);
+      const int t0 = (int)(local % units);
       const int g = seg_local;
       const int64_t left = u1 - u0;
-      const int nt = (int)(left < (int64_t)(si.tiles - t0) ? left : (int64_t)(si.tiles - t0));
+      const int nt = (int)(left < (int64_t)(units - t0) ? left : (int64_t)(units - t0));
       const int64_t seg = (int64_t)__builtin_amdgcn_readlane(win.cum_segs, b - win.first) + seg_local;
       // At most 64 rows: row tiles 0 and 1 of four, times two key groups.  (Two row tiles x four
       // key groups would keep every wavefront busy but leaves only one iteration of fetches in
       // flight; measured slower.)
+      if (kFinish) {
+        const Finish f = finish_of(u0 - t0, units, U, W, w, seg, base, g, si.n * a.G, 0);
+        grouped_segment<4, true>(a, b, g, base, min(t0, si.tiles), min(t0 + nt, si.tiles), si, nullptr, kMediumRows, wv, lane, lds,
+                                 t0 + nt == units, &f);
+      } else
       grouped_segment<4>(a, b, g, base, t0, t0 + nt, si, a.ws[1] + (size_t)(w + seg) * kMediumSlot, kMediumRows, wv,
                          lane, lds);
       u0 += nt;
     } else {
       // the unit space of class 2 is a cost: see large_spans and large_tile_at
-      const LargeSpans ls = large_spans(si, a.G);
+      const LargeSpans ls = large_spans<kFinish>(si, a.G, a.tree_cost);
       const int g = (int)(local / ls.span_head);
       const int64_t in_head = local - (int64_t)g * ls.span_head;
       int rgi = (int)(in_head / ls.span_full);
@@ -1943,8 +2536,20 @@ __device__ inline void staged_worker(const MainArgs& a, int64_t w, ClassPlan& cp
       const int64_t stop = u1 < seg_end ? u1 : seg_end;
       const int t0 = large_tile_at(off, cost, si.tiles);
       const int t1 = stop == seg_end ? si.tiles : large_tile_at(off + (stop - u0), cost, si.tiles);
+      const int64_t ub = u0 - off;
       u0 = stop;
       const int64_t seg = (int64_t)__builtin_amdgcn_readlane(win.cum_segs, b - win.first) + seg_local;
+      // rows of the group are dealt to the eight wavefronts in 32-row tiles
+      const int row0 = rgi * kLargeRows + wv * 32;
+      if (kFinish) {
+        const Finish f = finish_of(ub, span, U, W, w, seg, base, g, si.n * a.G, rgi * kLargeRows);
+        // (a share that covers less than a tile of the segment counts its empty state in)
+        if (row0 < f.rows)
+          staged_segment<true, kFp8, true>(a, b, g, base, row0, t0, t1, si, nullptr, wv, lane, lds, stop == seg_end, &f);
+        else
+          staged_segment<false, kFp8, true>(a, b, g, base, row0, t0, t1, si, nullptr, wv, lane, lds, stop == seg_end, &f);
+        continue;
+      }
       float* slot = a.ws[2] + (size_t)(w + seg) * kLargeSlot;
       if (t1 <= t0) {
         // The share covers less than a tile of this segment (rare).  The combine step
@@ -1954,8 +2559,6 @@ __device__ inline void staged_worker(const MainArgs& a, int64_t w, ClassPlan& cp
           slot[i] = i >= kLargeRows * kD && i < kLargeRows * kD + kLargeRows ? -INFINITY : 0.f;
         continue;
       }
-      // rows of the group are dealt to the eight wavefronts in 32-row tiles
-      const int row0 = rgi * kLargeRows + wv * 32;
       if (row0 < si.n * a.G) staged_segment<true, kFp8>(a, b, g, base, row0, t0, t1, si, slot, wv, lane, lds);
       else staged_segment<false, kFp8>(a, b, g, base, row0, t0, t1, si, slot, wv, lane, lds);
     }
@@ -1965,7 +2568,7 @@ __device__ inline void staged_worker(const MainArgs& a, int64_t w, ClassPlan& cp
 // ---- the prefix kernel: one launch, workgroups apportioned to the classes by the plan ------
 // kFp8: the cache holds E4M3 bytes; trees of up to 64 rows are class 1 and streamed into registers by
 // fp8_worker, larger ones are class 2 and go through the staged loop after conversion to bf16 in LDS.
-template <bool kFp8, bool kPair = false>
+template <bool kFp8, bool kPair, bool kFinish>
 __global__ __launch_bounds__(kWgWaves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tva_prefix_kernel(MainArgs a) {
   __shared__ float4 lds_raw[8448];  // 132 KB, carved up per class (class 0: eight states of 16.5 KB)
@@ -1977,14 +2580,19 @@ void tva_prefix_kernel(MainArgs a) {
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   ClassPlan cp;
   int64_t first1, first2, end;
+  if (kFinish && a.status && (wv > 0 || a.batch > kWave)) {  // the block-table check, while wavefront 0 plans
+    for (int64_t b = blockIdx.x + (int64_t)gridDim.x * (wv - (a.batch <= kWave ? 1 : 0)); b < a.batch;
+         b += (int64_t)gridDim.x * (a.batch <= kWave ? kWgWaves - 1 : kWgWaves))
+      smart::tva_validate_block_table((int)b, a.block_table, a.prefix_len, a.max_blocks, kBlock, a.num_blocks, a.status, lane);
+  }
   if (a.batch <= kWave) {
     // No planning kernel ran: wavefront 0 derives the plan and hands it to the others through
     // LDS; workgroup 0 also writes it to memory for the combine kernel.
     __shared__ PlanShare share;
     if (wv == 0) {
       LanePlan lp;
-      lane_plan<kFp8>(lp, a.prefix_len, a.cu_nodes, a.batch, a.total_nodes, a.G, a.Hkv, a.max_blocks, a.workgroups, a.caps,
-                      lane);
+      lane_plan<kFp8, kFinish>(lp, a.prefix_len, a.cu_nodes, a.batch, a.total_nodes, a.G, a.Hkv, a.max_blocks, a.workgroups, a.caps,
+                               a.tree_cost, lane);
 #pragma unroll
       for (int c = 0; c < kClasses; ++c) {
         share.cum_units[c][lane] = lp.cum_units[c];
@@ -2001,7 +2609,7 @@ void tva_prefix_kernel(MainArgs a) {
         }
         share.first_wg[kClasses] = lp.first_wg[kClasses];
       }
-      if (wg == 0) {
+      if (!kFinish && wg == 0) {
         const PlanView pv = plan_view(a.plan, a.batch);
         if (lane <= a.batch) {
 #pragma unroll
@@ -2067,17 +2675,17 @@ void tva_prefix_kernel(MainArgs a) {
     }
   };)
   if (kFp8) {
-    if (wg >= first1 && wg < first2) fp8_worker<kPair>(a, wg - first1, cp, (float*)lds_raw);
-    else if (wg >= first2) staged_worker<2, true>(a, wg - first2, cp, (bf16x8*)lds_raw);
+    if (wg >= first1 && wg < first2) fp8_worker<kPair, kFinish>(a, wg - first1, cp, (float*)lds_raw);
+    else if (wg >= first2) staged_worker<2, true, kFinish>(a, wg - first2, cp, (bf16x8*)lds_raw);
     SMART_TIMELINE(tl_end();)
     return;
   }
   if (wg < first1) {
-    small_worker(a, wg, cp, (float*)lds_raw);
+    small_worker<kFinish>(a, wg, cp, (float*)lds_raw);
   } else if (wg < first2) {
-    staged_worker<1>(a, wg - first1, cp, (bf16x8*)lds_raw);
+    staged_worker<1, false, kFinish>(a, wg - first1, cp, (bf16x8*)lds_raw);
   } else {
-    staged_worker<2>(a, wg - first2, cp, (bf16x8*)lds_raw);
+    staged_worker<2, false, kFinish>(a, wg - first2, cp, (bf16x8*)lds_raw);
   }
   SMART_TIMELINE(tl_end();)
 }
@@ -2266,7 +2874,7 @@ __global__ __launch_bounds__(kWave) void tva_combine_kernel(CombineArgs a) {
     const int rgi = rho / rows_per_group;
     const int seg_local = g * si.rg + rgi;
     const int64_t seg = seg_base + seg_local;
-    const LargeSpans ls = large_spans(si, a.G);
+    const LargeSpans ls = large_spans<false>(si, a.G, TreeCost{0, 0});
     const bool last_group = rgi == si.rg - 1;
     const int64_t span = cls < 2 ? si.tiles : (last_group ? ls.span_last : ls.span_full);
     const int64_t ub = unit_base + (cls < 2 ? (int64_t)seg_local * si.tiles : g * ls.span_head + rgi * ls.span_full);
@@ -2367,14 +2975,29 @@ static size_t class_slots(const smart_ctx* ctx, int cls, int64_t segs) {
   return (size_t)class_workers(ctx, cls) + (size_t)segs + 1;
 }
 
+// Partial-result slots and arrival counters of a call with these segments.
+struct Slots {
+  size_t count[kClasses], floats, counters;
+};
+static Slots slots_for(const smart_ctx* ctx, const int64_t (&segs)[kClasses], bool finish) {
+  Slots s;
+  s.floats = s.counters = 0;
+  for (int c = 0; c < kClasses; ++c) {
+    s.count[c] = class_slots(ctx, c, segs[c]);
+    s.floats += s.count[c] * (finish ? finish_slot(c) : class_slot(c));
+    s.counters += (size_t)segs[c] * kWgWaves;
+  }
+  return s;
+}
+
 void tva_mfma_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes, int32_t num_q_heads,
-                        int32_t num_kv_heads, size_t* ws_bytes, size_t* plan_bytes) {
+                        int32_t num_kv_heads, size_t* ws_bytes, size_t* plan_bytes, size_t* counters) {
   int64_t segs[kClasses];
   segment_bounds(batch, total_nodes, num_q_heads, num_kv_heads, segs);
-  size_t floats = 0;
-  for (int c = 0; c < kClasses; ++c) floats += class_slots(ctx, c, segs[c]) * class_slot(c);
-  *ws_bytes = floats * sizeof(float);
+  const Slots s = slots_for(ctx, segs, true);  // (the larger of the two forms)
+  *ws_bytes = s.floats * sizeof(float);
   *plan_bytes = plan_bytes_for(batch);
+  *counters = s.counters;
 }
 
 bool tva_mfma_supported(const tva_params& p) {
@@ -2383,6 +3006,48 @@ bool tva_mfma_supported(const tva_params& p) {
          p.block_size == kBlock && p.cache_block_stride % 8 == 0 && p.cache_head_stride % 8 == 0 &&
          aligned16(p.d_q) && aligned16(p.d_k_cache) && aligned16(p.d_v_cache) &&
          aligned16(p.d_k_tree) && aligned16(p.d_v_tree) && aligned16(p.d_out) && p.num_blocks > 0;
+}
+
+// Tiles of the longest prefix that the block table has room for.
+static int64_t longest_prefix(const tva_params& p) {
+  return ((int64_t)p.max_blocks_per_seq * kBlock + kTile - 1) / kTile;
+}
+
+// fp8 cache: the host knows the trees' mean size and what the block table can hold.  A batch of trees of one row tile has
+// a mean of at most 32 rows, and a table that holds fewer than kPairTiles tiles a sequence, or too few in all for such
+// shares, has no long pieces: those run the kernel that has no pairs.  With a larger mean and longer tables trees of two
+// row tiles are the usual ones and gain most (64 sequences of 16384 tokens, 4 .. 10 nodes of 8 rows, 712 -> 503 us); the
+// rest is decided by each worker (fp8_worker).
+static bool pairs(const tva_params& p, int32_t workgroups) {
+  const int64_t G = p.num_q_heads / p.num_kv_heads, longest = longest_prefix(p);
+  return p.total_nodes * G > (int64_t)kSmallRows * p.batch && longest >= kPairTiles &&
+         longest * p.batch * p.num_kv_heads >= (int64_t)kPairTiles * workgroups;
+}
+
+// Whether the prefix kernel finishes the rows itself.  The last of a segment's pieces is merged by one workgroup, about
+// 0.85 us for each other piece of 256 rows; the combine kernel spreads that over the chip and costs a launch.  So it is left
+// to the combine kernel where few segments may be long: one sequence, 8 kv heads, 60 nodes: 1000 tokens 34.5 us (combine
+// 34.2), 2000 45.4 (39.0), 16384 80 (58); 16 segments of 4000 tokens 49.9 (44.8); but 32 segments of 2048 33.5 (38.5), of
+// 16384 102.8 (106.9).  And pairs of row tiles from an fp8 cache have no registers left for it: 64 sequences of 3600 tokens,
+// 9 .. 16 nodes 138 .. 153 us (128); by halves, and finished, they win only while prefixes are shorter: 64 sequences of 2400
+// tokens 80 us (107), 32 of 4000 76 (74).
+constexpr int kFewTiles = 32, kFewPieces = 8, kLongPairTiles = 120;
+static bool finishes(const tva_params& p, int32_t workgroups, bool pairs_pay) {
+  const int64_t longest = longest_prefix(p);
+  if (pairs_pay && longest >= kLongPairTiles) return false;
+  return longest <= kFewTiles || (int64_t)p.batch * p.num_kv_heads * kFewPieces >= workgroups;
+}
+
+// With many segments a worker holds several, and each costs a start, a fold and a tree part beside its tiles; where every
+// worker has a part of one segment, all have a start and an end, and only the tree part sets the last one apart.  (The lengths
+// are not known here; the line is at a third of a segment per workgroup.)  Calls with ragged prefixes, no cost / these: 96
+// sequences of 100 .. 2000 tokens, 4 .. 7 nodes 108 / 89 us, 24 .. 48 nodes 184 / 145; 64 of 100 .. 4096, 1 .. 64 nodes
+// 186 / 163.  4 sequences of 2048, 4 .. 7 nodes (4, 60) 18.7, (12, 160) 21.2 us; 24 of 500, 40 nodes 33.7 and 32.2.  From an
+// fp8 cache a unit of class 1 is less than half as long.
+static TreeCost tree_cost(const tva_params& p, int32_t workgroups) {
+  const bool fp8 = p.kv_cache_dtype == SMART_FP8_E4M3;
+  if ((int64_t)p.batch * p.num_kv_heads * 3 < workgroups) return fp8 ? TreeCost{8, 60} : TreeCost{4, 60};
+  return fp8 ? TreeCost{40, 160} : TreeCost{12, 160};
 }
 
 int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p, const TvaWorkspace* fixed) {
@@ -2399,37 +3064,46 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   } else if (!segment_counts(p.h_cu_nodes, p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads, fp8, caps.segs)) {
     return SMART_EINVAL;
   }
-  size_t slots[kClasses], floats = 0;
-  for (int c = 0; c < kClasses; ++c) {
-    slots[c] = class_slots(ctx, c, caps.segs[c]);
-    floats += slots[c] * class_slot(c);
-  }
-  const size_t ws_bytes = floats * sizeof(float), plan_bytes = plan_bytes_for(p.batch);
   void* ws_base;
   void* plan_base;
+  int32_t* arrive = nullptr;
+  const bool pairs_pay = fp8 && pairs(p, workgroups);
+  bool finish = finishes(p, workgroups, pairs_pay);
+  const TreeCost tc = tree_cost(p, workgroups);
+  Slots slots = slots_for(ctx, caps.segs, finish);
+  const size_t plan_bytes = plan_bytes_for(p.batch);
   if (fixed) {
-    if (ws_bytes > fixed->ws_bytes || plan_bytes > fixed->plan_bytes) return SMART_ECAP;
+    if (finish && slots.floats * sizeof(float) + slots.counters * sizeof(int32_t) > fixed->ws_bytes) {
+      finish = false;  // (it needs the larger slots, and counters)
+      slots = slots_for(ctx, caps.segs, false);
+    }
+    if (slots.floats * sizeof(float) > fixed->ws_bytes || plan_bytes > fixed->plan_bytes) return SMART_ECAP;
     ws_base = fixed->ws;
     plan_base = fixed->plan;
+    if (finish) {  // (nothing in this buffer is known to hold zeros)
+      arrive = (int32_t*)((float*)fixed->ws + slots.floats);
+      int32_t rc = zero_counters(stream, arrive, slots.counters);
+      if (rc != SMART_OK) return rc;
+    }
   } else {
-    int32_t rc = ensure_workspace(ctx, stream, ws_bytes, plan_bytes);
+    size_t ws_most, plan_most, counters;
+    tva_mfma_workspace(ctx, p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads, &ws_most, &plan_most, &counters);
+    int32_t rc = ensure_workspace(ctx, stream, ws_most, plan_most, counters);
     if (rc != SMART_OK) return rc;
     ws_base = ctx->ws;
     plan_base = ctx->plan;
+    arrive = ctx->arrive;
   }
   float* ws[kClasses];
   ws[0] = (float*)ws_base;
-  for (int c = 1; c < kClasses; ++c) ws[c] = ws[c - 1] + slots[c - 1] * class_slot(c - 1);
+  for (int c = 1; c < kClasses; ++c)
+    ws[c] = ws[c - 1] + slots.count[c - 1] * (finish ? finish_slot(c - 1) : class_slot(c - 1));
 
   if (p.batch > kWave) {  // smaller batches: the prefix kernel derives the plan itself
-    if (fp8)
-      hipLaunchKernelGGL(tva_plan_kernel<true>, dim3(1), dim3(kWave), 0, stream, plan_base, p.batch,
-                         p.total_nodes, G, p.num_kv_heads, p.max_blocks_per_seq, workgroups, caps, p.d_prefix_len,
-                         p.d_cu_nodes);
-    else
-      hipLaunchKernelGGL(tva_plan_kernel<false>, dim3(1), dim3(kWave), 0, stream, plan_base, p.batch,
-                         p.total_nodes, G, p.num_kv_heads, p.max_blocks_per_seq, workgroups, caps, p.d_prefix_len,
-                         p.d_cu_nodes);
+    auto plan = fp8 ? (finish ? tva_plan_kernel<true, true> : tva_plan_kernel<true, false>)
+                    : (finish ? tva_plan_kernel<false, true> : tva_plan_kernel<false, false>);
+    hipLaunchKernelGGL(plan, dim3(1), dim3(kWave), 0, stream, plan_base, p.batch, p.total_nodes, G, p.num_kv_heads,
+                       p.max_blocks_per_seq, workgroups, caps, tc, p.d_prefix_len, p.d_cu_nodes);
     SMART_HIP_CHECK(hipGetLastError());
   }
 
@@ -2444,6 +3118,7 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   ma.workgroups = workgroups;
   ma.plan = plan_base;
   ma.caps = caps;
+  ma.tree_cost = tc;
   for (int c = 0; c < kClasses; ++c) ma.ws[c] = ws[c];
   ma.block_stride = p.cache_block_stride;
   ma.head_stride = p.cache_head_stride;
@@ -2456,28 +3131,38 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   ma.scale_log2e = p.softmax_scale * kLog2e * (fp8 ? p.k_scale : 1.f);
   ma.m_scale = fp8 ? p.k_scale : 1.f;
   ma.o_scale = fp8 ? p.v_scale : 1.f;
+  ma.status = p.d_status;
+  ma.fin.q = ma.q;
+  ma.fin.k_tree = (const __bf16*)p.d_k_tree;
+  ma.fin.v_tree = (const __bf16*)p.d_v_tree;
+  ma.fin.anc_mask = (const uint32_t*)p.d_anc_mask;
+  ma.fin.out = (__bf16*)p.d_out;
+  ma.fin.lse = p.d_lse;
+  ma.fin.arrive = arrive;
+  for (int c = 0, first = 0; c < kClasses; first += (int)caps.segs[c++]) {
+    ma.fin.ws[c] = ws[c];
+    ma.fin.arrive_first[c] = first;
+  }
+  ma.fin.Hq = p.num_q_heads;
+  ma.fin.Hkv = p.num_kv_heads;
+  ma.fin.G = G;
+  ma.fin.scale = p.softmax_scale;
+  ma.fin.scale_log2e = p.softmax_scale * kLog2e;
   // (every class with work needs a workgroup, however few were asked for)
   const dim3 grid(workgroups > kClasses ? workgroups : kClasses);
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
   // (no events: an ordinary launch; else the events ride on the dispatch and hold the kernel's own start and end)
   const bool recorded = profile_events(ctx, &ev_start, &ev_stop);
-  // fp8 cache: the host knows the trees' mean size and what the block table can hold.  A batch of trees of one row tile has
-  // a mean of at most 32 rows, and a table that holds fewer than kPairTiles tiles a sequence, or too few in all for such
-  // shares, has no long pieces: those run the kernel that has no pairs.  With a larger mean and longer tables trees of two
-  // row tiles are the usual ones and gain most (64 sequences of 16384 tokens, 4 .. 10 nodes of 8 rows, 712 -> 503 us); the
-  // rest is decided by each worker (fp8_worker).
-  const int64_t longest = ((int64_t)p.max_blocks_per_seq * kBlock + kTile - 1) / kTile;  // tiles
-  const bool pair = fp8 && (int64_t)p.total_nodes * G > (int64_t)kSmallRows * p.batch && longest >= kPairTiles &&
-                    longest * p.batch * p.num_kv_heads >= (int64_t)kPairTiles * workgroups;
   auto launch = [&](void (*kernel)(MainArgs)) {
     if (recorded) hipExtLaunchKernelGGL(kernel, grid, dim3(kWgWaves * kWave), 0, stream, ev_start, ev_stop, 0, ma);
     else hipLaunchKernelGGL(kernel, grid, dim3(kWgWaves * kWave), 0, stream, ma);
   };
-  if (pair) launch(tva_prefix_kernel<true, true>);
-  else if (fp8) launch(tva_prefix_kernel<true>);
-  else launch(tva_prefix_kernel<false>);
+  if (pairs_pay && !finish) launch(tva_prefix_kernel<true, true, false>);
+  else if (fp8) launch(finish ? tva_prefix_kernel<true, false, true> : tva_prefix_kernel<true, false, false>);
+  else launch(finish ? tva_prefix_kernel<false, false, true> : tva_prefix_kernel<false, false, false>);
   SMART_HIP_CHECK(hipGetLastError());
   if (recorded) profile_launched(ctx);
+  if (finish) return SMART_OK;
 
   CombineArgs ca;
   ca.q = (const uint16_t*)p.d_q;

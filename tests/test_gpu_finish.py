@@ -1,0 +1,87 @@
+"""The one-launch form of the interleaved kernels (bf16, head dim 128, block size 16; bf16 and fp8 caches), which evaluates
+the tree part on the matrix cores and merges a segment's pieces where the last of them ends, and the two-launch form, taken
+where few sequences have room for long prefixes: both against the general kernel, which holds probabilities in binary32.
+
+Tolerance, element by element, as for one and two row tiles of the fp8 cache (test_gpu_fp8_row_tiles): every probability,
+those of the tree's own keys included, is rounded to bf16 (u = 2^-8), which moves an output by at most u times the weighted
+mean of |V|, and both sides round the output once."""
+import numpy as np
+import pytest
+
+from paper_2604_09731_amd import binding as B
+from tests.test_gpu_tiled_attention import Inputs
+
+pytestmark = pytest.mark.gpu
+
+WIDE = 1000          # spare columns of the block table: room for 16000 tokens
+#        tree sizes (edges of the classes and of the 32-key tiles), prefixes (edges of the 32-key tiles, none), heads
+SHAPES = [([1, 8, 9, 16, 17, 64, 65, 128], [0, 1, 31, 32, 33, 517, 1000, 95], 8, 2),
+          ([1, 31, 32, 33, 64, 65, 128], [500, 0, 64, 700, 2, 33, 0], 2, 2),
+          ([4, 5, 9, 10, 36, 37, 74], [900, 33, 95, 0, 700, 1, 300], 14, 2)]
+
+
+def bound_of(x, lib, ref):
+    v, v_tree = x.v, x.v_tree
+    x.v, x.v_tree = (v & 0x7F) if x.kw else v.abs(), v_tree.abs()
+    spread = x.run(lib, general=True)[0].double()
+    x.v, x.v_tree = v, v_tree
+    u = 2.0 ** -8
+    return (u * (1 + u) + 2.0 ** -16) * spread + 2 * u * (1 + u) * ref.double().abs()
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("shape", range(len(SHAPES)))
+@pytest.mark.parametrize("workers", [0, 1, 3, 40, 300])
+def test_both_forms_equal_the_general_kernel(shape, workers, fp8):
+    """Segments of one worker, of two and of up to 30; shares that end in a prefix, between it and its tree part, and
+    inside a tile; the plan made by the workgroups (few sequences) and by a kernel of its own (more than 64)."""
+    import torch
+    sizes, lens, Hq, Hkv = SHAPES[shape]
+    lib = B.SmartTree(0)
+    for times, spare in ((1, 1), (1, WIDE), (10, 1)):
+        x = Inputs(sizes * times, lens * times, Hq, Hkv, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, fp8, seed=shape + workers,
+                   spare_columns=spare)
+        ref, ref_lse = x.run(lib, general=True)
+        bound = bound_of(x, lib, ref)
+        lib.set_option(B.SMART_OPT_TVA_WORKERS, workers)
+        for static in (False, True):
+            status = torch.full((len(sizes) * times,), -3, dtype=torch.int32, device="cuda")
+            out, lse = x.run(lib, static=static, status=status)
+            assert bool(((out.double() - ref.double()).abs() <= bound).all())      # (false for NaN)
+            assert float((lse - ref_lse).abs().max()) <= 1e-3
+            assert not status.any()
+            for _ in range(3):           # pieces are merged in a fixed order, whoever comes last: the same bits every time
+                again, again_lse = x.run(lib, static=static)
+                assert torch.equal(again, out) and torch.equal(again_lse, lse)
+        lib.set_option(B.SMART_OPT_TVA_WORKERS, 0)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("size,Hq,Hkv", [(8, 8, 2), (16, 8, 2), (50, 4, 4), (64, 8, 2), (128, 8, 2)])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_what_one_node_holds_reaches_only_its_descendants(bad, size, Hq, Hkv, fp8):
+    """A value, and the key, of one node: rows that do not see it keep their bits; rows that do are what the general kernel
+    makes of them (row groups of every class, both tiles of tree keys and the four of the largest tree)."""
+    import torch
+    lib = B.SmartTree(0)
+    x = Inputs([size, 3], [200, 40], Hq, Hkv, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, fp8, seed=size)
+    _, _, _, mask, _ = lib.tree_pack(x.cu, x.parent, x.len)
+    words = mask.cpu().numpy().view(np.uint64).reshape(-1, 2)
+    clean, _ = x.run(lib)
+    for node in (size // 3, size - 1):
+        sees = torch.from_numpy((words[:size, node // 64] >> np.uint64(node % 64)) & np.uint64(1) == 1).cuda()
+        v = x.v_tree.clone()
+        x.v_tree[node, :, 5], x.v_tree[node, :, 77] = bad, -bad
+        out, _ = x.run(lib)
+        ref, _ = x.run(lib, general=True)
+        assert torch.equal(out[:size][~sees], clean[:size][~sees]) and torch.equal(out[size:], clean[size:])
+        got, want = out[:size][sees], ref[:size][sees]
+        assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(got[torch.isinf(got)], want[torch.isinf(want)])
+        others = [d for d in range(128) if d not in (5, 77)]
+        assert torch.equal(got[..., others], clean[:size][sees][..., others])
+        x.v_tree = v
+        k = x.k_tree.clone()
+        x.k_tree[node, :, 9] = bad
+        out, _ = x.run(lib)
+        assert torch.equal(out[:size][~sees], clean[:size][~sees]) and torch.equal(out[size:], clean[size:])
+        x.k_tree = k
