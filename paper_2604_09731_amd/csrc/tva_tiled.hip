@@ -38,7 +38,7 @@
 // Measured against the general kernel (whole call): bf16 plain pages, batch 16, 32 / 8 heads of 128, prefixes of
 // 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 102 us (prefix kernel 91, of which 62 are the MFMAs of its fullest
 // workgroups; finishing kernel 18); fp32 plain pages, batch 8, 8 / 2 heads of 64, prefixes of 128 .. 1536, 15-node trees
-// 778 -> 24 us, and its error against binary64 falls from 5.6e-7 to 3.1e-7 (shorter sums).
+// 778 -> 19 us, and its error against binary64 falls from 5.6e-7 to 3.1e-7 (shorter sums).
 //
 // The paper (Sec. 1) has the target model verify the tree in one forward pass; this is the attention sub-step.
 #include <math.h>
@@ -62,7 +62,6 @@ typedef __attribute__((ext_vector_type(2))) float floatx2;
 constexpr int kWave = 64;
 constexpr int kWaves = 8;
 constexpr int kThreads = kWave * kWaves;
-constexpr int kFinishWaves = 4;
 constexpr int kRowTile = 32;
 constexpr int kGroupRows = 128;      // rows of a row group: four row tiles
 constexpr int kTilesPerStep = 4;
@@ -642,14 +641,17 @@ struct Finish {
   floatx4 acc[K4];
   float m = -INFINITY, l = 0.f;
 
+  __device__ void clear() {
+#pragma unroll
+    for (int k = 0; k < K4; ++k) acc[k] = (floatx4)(0.f);
+  }
   __device__ void request(const TiledArgs& a, int node, int head, bool active, int e) {
     mlo = active ? a.anc_mask[2 * (size_t)node] : 0ull;
     mhi = active ? a.anc_mask[2 * (size_t)node + 1] : 0ull;
     const T* qp = (const T*)a.q + ((int64_t)node * a.Hq + head) * D;
 #pragma unroll
     for (int k = 0; k < K4; ++k) q[k] = active ? *(const Raw*)(qp + 4 * (e + 8 * k)) : Raw();
-#pragma unroll
-    for (int k = 0; k < K4; ++k) acc[k] = (floatx4)(0.f);
+    clear();
   }
 
   struct Keys {
@@ -1080,23 +1082,34 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
 }
 
 // ---- split form: merging the partials, with the tree part ----------------------------------------------------------
-// One wavefront per eight (node, head) rows.
-template <typename T, int D>
-__global__ __launch_bounds__(kFinishWaves * kWave, 2) void tva_tiled_finish_kernel(TiledArgs a) {
+// A row is two chains of memory round trips, the tree part (mask, keys two at a time) and the partials (plan, then two at a
+// time).  kParts > 0: a workgroup per eight (node, head) rows, one wavefront for the tree part and kParts that share the
+// partials, merged by the first in a fixed order; for launches that leave wavefront slots idle (see finish_parts).
+// kParts = 0: a wavefront per eight rows goes through both.
+constexpr int finish_waves(int parts) { return parts > 0 ? 1 + parts : 4; }
+template <typename T, int D, int kParts>
+__global__ __launch_bounds__(finish_waves(kParts) * kWave, kParts == 0 ? 2 : 1) void tva_tiled_finish_kernel(TiledArgs a) {
+  constexpr int kRows = kWave / kCombineLanes, K4 = D / 32;
+  constexpr int kStates = kParts > 0 ? kParts : 1;
+  __shared__ floatx4 s_acc[kStates][K4][kWave];
+  __shared__ float s_m[kStates][kRows], s_l[kStates][kRows];
   const int lane = threadIdx.x & (kWave - 1), e = lane & (kCombineLanes - 1);
-  const int64_t wave = (int64_t)blockIdx.x * kFinishWaves + (threadIdx.x >> 6);
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int part = kParts > 0 ? wv - 1 : -1;  // -1: the tree part
+  const int64_t wave = (int64_t)blockIdx.x * finish_waves(kParts) + wv;
   if (a.status)
-    for (int64_t b = wave; b < a.batch; b += (int64_t)gridDim.x * kFinishWaves)
+    for (int64_t b = wave; b < a.batch; b += (int64_t)gridDim.x * finish_waves(kParts))
       smart::tva_validate_block_table((int)b, a.block_table, a.prefix_len, a.max_blocks, a.block_size, a.num_blocks,
                                       a.status, lane);
-  const int64_t n_rows = (int64_t)a.total_nodes * a.Hq;
-  const int64_t row_raw = wave * (kWave / kCombineLanes) + lane / kCombineLanes;
-  if (wave * (kWave / kCombineLanes) >= n_rows) return;
+  const int64_t n_rows = (int64_t)a.total_nodes * a.Hq, first = (kParts > 0 ? (int64_t)blockIdx.x : wave) * kRows;
+  if (first >= n_rows) return;
+  const int64_t row_raw = first + lane / kCombineLanes;
   const bool there = row_raw < n_rows;
   const int64_t row = there ? row_raw : n_rows - 1;
   const int node = (int)(row / a.Hq), head = (int)(row % a.Hq), g = head / a.G;
   Finish<T, D> f;
-  f.request(a, node, head, there, e);
+  if (part < 0) f.request(a, node, head, there, e);
+  else f.clear();
   const int64_t U = a.plan[0], W = a.plan[1];
   int b;
   if (a.batch <= kWave) {
@@ -1113,10 +1126,10 @@ __global__ __launch_bounds__(kFinishWaves * kWave, 2) void tva_tiled_finish_kern
   }
   if (U < 0) b = owner_of(a, node);  // offsets that are not ascending
   const Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
-  const int64_t units_before = a.plan[2 + b], segs_before = a.plan[2 + a.batch + b];
   const bool owned = there && node >= sh.base && (int64_t)node - sh.base < sh.n;
-  f.tree(a, g, sh.base, owned ? sh.n : 0, e);
-  if (owned && sh.steps > 0 && U > 0) {
+  if (part < 0) f.tree(a, g, sh.base, owned ? sh.n : 0, e);
+  if ((kParts == 0 || part >= 0) && owned && sh.steps > 0 && U > 0) {
+    const int64_t units_before = a.plan[2 + b], segs_before = a.plan[2 + a.batch + b];
     const int rho = (node - sh.base) * a.G + head % a.G;
     const int group = rho / kGroupRows, r = rho % kGroupRows, local = g * sh.groups + group;
     const int64_t ub = units_before + g * sh.head + group * sh.full;
@@ -1126,12 +1139,33 @@ __global__ __launch_bounds__(kFinishWaves * kWave, 2) void tva_tiled_finish_kern
       const float* slot = a.ws + (w + segs_before + local) * slot_floats(D);
       return f.fetch(slot[kGroupRows * D + r], slot[kGroupRows * D + kGroupRows + r], slot + r * 4, kGroupRows * 4, e);
     };
-    for (int64_t w = w_first; w <= w_last; w += 2) {
+    for (int64_t w = w_first + (kParts > 0 ? part : 0); w <= w_last; w += 2 * kStates) {
       const auto p0 = partial(w);
-      auto p1 = partial(min(w + 1, w_last));  // (no branch around it, so that both are requested before the first is used)
-      if (w == w_last) p1.m = -INFINITY;
+      auto p1 = partial(min(w + kStates, w_last));  // (no branch around it: both are requested before the first is used)
+      if (w + kStates > w_last) p1.m = -INFINITY;
       f.merge(p0, a.c);
       f.merge(p1, a.c);
+    }
+  }
+  if (kParts > 0) {
+    if (part >= 0) {
+#pragma unroll
+      for (int k = 0; k < K4; ++k) s_acc[part][k][lane] = f.acc[k];
+      if (e == 0) {
+        s_m[part][lane / kCombineLanes] = f.m;
+        s_l[part][lane / kCombineLanes] = f.l;
+      }
+    }
+    __syncthreads();
+    if (part >= 0) return;
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) {
+      typename Finish<T, D>::Partial x;
+      x.m = s_m[p][lane / kCombineLanes];
+      x.l = s_l[p][lane / kCombineLanes];
+#pragma unroll
+      for (int k = 0; k < K4; ++k) x.o[k] = s_acc[p][k][lane];
+      f.merge(x, a.c);
     }
   }
   if (owned) f.write(a, node, head, e);
@@ -1180,6 +1214,20 @@ bool tva_tiled_supported(const tva_params& p) {
          aligned(p.d_k_tree, 16) && aligned(p.d_v_tree, 16) && aligned(p.d_out, 16);
 }
 
+// `rows8`: groups of eight rows.  Whole calls, one wavefront for both chains / a second for the partials / seven for them:
+// 28 groups, one sequence of 4000 tokens, plain bf16 36.1 / 26.4 / 22.7 us; 120 groups, the fp32 workload above (up to 24
+// partials a row) 23.1 / 20.8 / 19.0; 480 groups, 4 sequences of 1000 33.7 / 30.4 / 36.2; 832 44.0 / 42.5 / 51.7; 1500, 16
+// sequences of 60 .. 128 nodes, 31.9 / 34.6 / 42.7; 2016 42.2 / 47.7 / 70.6; the bf16 workload above (2176) 95.2 / 97.1 / 117.6.
+static int finish_parts(int64_t rows8) { return rows8 <= 128 ? 7 : (rows8 <= 1024 ? 1 : 0); }
+template <typename T, int D>
+static void launch_finish(const TiledArgs& a, int64_t rows8, hipStream_t stream) {
+  const int parts = finish_parts(rows8), waves = finish_waves(parts);
+  const dim3 grid((unsigned)(parts > 0 ? rows8 : (rows8 + waves - 1) / waves)), block(waves * kWave);
+  if (parts == 7) hipLaunchKernelGGL((tva_tiled_finish_kernel<T, D, 7>), grid, block, 0, stream, a);
+  else if (parts == 1) hipLaunchKernelGGL((tva_tiled_finish_kernel<T, D, 1>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((tva_tiled_finish_kernel<T, D, 0>), grid, block, 0, stream, a);
+}
+
 template <typename T, bool kFp8, bool kPlain, int D>
 static hipError_t launch_tiled(const TiledArgs& a, bool direct, unsigned grid, hipStream_t stream) {
   if (direct)
@@ -1193,7 +1241,7 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   const int G = p.num_q_heads / p.num_kv_heads;
   const bool fp8 = p.kv_cache_dtype == SMART_FP8_E4M3, f32 = p.dtype == SMART_F32;
   const int64_t segs = tiled_segments(p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads);
-  const int64_t finish_waves = ((int64_t)p.total_nodes * p.num_q_heads + kWave / kCombineLanes - 1) / (kWave / kCombineLanes);
+  const int64_t rows8 = ((int64_t)p.total_nodes * p.num_q_heads + kWave / kCombineLanes - 1) / (kWave / kCombineLanes);
   if (segs > 0x7FFFFFFF) return SMART_EINVAL;
   // The workspace-free form: for callers that cannot allocate, for launches that are being captured (a graph must not
   // hold a workspace that a later, larger call replaces), and when no memory is left.  It is also the faster one, by the
@@ -1281,13 +1329,12 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   SMART_HIP_CHECK(err);
   rc = profile_end(ctx, stream);
   if (rc != SMART_OK || direct) return rc;
-  const dim3 fgrid((unsigned)((finish_waves + kFinishWaves - 1) / kFinishWaves));
   if (f32) {
-    if (p.head_dim == 128) hipLaunchKernelGGL((tva_tiled_finish_kernel<float, 128>), fgrid, dim3(kFinishWaves * kWave), 0, stream, a);
-    else hipLaunchKernelGGL((tva_tiled_finish_kernel<float, 64>), fgrid, dim3(kFinishWaves * kWave), 0, stream, a);
+    if (p.head_dim == 128) launch_finish<float, 128>(a, rows8, stream);
+    else launch_finish<float, 64>(a, rows8, stream);
   } else {
-    if (p.head_dim == 128) hipLaunchKernelGGL((tva_tiled_finish_kernel<__bf16, 128>), fgrid, dim3(kFinishWaves * kWave), 0, stream, a);
-    else hipLaunchKernelGGL((tva_tiled_finish_kernel<__bf16, 64>), fgrid, dim3(kFinishWaves * kWave), 0, stream, a);
+    if (p.head_dim == 128) launch_finish<__bf16, 128>(a, rows8, stream);
+    else launch_finish<__bf16, 64>(a, rows8, stream);
   }
   SMART_HIP_CHECK(hipGetLastError());
   return SMART_OK;
