@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libsmart_tree.so (argument marshalling only).
+"""Thin binding of libsmart_tree.so (argument marshalling only): ctypes, and native code (csrc/marshal.cpp) for the device
+entry points that a small call spends more host than device time in.
 
 Every step runs in the library's kernels (or, for selection, its host C++).
 PyTorch supplies device memory and streams.  There is no fallback: if the
@@ -374,11 +375,35 @@ def _torch():
     return torch
 
 
-# Marshalling is most of a small call's host time (a step of a few users waits for the host, not for the GPU): addresses
-# go to ctypes as plain integers (its argument types convert them; an object per address costs 0.2 us more), and
-# int32 outputs of one length are rows of one allocation, each where an allocation of its own would begin (the device
+# Marshalling is most of a small call's host time (a step of a few users waits for the host, not for the GPU), so the entry
+# points that are called per step or layer go through _marshal: outputs, addresses and the call in native code.  int32
+# outputs of one length are rows of one allocation, each where an allocation of its own would begin (the device
 # allocator hands out multiples of 512 bytes).  Whoever keeps one of them keeps the memory of all: clone() it instead.
 _ROW = 128      # int32 elements
+
+
+_NATIVE_ENTRIES = ("smart_select_begin_device", "smart_select_layer_device", "tree_compact_pack", "tree_upload_pack",
+                   "tree_rope", "kv_cache_write", "kv_cache_write_fp8", "tree_verify_attention",
+                   "tree_verify_attention_static", "tree_accept", "tree_accept_sample", "tree_commit", "tree_commit_fp8")
+_nativeh = None
+
+
+def _native():
+    global _nativeh
+    if _nativeh is None:
+        torch = _torch()            # (the module links against it)
+        path = os.path.join(_HERE, "_marshal.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: build it with `python -m paper_2604_09731_amd.build`")
+        from . import _marshal
+        lib = _lib()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            raw = lambda device: torch.cuda.current_stream(device).cuda_stream
+        _marshal.setup(tuple(ctypes.cast(getattr(lib, f), ctypes.c_void_p).value for f in _NATIVE_ENTRIES), _check,
+                       torch.cuda.current_device, raw)
+        _nativeh = _marshal
+    return _nativeh
 
 
 def _stream_ptr():
@@ -433,6 +458,7 @@ class SmartTree:
         h = ctypes.c_void_p()
         _check(_lib().smart_create(ctypes.byref(h), self.device), "smart_create")
         self._h = h
+        self._native = _native()
 
     def close(self):
         if getattr(self, "_h", None):
@@ -444,6 +470,10 @@ class SmartTree:
             self.close()
         except Exception:
             pass
+
+    @property
+    def _ctx(self):
+        return self._h.value if self._h else 0
 
     def set_option(self, key: int, value: int):
         _check(_lib().smart_set_option(self._h, key, int(value)), "smart_set_option")
@@ -474,77 +504,28 @@ class SmartTree:
     def tree_upload_pack(self, pinned_cu_nodes, pinned_parent, pinned_token, prefix_len):
         """Pinned host tree CSR -> device copies + tree_pack outputs, one launch.  Returns
         (cu_nodes, parent, token, depth, position, node_seq, anc_mask, status) on the device."""
-        torch = _torch()
-        B = pinned_cu_nodes.shape[0] - 1
-        N = int(pinned_cu_nodes[B])
-        dev = prefix_len.device
-        par, depth, position, node_seq, *tok = _i32_rows(4 if pinned_token is None else 5, N, dev)
-        tok = tok[0] if tok else None
-        cu = torch.empty(B + 1, dtype=torch.int32, device=dev)
-        status = torch.empty(B, dtype=torch.int32, device=dev)
-        anc_mask = torch.empty((N, 2), dtype=torch.int64, device=dev)
-        rc = _lib().tree_upload_pack(self._h, _stream_ptr(), B, N, _ptr(pinned_cu_nodes), _ptr(pinned_parent),
-                                     _ptr(pinned_token), _ptr(cu), _ptr(par), _ptr(tok), _ptr(prefix_len),
-                                     _ptr(depth), _ptr(position), _ptr(node_seq), _ptr(anc_mask), _ptr(status))
-        _check(rc, "tree_upload_pack")
-        return cu, par, tok, depth, position, node_seq, anc_mask, status
+        return self._native.upload_pack(self._ctx, pinned_cu_nodes, pinned_parent, pinned_token, prefix_len)
 
     # -- Algorithm 1 one layer at a time, on the device ---------------------
     def select_begin(self, state: DeviceLayerState, root_token, cost):
-        rc = _lib().smart_select_begin_device(self._h, _stream_ptr(), ctypes.byref(state.struct), _ptr(root_token),
-                                              _ptr(cost))
-        _check(rc, "smart_select_begin_device")
+        self._native.select_begin(self._ctx, ctypes.addressof(state.struct), root_token, cost)
 
     def select_layer(self, state: DeviceLayerState, cand_cu, cand_parent_node, cand_prob, cand_token, cost,
                      dcost=None, alpha=0.8, dilution=SMART_DILUTION_NONE, out_node=None, status=None):
         """Device tensors in, (out_node, status) device tensors out; nothing synchronises."""
-        torch = _torch()
-        cap = cand_parent_node.shape[0]
-        if out_node is None:
-            out_node = torch.empty(max(1, cap), dtype=torch.int32, device=cand_cu.device)
-        if status is None:
-            status = torch.empty(max(1, state.batch), dtype=torch.int32, device=cand_cu.device)
-        rc = _lib().smart_select_layer_device(self._h, _stream_ptr(), ctypes.byref(state.struct), _ptr(cand_cu),
-                                              _ptr(cand_parent_node), _ptr(cand_prob), _ptr(cand_token), cap,
-                                              _ptr(cost), _ptr(dcost), float(alpha), int(dilution), _ptr(out_node),
-                                              _ptr(status))
-        _check(rc, "smart_select_layer_device")
-        return (out_node if out_node.shape[0] == cap else out_node[:cap],
-                status if status.shape[0] == state.batch else status[:state.batch])
+        return self._native.select_layer(self._ctx, ctypes.addressof(state.struct), state.batch, cand_cu, cand_parent_node,
+                                         cand_prob, cand_token, cost, dcost, alpha, dilution, out_node, status)
 
     def tree_compact_pack(self, state: DeviceLayerState, prefix_len, total_cap=None):
         """Returns (cu_nodes, parent, token, depth, position, node_seq, anc_mask, status); the per-node
         tensors have total_cap rows of which cu_nodes[-1] are in use."""
-        torch = _torch()
-        B = state.batch
-        N = int(total_cap if total_cap is not None else B * state.budget)
-        dev = prefix_len.device
-        # one allocation and one fill for everything: the masks (16 bytes a node), the rows of node values, the offsets, the
-        # statuses, each in whole rows
-        n1, b1 = max(1, N), max(1, B)
-        p, at = _whole_rows(n1), _whole_rows(4 * n1)
-        buf = torch.zeros(at + 5 * p + _whole_rows(B + 1) + b1, dtype=torch.int32, device=dev)
-        anc_mask = buf[:4 * n1].view(torch.int64).view(n1, 2)
-        par, tok, depth, position, node_seq = buf.as_strided((5, n1), (p, 1), at).unbind(0)
-        cu = buf.as_strided((B + 1,), (1,), at + 5 * p)
-        status = buf.as_strided((b1,), (1,), at + 5 * p + _whole_rows(B + 1))
-        rc = _lib().tree_compact_pack(self._h, _stream_ptr(), ctypes.byref(state.struct), N, _ptr(prefix_len),
-                                      _ptr(cu), _ptr(par), _ptr(tok), _ptr(depth), _ptr(position), _ptr(node_seq),
-                                      _ptr(anc_mask), _ptr(status))
-        _check(rc, "tree_compact_pack")
-        if N == 0 or B == 0:
-            return cu, par[:N], tok[:N], depth[:N], position[:N], node_seq[:N], anc_mask[:N], status[:B]
-        return cu, par, tok, depth, position, node_seq, anc_mask, status
+        N = total_cap if total_cap is not None else state.batch * state.budget
+        return self._native.compact(self._ctx, ctypes.addressof(state.struct), state.batch, N, prefix_len)
 
     # -- tree_rope ---------------------------------------------------------
     def tree_rope(self, position, q, k_tree, base=10000.0, rotary_dim=None, pairing=SMART_ROPE_HALF_SPLIT):
         """Rotates q [N, Hq, D] and k_tree [N, Hkv, D] in place by the nodes' position ids."""
-        N, Hq, D = q.shape
-        Hkv = k_tree.shape[1]
-        rc = _lib().tree_rope(self._h, _stream_ptr(), _dtype_code(q), N, Hq, Hkv, D,
-                              int(D if rotary_dim is None else rotary_dim), int(pairing), float(base),
-                              _ptr(position), _ptr(q), _ptr(k_tree))
-        _check(rc, "tree_rope")
+        self._native.rope(self._ctx, position, q, k_tree, base, rotary_dim, pairing)
 
     # -- tree_pack ---------------------------------------------------------
     def tree_pack(self, cu_nodes, parent, prefix_len):
@@ -564,22 +545,14 @@ class SmartTree:
     # -- kv_cache_write ----------------------------------------------------
     def kv_cache_write(self, k_src, v_src, slot_mapping, k_cache, v_cache, layout, block_size,
                        num_blocks, block_stride, head_stride, token_stride=0):
-        n, Hkv, D = k_src.shape
-        rc = _lib().kv_cache_write(self._h, _stream_ptr(), _dtype_code(k_src), layout, n, Hkv, D,
-                                   block_size, num_blocks, _ptr(k_src), _ptr(v_src),
-                                   _ptr(slot_mapping), _ptr(k_cache), _ptr(v_cache),
-                                   block_stride, head_stride, token_stride)
-        _check(rc, "kv_cache_write")
+        self._native.cache_write(self._ctx, k_src, v_src, slot_mapping, k_cache, v_cache, layout, block_size, num_blocks,
+                                 block_stride, head_stride, token_stride, False, None, None)
 
     def kv_cache_write_fp8(self, k_src, v_src, slot_mapping, k_cache, v_cache, layout, block_size,
                            num_blocks, block_stride, head_stride, k_scale, v_scale, token_stride=0):
         """k_cache / v_cache: uint8 tensors (E4M3); strides in elements."""
-        n, Hkv, D = k_src.shape
-        rc = _lib().kv_cache_write_fp8(self._h, _stream_ptr(), _dtype_code(k_src), layout, n, Hkv, D,
-                                       block_size, num_blocks, _ptr(k_src), _ptr(v_src), _ptr(slot_mapping),
-                                       _ptr(k_cache), _ptr(v_cache), block_stride, head_stride, token_stride,
-                                       float(k_scale), float(v_scale))
-        _check(rc, "kv_cache_write_fp8")
+        self._native.cache_write(self._ctx, k_src, v_src, slot_mapping, k_cache, v_cache, layout, block_size, num_blocks,
+                                 block_stride, head_stride, token_stride, True, k_scale, v_scale)
 
     # -- tree_verify_attention ---------------------------------------------
     def tree_verify_attention(self, q, k_tree, v_tree, k_cache, v_cache, block_table, prefix_len,
@@ -591,77 +564,23 @@ class SmartTree:
         ``status``: optional int32 [B] tensor that receives the per-sequence block-table check.
         ``static``: call tree_verify_attention_static (no device allocation inside the library;
         pass ``out`` / ``lse`` so that nothing is allocated here either)."""
-        torch = _torch()
-        N, Hq, D = q.shape
-        Hkv = k_tree.shape[1]
-        B = cu_nodes.shape[0] - 1
-        if out is None:
-            out = torch.empty_like(q)
-        if lse is None and want_lse:
-            lse = torch.empty((N, Hq), dtype=torch.float32, device=q.device)
-        p = TvaParams()
-        p.dtype = _dtype_code(q)
-        p.kv_layout = kv_layout
-        p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads, p.head_dim = B, N, Hq, Hkv, D
-        p.block_size = block_size
-        p.max_blocks_per_seq = block_table.shape[1] if block_table is not None else 0
-        p.num_blocks = k_cache.shape[0] if k_cache is not None else 0
-        p.softmax_scale = float(softmax_scale)
-        p.d_q, p.d_k_tree, p.d_v_tree = q.data_ptr(), k_tree.data_ptr(), v_tree.data_ptr()
-        if k_cache is not None:
-            assert k_cache.stride(0) == v_cache.stride(0) and k_cache.stride(1) == v_cache.stride(1)
-            p.d_k_cache, p.d_v_cache = k_cache.data_ptr(), v_cache.data_ptr()
-            p.cache_block_stride, p.cache_head_stride = k_cache.stride(0), k_cache.stride(1)
-            p.cache_token_stride = k_cache.stride(2) if kv_layout == SMART_KV_PLAIN else D
-            p.d_block_table = block_table.data_ptr()
-        else:
-            p.cache_block_stride = p.cache_head_stride = block_size * D
-            p.cache_token_stride = D
-        if k_cache is not None and k_cache.dtype == torch.uint8:      # an fp8 (E4M3) cache
-            p.kv_cache_dtype = SMART_FP8_E4M3
-            p.k_scale, p.v_scale = float(k_scale), float(v_scale)
-        p.d_prefix_len, p.d_cu_nodes = prefix_len.data_ptr(), cu_nodes.data_ptr()
-        p.d_anc_mask = anc_mask.data_ptr()
-        p.d_out = out.data_ptr()
-        p.d_lse = lse.data_ptr() if lse is not None else None
-        p.d_status = status.data_ptr() if status is not None else None
+        h_address = 0
         if h_cu_nodes is not None:      # numpy int32 [B+1], host copy of cu_nodes
             h_cu_nodes = np.ascontiguousarray(h_cu_nodes, np.int32)
-            assert h_cu_nodes.shape[0] == B + 1
-            p.h_cu_nodes = h_cu_nodes.ctypes.data
-        entry = _lib().tree_verify_attention_static if static else _lib().tree_verify_attention
-        _check(entry(self._h, _stream_ptr(), ctypes.byref(p)),
-               "tree_verify_attention_static" if static else "tree_verify_attention")
-        return (out, lse) if (want_lse or lse is not None) else out
+            assert h_cu_nodes.shape[0] == cu_nodes.shape[0]
+            h_address = h_cu_nodes.ctypes.data
+        return self._native.attention(self._ctx, q, k_tree, v_tree, k_cache, v_cache, block_table, prefix_len, cu_nodes,
+                                      anc_mask, softmax_scale, kv_layout, block_size, out, lse, want_lse, h_address,
+                                      k_scale, v_scale, static, status)
 
     # -- tree_accept -------------------------------------------------------
     def tree_accept(self, cu_nodes, parent, token, target_next, max_depth):
-        torch = _torch()
-        B = cu_nodes.shape[0] - 1
-        dev = cu_nodes.device
-        accept_len, bonus = _i32_rows(2, B, dev)
-        accept_path = torch.empty((B, max_depth + 1), dtype=torch.int32, device=dev)
-        rc = _lib().tree_accept(self._h, _stream_ptr(), B, max_depth, _ptr(cu_nodes), _ptr(parent),
-                                _ptr(token), _ptr(target_next), _ptr(accept_len), _ptr(accept_path),
-                                _ptr(bonus))
-        _check(rc, "tree_accept")
-        return accept_len, accept_path, bonus
+        return self._native.accept(self._ctx, cu_nodes, parent, token, target_next, max_depth)
 
     # -- tree_accept_sample ------------------------------------------------
     def tree_accept_sample(self, cu_nodes, parent, token, target_prob, max_depth, seed, step):
         """Temperature-1 verification; target_prob [N, V] float32 (rows may be strided)."""
-        torch = _torch()
-        B = cu_nodes.shape[0] - 1
-        dev = cu_nodes.device
-        N, V = target_prob.shape
-        assert target_prob.dtype == torch.float32 and target_prob.stride(1) == 1
-        accept_len, bonus = _i32_rows(2, B, dev)
-        accept_path = torch.empty((B, max_depth + 1), dtype=torch.int32, device=dev)
-        rc = _lib().tree_accept_sample(self._h, _stream_ptr(), B, N, max_depth, V, _ptr(cu_nodes), _ptr(parent),
-                                       _ptr(token), _ptr(target_prob), target_prob.stride(0), int(seed), int(step),
-                                       _ptr(accept_len), _ptr(accept_path), _ptr(bonus))
-        _check(rc, "tree_accept_sample")
-        return accept_len, accept_path, bonus
+        return self._native.sample(self._ctx, cu_nodes, parent, token, target_prob, max_depth, seed, step)
 
     # -- tree_commit -------------------------------------------------------
     def tree_commit(self, cu_nodes, accept_len, accept_path, k_tree, v_tree, k_cache, v_cache, block_table,
@@ -669,18 +588,6 @@ class SmartTree:
                     k_scale=None, v_scale=None):
         """Appends the accepted path's K/V rows to the paged cache (in place); returns
         (new_prefix_len, status)."""
-        torch = _torch()
-        B = cu_nodes.shape[0] - 1
-        _, Hkv, D = k_tree.shape
-        new_len, status = _i32_rows(2, B, cu_nodes.device)
-        args = (self._h, _stream_ptr(), _dtype_code(k_tree), layout, B, accept_path.shape[1] - 1,
-                Hkv, D, block_size, block_table.shape[1], num_blocks, _ptr(cu_nodes),
-                _ptr(accept_len), _ptr(accept_path), _ptr(k_tree), _ptr(v_tree), _ptr(block_table),
-                _ptr(prefix_len), _ptr(k_cache), _ptr(v_cache), block_stride, head_stride,
-                token_stride, _ptr(new_len), _ptr(status))
-        if k_cache.dtype == torch.uint8:                          # an fp8 (E4M3) cache
-            rc = _lib().tree_commit_fp8(*args, float(k_scale), float(v_scale))
-        else:
-            rc = _lib().tree_commit(*args)
-        _check(rc, "tree_commit")
-        return new_len, status
+        return self._native.commit(self._ctx, cu_nodes, accept_len, accept_path, k_tree, v_tree, k_cache, v_cache,
+                                   block_table, prefix_len, layout, block_size, num_blocks, block_stride, head_stride,
+                                   token_stride, k_scale, v_scale)

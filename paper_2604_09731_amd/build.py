@@ -1,16 +1,19 @@
 """Builds the C-ABI library (libsmart_tree.so) in-tree with hipcc for gfx950, and beside it the timeline build
 (libsmart_tree_timeline.so: the same library with wall-clock stamps in the attention kernels, for
-`python -m paper_2604_09731_amd.timeline`; nothing else loads it)."""
+`python -m paper_2604_09731_amd.timeline`; nothing else loads it) and the binding's native part (_marshal.so, an extension
+module against torch's headers)."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libsmart_tree.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 TIMELINE_LIB = os.path.join(HERE, "libsmart_tree_timeline.so")
 TIMELINE_SOURCE = "tva_mfma.hip"        # the one source with stamps (-DSMART_TVA_TIMELINE)
 OBJ_DIR = os.path.join(HERE, "_build")
@@ -40,6 +43,19 @@ def _run(cmd):
         print(out)
 
 
+def build_marshal(verbose: bool = False) -> str:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+          "-I", INCLUDE, "-isystem", sysconfig.get_paths()["include"], *[x for p in include_paths() for x in ("-isystem", p)],
+          os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L", libs, "-lc10", "-ltorch_cpu", "-ltorch_python",
+          f"-Wl,-rpath,{libs}"])
+    if verbose:
+        print("built", MARSHAL)
+    return MARSHAL
+
+
 def build_library(verbose: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     objs = []
@@ -54,6 +70,7 @@ def build_library(verbose: bool = False) -> str:
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs, "-pthread"])
     if verbose:
         print("built", LIB)
+    build_marshal(verbose)
     # the timeline build: one object compiled again with the stamps, the rest shared
     plain = os.path.join(OBJ_DIR, TIMELINE_SOURCE + ".o")
     stamped = os.path.join(OBJ_DIR, TIMELINE_SOURCE + ".timeline.o")
