@@ -36,7 +36,7 @@
 // on the vector ALUs in fp32 by walking the set bits, so what other nodes hold never enters a row.
 //
 // Measured against the general kernel (whole call): bf16 plain pages, batch 16, 32 / 8 heads of 128, prefixes of
-// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 102 us (prefix kernel 91, of which 62 are the MFMAs of its fullest
+// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 90 us (prefix kernel XX, of which 62 are the MFMAs of its fullest
 // workgroups; finishing kernel 18); fp32 plain pages, batch 8, 8 / 2 heads of 64, prefixes of 128 .. 1536, 15-node trees
 // 778 -> 19 us, and its error against binary64 falls from 5.6e-7 to 3.1e-7 (shorter sums).
 //
@@ -95,6 +95,7 @@ struct TiledArgs {
   int64_t* plan;   // split form: units, workers, then per sequence the units and the segments before it
   int64_t block_stride, head_stride, token_stride;
   int32_t batch, total_nodes, Hq, Hkv, G, block_size, max_blocks, num_blocks;
+  int32_t segment_cost;   // units of a segment beside its steps
   bool fp8, plain;        // the cache's element type and layout, where they are no template arguments
   uint32_t block8_magic;  // token / 8 / (block_size / 8) by multiplication
   float scale;
@@ -104,7 +105,8 @@ struct TiledArgs {
   float o_scale;   // = v_scale
 };
 
-// The unit the split form cuts into shares is a cost: a step of a row group with r row tiles counts kStepCost[r].  The
+// The unit the split form cuts into shares is a cost: a step of a row group with r row tiles counts StepCost, a segment
+// beside its steps segment_cost (behind them; a share that begins there leaves no partial).  The
 // two wavefronts of a SIMD have one tile of a step between them with one row tile, two with two, four with three or four
 // (the third's SIMD partner idles); up to two tiles of bf16 a step takes what its loads take (1.9 us measured), with
 // four what its products take (3.4 us); the fp32 products always set the pace.  Against shares of equal step counts the
@@ -136,8 +138,9 @@ __device__ inline Shape shape_of(const TiledArgs& a, int len, int base, int next
   s.steps = s.groups > 0 ? (s.len + step_keys<T>() - 1) / step_keys<T>() : 0;
   const int last = s.rows - (s.groups - 1) * kGroupRows;
   s.cost_last = last <= kRowTile ? StepCost<T>::one : (last <= 2 * kRowTile ? StepCost<T>::two : StepCost<T>::four);
-  s.full = (int64_t)s.steps * StepCost<T>::four;
-  s.head = s.groups > 0 ? (s.groups - 1) * s.full + (int64_t)s.steps * s.cost_last : 0;
+  const int extra = s.steps > 0 ? a.segment_cost : 0;
+  s.full = (int64_t)s.steps * StepCost<T>::four + extra;
+  s.head = s.groups > 0 ? (s.groups - 1) * s.full + (int64_t)s.steps * s.cost_last + extra : 0;
   return s;
 }
 
@@ -935,6 +938,14 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
     int b = at.b;
     Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
     while (u0 < u1) {
+      // on to the next sequence with units
+      while (!kDirect && u0 >= at.units_before + a.Hkv * sh.head) {
+        at.units_before += a.Hkv * sh.head;
+        at.segs_before += (int64_t)a.Hkv * sh.groups;
+        ++b;
+        if (b >= a.batch) return;
+        sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
+      }
       int g, group, t0, t1;
       if (kDirect) {
         const int local = (int)(wg - at.segs_before);
@@ -950,10 +961,12 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
         group = (int)min(in_head / sh.full, (int64_t)sh.groups - 1);
         const int64_t off = in_head - group * sh.full;
         const int cost = group < sh.groups - 1 ? StepCost<T>::four : sh.cost_last;
-        const int64_t left = (int64_t)sh.steps * cost - off;  // units to the segment's end
+        const int64_t left = (int64_t)sh.steps * cost - off;  // units to the end of the segment's steps
+        const int64_t share = u1 - u0;
+        u0 = min(u1, u0 + left + a.segment_cost);
+        if (left <= 0) continue;  // (the finishing step does not count this worker)
         t0 = (int)(off / cost);
-        t1 = u1 - u0 >= left ? sh.steps : (int)((off + u1 - u0) / cost);
-        u0 = min(u1, u0 + left);
+        t1 = share >= left ? sh.steps : (int)((off + share) / cost);
       }
       b = __builtin_amdgcn_readfirstlane(b);
       g = __builtin_amdgcn_readfirstlane(g);
@@ -1050,14 +1063,6 @@ __global__ __launch_bounds__(kThreads, 2) void tva_tiled_kernel(TiledArgs a) {
         }
         break;
       }
-      // on to the next sequence with units
-      while (u0 < u1 && u0 >= at.units_before + a.Hkv * sh.head) {
-        at.units_before += a.Hkv * sh.head;
-        at.segs_before += (int64_t)a.Hkv * sh.groups;
-        ++b;
-        if (b >= a.batch) return;
-        sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
-      }
     }
   }
 
@@ -1127,13 +1132,13 @@ __global__ __launch_bounds__(finish_waves(kParts) * kWave, kParts == 0 ? 2 : 1) 
   if (U < 0) b = owner_of(a, node);  // offsets that are not ascending
   const Shape sh = shape_of<T>(a, a.prefix_len[b], a.cu_nodes[b], a.cu_nodes[b + 1]);
   const bool owned = there && node >= sh.base && (int64_t)node - sh.base < sh.n;
+  const int64_t units_before = a.plan[2 + b], segs_before = a.plan[2 + a.batch + b];
   if (part < 0) f.tree(a, g, sh.base, owned ? sh.n : 0, e);
   if ((kParts == 0 || part >= 0) && owned && sh.steps > 0 && U > 0) {
-    const int64_t units_before = a.plan[2 + b], segs_before = a.plan[2 + a.batch + b];
     const int rho = (node - sh.base) * a.G + head % a.G;
     const int group = rho / kGroupRows, r = rho % kGroupRows, local = g * sh.groups + group;
     const int64_t ub = units_before + g * sh.head + group * sh.full;
-    const int64_t ue = ub + (group < sh.groups - 1 ? sh.full : (int64_t)sh.steps * sh.cost_last) - 1;
+    const int64_t ue = ub + (int64_t)sh.steps * (group < sh.groups - 1 ? StepCost<T>::four : sh.cost_last) - 1;
     const int64_t w_first = ((ub + 1) * W - 1) / U, w_last = ((ue + 1) * W - 1) / U;
     auto partial = [&](int64_t w) {
       const float* slot = a.ws + (w + segs_before + local) * slot_floats(D);
@@ -1214,11 +1219,23 @@ bool tva_tiled_supported(const tva_params& p) {
          aligned(p.d_k_tree, 16) && aligned(p.d_v_tree, 16) && aligned(p.d_out, 16);
 }
 
+// A piece takes 3 us to start and 4 to fold, which a worker that holds the ends of two segments pays twice: counted like two
+// steps of one row tile (bf16), it leaves such a worker fewer steps.  Without / with, us: the bf16 workload above 95 / 84.6,
+// 16 sequences of 60 .. 500 tokens, 4 .. 64 nodes 45.6 / 37.3, of 100 .. 800, 30 .. 66 nodes, 64 / 8 heads of 64 65.8 / 49.4,
+// fp32, 10 of 200 .. 1600 41.3 / 36.0; 4 and 12 in its place 86.6 and 84.9, 37.8 and 36.9, 52.5 and 50.3, 37.3 and 38.2.
+// Few segments are cut into many pieces of a step or two each, and where they are equally long the cuts fall on whole steps
+// without it: 4 sequences of 1000, 8 kv heads 30.4 / 33.3, 16 of 2000, 2 kv heads 33.1 / 36.2, but 5 of 1000, 8 kv heads
+// 38.6 / 33.6.
+static int32_t segment_cost(const tva_params& p, int32_t workgroups) {
+  return (int64_t)p.batch * p.num_kv_heads * 8 > workgroups ? 8 : 0;
+}
+
 // `rows8`: groups of eight rows.  Whole calls, one wavefront for both chains / a second for the partials / seven for them:
 // 28 groups, one sequence of 4000 tokens, plain bf16 36.1 / 26.4 / 22.7 us; 120 groups, the fp32 workload above (up to 24
-// partials a row) 23.1 / 20.8 / 19.0; 480 groups, 4 sequences of 1000 33.7 / 30.4 / 36.2; 832 44.0 / 42.5 / 51.7; 1500, 16
-// sequences of 60 .. 128 nodes, 31.9 / 34.6 / 42.7; 2016 42.2 / 47.7 / 70.6; the bf16 workload above (2176) 95.2 / 97.1 / 117.6.
-static int finish_parts(int64_t rows8) { return rows8 <= 128 ? 7 : (rows8 <= 1024 ? 1 : 0); }
+// partials a row) 23.1 / 20.8 / 19.0; 480 groups, 4 sequences of 1000 33.7 / 30.4 / 36.2; 576 37.1 / 34.2; from there on either way
+// (720 53.5 / 51.0, 756 27.0 / 28.3, 832 44.0 / 42.5); 1500, 16 sequences of 60 .. 128 nodes, 31.9 / 34.6 / 42.7; 2016 42.2 /
+// 47.7 / 70.6; the bf16 workload above (2176) 95.2 / 97.1 / 117.6.
+static int finish_parts(int64_t rows8) { return rows8 <= 128 ? 7 : (rows8 <= 640 ? 1 : 0); }
 template <typename T, int D>
 static void launch_finish(const TiledArgs& a, int64_t rows8, hipStream_t stream) {
   const int parts = finish_parts(rows8), waves = finish_waves(parts);
@@ -1301,6 +1318,7 @@ int32_t tva_launch_tiled(smart_ctx* ctx, hipStream_t stream, const tva_params& p
   a.block_size = p.block_size;
   a.max_blocks = p.max_blocks_per_seq;
   a.num_blocks = p.num_blocks;
+  a.segment_cost = segment_cost(p, tiled_workgroups(ctx));
   a.fp8 = fp8;
   a.plain = p.kv_layout == SMART_KV_PLAIN;
   // t8 / d as the high word of 2 t8 * (floor(2^31 / d) + 1): exact for t8 < 2^28 and d <= 8
