@@ -120,8 +120,12 @@ struct SeqInfo {
 // of 0.06 us: kLargeTileCost[row tiles] per tile.  (Starting and finishing a piece takes 11 .. 13 us on top; a
 // start cost per segment in the unit space, 0 .. 200 units, changed nothing measurable and is not modelled.)
 constexpr int kLargeTileCost[kLargeRows / 32 + 1] = {11, 11, 11, 12, 12, 16, 16, 17, 17};
-// (the same currency for a tile of classes 0 and 1, for dealing the workgroups to the classes)
-constexpr int kClassTileCost[kClasses] = {10, 10, 1};
+// (the same currency for a tile of classes 0 and 1, for dealing the workgroups to the classes.  A class 0 tile takes 10 where
+// all workgroups stream, 6 .. 7 among many of class 2 (with 10, class 0 ended at 88 us of 128 and at 775 of 1333); 8 / 9 / 10
+// us: 60 sequences of 500 .. 4000 tokens, 1 .. 24 nodes 122 / 129 / 129, 64 of 16384, 1 .. 48 nodes 1227 / 1236 / 1240, 32 of
+// 3072 .. 4096, 1 .. 14 nodes 92.5 / 90.4 / 96.4, 64 of 4096, 4 .. 10 nodes 203 / 199 / 202, 48 of 100 .. 8000, 2 kv heads
+// 69 / 67 / 65.)
+constexpr int kClassTileCost[kClasses] = {8, 10, 1};
 constexpr int kFp8StreamTileCost = 5;
 // What a segment costs beside its prefix tiles where the prefix kernel finishes the rows itself (kFinish): its tree part,
 // and where workers hold several segments its start and end, in units of classes 0 and 1 (a tile) and of class 2: see
