@@ -31,7 +31,7 @@ SMART_MAX_LAYER_CAND = 2048
 
 EXPORTS = ["smart_strerror", "smart_last_hip_error", "smart_create", "smart_destroy",
            "smart_reserve", "smart_set_option", "smart_tva_profile_read", "smart_select_tree", "smart_select_tree_budgets", "smart_baseline_tree", "smart_product_forest", "smart_select_begin", "smart_select_layer",
-           "smart_select_begin_device", "smart_select_layer_device", "tree_compact_pack", "tree_rope", "smart_cost_tables", "smart_cost_tables_biased", "smart_fit_cost_models", "tree_upload",
+           "smart_select_begin_device", "smart_select_layer_device", "tree_compact_pack", "tree_compact_pack_fill", "tree_rope", "smart_cost_tables", "smart_cost_tables_biased", "smart_fit_cost_models", "tree_upload",
            "tree_upload_pack", "tree_pack",
            "kv_cache_write", "kv_cache_write_fp8", "tree_verify_attention", "tree_verify_attention_static", "tree_accept", "tree_accept_sample", "tree_commit", "tree_commit_fp8"]
 
@@ -120,6 +120,8 @@ def _lib():
         lib.smart_select_layer_device.argtypes = [vp, vp, sp, vp, vp, vp, vp, i64, vp, vp, f64, i32, vp, vp]
         lib.tree_compact_pack.restype = i32
         lib.tree_compact_pack.argtypes = [vp, vp, sp, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+        lib.tree_compact_pack_fill.restype = i32
+        lib.tree_compact_pack_fill.argtypes = lib.tree_compact_pack.argtypes
         lib.tree_rope.restype = i32
         lib.tree_rope.argtypes = [vp, vp, i32, i32, i32, i32, i32, i32, i32, f64, vp, vp, vp]
         lib.smart_cost_tables.restype = i32
@@ -382,7 +384,7 @@ def _torch():
 _ROW = 128      # int32 elements
 
 
-_NATIVE_ENTRIES = ("smart_select_begin_device", "smart_select_layer_device", "tree_compact_pack", "tree_upload_pack",
+_NATIVE_ENTRIES = ("smart_select_begin_device", "smart_select_layer_device", "tree_compact_pack_fill", "tree_upload_pack",
                    "tree_rope", "kv_cache_write", "kv_cache_write_fp8", "tree_verify_attention",
                    "tree_verify_attention_static", "tree_accept", "tree_accept_sample", "tree_commit", "tree_commit_fp8")
 _nativeh = None
@@ -518,7 +520,7 @@ class SmartTree:
 
     def tree_compact_pack(self, state: DeviceLayerState, prefix_len, total_cap=None):
         """Returns (cu_nodes, parent, token, depth, position, node_seq, anc_mask, status); the per-node
-        tensors have total_cap rows of which cu_nodes[-1] are in use."""
+        tensors have total_cap rows of which cu_nodes[-1] are in use; the others are zero."""
         N = total_cap if total_cap is not None else state.batch * state.budget
         return self._native.compact(self._ctx, ctypes.addressof(state.struct), state.batch, N, prefix_len)
 

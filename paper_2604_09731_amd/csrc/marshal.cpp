@@ -18,7 +18,7 @@ namespace {
 struct Entries {
   decltype(&smart_select_begin_device) begin;
   decltype(&smart_select_layer_device) layer;
-  decltype(&tree_compact_pack) compact;
+  decltype(&tree_compact_pack_fill) compact;
   decltype(&tree_upload_pack) upload_pack;
   decltype(&tree_rope) rope;
   decltype(&kv_cache_write) cache_write;
@@ -221,17 +221,19 @@ PyObject* compact(PyObject* const* a) {  // ctx, state, batch, rows, prefix_len
   auto state = pointer<const smart_layer_state>(a[1]);
   const int64_t batch = integer(a[2]), rows = integer(a[3]);
   const at::Tensor& prefix = tensor(a[4]);
-  // one allocation and one fill for everything: the masks (16 bytes a node), the rows of node values, the offsets, the
-  // statuses, each in whole rows
+  // one allocation for everything: the masks (16 bytes a node), the rows of node values, the offsets, the statuses, each in
+  // whole rows; the launch writes all of it, and there is none for an empty batch
   const int64_t n1 = std::max<int64_t>(1, rows), b1 = std::max<int64_t>(1, batch), p = whole_rows(n1), at = whole_rows(4 * n1);
-  at::Tensor buf = at::zeros({at + 5 * p + whole_rows(batch + 1) + b1}, at::TensorOptions().dtype(at::kInt).device(prefix.device()));
+  const int64_t words = at + 5 * p + whole_rows(batch + 1) + b1;
+  at::Tensor buf = fresh(prefix, at::kInt, {words});
+  if (batch <= 0 || rows <= 0) buf.zero_();
   at::Tensor mask = buf.slice(0, 0, 4 * n1).view(at::kLong).view({n1, 2});
   at::Tensor row[5];
   for (int i = 0; i < 5; ++i) row[i] = buf.as_strided({n1}, {1}, at + i * p);
   at::Tensor cu = buf.as_strided({batch + 1}, {1}, at + 5 * p);
   at::Tensor status = buf.as_strided({b1}, {1}, at + 5 * p + whole_rows(batch + 1));
   void* s = stream();
-  call("tree_compact_pack", [&] {
+  call("tree_compact_pack", [&] {  // (named as the binding's call)
     return lib.compact(ctx, s, state, (int32_t)rows, address<int32_t>(prefix), address<int32_t>(cu), address<int32_t>(row[0]),
                        address<int32_t>(row[1]), address<int32_t>(row[2]), address<int32_t>(row[3]), address<int32_t>(row[4]),
                        address<uint64_t>(mask), address<int32_t>(status));

@@ -2,6 +2,8 @@
 smart_select_layer_device) and of tree_compact_pack, against the CPU oracle, through the C ABI.
 Everything here is compared bit for bit: decisions, node order, P, L and R are binary64 values
 that both sides must compute with the same operations in the same order."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -220,3 +222,33 @@ def test_compact_pack_then_attention_with_a_capacity_instead_of_a_size(lib, orac
         assert H.rel_err(got[:N], ref) <= H.TOL[dtype]
         tail = got[N:]
         assert np.isfinite(tail).all() and (np.all(tail == 7.0) or np.all(tail == 0.0))   # untouched or zero-filled
+
+
+@pytest.mark.parametrize("batch,budget,spare", [(1, 2, 0), (1, 1, 1), (3, 7, 1), (2, 128, 63), (65, 5, 200), (130, 64, 1)])
+def test_compact_pack_leaves_zeros_behind_the_last_node(lib, batch, budget, spare):
+    """Trees of 0 (a size that counts as malformed) .. budget nodes in memory that held something else before; the rows in use
+    are those of the entry that fills nothing."""
+    import torch
+    g = np.random.default_rng(batch * 1000 + budget)
+    n = g.integers(0, budget + 2, batch).astype(np.int32)       # 0 and budget + 1: no nodes
+    used = np.where((n >= 1) & (n <= budget), n, 0)
+    parent = np.concatenate([[np.int32(-1)] + [g.integers(0, i) for i in range(1, budget)] for _ in range(batch)])
+    state = B.DeviceLayerState(batch, budget, "cuda:0")
+    state.n.copy_(torch.from_numpy(n))
+    state.parent.view(-1).copy_(torch.from_numpy(parent.astype(np.int32)))
+    state.token.view(-1).copy_(torch.from_numpy(g.integers(1, 1000, batch * budget).astype(np.int32)))
+    lens = torch.from_numpy(g.integers(1, 100, batch).astype(np.int32)).cuda()
+    cap, total = batch * budget + spare, int(used.sum())
+    dirty = [torch.full((1 << 16,), -7, dtype=torch.int32, device="cuda") for _ in range(4)]
+    del dirty
+    cu, *rows, mask, status = lib.tree_compact_pack(state, lens, cap)
+    assert cu.cpu().tolist() == np.concatenate([[0], np.cumsum(used)]).tolist()
+    plain = [torch.full_like(x, -7) for x in (cu, *rows, mask, status)]
+    rc = B._lib().tree_compact_pack(lib._ctx, B._stream_ptr(), ctypes.byref(state.struct), cap, B._ptr(lens), *[B._ptr(x) for x in plain])
+    assert rc == 0
+    torch.cuda.synchronize()
+    for x, y in zip((cu, status), (plain[0], plain[-1])):
+        assert torch.equal(x, y)
+    for x, y in zip((*rows, mask), plain[1:-1]):
+        assert torch.equal(x[:total], y[:total])
+        assert not x[total:].any() and bool((y[total:] == -7).all())
