@@ -36,7 +36,7 @@
 // on the vector ALUs in fp32 by walking the set bits, so what other nodes hold never enters a row.
 //
 // Measured against the general kernel (whole call): bf16 plain pages, batch 16, 32 / 8 heads of 128, prefixes of
-// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 101 us (prefix kernel 88, of which 62 are the MFMAs of its fullest
+// 1024 .. 4096, trees of 4 .. 64 nodes 12.9 ms -> 96 us (prefix kernel 86, of which 62 are the MFMAs of its fullest
 // workgroups; finishing kernel 18); fp32 plain pages, batch 8, 8 / 2 heads of 64, prefixes of 128 .. 1536, 15-node trees
 // 778 -> 19 us, and its error against binary64 falls from 5.6e-7 to 3.1e-7 (shorter sums).
 //
@@ -109,7 +109,7 @@ struct TiledArgs {
 // beside its steps segment_cost (behind them; a share that begins there leaves no partial).  The two wavefronts of a SIMD
 // have one tile of a step between them with one row tile, two with two, four with three or four (the third's SIMD partner
 // idles).  Stamps, bf16, the first workload above: 2.06 us a step with one row tile, 2.75 with two, 4.35 with three, 4.42 with
-// four (4, 4, 7 units until these were taken: the call 104 us, now 101); the fp32 products always set the pace.
+// four (with 4, 4, 7 units the call took 104 us, with these 101); the fp32 products always set the pace.
 template <typename T> struct StepCost;
 template <> struct StepCost<__bf16> { static constexpr int one = 4, two = 5, four = 8; };
 template <> struct StepCost<float> { static constexpr int one = 4, two = 7, four = 14; };
