@@ -57,6 +57,26 @@ def test_both_forms_equal_the_general_kernel(shape, workers, fp8):
 
 
 @pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("lens,size,Hq,Hkv", [([64, 0, 0, 0], 4, 16, 4), ([40] + [0] * 6, 3, 28, 4), ([128, 32] + [0] * 6, 8, 8, 2),
+                                              ([33] + [0] * 14, 100, 2, 2), ([0] * 9 + [64] + [0] * 5, 50, 2, 2)])
+def test_mostly_empty_prefixes_under_a_wide_table(lens, size, Hq, Hkv, fp8):
+    """Two launches, and more segments than units of prefix: no partial is merged that this call did not write.  A larger call
+    leaves its own in the workspace first; values of its cache are far from those of the calls behind it."""
+    lib = B.SmartTree(0)
+    x = Inputs([size] * len(lens), lens, Hq, Hkv, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, fp8, seed=len(lens), spare_columns=WIDE)
+    big = Inputs([size] * len(lens), [3000] * len(lens), Hq, Hkv, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, False, seed=1,
+                 spare_columns=WIDE)
+    big.v.mul_(1e4)
+    ref, ref_lse = x.run(lib, general=True)
+    bound = bound_of(x, lib, ref)
+    for static in (False, True):
+        big.run(lib, static=static)
+        out, lse = x.run(lib, static=static)
+        assert bool(((out.double() - ref.double()).abs() <= bound).all())
+        assert float((lse - ref_lse).abs().max()) <= 1e-3
+
+
+@pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("size,Hq,Hkv", [(8, 8, 2), (16, 8, 2), (50, 4, 4), (64, 8, 2), (128, 8, 2)])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 def test_what_one_node_holds_reaches_only_its_descendants(bad, size, Hq, Hkv, fp8):
