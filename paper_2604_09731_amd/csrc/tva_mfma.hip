@@ -805,11 +805,12 @@ __device__ inline void clear_not_finite(ushort8& v) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) v[e] = (v[e] & 0x7F80) == 0x7F80 ? 0 : v[e];
 }
-// What clear_not_finite took away, added to the rows that do see it: a positive probability times an infinity is that
-// infinity, and NaN stays NaN.
+// What clear_not_finite took away of tiles tt .. tt_end - 1, added to the rows that do see it: a positive probability times an
+// infinity is that infinity, and NaN stays NaN.  (To the state that carries the tile, whose maximum is no less than the key's
+// score: one without the tile may have no weight in the fold, and zero times an infinity is NaN.)
 __device__ inline void add_not_finite(floatx16 (&o)[4], const FinishArgs& a, const TreeRows& t, int base, int rows, int rho, int n,
-                                      int lane) {
-  for (int tt = 0; 32 * tt < n; ++tt) {
+                                      int tt, int tt_end, int lane) {
+  for (; tt < tt_end && 32 * tt < n; ++tt) {
     uint32_t bits = mask_word(a, base, rows, rho, n, tt);
     while (__any(bits != 0u)) {
       const uint32_t at = (bits != 0u ? 32 * tt + __ffs(bits) - 1 : 0) * t.pitch + (lane >> 5) * 8;
@@ -864,7 +865,7 @@ __device__ inline void tree_tile(floatx16 (&o)[4], float& m, float& l, const Fin
     o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v[0][jt]), pb0, o[jt], 0, 0, 0);
     o[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v[1][jt]), pb1, o[jt], 0, 0, 0);
   }
-  if (mend) add_not_finite(o, a, t, base, rows, rho, n, lane);
+  if (mend) add_not_finite(o, a, t, base, rows, rho, n, tt, tt + 1, lane);
 }
 
 // The whole workgroup puts up to four tiles of tree keys into LDS stages 0 .. 3 in operand order: wavefront w K step w and
@@ -2078,7 +2079,7 @@ __device__ inline void staged_segment(const MainArgs& a, int b, int g, int base,
       for (int tt = 0; 32 * tt < si.n; ++tt)
         staged_tree_tile(o, m, l, q, tt == 0 ? word[0] : tt == 1 ? word[1] : tt == 2 ? word[2] : word[3], lds, tt,
                          fa.scale_log2e, ln);
-      if (mend) add_not_finite(o, fa, t, base, M, row0 + (ln & 31), si.n, ln);
+      if (mend) add_not_finite(o, fa, t, base, M, row0 + (ln & 31), si.n, 0, 4, ln);
     }
   }
   if (kRows) {
@@ -2296,7 +2297,7 @@ __device__ inline void grouped_segment(const MainArgs& a, int b, int g, int base
     const bool mend = stage_tree(pair, t, lds, (uint32_t*)(lds + kStages * kStageVecs), wv, ln);
     if (has_rows) {
       if (32 * kg < si.n) staged_tree_tile(S.o, S.m, S.l, q, word, lds, kg, c, ln);
-      if (mend && kg == 0) add_not_finite(S.o, fa, t, base, M, rt * 32 + (ln & 31), si.n, ln);
+      if (mend) add_not_finite(S.o, fa, t, base, M, rt * 32 + (ln & 31), si.n, kg, kg + 1, ln);
     }
     __syncthreads();
   }

@@ -105,3 +105,38 @@ def test_what_one_node_holds_reaches_only_its_descendants(bad, size, Hq, Hkv, fp
         out, _ = x.run(lib)
         assert torch.equal(out[:size][~sees], clean[:size][~sees]) and torch.equal(out[size:], clean[size:])
         x.k_tree = k
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("size,prefix", [(33, 20), (50, 0), (50, 20), (64, 100), (100, 20)])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_bad_values_in_several_tiles_of_tree_keys(bad, size, prefix, fp8):
+    """One in each tile of 32 tree keys, and prefixes so short that the wavefronts that carry those tiles have no other key:
+    each row is what the general kernel makes of it."""
+    import torch
+    lib = B.SmartTree(0)
+    x = Inputs([size, 3], [prefix, 40], 4, 4, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, fp8, seed=size)
+    for at, node in enumerate(range(5, size, 27)):
+        x.v_tree[node, :, 7 * at + 1], x.v_tree[node, :, 7 * at + 2] = bad, -bad
+    out, _ = x.run(lib)
+    ref, _ = x.run(lib, general=True)
+    assert torch.isnan(ref).any() if np.isnan(bad) else torch.isinf(ref).any()
+    assert torch.equal(torch.isnan(out), torch.isnan(ref)) and torch.equal(out[torch.isinf(out)], ref[torch.isinf(ref)])
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("size,Hq,Hkv", [(16, 8, 2), (50, 4, 4), (64, 8, 2), (128, 8, 2)])
+def test_an_infinite_value_of_the_key_with_all_the_weight(size, Hq, Hkv, fp8):
+    """A node whose score is 181 above all others it sees (their probabilities are zero in binary32) and whose value is
+    infinite: its row is infinite there, not NaN."""
+    import torch
+    lib = B.SmartTree(0)
+    x = Inputs([size, 3], [200, 40], Hq, Hkv, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, fp8, seed=size)
+    x.k_tree.mul_(0.01)
+    for node in (size // 2 + 15 if size > 32 else size // 2, size - 1):
+        q, k, v = x.q.clone(), x.k_tree.clone(), x.v_tree.clone()
+        x.q[node], x.k_tree[node], x.v_tree[node, :, 5] = 8.0, 2.0, np.inf
+        out, _ = x.run(lib)
+        assert bool((out[node, :, 5] == np.inf).all())
+        assert torch.isfinite(out[node][:, [d for d in range(128) if d != 5]]).all()
+        x.q, x.k_tree, x.v_tree = q, k, v
