@@ -16,8 +16,12 @@ struct smart_ctx {
   size_t ws_bytes = 0;
   int32_t* plan = nullptr;    // launch plan written by the planning kernel
   size_t plan_bytes = 0;
-  int32_t* arrive = nullptr;  // arrival counters of the matrix-core path, behind the plan; zero between calls
+  int32_t* arrive = nullptr;  // arrival counters of the matrix-core path, behind the plan or in the newest block; zero between calls
   size_t counters = 0;
+  // blocks of counters by themselves, for calls that need more of them but no larger plan; kept until smart_destroy, because a
+  // captured launch may hold an older one (each at least twice the one before)
+  void* counter_blocks[32] = {};
+  int32_t n_counter_blocks = 0;
   void* tiled_ws = nullptr;   // the tiled path's partial results and plan where ws is too small; no graph ever holds it
   size_t tiled_ws_bytes = 0;
   size_t tiled_refused = SIZE_MAX;  // the smallest size of it that there was no memory for

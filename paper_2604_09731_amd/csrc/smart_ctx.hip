@@ -32,23 +32,33 @@ int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, si
     if (e != hipSuccess) { set_last_hip_error(e); (void)hipGetLastError(); return SMART_ENOMEM; }
     ctx->ws_bytes = ws_bytes;
   }
-  if (plan_bytes > ctx->plan_bytes || counters > ctx->counters) {
-    if (plan_bytes < ctx->plan_bytes) plan_bytes = ctx->plan_bytes;
+  const bool plan_grows = plan_bytes > ctx->plan_bytes;
+  if (plan_grows || counters > ctx->counters) {
+    constexpr int kBlocks = sizeof(ctx->counter_blocks) / sizeof(ctx->counter_blocks[0]);
     if (counters < ctx->counters) counters = ctx->counters;
-    plan_bytes = (plan_bytes + 255) & ~(size_t)255;
-    if (ctx->plan) SMART_HIP_CHECK(hipFree(ctx->plan));
-    ctx->plan = ctx->arrive = nullptr;
-    ctx->plan_bytes = ctx->counters = 0;
-    hipError_t e = hipMalloc((void**)&ctx->plan, plan_bytes + counters * sizeof(int32_t));
+    if (plan_grows) {
+      plan_bytes = (plan_bytes + 255) & ~(size_t)255;
+      if (ctx->plan) SMART_HIP_CHECK(hipFree(ctx->plan));
+      ctx->plan = ctx->arrive = nullptr;
+      ctx->plan_bytes = ctx->counters = 0;
+    } else {
+      // a captured launch may still hold the plan and the counters, which were large enough for it
+      if (ctx->n_counter_blocks == kBlocks) return SMART_ENOMEM;
+      if (counters < 2 * ctx->counters) counters = 2 * ctx->counters;
+    }
+    void* block = nullptr;
+    hipError_t e = hipMalloc(&block, (plan_grows ? plan_bytes : 0) + counters * sizeof(int32_t));
     if (e != hipSuccess) { set_last_hip_error(e); (void)hipGetLastError(); return SMART_ENOMEM; }
+    if (plan_grows) ctx->plan = (int32_t*)block;
+    else ctx->counter_blocks[ctx->n_counter_blocks++] = block;
     // the counters start from zero and every launch leaves them so
-    int32_t* const arrive = (int32_t*)((char*)ctx->plan + plan_bytes);
+    int32_t* const arrive = (int32_t*)((char*)block + (plan_grows ? plan_bytes : 0));
     if (counters > 0) {
       const int32_t rc = zero_counters(stream, arrive, counters);
       if (rc != SMART_OK) return rc;
       SMART_HIP_CHECK(hipStreamSynchronize(stream));  // (the next call may be on another stream)
     }
-    ctx->plan_bytes = plan_bytes;
+    if (plan_grows) ctx->plan_bytes = plan_bytes;
     ctx->arrive = arrive;
     ctx->counters = counters;
   }
@@ -179,6 +189,8 @@ extern "C" int32_t smart_destroy(smart_ctx* ctx) {
       if (ctx->ws && hipFree(ctx->ws) != hipSuccess) rc = SMART_EHIP;
       if (ctx->plan && hipFree(ctx->plan) != hipSuccess) rc = SMART_EHIP;
       if (ctx->tiled_ws && hipFree(ctx->tiled_ws) != hipSuccess) rc = SMART_EHIP;
+      for (int i = 0; i < ctx->n_counter_blocks; ++i)
+        if (hipFree(ctx->counter_blocks[i]) != hipSuccess) rc = SMART_EHIP;
       smart::profile_free(ctx);
       (void)hipSetDevice(prev);
     } else {

@@ -9,7 +9,7 @@
 
 #include "smart_tree.h"
 
-static int mallocs, launches;
+static int mallocs, frees, launches;
 static size_t allocated, refuse_from = (size_t)-1;
 static hipError_t sync_result = hipSuccess, malloc_result = hipErrorOutOfMemory;
 
@@ -30,7 +30,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   *p = malloc(64);
   return hipSuccess;
 }
-hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipFree(void* p) { ++frees; free(p); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return sync_result; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -118,6 +118,17 @@ int main() {
   EXPECT(call(ctx, 128, 8192, 32, 4) == SMART_EHIP);
   EXPECT(call(ctx, 64, 4096, 32, 4) == 2);
   EXPECT(smart_destroy(ctx) == SMART_OK);
+  // more arrival counters, but no larger partial results or plan: what a captured launch of an earlier call holds stays
+  refuse_from = (size_t)-1;
+  EXPECT(smart_create(&ctx, 0) == SMART_OK);
+  EXPECT(call(ctx, 4, 512, 128, 2, true) > 0);
+  mallocs = frees = 0;
+  for (int hkv = 32; hkv <= 40; hkv += 2) EXPECT(call(ctx, 4, 4, hkv, hkv, true) > 0);
+  EXPECT(frees == 0 && mallocs == 1);  // (a block at least twice the last holds the next ones too)
+  EXPECT(call(ctx, 4, 512, 128, 2, true) == 2);
+  EXPECT(frees == 0 && mallocs == 1);
+  EXPECT(smart_destroy(ctx) == SMART_OK);
+  EXPECT(frees == 3);  // partial results, plan, counters
   puts(failures ? "failed" : "workspace driver ok");
   return failures != 0;
 }
