@@ -616,8 +616,10 @@ __device__ inline float load_word(__amdgpu_buffer_rsrc_t r, int offset) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, offset, 0, kDevicePolicy));
 }
 
+// (one reading for the whole wavefront: others count meanwhile, lanes might read different values, and what follows is decided
+// for all of them)
 __device__ inline int arrivals(const int32_t* counter) {
-  return __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __builtin_amdgcn_readfirstlane(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
 // (x, m, l) and (y, mc, lc) -> (x, m, l); an empty state has maximum -inf and sums of zero.
@@ -665,8 +667,7 @@ __device__ inline void write_rows(const FinishArgs& a, const Finish& f, const fl
 }
 
 // One wavefront's part of a piece, quads quad0 .. of row tile rt (l: of the whole row).
-// `early`: the counter as read some time before; it only grows until everyone is counted.  The lanes may have read different
-// values (others count meanwhile); what follows is decided for the whole wavefront, by its first lane's.
+// `early`: the counter as read some time before; it only grows until everyone is counted.
 template <int kCls, int kQuads>
 __device__ inline void finish_part(const FinishArgs& a, const Finish& f, floatx4 (&x)[kQuads], float m, float l, int quad0,
                                    int rt, int early, int wv, int lane) {
@@ -677,7 +678,7 @@ __device__ inline void finish_part(const FinishArgs& a, const Finish& f, floatx4
     const float c = a.scale_log2e;
     int32_t* const counter = counter_of<kCls>(a, f, wv);
     const int at = ((rt * 32 + 2 * quad0 + h) * 32 + j) * 16, ml = (kO + wv * 64 + j) * 4;
-    const bool in_place = __builtin_amdgcn_readfirstlane(early) == f.pieces - 1 && (f.mine == 0 || f.pieces == 2);
+    const bool in_place = early == f.pieces - 1 && (f.mine == 0 || f.pieces == 2);
     if (!in_place) {
       const __amdgpu_buffer_rsrc_t r = slot_buffer(a.ws[kCls] + (size_t)f.slot * kSlot, kSlot);
 #pragma unroll
