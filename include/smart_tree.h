@@ -37,13 +37,18 @@
  *   - Pointers named d_* are device memory, h_* host memory.  The caller owns
  *     every buffer passed in; the library neither frees nor retains them.
  *   - A smart_ctx owns only internal device workspace (split-KV partial
- *     results and the launch plan).  It is bound to one device.
+ *     results, the launch plan, and arrival counters, which are zero when a
+ *     call begins).  It is bound to one device.
  *   - Device entry points are asynchronous on the given hipStream_t (passed as
  *     void*; NULL is the default stream) and never synchronise, except that
  *     growing the workspace inside tree_verify_attention synchronises the
  *     stream once (avoid by calling smart_reserve up front).
  *   - Calls that share one smart_ctx must be issued on one stream or otherwise
- *     serialised by the caller: they share its workspace.
+ *     serialised by the caller: they share its workspace.  The results of
+ *     attention calls that overlap all the same are undefined, and so may be
+ *     those of the call after them; the ones behind that are right again
+ *     (a graph's replays use the counters of its capture: there, once the
+ *     context's calls, captured or not, have come round to them).
  *   - Element types: SMART_F32 (float) or SMART_BF16 (bfloat16, upper half of
  *     an IEEE binary32, round-to-nearest-even on output).
  *   - Trees: local node 0 of every sequence is the root; parent[i] < i

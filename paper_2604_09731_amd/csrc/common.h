@@ -16,8 +16,11 @@ struct smart_ctx {
   size_t ws_bytes = 0;
   int32_t* plan = nullptr;    // launch plan written by the planning kernel
   size_t plan_bytes = 0;
-  int32_t* arrive = nullptr;  // arrival counters of the matrix-core path, behind the plan or in the newest block; zero between calls
-  size_t counters = 0;
+  // arrival counters of the matrix-core path (behind the plan, or the newest of the blocks below): three sets, one a call in turn
+  // (see next_counters); a set is zero when its call begins
+  int32_t* arrive = nullptr;
+  size_t counters = 0;        // of a set, a multiple of 64
+  int32_t turn = 0;           // the set of the next call
   // blocks of counters by themselves, for calls that need more of them but no larger plan; kept until smart_destroy, because a
   // captured launch may hold an older one (each at least twice the one before)
   void* counter_blocks[32] = {};
@@ -67,6 +70,10 @@ int32_t tiled_workspace(smart_ctx* ctx, hipStream_t stream, size_t bytes, void**
 
 // Enqueues the clearing of arrival counters.
 int32_t zero_counters(hipStream_t stream, int32_t* counters, size_t n);
+// The counters of a call, and those of the call after it, which this one clears.  Every call leaves its own at zero too; but
+// calls of a context that overlap, which its contract excludes, may not, and would spoil every later call that came to the
+// same set.  So they spoil themselves only.
+void next_counters(smart_ctx* ctx, int32_t** counters, int32_t** clear);
 
 // Profiling hooks: bracket the dominant kernel of the current call.
 int32_t profile_begin(smart_ctx* ctx, hipStream_t stream);

@@ -8,6 +8,15 @@ namespace smart {
 static thread_local hipError_t g_last_hip_error = hipSuccess;
 void set_last_hip_error(hipError_t e) { g_last_hip_error = e; }
 
+constexpr int kCounterSets = 3;  // (two would do but for a call that clears the set of one it overlaps)
+
+void next_counters(smart_ctx* ctx, int32_t** counters, int32_t** clear) {
+  const int32_t next = (ctx->turn + 1) % kCounterSets;
+  *counters = ctx->arrive + (size_t)ctx->turn * ctx->counters;
+  *clear = ctx->arrive + (size_t)next * ctx->counters;
+  ctx->turn = next;
+}
+
 static __global__ void zero_counters_kernel(int32_t* counters, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) counters[i] = 0;
@@ -35,6 +44,7 @@ int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, si
   const bool plan_grows = plan_bytes > ctx->plan_bytes;
   if (plan_grows || counters > ctx->counters) {
     constexpr int kBlocks = sizeof(ctx->counter_blocks) / sizeof(ctx->counter_blocks[0]);
+    counters = (counters + 63) & ~(size_t)63;  // (they are cleared by whole wavefronts)
     if (counters < ctx->counters) counters = ctx->counters;
     if (plan_grows) {
       plan_bytes = (plan_bytes + 255) & ~(size_t)255;
@@ -47,14 +57,14 @@ int32_t ensure_workspace(smart_ctx* ctx, hipStream_t stream, size_t ws_bytes, si
       if (counters < 2 * ctx->counters) counters = 2 * ctx->counters;
     }
     void* block = nullptr;
-    hipError_t e = hipMalloc(&block, (plan_grows ? plan_bytes : 0) + counters * sizeof(int32_t));
+    hipError_t e = hipMalloc(&block, (plan_grows ? plan_bytes : 0) + kCounterSets * counters * sizeof(int32_t));
     if (e != hipSuccess) { set_last_hip_error(e); (void)hipGetLastError(); return SMART_ENOMEM; }
     if (plan_grows) ctx->plan = (int32_t*)block;
     else ctx->counter_blocks[ctx->n_counter_blocks++] = block;
-    // the counters start from zero and every launch leaves them so
+    // the counters start from zero
     int32_t* const arrive = (int32_t*)((char*)block + (plan_grows ? plan_bytes : 0));
     if (counters > 0) {
-      const int32_t rc = zero_counters(stream, arrive, counters);
+      const int32_t rc = zero_counters(stream, arrive, kCounterSets * counters);
       if (rc != SMART_OK) return rc;
       SMART_HIP_CHECK(hipStreamSynchronize(stream));  // (the next call may be on another stream)
     }

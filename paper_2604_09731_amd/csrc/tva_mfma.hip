@@ -278,6 +278,8 @@ struct FinishArgs {
   float* lse;
   float* ws[3];
   int32_t* arrive;
+  int32_t* clear;  // counters of the context's next call, cleared by this one: n_clear, a multiple of 64
+  int32_t n_clear;
   int32_t arrive_first[3];
   int32_t Hq, Hkv, G;
   float scale, scale_log2e;  // (without k_scale)
@@ -549,7 +551,8 @@ __device__ inline void store_partial(float* slot, int rows_in_slot, int qt, cons
 // another); who finds all others counted takes their parts and writes the rows.  Nobody ever waits for another workgroup.
 // Usually a worker's last piece begins a segment that its neighbour ended first thing, so it finds the neighbour counted
 // before it has written anything, and merges from registers.  The parts are merged in the order of the workers with the
-// same operations whoever does it, so the result does not depend on timing.  The counters return to zero.
+// same operations whoever does it, so the result does not depend on timing.  The counters return to zero, and a call clears those
+// of the context's next one besides (smart::next_counters; 0.0 .. 0.2 us of a call).
 // What it costs and saves (stamps; 32 sequences of 4 .. 64 nodes, 8B shapes): the tree part 3.4 .. 5 us and a part's store
 // and count 2.2 us per segment, merge and rows at the end 3.2 us, where the combine kernel took 18 us and a launch; the call
 // 128.9 -> 116.4 us, one sequence of 7 nodes and 517 tokens 19.0 -> 14.9.
@@ -2507,6 +2510,9 @@ void tva_prefix_kernel(MainArgs a) {
       d[3] = (unsigned long long)(wg < first1 ? 0 : (wg < first2 ? 1 : 2)) | ((unsigned long long)wg << 8) | (1ull << 63);
     }
   };)
+  if (kFinish)
+    for (int i = (int)(blockIdx.x * kWgWaves + wv) * kWave; i < a.fin.n_clear; i += (int)gridDim.x * kWgWaves * kWave)
+      a.fin.clear[i + (int)(threadIdx.x & (kWave - 1))] = 0;
   if (kFp8) {
     if (wg >= first1 && wg < first2) fp8_worker<kPair, kFinish>(a, wg - first1, cp, (float*)lds_raw);
     else if (wg >= first2) staged_worker<2, true, kFinish>(a, wg - first2, cp, (bf16x8*)lds_raw);
@@ -2898,7 +2904,7 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   }
   void* ws_base;
   void* plan_base;
-  int32_t* arrive = nullptr;
+  int32_t *arrive = nullptr, *clear = nullptr;
   const bool pairs_pay = fp8 && pairs(p, workgroups);
   bool finish = finishes(p, workgroups, pairs_pay);
   const TreeCost tc = tree_cost(p, workgroups);
@@ -2924,7 +2930,7 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
     if (rc != SMART_OK) return rc;
     ws_base = ctx->ws;
     plan_base = ctx->plan;
-    arrive = ctx->arrive;
+    if (finish) next_counters(ctx, &arrive, &clear);
   }
   float* ws[kClasses];
   ws[0] = (float*)ws_base;
@@ -2971,6 +2977,8 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   ma.fin.out = (__bf16*)p.d_out;
   ma.fin.lse = p.d_lse;
   ma.fin.arrive = arrive;
+  ma.fin.clear = clear;
+  ma.fin.n_clear = clear ? (int32_t)ctx->counters : 0;
   for (int c = 0, first = 0; c < kClasses; first += (int)caps.segs[c++]) {
     ma.fin.ws[c] = ws[c];
     ma.fin.arrive_first[c] = first;
