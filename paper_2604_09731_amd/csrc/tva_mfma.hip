@@ -2499,6 +2499,10 @@ void tva_prefix_kernel(MainArgs a) {
     cp.W = sload(pv.header + 2 * cls + 1);
     cp.resident = false;
   }
+  // (by every workgroup, before those without a worker leave)
+  if (kFinish)
+    for (int i = (int)(blockIdx.x * kWgWaves + wv) * kWave; i < a.fin.n_clear; i += (int)gridDim.x * kWgWaves * kWave)
+      a.fin.clear[i + (int)(threadIdx.x & (kWave - 1))] = 0;
   if (wg >= end) return;
   SMART_TIMELINE(auto tl_end = [&]() {
     __syncthreads();  // the workgroup's end is its last wavefront's
@@ -2510,9 +2514,6 @@ void tva_prefix_kernel(MainArgs a) {
       d[3] = (unsigned long long)(wg < first1 ? 0 : (wg < first2 ? 1 : 2)) | ((unsigned long long)wg << 8) | (1ull << 63);
     }
   };)
-  if (kFinish)
-    for (int i = (int)(blockIdx.x * kWgWaves + wv) * kWave; i < a.fin.n_clear; i += (int)gridDim.x * kWgWaves * kWave)
-      a.fin.clear[i + (int)(threadIdx.x & (kWave - 1))] = 0;
   if (kFp8) {
     if (wg >= first1 && wg < first2) fp8_worker<kPair, kFinish>(a, wg - first1, cp, (float*)lds_raw);
     else if (wg >= first2) staged_worker<2, true, kFinish>(a, wg - first2, cp, (bf16x8*)lds_raw);
