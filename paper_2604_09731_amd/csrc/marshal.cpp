@@ -53,14 +53,20 @@ template <typename T = void>
 T* address(PyObject* o) {  // None: NULL
   return o == Py_None ? nullptr : (T*)tensor(o).data_ptr();
 }
-uint64_t bits64(PyObject* o) {  // what int(o) gives, modulo 2^64
-  PyObject* n = PyLong_Check(o) ? (Py_INCREF(o), o) : must(PyNumber_Long(o));
-  const unsigned long long v = PyLong_AsUnsignedLongLongMask(n);
+uint64_t low_bits(PyObject* n) {  // of an int, whose reference it takes
+  const unsigned long long v = PyLong_AsUnsignedLongLongMask(must(n));
   Py_DECREF(n);
   if (v == (unsigned long long)-1 && PyErr_Occurred()) throw Failed();
   return v;
 }
-int64_t integer(PyObject* o) { return (int64_t)bits64(o); }
+uint64_t bits64(PyObject* o) { return low_bits(PyNumber_Long(o)); }  // what int(o) gives, modulo 2^64
+// An integer; anything else, a float of a whole value among them, is refused as ctypes refuses it.
+int64_t integer(PyObject* o) { return (int64_t)low_bits(PyNumber_Index(o)); }
+bool truth(PyObject* o) {
+  const int v = PyObject_IsTrue(o);
+  if (v < 0) throw Failed();
+  return v != 0;
+}
 double real(PyObject* o) {
   const double v = PyFloat_AsDouble(o);
   if (v == -1.0 && PyErr_Occurred()) throw Failed();
@@ -68,7 +74,7 @@ double real(PyObject* o) {
 }
 template <typename T>
 T* pointer(PyObject* o) {
-  return (T*)(uintptr_t)bits64(o);
+  return (T*)(uintptr_t)integer(o);
 }
 int64_t extent(const at::Tensor& t, int64_t dim) {
   if (dim >= t.dim()) {
@@ -198,7 +204,7 @@ PyObject* select_layer(PyObject* const* a) {
   const at::Tensor& cu = tensor(a[3]);
   const int64_t cap = extent(tensor(a[4]), 0);
   const double alpha = real(a[9]);
-  const int32_t dilution = (int32_t)integer(a[10]);
+  const int32_t dilution = (int32_t)bits64(a[10]);
   at::Tensor out = a[11] == Py_None ? fresh(cu, at::kInt, {std::max<int64_t>(1, cap)}) : tensor(a[11]);
   at::Tensor status = a[12] == Py_None ? fresh(cu, at::kInt, {std::max<int64_t>(1, batch)}) : tensor(a[12]);
   auto parent = address<int32_t>(a[4]);
@@ -219,7 +225,7 @@ PyObject* select_layer(PyObject* const* a) {
 PyObject* compact(PyObject* const* a) {  // ctx, state, batch, rows, prefix_len
   auto ctx = pointer<smart_ctx>(a[0]);
   auto state = pointer<const smart_layer_state>(a[1]);
-  const int64_t batch = integer(a[2]), rows = integer(a[3]);
+  const int64_t batch = integer(a[2]), rows = (int64_t)bits64(a[3]);
   const at::Tensor& prefix = tensor(a[4]);
   // one allocation for everything: the masks (16 bytes a node), the rows of node values, the offsets, the statuses, each in
   // whole rows; the launch writes all of it, and there is none for an empty batch
@@ -275,7 +281,7 @@ PyObject* rope(PyObject* const* a) {  // ctx, position, q, k_tree, base, rotary_
   three_dims(q);
   const int32_t nodes = (int32_t)q.size(0), Hq = (int32_t)q.size(1), D = (int32_t)q.size(2), Hkv = (int32_t)extent(k, 1);
   const double base = real(a[4]);
-  const int32_t type = element_type(q), rotary = a[5] == Py_None ? D : (int32_t)integer(a[5]), pairing = (int32_t)integer(a[6]);
+  const int32_t type = element_type(q), rotary = a[5] == Py_None ? D : (int32_t)bits64(a[5]), pairing = (int32_t)bits64(a[6]);
   void* s = stream();
   call("tree_rope", [&] {
     return lib.rope(ctx, s, type, nodes, Hq, Hkv, D, rotary, pairing, base, position, address(q), address(k));
@@ -294,7 +300,7 @@ PyObject* cache_write(PyObject* const* a) {
   const int32_t layout = (int32_t)integer(a[6]), bs = (int32_t)integer(a[7]), nb = (int32_t)integer(a[8]);
   const int64_t block = integer(a[9]), head = integer(a[10]), token = integer(a[11]);
   void* s = stream();
-  if (PyObject_IsTrue(a[12])) {
+  if (truth(a[12])) {
     const float ks = (float)real(a[13]), vs = (float)real(a[14]);
     call("kv_cache_write_fp8", [&] {
       return lib.cache_write_fp8(ctx, s, type, layout, n, Hkv, D, bs, nb, address(k), v, slots, kc, vc, block, head, token, ks, vs);
@@ -314,7 +320,7 @@ PyObject* attention(PyObject* const* a) {
   const at::Tensor &q = tensor(a[1]), &kt = tensor(a[2]), &vt = tensor(a[3]), &cu = tensor(a[8]);
   three_dims(q);
   at::Tensor out = a[13] == Py_None ? at::empty_like(q) : tensor(a[13]), lse;
-  const bool want_lse = PyObject_IsTrue(a[15]);
+  const bool want_lse = truth(a[15]);
   tva_params p = {};
   p.dtype = element_type(q);
   p.kv_layout = (int32_t)integer(a[11]);
@@ -365,7 +371,7 @@ PyObject* attention(PyObject* const* a) {
   p.d_status = address<int32_t>(a[20]);
   p.h_cu_nodes = pointer<const int32_t>(a[16]);
   void* s = stream();
-  if (PyObject_IsTrue(a[19])) call("tree_verify_attention_static", [&] { return lib.attention_static(ctx, s, &p); });
+  if (truth(a[19])) call("tree_verify_attention_static", [&] { return lib.attention_static(ctx, s, &p); });
   else call("tree_verify_attention", [&] { return lib.attention(ctx, s, &p); });
   return lse.defined() ? tuple_of(out, lse) : wrap(out);
 }
