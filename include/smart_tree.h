@@ -354,7 +354,8 @@ int32_t tree_compact_pack(smart_ctx* ctx, void* stream, const smart_layer_state*
                           int32_t* d_position, int32_t* d_node_seq, uint64_t* d_anc_mask,
                           int32_t* d_status);
 
-/* The same, and the rows behind the last node up to total_cap become zero. */
+/* The same, and the rows behind the last node up to total_cap become zero (of an empty batch too, whose d_cu_nodes[0] also
+ * becomes zero). */
 int32_t tree_compact_pack_fill(smart_ctx* ctx, void* stream, const smart_layer_state* d_state,
                                int32_t total_cap, const int32_t* d_prefix_len, int32_t* d_cu_nodes,
                                int32_t* d_parent, int32_t* d_token, int32_t* d_depth,

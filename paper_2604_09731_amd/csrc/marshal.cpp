@@ -228,11 +228,10 @@ PyObject* compact(PyObject* const* a) {  // ctx, state, batch, rows, prefix_len
   const int64_t batch = integer(a[2]), rows = (int64_t)bits64(a[3]);
   const at::Tensor& prefix = tensor(a[4]);
   // one allocation for everything: the masks (16 bytes a node), the rows of node values, the offsets, the statuses, each in
-  // whole rows; the launch writes all of it, and there is none for an empty batch
+  // whole rows; the launch writes all of it
   const int64_t n1 = std::max<int64_t>(1, rows), b1 = std::max<int64_t>(1, batch), p = whole_rows(n1), at = whole_rows(4 * n1);
   const int64_t words = at + 5 * p + whole_rows(batch + 1) + b1;
   at::Tensor buf = fresh(prefix, at::kInt, {words});
-  if (batch <= 0 || rows <= 0) buf.zero_();
   at::Tensor mask = buf.slice(0, 0, 4 * n1).view(at::kLong).view({n1, 2});
   at::Tensor row[5];
   for (int i = 0; i < 5; ++i) row[i] = buf.as_strided({n1}, {1}, at + i * p);

@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kWave) void tree_compact_pack_kernel(
   __shared__ int32_t par[SMART_MAX_NODES];
   const int b = blockIdx.x;
   const int lane = threadIdx.x;
-  if (b >= batch) return;
+  if (b >= batch && !kFill) return;
   auto nodes_of = [&](int i) {
     const int n = n_of[i];
     return (n >= 1 && n <= stride) ? n : 0;
@@ -186,10 +186,14 @@ __global__ __launch_bounds__(kWave) void tree_compact_pack_kernel(
   }
   const int base = before;
   if (kFill)
-    for (int64_t i = (int64_t)all + b * kWave + lane; i < capacity; i += (int64_t)batch * kWave) {
+    for (int64_t i = (int64_t)all + b * kWave + lane; i < capacity; i += (int64_t)gridDim.x * kWave) {
       parent[i] = token[i] = depth[i] = position[i] = node_seq[i] = 0;
       anc_mask[2 * i] = anc_mask[2 * i + 1] = 0;
     }
+  if (kFill && b >= batch) {  // an empty batch: no nodes
+    if (lane == 0) cu_nodes[0] = 0;
+    return;
+  }
   const int n = nodes_of(b);
   if (lane == 0) {
     cu_nodes[b] = base;
@@ -354,11 +358,12 @@ static int32_t compact_pack(smart_ctx* ctx, void* stream, const smart_layer_stat
   if (!d_cu_nodes || !d_prefix_len || !d_status) return SMART_EINVAL;
   const int32_t batch = d_state->batch;
   if (total_cap < 0 || (int64_t)total_cap < (int64_t)batch * d_state->budget) return SMART_EINVAL;
-  if (batch == 0) return SMART_OK;
-  if (!d_state->n || !d_state->parent || !d_state->token || !d_parent || !d_token || !d_depth || !d_position ||
-      !d_node_seq || !d_anc_mask)
+  if (batch == 0 && !kFill) return SMART_OK;
+  if ((batch > 0 && (!d_state->n || !d_state->parent || !d_state->token)) ||
+      ((batch > 0 || total_cap > 0) && (!d_parent || !d_token || !d_depth || !d_position || !d_node_seq || !d_anc_mask)))
     return SMART_EINVAL;
-  hipLaunchKernelGGL(tree_compact_pack_kernel<kFill>, dim3(batch), dim3(kWave), 0, (hipStream_t)stream, batch,
+  // (an empty batch has rows to clear all the same)
+  hipLaunchKernelGGL(tree_compact_pack_kernel<kFill>, dim3(batch > 0 ? batch : 1), dim3(kWave), 0, (hipStream_t)stream, batch,
                      total_cap, d_state->budget, d_state->n, d_state->parent, d_state->token, d_cu_nodes, d_parent, d_token,
                      d_prefix_len, d_depth, d_position, d_node_seq, d_anc_mask, d_status);
   SMART_HIP_CHECK(hipGetLastError());

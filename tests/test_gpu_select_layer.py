@@ -252,3 +252,24 @@ def test_compact_pack_leaves_zeros_behind_the_last_node(lib, batch, budget, spar
     for x, y in zip((*rows, mask), plain[1:-1]):
         assert torch.equal(x[:total], y[:total])
         assert not x[total:].any() and bool((y[total:] == -7).all())
+
+
+@pytest.mark.parametrize("cap", [0, 1, 64, 300])
+def test_compact_pack_of_an_empty_batch(lib, cap):
+    """No sequence: every row becomes zero, and the one offset."""
+    import torch
+    state = B.DeviceLayerState(0, 8, "cuda:0")
+    lens = torch.zeros(1, dtype=torch.int32, device="cuda")
+    rows = [torch.full((max(1, cap),), -7, dtype=torch.int32, device="cuda") for _ in range(5)]
+    mask = torch.full((max(1, cap), 2), -7, dtype=torch.int64, device="cuda")
+    cu, status = torch.full((1,), -7, dtype=torch.int32, device="cuda"), torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    rc = B._lib().tree_compact_pack_fill(lib._ctx, B._stream_ptr(), ctypes.byref(state.struct), cap, B._ptr(lens),
+                                         *[B._ptr(x) for x in (cu, *rows, mask, status)])
+    assert rc == 0 and cu.item() == 0 and status.item() == -7
+    for x in (*rows, mask):
+        assert not x[:cap].any() and bool((x[cap:] == -7).all())
+    dirty = [torch.full((1 << 16,), -7, dtype=torch.int32, device="cuda") for _ in range(4)]
+    del dirty
+    cu, *rows, mask, status = lib.tree_compact_pack(state, lens, cap)
+    assert cu.tolist() == [0] and status.shape == (0,) and mask.shape == (cap, 2)
+    assert not mask.any() and all(x.shape == (cap,) and not x.any() for x in rows)
