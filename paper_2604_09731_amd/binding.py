@@ -429,15 +429,6 @@ def _i32_rows(rows, n, device):
     return torch.empty_strided((rows, n), (_whole_rows(n), 1), dtype=torch.int32, device=device).unbind(0)
 
 
-def _dtype_code(t):
-    torch = _torch()
-    if t.dtype == torch.float32:
-        return SMART_F32
-    if t.dtype == torch.bfloat16:
-        return SMART_BF16
-    raise TypeError(f"unsupported element type {t.dtype}")
-
-
 def interleave_kv_cache(k_plain, v_plain):
     """[num_blocks, Hkv, block_size, D] plain caches -> the interleaved layout
     (pure data movement; shapes [nb, Hkv, D/8, bs, 8] and [nb, Hkv, bs/8, D, 8])."""

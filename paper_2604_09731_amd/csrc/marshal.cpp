@@ -76,11 +76,13 @@ template <typename T>
 T* pointer(PyObject* o) {
   return (T*)(uintptr_t)integer(o);
 }
+void at_least(const at::Tensor& t, int64_t dims) {
+  if (t.dim() >= dims) return;
+  PyErr_SetString(PyExc_IndexError, "tensor has too few dimensions");
+  throw Failed();
+}
 int64_t extent(const at::Tensor& t, int64_t dim) {
-  if (dim >= t.dim()) {
-    PyErr_SetString(PyExc_IndexError, "tensor has too few dimensions");
-    throw Failed();
-  }
+  at_least(t, dim + 1);
   return t.size(dim);
 }
 void three_dims(const at::Tensor& t) {
@@ -336,7 +338,9 @@ PyObject* attention(PyObject* const* a) {
   p.d_v_tree = address(vt);
   if (a[4] != Py_None) {
     const at::Tensor &kc = tensor(a[4]), &vc = tensor(a[5]);
-    if (extent(kc, 1) < 0 || extent(vc, 1) < 0 || kc.stride(0) != vc.stride(0) || kc.stride(1) != vc.stride(1)) {
+    at_least(kc, 2);
+    at_least(vc, 2);
+    if (kc.stride(0) != vc.stride(0) || kc.stride(1) != vc.stride(1)) {
       PyErr_SetString(PyExc_AssertionError, "the two caches have different strides");
       throw Failed();
     }
@@ -347,7 +351,7 @@ PyObject* attention(PyObject* const* a) {
     p.cache_head_stride = kc.stride(1);
     p.cache_token_stride = p.head_dim;
     if (p.kv_layout == SMART_KV_PLAIN) {
-      (void)extent(kc, 2);
+      at_least(kc, 3);
       p.cache_token_stride = kc.stride(2);
     }
     p.d_block_table = address<int32_t>(tensor(a[6]));
