@@ -736,7 +736,9 @@ __device__ inline uint32_t mask_word(const FinishArgs& a, int base, int rows, in
 }
 
 // Scores of a tile of tree keys -> probabilities (softmax_tile, for masked keys; the reference follows the maximum at
-// once, so that a probability is at most 1 however large the tree's values are).
+// once, so that a probability is at most 1 however large the tree's values are).  A row sees few tree keys and often has most of
+// its weight on one of them, whose rounding does not average out as that of a prefix's many does: the reference is raised by
+// less than a power of two so that the largest probability of the tile is one, which bf16 holds exactly.
 __device__ inline void softmax_tree(floatx16& s, uint32_t word, float& m, float& l, floatx16 (&o)[4], bf16x8& pb0,
                                     bf16x8& pb1, float c, int h) {
   const uint32_t bits = word >> (8 * h);  // register r holds key 16 (r / 8) + 8 h + r % 8: see sigma
@@ -744,7 +746,9 @@ __device__ inline void softmax_tree(floatx16& s, uint32_t word, float& m, float&
 #pragma unroll
   for (int r = 0; r < 16; ++r) mx = fmaxf(mx, (bits >> (16 * (r >> 3) + (r & 7))) & 1u ? s[r] : -INFINITY);
   mx = max_across_halves(mx);
-  const float m_new = fmaxf(m, mx);
+  float m_new = fmaxf(m, mx);
+  const float below = (m_new - mx) * c;  // (infinite, or NaN, if there is no key or an infinite score)
+  if (below > 0.f && below < 64.f) m_new = fmaf(ceilf(below), __builtin_amdgcn_rcpf(c), mx);
   const float alpha = m_new == m ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * c);
   l *= alpha;
 #pragma unroll

@@ -140,3 +140,22 @@ def test_an_infinite_value_of_the_key_with_all_the_weight(size, Hq, Hkv, fp8):
         assert bool((out[node, :, 5] == np.inf).all())
         assert torch.isfinite(out[node][:, [d for d in range(128) if d != 5]]).all()
         x.q, x.k_tree, x.v_tree = q, k, v
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("size,Hq,Hkv", [(1, 32, 8), (7, 32, 8), (10, 32, 8), (40, 8, 2), (64, 8, 2), (128, 8, 2)])
+def test_the_largest_probability_of_a_tree_tile_is_not_rounded(size, Hq, Hkv, fp8):
+    """One prefix key of score and value 0 and tree values of 1: a root's row, which sees one tree key, is p / (1 + p).  Nothing
+    is rounded to 16 bits but the output (half a unit in its last place)."""
+    lib = B.SmartTree(0)
+    x = Inputs([size] * 40, [1] * 40, Hq, Hkv, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, fp8, seed=size)
+    x.k.zero_()
+    x.v.zero_()
+    x.v_tree.fill_(1)
+    s = (x.q[::size].double().view(40, Hkv, -1, 128) * x.k_tree[::size, :, None].double()).sum(-1) / np.sqrt(128)
+    p = s.exp().view(40, Hq, 1)
+    ref = p / (1 + p)
+    out, lse = x.run(lib)
+    bound = 2.0 ** (ref.log2().floor() - 8) + 1e-5 * ref           # (1e-5: scores and exponentials in binary32)
+    assert bool(((out[::size].double() - ref).abs() <= bound).all())
+    assert float((lse[::size].double() - (1 + p[..., 0]).log()).abs().max()) <= 1e-5
