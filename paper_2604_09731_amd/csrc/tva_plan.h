@@ -175,17 +175,18 @@ __host__ __device__ inline void apportion(const int64_t (&all_u)[kClasses], cons
   int64_t first = 0;
 #pragma unroll
   for (int c = 0; c < kClasses; ++c) {
-    int64_t w = wg[c];  // a worker is a workgroup in every class
-    // (by the prefix tiles alone, so that segments of 64 tiles go to four workers each, tree parts or not; and a worker for
-    // every segment: one sequence of 200 tokens, 8 kv heads, on three workers 26.7 us, on eight 10.4.  Never more workers than
-    // units: where partials are merged by another kernel (not kFinish) a segment without prefix has no unit, and a worker
-    // without one would leave no partial between those of its neighbours, which are merged without a gap)
-    int64_t cap = (tot_u[c] - (kFinish ? all_s[c] * (c == 2 ? tc.large : tc.small) : 0)) /
-                  (kMinTilesPerWorker[c] * (c == 2 ? kLargeTileCost[0] : 1));
-    if (cap < all_s[c]) cap = all_s[c];
-    if (cap > tot_u[c]) cap = tot_u[c];
-    if (w > cap) w = cap;
-    if (tot_u[c] > 0 && w < 1) w = 1;
+    // A worker is a workgroup in every class, as many as pay by the prefix tiles alone (so that segments of 64 tiles go to four
+    // workers each, tree parts or not), but one for every segment: one sequence of 200 tokens, 8 kv heads, on three workers
+    // 26.7 us, on eight 10.4.  Never more workers than units: where partials are merged by another kernel (not kFinish) a segment
+    // without prefix has no unit, and a worker without one would leave no partial between those of its neighbours, which are
+    // merged without a gap.  (With kFinish every segment has the units of its tree part.  Few 64-bit comparisons: all
+    // wavefronts of a workgroup wait for this.)
+    const int64_t pay = (tot_u[c] - (kFinish ? all_s[c] * (c == 2 ? tc.large : tc.small) : 0)) /
+                        (kMinTilesPerWorker[c] * (c == 2 ? kLargeTileCost[0] : 1));
+    const int32_t dealt = (int32_t)wg[c], segs = (int32_t)all_s[c];
+    int32_t w = pay < dealt ? (int32_t)pay : dealt;
+    if (w < segs) w = segs < dealt ? segs : dealt;
+    if (!kFinish && w > tot_u[c]) w = (int32_t)tot_u[c];
     workers[c] = w;
     first_wg[c] = first;
     first += w;
