@@ -2415,14 +2415,16 @@ void tva_prefix_kernel(MainArgs a) {
   SMART_TIMELINE(const unsigned long long tl_start = wall_clock64(); const unsigned long long tl_cycles = clock64();)
   // Workgroups are dealt to the eight XCDs round robin; consecutive WORKERS (consecutive unit ranges: the row groups
   // of one segment, the two ends of a segment) are put on one XCD so that what they read in common meets in its L2.
-  const int64_t wg = gridDim.x % 8 == 0 ? (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8 : (int64_t)blockIdx.x;
+  // (The grid's size from the arguments: gridDim lies behind them, a line of host memory further.)
+  const unsigned grid = a.workgroups > kClasses ? a.workgroups : kClasses;
+  const int64_t wg = grid % 8 == 0 ? (int64_t)(blockIdx.x % 8) * (grid / 8) + blockIdx.x / 8 : (int64_t)blockIdx.x;
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   ClassPlan cp;
   int64_t first1, first2, end;
   if (kFinish && a.status && (wv > 0 || a.batch > kWave)) {  // the block-table check, while wavefront 0 plans
-    for (int64_t b = blockIdx.x + (int64_t)gridDim.x * (wv - (a.batch <= kWave ? 1 : 0)); b < a.batch;
-         b += (int64_t)gridDim.x * (a.batch <= kWave ? kWgWaves - 1 : kWgWaves))
+    for (int64_t b = blockIdx.x + (int64_t)grid * (wv - (a.batch <= kWave ? 1 : 0)); b < a.batch;
+         b += (int64_t)grid * (a.batch <= kWave ? kWgWaves - 1 : kWgWaves))
       smart::tva_validate_block_table((int)b, a.block_table, a.prefix_len, a.max_blocks, kBlock, a.num_blocks, a.status, lane);
   }
   if (a.batch <= kWave) {
@@ -2505,7 +2507,7 @@ void tva_prefix_kernel(MainArgs a) {
   }
   // (by every workgroup, before those without a worker leave)
   if (kFinish)
-    for (int i = (int)(blockIdx.x * kWgWaves + wv) * kWave; i < a.fin.n_clear; i += (int)gridDim.x * kWgWaves * kWave)
+    for (int i = (int)(blockIdx.x * kWgWaves + wv) * kWave; i < a.fin.n_clear; i += (int)grid * kWgWaves * kWave)
       a.fin.clear[i + (int)(threadIdx.x & (kWave - 1))] = 0;
   if (wg >= end) return;
   SMART_TIMELINE(auto tl_end = [&]() {
