@@ -1594,7 +1594,7 @@ __device__ inline void fp8_pieces(const MainArgs& a0, int64_t w, ClassPlan& cp, 
     const int64_t left = u1 - u0;
     const int end = begin + (int)(left < (int64_t)(units - begin) ? left : (int64_t)(units - begin));
     // prefix tiles t0 .. t1 of the piece; its tree part counts as one more
-    const int t0 = min(begin, si.tiles), t1 = min(end, si.tiles);
+    const int t0 = kFinish ? min(begin, si.tiles) : begin, t1 = kFinish ? min(end, si.tiles) : end;
     const bool tree = kFinish && end == units;
     const int nt = t1 - t0 + (tree ? 1 : 0);
     const int64_t seg = (int64_t)__builtin_amdgcn_readlane(win.cum_segs, b - win.first) + g;
@@ -1615,8 +1615,11 @@ __device__ inline void fp8_pieces(const MainArgs& a0, int64_t w, ClassPlan& cp, 
       o_scale = z.o_scale;
       if (fin.pieces > 1) early = arrivals(counter_of<1>(fa, fin, wv));
     };
-    const int s0 = min(t1, t0 + (int)(((int64_t)nt * wv) / kWgWaves));
-    const int s1 = min(t1, t0 + (int)(((int64_t)nt * (wv + 1)) / kWgWaves));
+    auto cut = [&](int part, int of) {
+      const int t = t0 + (int)(((int64_t)nt * part) / of);
+      return kFinish ? min(t1, t) : t;
+    };
+    const int s0 = cut(wv, kWgWaves), s1 = cut(wv + 1, kWgWaves);
     if (M <= kSmallRows) {
       SmallState S;
       small_segment<fp8x8>(S, kFinish ? stream_args(a) : a, b, g, base, s0, s1, si, lane);
@@ -1634,8 +1637,7 @@ __device__ inline void fp8_pieces(const MainArgs& a0, int64_t w, ClassPlan& cp, 
       fold_pairs_and_store(P, merge_lds, slot, wv, lane, c, m_scale, o_scale);
     } else {
       const int rt = wv >> 2, sub = wv & 3;
-      const int h0 = min(t1, t0 + (int)(((int64_t)nt * sub) / 4));
-      const int h1 = min(t1, t0 + (int)(((int64_t)nt * (sub + 1)) / 4));
+      const int h0 = cut(sub, 4), h1 = cut(sub + 1, 4);
       SmallState S;
       small_segment<fp8x8, false>(S, kFinish ? stream_args(a) : a, b, g, base, h0, h1, si, lane, rt * kSmallRows);
       streamed();
