@@ -36,14 +36,14 @@ struct SeqInfo {
 // Class 2 shares its workers by time rather than by tiles.  The eight wavefronts of a workgroup take one 32-row
 // tile each (two per SIMD), so a 32-key tile of a segment with up to four row tiles takes what one wavefront
 // takes (measured: 0.68 .. 0.76 us), and with five or more what two on one SIMD take (0.9 .. 1.07 us).  In units
-// of 0.06 us: kLargeTileCost[row tiles] per tile.  (Starting and finishing a piece takes 11 .. 13 us on top; a
-// start cost per segment in the unit space, 0 .. 200 units, changed nothing measurable and is not modelled.)
+// of 0.06 us: kLargeTileCost[row tiles] per tile.  (What a segment costs beside its tiles: TreeCost.)
 constexpr int kLargeTileCost[kLargeRows / 32 + 1] = {11, 11, 11, 12, 12, 16, 16, 17, 17};
 // (the same currency for a tile of classes 0 and 1, for dealing the workgroups to the classes.  A class 0 tile takes 10 where
-// all workgroups stream, 6 .. 7 among many of class 2 (with 10, class 0 ended at 88 us of 128 and at 775 of 1333); 8 / 9 / 10
-// us: 60 sequences of 500 .. 4000 tokens, 1 .. 24 nodes 122 / 129 / 129, 64 of 16384, 1 .. 48 nodes 1227 / 1236 / 1240, 32 of
-// 3072 .. 4096, 1 .. 14 nodes 92.5 / 90.4 / 96.4, 64 of 4096, 4 .. 10 nodes 203 / 199 / 202, 48 of 100 .. 8000, 2 kv heads
-// 69 / 67 / 65.)
+// all workgroups stream and 6 .. 7 among many of class 2, so no one number fits all.  Over 19 calls with class 0 trees among
+// others 9 takes 0.1 % longer than 8 and 10 takes 1.1 %; 8 / 9 / 10 us: 60 sequences of 500 .. 4000 tokens, 1 .. 24 nodes 113.3 /
+// 118.0 / 119.4, 64 of 16384, 1 .. 48 nodes 1231 / 1245 / 1239, 32 of 3072 .. 4096, 1 .. 14 nodes 92.4 / 92.2 / 94.6, 64 of 4096,
+// 4 .. 10 nodes 184.0 / 178.9 / 182.9, 48 of 100 .. 8000, 1 .. 48 nodes, 2 kv heads 54.6 / 54.6 / 56.4, 48 of 200 .. 3000, 1 .. 64
+// nodes 98.8 / 97.3 / 97.7.)
 constexpr int kClassTileCost[kClasses] = {8, 10, 1};
 constexpr int kFp8StreamTileCost = 5;
 // What a segment costs beside its prefix tiles where the prefix kernel finishes the rows itself (kFinish): its tree part,
