@@ -10,10 +10,12 @@ loop); every input (draft distributions on the host, Q / K / V / paged cache /
 block table / target tokens on the GPU) is resident before the clock starts.
 
 Prints ONE JSON line.  `value` = microseconds per step.  `roofline` is for the
-dominant kernel (the prefix-streaming attention kernel), timed with HIP events
-the library attaches to its dispatch during the timed steps; `roofline_call` is
-the same bound for the whole tree_verify_attention call (that kernel plus the
-combine kernel, timed with events around the call).  `cpu_baseline` is the CPU
+dominant kernel (the prefix-streaming attention kernel; its bytes are counted
+without the tree's rows and the outputs, which it also moves where it finishes
+the rows), timed with HIP events the library attaches to its dispatch during the
+timed steps; `roofline_call` is the same bound for the whole
+tree_verify_attention call (that kernel, and the combine kernel where the call
+takes two launches; timed with events around the call).  `cpu_baseline` is the CPU
 oracle's attention on a bounded sample of the same workload, extrapolated to a
 full step; `parity_err` compares the GPU output of the last timed step with the
 rows the oracle computed for it.  With the default workload (cfg3a, trees as the
