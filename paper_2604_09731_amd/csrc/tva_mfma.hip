@@ -2843,8 +2843,11 @@ void tva_mfma_workspace(const smart_ctx* ctx, int32_t batch, int32_t total_nodes
                         int32_t num_kv_heads, size_t* ws_bytes, size_t* plan_bytes, size_t* counters) {
   int64_t segs[kClasses];
   segment_bounds(batch, total_nodes, num_q_heads, num_kv_heads, segs);
-  const Slots s = slots_for(ctx, segs, true);  // (the larger of the two forms)
-  *ws_bytes = s.floats * sizeof(float);
+  const Slots s = slots_for(ctx, segs, false);
+  // Room for both forms.  The finishing form's slots are larger, class 0's by the most; every class's are counted that much
+  // larger here, so that a call whose two-launch form fits a buffer fits it in either form: it must not replace a buffer that a
+  // captured launch of another call still holds.
+  *ws_bytes = (s.floats * finish_slot(0) / class_slot(0) + 1) * sizeof(float);
   *plan_bytes = plan_bytes_for(batch);
   *counters = s.counters;
 }

@@ -129,6 +129,13 @@ int main() {
   EXPECT(frees == 0 && mallocs == 1);
   EXPECT(smart_destroy(ctx) == SMART_OK);
   EXPECT(frees == 3);  // partial results, plan, counters
+  // as many partial results of the two-launch form, more of the finishing form: what a captured launch holds stays
+  EXPECT(smart_create(&ctx, 0) == SMART_OK);
+  EXPECT(call(ctx, 4, 128, 64, 1, true) > 0);
+  frees = 0;
+  EXPECT(call(ctx, 4, 448, 12, 3, true) > 0);
+  EXPECT(frees == 0);
+  EXPECT(smart_destroy(ctx) == SMART_OK);
   puts(failures ? "failed" : "workspace driver ok");
   return failures != 0;
 }
