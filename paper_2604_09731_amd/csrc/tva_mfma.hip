@@ -2940,6 +2940,17 @@ int32_t tva_launch_mfma(smart_ctx* ctx, hipStream_t stream, const tva_params& p,
   } else {
     size_t ws_most, plan_most, counters;
     tva_mfma_workspace(ctx, p.batch, p.total_nodes, p.num_q_heads, p.num_kv_heads, &ws_most, &plan_most, &counters);
+    // a launch that is being captured cannot allocate: where it is only the counters that are too few, it takes the form that
+    // has none
+    if (counters > ctx->counters && stream != nullptr) {
+      hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();
+      if (capture != hipStreamCaptureStatusNone) {
+        finish = false;
+        slots = slots_for(ctx, caps.segs, false);
+        counters = 0;
+      }
+    }
     int32_t rc = ensure_workspace(ctx, stream, ws_most, plan_most, counters);
     if (rc != SMART_OK) return rc;
     ws_base = ctx->ws;

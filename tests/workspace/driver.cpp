@@ -6,11 +6,13 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <tuple>
 
 #include "smart_tree.h"
 
 static int mallocs, frees, launches;
 static size_t allocated, refuse_from = (size_t)-1;
+static bool capturing;  // of a stream other than the default one
 static hipError_t sync_result = hipSuccess, malloc_result = hipErrorOutOfMemory;
 
 extern "C" {
@@ -34,7 +36,10 @@ hipError_t hipFree(void* p) { ++frees; free(p); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return sync_result; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
 hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { ++launches; return hipSuccess; }
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
@@ -62,7 +67,7 @@ static int call(smart_ctx* ctx, int batch, int nodes, int hq, int hkv, bool inte
   p.d_block_table = p.d_prefix_len = p.d_cu_nodes = (const int32_t*)x;
   p.d_anc_mask = (const uint64_t*)x;
   launches = 0;
-  const int32_t rc = tree_verify_attention(ctx, nullptr, &p);
+  const int32_t rc = tree_verify_attention(ctx, capturing ? x : nullptr, &p);
   return rc == SMART_OK ? launches : rc;
 }
 
@@ -136,6 +141,23 @@ int main() {
   EXPECT(call(ctx, 4, 448, 12, 3, true) > 0);
   EXPECT(frees == 0);
   EXPECT(smart_destroy(ctx) == SMART_OK);
+  // under capture nothing can be allocated: a call that is short of counters only takes two launches, which need none
+  // (nodes of the call before it; this call's heads; whether it takes one launch elsewhere)
+  for (const auto& [nodes, hkv, one_launch] : {std::tuple{128, 5, false}, {512, 20, true}}) {
+    EXPECT(smart_create(&ctx, 0) == SMART_OK);
+    EXPECT(call(ctx, 4, nodes, 64, 1, true) > 0);
+    mallocs = 0;
+    capturing = true;
+    sync_result = hipErrorStreamCaptureUnsupported;
+    EXPECT(call(ctx, 4, 4, hkv, hkv, true) == 2);
+    EXPECT(mallocs == 0);
+    capturing = false;
+    sync_result = hipSuccess;
+    EXPECT(call(ctx, 4, 4, hkv, hkv, true) > 0);
+    EXPECT(call(ctx, 4, 4, hkv, hkv, true) == (one_launch ? 1 : 2));
+    EXPECT(mallocs == 1);
+    EXPECT(smart_destroy(ctx) == SMART_OK);
+  }
   puts(failures ? "failed" : "workspace driver ok");
   return failures != 0;
 }
