@@ -749,8 +749,10 @@ __device__ inline void softmax_tree(floatx16& s, uint32_t word, float& m, float&
   for (int r = 0; r < 16; ++r) mx = fmaxf(mx, (bits >> (16 * (r >> 3) + (r & 7))) & 1u ? s[r] : -INFINITY);
   mx = max_across_halves(mx);
   float m_new = fmaxf(m, mx);
-  const float below = (m_new - mx) * c;  // (infinite, or NaN, if there is no key or an infinite score)
-  if (below > 0.f && below < 64.f) m_new = fmaf(ceilf(below), __builtin_amdgcn_rcpf(c), mx);
+  // (infinite, or NaN, if there is no key or an infinite score.  Less than a millionth needs nothing, and a softmax scale whose
+  // reciprocal is infinite gives no more)
+  const float below = (m_new - mx) * c;
+  if (below > 1e-6f && below < 64.f) m_new = fmaf(ceilf(below), __builtin_amdgcn_rcpf(c), mx);
   const float alpha = m_new == m ? 1.f : __builtin_amdgcn_exp2f((m - m_new) * c);
   l *= alpha;
 #pragma unroll

@@ -159,3 +159,21 @@ def test_the_largest_probability_of_a_tree_tile_is_not_rounded(size, Hq, Hkv, fp
     bound = 2.0 ** (ref.log2().floor() - 8) + 1e-5 * ref           # (1e-5: scores and exponentials in binary32)
     assert bool(((out[::size].double() - ref).abs() <= bound).all())
     assert float((lse[::size].double() - (1 + p[..., 0]).log()).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("scale", [1e-39, 2e-38, 1e-30])
+@pytest.mark.parametrize("size,Hq,Hkv", [(7, 32, 8), (40, 8, 2), (128, 8, 2)])
+def test_a_softmax_scale_near_zero(size, Hq, Hkv, scale):
+    """Every key a row sees has the same weight, also where the scale's reciprocal is no binary32: the two sides differ by a
+    unit of bf16 at most, and by what sums in another order move in binary32."""
+    lib = B.SmartTree(0)
+    x = Inputs([size] * 40, [40] * 40, Hq, Hkv, 128, 16, "bf16", B.SMART_KV_INTERLEAVED, seed=size)
+    _, _, _, mask, _ = lib.tree_pack(x.cu, x.parent, x.len)
+    got = {}
+    for general in (1, 0):
+        lib.set_option(B.SMART_OPT_TVA_FORCE_GENERAL, general)
+        got[general] = lib.tree_verify_attention(x.q, x.k_tree, x.v_tree, x.k, x.v, x.table, x.len, x.cu, mask, scale, x.layout,
+                                                 block_size=16, want_lse=True)
+    (out, lse), (ref, ref_lse) = got[0], got[1]
+    assert bool(((out.double() - ref.double()).abs() <= 2.0 ** -7 * ref.double().abs() + 1e-5).all())
+    assert float((lse - ref_lse).abs().max()) <= 1e-5
