@@ -2421,8 +2421,10 @@ void tva_prefix_kernel(MainArgs a) {
   SMART_TIMELINE(const unsigned long long tl_start = wall_clock64(); const unsigned long long tl_cycles = clock64();)
   // Workgroups are dealt to the eight XCDs round robin; consecutive WORKERS (consecutive unit ranges: the row groups
   // of one segment, the two ends of a segment) are put on one XCD so that what they read in common meets in its L2.
-  // (The grid's size from the arguments: gridDim lies behind them, a line of host memory further.)
-  const unsigned grid = a.workgroups > kClasses ? a.workgroups : kClasses;
+  // (The grid's size from the arguments: gridDim lies behind them, a line of host memory further; 0.15 .. 0.35 us of a call.  From
+  // an fp8 cache in two launches that gains nothing, and the kernel that holds a.workgroups takes longer, compiled: 2 sequences
+  // of 2048 tokens and 44 nodes 42.7 us, this way 42.3, of 8000 and 60 51.1 and 50.7.)
+  const unsigned grid = kFp8 && !kFinish ? gridDim.x : (a.workgroups > kClasses ? a.workgroups : kClasses);
   const int64_t wg = grid % 8 == 0 ? (int64_t)(blockIdx.x % 8) * (grid / 8) + blockIdx.x / 8 : (int64_t)blockIdx.x;
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
