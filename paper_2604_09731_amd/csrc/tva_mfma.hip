@@ -2887,11 +2887,21 @@ static bool pairs(const tva_params& p, int32_t workgroups) {
 // 16384 102.8 (106.9).  And pairs of row tiles from an fp8 cache have no registers left for it: 64 sequences of 3600 tokens,
 // 9 .. 16 nodes 138 .. 153 us (128); by halves, and finished, they win only while prefixes are shorter: 64 sequences of 2400
 // tokens 80 us (107), 32 of 4000 76 (74).
+// Nor do trees of a node or a few gain where segments of long prefixes are cut into many pieces: their rows take the combine
+// kernel one round trip each, and the last piece is as long as the others.  One launch / two: 8 sequences of 1 node, 8 kv heads,
+// 2000 tokens 26.4 / 23.8 us, 4000 35.1 / 31.7, of 4 nodes about 6 % more, of 5 and 8 nodes 0 .. 4, but a mean of 1 .. 4 and 256
+// segments 0.97 .. 1.00, 1000 tokens 0.94 .. 1.06; fp8 cache, 16 of 1 node, 4000 tokens 34.2 / 31.0, 1500 0.93 .. 1.04.  And one
+// or two sequences whose trees fill several row groups leave all of them to few workgroups, with a part of 256 rows from each
+// piece: one of 128 nodes, 8 kv heads, 700 tokens 40.5 / 33.5, 500 37.5 / 34.0, but 200 1.01; 16 segments 0.84 .. 1.05.
 constexpr int kFewTiles = 32, kFewPieces = 8, kLongPairTiles = 120;
 static bool finishes(const tva_params& p, int32_t workgroups, bool pairs_pay) {
-  const int64_t longest = longest_prefix(p);
+  const int64_t longest = longest_prefix(p), segs = (int64_t)p.batch * p.num_kv_heads;
+  const int64_t rows = (int64_t)p.total_nodes * (p.num_q_heads / p.num_kv_heads);
   if (pairs_pay && longest >= kLongPairTiles) return false;
-  return longest <= kFewTiles || (int64_t)p.batch * p.num_kv_heads * kFewPieces >= workgroups;
+  if (p.total_nodes <= 4 * (int64_t)p.batch && longest > (p.kv_cache_dtype == SMART_FP8_E4M3 ? 60 : 40) && 2 * segs <= workgroups)
+    return false;
+  if (rows > (int64_t)kLargeRows * p.batch && longest > 10 && 32 * segs <= workgroups) return false;
+  return longest <= kFewTiles || segs * kFewPieces >= workgroups;
 }
 
 // With many segments a worker holds several, and each costs a start, a fold and a tree part beside its tiles; where every

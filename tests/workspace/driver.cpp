@@ -149,15 +149,23 @@ int main() {
     mallocs = 0;
     capturing = true;
     sync_result = hipErrorStreamCaptureUnsupported;
-    EXPECT(call(ctx, 4, 4, hkv, hkv, true) == 2);
+    EXPECT(call(ctx, 4, 20, hkv, hkv, true) == 2);
     EXPECT(mallocs == 0);
     capturing = false;
     sync_result = hipSuccess;
-    EXPECT(call(ctx, 4, 4, hkv, hkv, true) > 0);
-    EXPECT(call(ctx, 4, 4, hkv, hkv, true) == (one_launch ? 1 : 2));
+    EXPECT(call(ctx, 4, 20, hkv, hkv, true) > 0);
+    EXPECT(call(ctx, 4, 20, hkv, hkv, true) == (one_launch ? 1 : 2));
     EXPECT(mallocs == 1);
     EXPECT(smart_destroy(ctx) == SMART_OK);
   }
+  // trees of a mean of at most four nodes take two launches under this table, but not if segments are many
+  EXPECT(smart_create(&ctx, 0) == SMART_OK);
+  EXPECT(smart_reserve(ctx, 17, 64, 64, 64) == SMART_OK);
+  EXPECT(call(ctx, 4, 16, 20, 20, true) == 2);
+  EXPECT(call(ctx, 4, 17, 20, 20, true) == 1);
+  EXPECT(call(ctx, 4, 4, 32, 32, true) == 2);
+  EXPECT(call(ctx, 4, 4, 33, 33, true) == 1);
+  EXPECT(smart_destroy(ctx) == SMART_OK);
   puts(failures ? "failed" : "workspace driver ok");
   return failures != 0;
 }
